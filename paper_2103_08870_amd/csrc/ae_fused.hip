@@ -1,0 +1,730 @@
+// The paper-size autoencoder (Sec. IV-C, Table I: 1-64-128-256-64-4; Table II: 4-4-32-64-128-32-1), each stack as
+// one launch on the bf16 matrix cores, in fp32 precision (gfx950, wave64, v_mfma_f32_32x32x16_bf16).
+//
+// A block takes a short run of latent positions through all layers.  The layers' windows overlap by one position
+// per layer only (31 positions of conv3, 63 of conv2, 127 of conv1 for 15 latent ones), so recomputing the edges
+// costs 3-6 % of the arithmetic, and no intermediate tensor leaves the LDS: what a block moves is its input, its
+// output and the weights, which it streams from the L2.
+//
+// fp32 precision from bf16 products: every fp32 operand is the exact sum of three bf16 numbers
+// (x = h + m + l: h = bf16(x), m = bf16(x - h), l = x - h - m has at most 8 bits left), and
+//   x w = h h' + (h m' + m h') + (m m' + h l' + l h') + terms below 2^-26 |x w|
+// so six bf16 products, exact in the fp32 accumulators' input, take the place of one fp32 product.  The matrix
+// cores run bf16 at 16 times the fp32 rate: 2.7 times fewer matrix-core cycles for the same precision (the sums are
+// rounded once per 16 products instead of once per 2, and come out slightly closer to the 64-bit result).
+// Measured against one fp32-MFMA launch per deep layer (ae_mfma.hip, which other stacks still use): 4 nodes x 25 600
+// values, encoder 79.3 -> 38.6 us, decoder 57.8 -> 21.5 us; 8 x 67 000, both together 468 -> 260 us; 1 x 1 023
+// (latency) 78.6 -> 37.0 us; relative error against 64 bits 1.2e-7 -> 1.0e-7 (latent), 2.9e-8 -> 2.7e-8.
+// The split is exact only for finite values; an Inf would meet products of both signs.  So every split carries
+// a check along, and a block that met an Inf or a NaN anywhere redoes its outputs in plain fp32 (plain_encoder /
+// plain_decoder), with the term order of the per-layer kernels.
+//
+// Operand layout of v_mfma_f32_32x32x16_bf16: lane l supplies A[i = l % 32][k = 8 (l / 32) + 0..7] and
+// B[k = 8 (l / 32) + 0..7][j = l % 32]; result r of 16 is C[i = 8 (r / 4) + 4 (l / 32) + r % 4][j = l % 32].  Here
+// i is the output channel, j the position, k runs over 16 input channels of one tap.  Weights are laid out in this
+// order when the handle is created (fragments of 1 KB, a step's three parts one after the other), activations are
+// kept in the LDS position by position, [h | m | l][channels], so that every operand is one 16-byte read per lane.  Rows are
+// padded by 16 bytes: eight neighbouring positions then start in eight different groups of banks.
+#include <type_traits>
+
+#include "lgc_internal.h"
+
+namespace lgc {
+
+typedef __bf16 bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef float f4v __attribute__((ext_vector_type(4)));
+typedef float acc16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u2v __attribute__((ext_vector_type(2)));
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+
+namespace {
+
+__device__ __forceinline__ float leaky_f(float x, float slope) { return x > 0.f ? x : slope * x; }
+
+// Two values split into three bf16 pairs.  `chk` turns into a NaN if either is not finite (or rounds to Inf).
+__device__ __forceinline__ void split2(const float a, const float b, uint32_t &h, uint32_t &m, uint32_t &l, float &chk) {
+    h = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){a, b}, bf2));
+    const float ha = __uint_as_float(h << 16), hb = __uint_as_float(h & 0xffff0000u);
+    chk = fmaf(ha, 0.f, chk);
+    chk = fmaf(hb, 0.f, chk);
+    const float ra = a - ha, rb = b - hb;
+    m = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){ra, rb}, bf2));
+    const float ma = __uint_as_float(m << 16), mb = __uint_as_float(m & 0xffff0000u);
+    l = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){ra - ma, rb - mb}, bf2));
+}
+
+// acc += A B for one step of 16 input channels, both operands in three parts; the smallest products first
+__device__ __forceinline__ acc16 mma6(const u4v (&a)[3], const u4v (&b)[3], acc16 acc) {
+    const bf8 ah = __builtin_bit_cast(bf8, a[0]), am = __builtin_bit_cast(bf8, a[1]), al = __builtin_bit_cast(bf8, a[2]);
+    const bf8 bh = __builtin_bit_cast(bf8, b[0]), bm = __builtin_bit_cast(bf8, b[1]), bl = __builtin_bit_cast(bf8, b[2]);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bm, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bh, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bm, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc, 0, 0, 0);
+    return acc;
+}
+
+__device__ __forceinline__ acc16 zero16() {
+    acc16 z;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) z[r] = 0.f;
+    return z;
+}
+
+// Bytes of one position with C channels in the LDS: three parts, 16 bytes of padding.
+constexpr int row_bytes(int c) { return 6 * c + 16; }
+
+// One 32 x 32 result tile with bias and non-linearity into the LDS: `row` is the lane's position, channels
+// co0 + 8 (r / 4) + 4 half + r % 4.  Positions that do not exist (valid false) hold zeros.
+template <int C>
+__device__ __forceinline__ void store_tile(unsigned char *row, const int co0, const int half, const acc16 &acc,
+                                           const float *__restrict__ bias, const float slope, const bool valid, float &chk) {
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const int co = co0 + 8 * g + 4 * half;
+        const f4v b = *(const f4v *)(bias + co);
+        float y[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            y[c] = leaky_f(acc[4 * g + c] + b[c], slope);
+            y[c] = valid ? y[c] : 0.f;
+        }
+        u2v h, m, l;
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            uint32_t x, z, w;
+            split2(y[2 * c], y[2 * c + 1], x, z, w, chk);
+            h[c] = x; m[c] = z; l[c] = w;
+        }
+        *(u2v *)(row + 2 * co) = h;
+        *(u2v *)(row + 2 * C + 2 * co) = m;
+        *(u2v *)(row + 4 * C + 2 * co) = l;
+    }
+}
+
+// ---- weights as bf16 fragments --------------------------------------------------------------------
+// out[((mt * steps + s) * 3 + part) * 512 + lane * 8 + e], s = tap * (c_in / 16) + ci / 16: part `part` of
+// w[co = 32 mt + lane % 32][ci = 16 (s % (c_in / 16)) + 8 (lane / 32) + e][tap].  One thread per (mt, s, lane).
+// *bad counts the weights that are not finite (the handle then keeps to the fp32 kernels).
+__global__ __launch_bounds__(256) void k_weights_split(const float *__restrict__ w, uint16_t *__restrict__ out, int c_in, int c_out,
+                                                       int transposed, uint32_t *bad) {
+    const int steps = 3 * (c_in / 16), total = (c_out / 32) * steps * 64;
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= total) return;
+    const int lane = i & 63, s = (i >> 6) % steps, mt = (i >> 6) / steps;
+    const int tap = s / (c_in / 16), co = 32 * mt + (lane & 31), ci0 = 16 * (s % (c_in / 16)) + 8 * (lane >> 5);
+    uint16_t *o = out + (size_t)((i >> 6) * 3) * 512 + lane * 8;
+    float chk = 0.f;
+    for (int e = 0; e < 8; e += 2) {
+        float x[2];
+        for (int c = 0; c < 2; ++c) {
+            const int ci = ci0 + e + c;
+            x[c] = transposed ? w[((size_t)ci * c_out + co) * 3 + tap] : w[((size_t)co * c_in + ci) * 3 + tap];
+        }
+        uint32_t h, m, l;
+        split2(x[0], x[1], h, m, l, chk);
+        *(uint32_t *)(o + e) = h;
+        *(uint32_t *)(o + 512 + e) = m;
+        *(uint32_t *)(o + 1024 + e) = l;
+    }
+    if (chk != chk) atomicAdd(bad, 1u);
+}
+
+}  // namespace
+
+void launch_weights_split(const float *w, uint16_t *out, int c_in, int c_out, bool transposed, uint32_t *bad, hipStream_t st) {
+    const int total = (c_out / 32) * 3 * (c_in / 16) * 64;
+    hipLaunchKernelGGL(k_weights_split, dim3((total + 255) / 256), dim3(256), 0, st, w, out, c_in, c_out, (int)transposed, bad);
+}
+
+// ---- encoder ---------------------------------------------------------------------------------------
+// Four kernel-3 / stride-2 layers 1 -> C1 -> C2 -> C3 -> C4 and a kernel-1 layer C4 -> C5.
+
+struct EncoderDev {
+    const float *w1, *b1;                       // [C1][1][3]
+    const float *w2, *w3, *w4, *b2, *b3, *b4;   // [c_out][c_in][3]
+    const uint16_t *s2, *s3, *s4;               // the same as bf16 fragments
+    const float *w5, *b5;                       // [C5][C4][1]
+};
+
+namespace {
+
+// The K loop of one convolution for MT x NT tiles: steps [S0, S1) of 16 input channels, tap-major.  `b`: the LDS
+// rows of this lane's positions for tap 0; the odd positions lie `odd` bytes behind the even ones, so that a
+// stride-2 window (2i, 2i + 1, 2i + 2) is a read of row i of either half, and of row i + 1.  `a`: fragments of the first tile's
+// first step, this lane's 16 bytes; the tiles are a_tile (in 16-byte units) apart.  The fragments come from the L2:
+// DEPTH steps are kept in flight.
+template <int C, int MT, int NT, int S0, int S1, int DEPTH>
+__device__ __forceinline__ void conv_mma(acc16 (&acc)[MT][NT], const u4v *__restrict__ a, const int a_tile,
+                                         const unsigned char *const (&b)[NT], const int odd) {
+    constexpr int kPer = C / 16;   // steps per tap
+    u4v ra[DEPTH][MT][3];
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int p = 0; p < 3; ++p) ra[d][i][p] = a[i * a_tile + ((S0 + d) * 3 + p) * 64];
+#pragma unroll
+    for (int s = S0; s < S1; ++s) {
+        const int tap = s / kPer, at = 32 * (s % kPer);
+        u4v rb[NT][3];
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+                rb[j][p] = *(const u4v *)(b[j] + (tap == 1 ? odd : (tap >> 1) * row_bytes(C)) + p * 2 * C + at);
+        const int d = (s - S0) % DEPTH;
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] = mma6(ra[d][i], rb[j], acc[i][j]);
+        if (s + DEPTH < S1) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int p = 0; p < 3; ++p) ra[d][i][p] = a[i * a_tile + ((s + DEPTH) * 3 + p) * 64];
+        }
+    }
+}
+
+// The latent positions [p0, p0 + count) in plain fp32, one after the other (buf: 2700 floats).
+template <int C1, int C2, int C3, int C4, int C5>
+__device__ __forceinline__ void plain_encoder(const float *x, float *out, const EncoderDev &w, float *buf, const long long p0,
+                                           const int count, const long long l0, const long long l1, const long long l2,
+                                           const long long l3, const long long l4, const float slope) {
+    float *h1 = buf, *h2 = h1 + 15 * C1, *h3 = h2 + 7 * C2, *h4 = h3 + 3 * C3;
+    const int tid = threadIdx.x, nt = blockDim.x;
+    auto layer = [&](const float *in, float *o, const float *wt, const float *bias, int c_in, int c_out, int n, long long q0, long long len) {
+        for (int i = tid; i < n * c_out; i += nt) {
+            const int j = i / c_out, co = i % c_out;
+            float a = bias[co];
+#pragma unroll 1
+            for (int ci = 0; ci < c_in; ++ci)
+                for (int t = 0; t < 3; ++t) a = fmaf(wt[((size_t)co * c_in + ci) * 3 + t], in[(2 * j + t) * c_in + ci], a);
+            o[i] = q0 + j >= 0 && q0 + j < len ? leaky_f(a, slope) : 0.f;
+        }
+        __syncthreads();
+    };
+#pragma unroll 1
+    for (int r = 0; r < count; ++r) {
+        const long long p = p0 + r;
+        for (int i = tid; i < 15 * C1; i += nt) {
+            const int j = i / C1, co = i % C1;
+            const long long q = 8 * p - 7 + j;
+            float a = w.b1[co];
+            for (int t = 0; t < 3; ++t) {
+                const long long e = 2 * q - 1 + t;
+                a = fmaf(w.w1[co * 3 + t], e >= 0 && e < l0 ? x[e] : 0.f, a);
+            }
+            h1[i] = q >= 0 && q < l1 ? leaky_f(a, slope) : 0.f;
+        }
+        __syncthreads();
+        layer(h1, h2, w.w2, w.b2, C1, C2, 7, 4 * p - 3, l2);
+        layer(h2, h3, w.w3, w.b3, C2, C3, 3, 2 * p - 1, l3);
+        layer(h3, h4, w.w4, w.b4, C3, C4, 1, p, l4);
+        if (tid < C5) {
+            float a = w.b5[tid];
+#pragma unroll 1
+            for (int ci = 0; ci < C4; ++ci) a = fmaf(w.w5[tid * C4 + ci], h4[ci], a);
+            out[(size_t)tid * l4 + p] = a;
+        }
+        __syncthreads();
+    }
+}
+
+}  // namespace
+
+// P latent positions per block of W wavefronts.  Local numbering: conv3's position i is 2 p0 - 1 + i, conv2's 4 p0 - 3 + i,
+// conv1's 8 p0 - 7 + i, the input's 16 p0 - 15 + i, so that position i of one layer takes 2i, 2i + 1, 2i + 2 of
+// the layer before; 2P + 1, 4P + 3, 8P + 7 and 16P + 15 of them are needed, and the tiles hold one more.
+template <int C1, int C2, int C3, int C4, int C5, int P, int W>
+__global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restrict__ x, float *__restrict__ out, EncoderDev w,
+                                                          uint32_t l0, uint32_t l1, uint32_t l2, uint32_t l3, uint32_t l4,
+                                                          float slope) {
+    constexpr int N4 = P + 1, N3 = 2 * N4, N2 = 4 * N4;   // tile widths (positions) of conv4, conv3, conv2
+    constexpr int R1 = row_bytes(C1), R2 = row_bytes(C2), R3 = row_bytes(C3);
+    constexpr int kBytes1 = (2 * N2 + 1) * R1, kBytes2 = (2 * N3 + 1) * R2, kBytes3 = (2 * N4 + 1) * R3;
+    constexpr int kBytes = kBytes1 > kBytes2 ? (kBytes1 > kBytes3 ? kBytes1 : kBytes3) : (kBytes2 > kBytes3 ? kBytes2 : kBytes3);
+    constexpr int kSplit = W / (C4 / 32);                 // conv4: wavefronts that share a tile, each a run of its steps
+    static_assert(C1 % 16 == 0 && C2 % 32 == 0 && C3 % 32 == 0 && C4 % 32 == 0 && N3 % 32 == 0 && N4 <= 32 && C5 <= 4, "tiles");
+    static_assert(kBytes >= (15 * C1 + 7 * C2 + 3 * C3 + C4) * 4, "plain_encoder's buffer");
+    __shared__ __align__(16) unsigned char buf[kBytes];
+    __shared__ float xs[4 * N2 + 4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, col = lane & 31;
+    const long long p0 = (long long)blockIdx.x * P;
+    x += (size_t)blockIdx.y * l0;
+    out += (size_t)blockIdx.y * C5 * l4;
+    float chk = 0.f;
+
+    for (int i = tid; i < 4 * N2 + 3; i += W * 64) {
+        const long long e = 16 * p0 - 15 + i;
+        xs[i] = e >= 0 && e < (long long)l0 ? x[e] : 0.f;
+    }
+    __syncthreads();
+
+    // conv1: a wavefront takes 64 positions x 8 channels at a time (weights wave-uniform)
+#pragma unroll 1
+    for (int unit = wave; unit < (C1 / 8) * (2 * N2 / 64); unit += W) {
+        const int o8 = unit % (C1 / 8), i = (unit / (C1 / 8)) * 64 + lane;
+        const long long q = 8 * p0 - 7 + i;
+        const bool valid = q >= 0 && q < (long long)l1;
+        const float x0 = xs[2 * i], x1 = xs[2 * i + 1], x2 = xs[2 * i + 2];
+        float y[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const float *wc = w.w1 + (o8 * 8 + c) * 3;
+            float a = w.b1[o8 * 8 + c];
+            a = fmaf(wc[0], x0, a);
+            a = fmaf(wc[1], x1, a);
+            a = fmaf(wc[2], x2, a);
+            y[c] = valid ? leaky_f(a, slope) : 0.f;
+        }
+        u4v h, m, l;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            uint32_t a, b, d;
+            split2(y[2 * c], y[2 * c + 1], a, b, d, chk);
+            h[c] = a; m[c] = b; l[c] = d;
+        }
+        unsigned char *row = buf + ((i & 1) ? (N2 + 1) * R1 : 0) + (i >> 1) * R1 + o8 * 16;
+        *(u4v *)row = h;
+        *(u4v *)(row + 2 * C1) = m;
+        *(u4v *)(row + 4 * C1) = l;
+    }
+    __syncthreads();
+
+    {   // conv2: C2 / 32 channel tiles x N2 / 32 position tiles
+        constexpr int kM = C2 / 32, kNW = W / kM, NT = N2 / 32 / kNW;
+        static_assert(W % kM == 0 && (N2 / 32) % kNW == 0, "conv2 tiles");
+        const int mt = wave / kNW, n0 = (wave % kNW) * NT;
+        acc16 acc[1][NT];
+        const unsigned char *b[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) { acc[0][j] = zero16(); b[j] = buf + ((n0 + j) * 32 + col) * R1 + half * 16; }
+        conv_mma<C1, 1, NT, 0, 3 * C1 / 16, 3>(acc, (const u4v *)w.s2 + (size_t)mt * (3 * C1 / 16) * 192 + lane, 0, b, (N2 + 1) * R1);
+        __syncthreads();   // conv1's outputs have been read
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int i = (n0 + j) * 32 + col;
+            const long long q = 4 * p0 - 3 + i;
+            store_tile<C2>(buf + ((i & 1) ? (N3 + 1) * R2 : 0) + (i >> 1) * R2, mt * 32, half, acc[0][j], w.b2, slope,
+                           q >= 0 && q < (long long)l2 && i < N2 - 1, chk);
+        }
+    }
+    __syncthreads();
+
+    {   // conv3
+        constexpr int kM = C3 / 32, kMW = kM < W ? kM : W, MT = kM / kMW, kNW = W / kMW, NT = N3 / 32 / kNW;
+        static_assert(kM % kMW == 0 && W % kMW == 0 && (N3 / 32) % kNW == 0, "conv3 tiles");
+        const int m0 = (wave / kNW) * MT, n0 = (wave % kNW) * NT;
+        acc16 acc[MT][NT];
+        const unsigned char *b[NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            b[j] = buf + ((n0 + j) * 32 + col) * R2 + half * 16;
+#pragma unroll
+            for (int i = 0; i < MT; ++i) acc[i][j] = zero16();
+        }
+        conv_mma<C2, MT, NT, 0, 3 * C2 / 16, 3>(acc, (const u4v *)w.s3 + (size_t)m0 * (3 * C2 / 16) * 192 + lane, (3 * C2 / 16) * 192, b,
+                                                (N3 + 1) * R2);
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            const int i = (n0 + j) * 32 + col;
+            const long long q = 2 * p0 - 1 + i;
+            unsigned char *row = buf + ((i & 1) ? (N4 + 1) * R3 : 0) + (i >> 1) * R3;
+#pragma unroll
+            for (int k = 0; k < MT; ++k)
+                store_tile<C3>(row, (m0 + k) * 32, half, acc[k][j], w.b3, slope, q >= 0 && q < (long long)l3 && i < N3 - 1, chk);
+        }
+    }
+    __syncthreads();
+
+    float *part = (float *)buf;                               // conv4's partial sums [kSplit][C4][33]
+    float *red = part + kSplit * C4 * 33;                     // conv5's [W * 2][C5][32]
+    static_assert(kBytes >= (kSplit * C4 * 33 + W * 2 * C5 * 32) * 4, "partial sums");
+    {   // conv4: one position tile (of which N4 columns are used); the steps are shared out over kSplit wavefronts
+        constexpr int kSteps = 3 * C3 / 16 / kSplit;
+        static_assert((3 * C3 / 16) % kSplit == 0, "conv4 steps");
+        const int mt = wave / kSplit, ks = wave % kSplit;
+        acc16 acc[1][1];
+        acc[0][0] = zero16();
+        const int c4 = col < N4 ? col : N4 - 1;
+        const u4v *a = (const u4v *)w.s4 + (size_t)mt * (3 * C3 / 16) * 192 + lane;
+        const unsigned char *b[1] = {buf + c4 * R3 + half * 16};
+        auto run = [&](auto k) {
+            constexpr int S = decltype(k)::value;
+            conv_mma<C3, 1, 1, S * kSteps, (S + 1) * kSteps, 4>(acc, a, 0, b, (N4 + 1) * R3);
+        };
+        if (ks == 0) run(std::integral_constant<int, 0>());    // wave-uniform
+        else if (ks == 1) run(std::integral_constant<int, 1 % kSplit>());
+        else if (ks == 2) run(std::integral_constant<int, 2 % kSplit>());
+        else run(std::integral_constant<int, 3 % kSplit>());
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+            part[(ks * C4 + mt * 32 + (r >> 2) * 8 + half * 4 + (r & 3)) * 33 + col] = acc[0][0][r];
+    }
+    __syncthreads();
+    {   // conv4's sums, bias and non-linearity; conv5's sums over this thread's channels
+        constexpr int kGroups = W * 2, kCh = C4 / kGroups;
+        const int p = tid & 31, cg = tid >> 5;
+        float t[C5];
+#pragma unroll
+        for (int c = 0; c < C5; ++c) t[c] = 0.f;
+#pragma unroll
+        for (int i = 0; i < kCh; ++i) {
+            const int co = cg * kCh + i;
+            float y = part[co * 33 + p];
+#pragma unroll
+            for (int s = 1; s < kSplit; ++s) y += part[(s * C4 + co) * 33 + p];
+            y = leaky_f(y + w.b4[co], slope);
+#pragma unroll
+            for (int c = 0; c < C5; ++c) t[c] = fmaf(w.w5[c * C4 + co], y, t[c]);
+        }
+#pragma unroll
+        for (int c = 0; c < C5; ++c) red[(cg * C5 + c) * 32 + p] = t[c];
+    }
+    __syncthreads();
+    const int c = tid >> 5, p = tid & 31;
+    const bool mine = c < C5 && p < P && p0 + p < (long long)l4;
+    float z = 0.f;
+    if (mine) {
+        z = w.b5[c];
+#pragma unroll
+        for (int g = 0; g < W * 2; ++g) z += red[(g * C5 + c) * 32 + p];
+        chk = fmaf(z, 0.f, chk);
+    }
+    if (!__syncthreads_or(chk != chk)) {
+        if (mine) out[(size_t)c * l4 + p0 + p] = z;
+        return;
+    }
+    const long long left = (long long)l4 - p0;
+    plain_encoder<C1, C2, C3, C4, C5>(x, out, w, (float *)buf, p0, left < P ? (int)left : P, l0, l1, l2, l3, l4, slope);
+}
+
+// ---- decoder ---------------------------------------------------------------------------------------
+// A kernel-3 / stride-1 transposed layer D0 -> D1, four kernel-3 / stride-2 ones D1 -> D2 -> D3 -> D4 -> D5 and a
+// kernel-1 layer D5 -> 1.  A stride-2 transposed layer is two products: output 2m from input m (tap 1), output
+// 2m + 1 from inputs m (tap 2) and m + 1 (tap 0).
+
+struct DecoderDev {
+    const float *w1, *w2, *w3, *w4, *w5, *w6;   // [c_in][c_out][3]; w6 [D5]
+    const float *b1, *b2, *b3, *b4, *b5, *b6;
+    const uint16_t *s3, *s4, *s5;               // the deep layers as bf16 fragments
+};
+
+namespace {
+
+// Fragments of one step of 16 input channels: the three parts of one tap
+__device__ __forceinline__ void load_a(u4v (&r)[3], const u4v *__restrict__ a, const int step) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) r[p] = a[(step * 3 + p) * 64];
+}
+
+template <int C>
+__device__ __forceinline__ void load_b(u4v (&r)[3], const unsigned char *b, const int at) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) r[p] = *(const u4v *)(b + p * 2 * C + at);
+}
+
+// The outputs of the latent positions [p0, p0 + count) in plain fp32, one position after the other.
+template <int D0, int D1, int D2, int D3, int D4, int D5>
+__device__ __forceinline__ void plain_decoder(const float *z, float *out, const DecoderDev &w, float *buf, const long long p0,
+                                           const int count, const long long lz, const long long l2, const long long l3,
+                                           const long long l4, const long long l5, const float slope) {
+    float *h1 = buf, *h2 = h1 + 2 * D1, *h3 = h2 + 3 * D2, *h4 = h3 + 5 * D3, *h5 = h4 + 9 * D4;
+    const int tid = threadIdx.x, nt = blockDim.x;
+    // n outputs from 2 m0 on, inputs from m0 on
+    auto layer = [&](const float *in, float *o, const float *wt, const float *bias, int c_in, int c_out, int n, long long q0, long long len) {
+        for (int i = tid; i < n * c_out; i += nt) {
+            const int j = i / c_out, co = i % c_out, m = j >> 1;
+            float a = bias[co];
+#pragma unroll 1
+            for (int ci = 0; ci < c_in; ++ci) {
+                const float *wc = wt + ((size_t)ci * c_out + co) * 3;
+                if (j & 1) {
+                    a = fmaf(wc[0], in[(m + 1) * c_in + ci], a);
+                    a = fmaf(wc[2], in[m * c_in + ci], a);
+                } else {
+                    a = fmaf(wc[1], in[m * c_in + ci], a);
+                }
+            }
+            o[i] = q0 + j < len ? leaky_f(a, slope) : 0.f;
+        }
+        __syncthreads();
+    };
+#pragma unroll 1
+    for (int r = 0; r < count; ++r) {
+        const long long p = p0 + r;
+        for (int i = tid; i < 2 * D1; i += nt) {
+            const int j = i / D1, co = i % D1;
+            float a = w.b1[co];
+            for (int ci = 0; ci < D0; ++ci)
+                for (int t = 0; t < 3; ++t) {
+                    const long long e = p + j + 1 - t;
+                    a = fmaf(w.w1[(ci * D1 + co) * 3 + t], e >= 0 && e < lz ? z[(size_t)ci * lz + e] : 0.f, a);
+                }
+            h1[i] = p + j < lz ? leaky_f(a, slope) : 0.f;
+        }
+        __syncthreads();
+        layer(h1, h2, w.w2, w.b2, D1, D2, 3, 2 * p, l2);
+        layer(h2, h3, w.w3, w.b3, D2, D3, 5, 4 * p, l3);
+        layer(h3, h4, w.w4, w.b4, D3, D4, 9, 8 * p, l4);
+        layer(h4, h5, w.w5, w.b5, D4, D5, 16, 16 * p, l5);
+        if (tid < 16 && 16 * p + tid < l5) {
+            float a = w.b6[0];
+#pragma unroll 1
+            for (int ci = 0; ci < D5; ++ci) a = fmaf(w.w6[ci], h5[tid * D5 + ci], a);
+            out[16 * p + tid] = a;
+        }
+        __syncthreads();
+    }
+}
+
+}  // namespace
+
+// T latent positions per block of four wavefronts.  Local numbering from 1, 2, 4, 8 and 16 p0 on: T + 1 outputs of
+// deconv1, 2T + 1 of deconv2, 4T + 1 of deconv3, 8T + 1 of deconv4 and 16T of deconv5.  deconv4's outputs are made
+// and consumed in two runs of D4 / 2 channels, so that two blocks fit a compute unit's LDS.
+template <int D0, int D1, int D2, int D3, int D4, int D5, int T>
+__global__ __launch_bounds__(256) void k_decoder_fused(const float *__restrict__ z, float *__restrict__ out, DecoderDev w,
+                                                       uint32_t lz, uint32_t l2, uint32_t l3, uint32_t l4, uint32_t l5,
+                                                       float slope) {
+    constexpr int M3 = 2 * (T + 1), M4 = 4 * (T + 1), M5 = 8 * (T + 1);   // tile widths: input positions of deconv3, 4, 5
+    constexpr int CH = D4 / 2;                                             // channels of deconv4 per run
+    constexpr int R2 = row_bytes(D2), R3 = row_bytes(D3), R4 = row_bytes(CH);
+    constexpr int kBytesA = (M5 + 1) * R4, kBytesB = (M4 + 1) * R3;
+    static_assert(M3 == 32 && M4 == 64 && M5 == 128 && D2 % 16 == 0 && D3 == 64 && CH == 64 && D5 == 32, "tiles");
+    static_assert((M3 + 1) * R2 <= kBytesA && 4 * 2 * 1024 * 4 <= kBytesA, "region A");
+    static_assert((2 * D1 + 3 * D2 + 5 * D3 + 9 * D4 + 16 * D5) * 4 <= kBytesA, "plain_decoder's buffer");
+    __shared__ __align__(16) unsigned char bufA[kBytesA];   // deconv2's outputs, then deconv4's run by run
+    __shared__ __align__(16) unsigned char bufB[kBytesB];   // deconv3's outputs
+    __shared__ float zs[D0 * (T + 3)], h1[D1 * (T + 1)];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, col = lane & 31;
+    const long long p0 = (long long)blockIdx.x * T;
+    z += (size_t)blockIdx.y * D0 * lz;
+    out += (size_t)blockIdx.y * l5;
+    float chk = 0.f;
+
+    for (int i = tid; i < D0 * (T + 3); i += 256) {
+        const int c = i / (T + 3);
+        const long long e = p0 - 1 + i % (T + 3);
+        zs[i] = e >= 0 && e < (long long)lz ? z[(size_t)c * lz + e] : 0.f;
+    }
+    __syncthreads();
+    for (int i = tid; i < D1 * (T + 1); i += 256) {   // deconv1
+        const int c = i / (T + 1), j = i % (T + 1);
+        float a = w.b1[c];
+#pragma unroll
+        for (int ci = 0; ci < D0; ++ci) {
+            const float *wc = w.w1 + (ci * D1 + c) * 3, *zc = zs + ci * (T + 3) + j;
+            a = fmaf(wc[0], zc[2], a);
+            a = fmaf(wc[1], zc[1], a);
+            a = fmaf(wc[2], zc[0], a);
+        }
+        h1[i] = p0 + j < (long long)lz ? leaky_f(a, slope) : 0.f;
+    }
+    __syncthreads();
+    {   // deconv2: thread = position x group of D2 / 8 channels
+        constexpr int kCh = D2 / 8;
+        const int j = tid & 31, cg = tid >> 5, m = j >> 1;
+        const bool odd = j & 1, valid = 2 * p0 + j < (long long)l2 && j < 2 * T + 1;
+        float y[kCh];
+#pragma unroll
+        for (int c = 0; c < kCh; ++c) y[c] = w.b2[cg * kCh + c];
+#pragma unroll
+        for (int ci = 0; ci < D1; ++ci) {
+            const float x0 = h1[ci * (T + 1) + m], x1 = m < T ? h1[ci * (T + 1) + m + 1] : 0.f;
+#pragma unroll
+            for (int c = 0; c < kCh; ++c) {
+                const float *wc = w.w2 + (ci * D2 + cg * kCh + c) * 3;
+                const float e = fmaf(wc[1], x0, y[c]), o = fmaf(wc[2], x0, fmaf(wc[0], x1, y[c]));
+                y[c] = odd ? o : e;
+            }
+        }
+        unsigned char *row = bufA + j * R2 + cg * kCh * 2;
+#pragma unroll
+        for (int c = 0; c < kCh; c += 2) {
+            uint32_t h, m_, l;
+            split2(valid ? leaky_f(y[c], slope) : 0.f, valid ? leaky_f(y[c + 1], slope) : 0.f, h, m_, l, chk);
+            *(uint32_t *)(row + 2 * c) = h;
+            *(uint32_t *)(row + 2 * D2 + 2 * c) = m_;
+            *(uint32_t *)(row + 4 * D2 + 2 * c) = l;
+        }
+    }
+    __syncthreads();
+    {   // deconv3: wavefront = channel tile x (even or odd outputs)
+        constexpr int kPer = D2 / 16;
+        const int mt = wave & 1, par = wave >> 1;
+        const u4v *a = (const u4v *)w.s3 + (size_t)mt * 3 * kPer * 192 + lane;
+        const unsigned char *b = bufA + col * R2 + half * 16;
+        acc16 acc = zero16();
+        u4v ra[3], rb[3];
+#pragma unroll
+        for (int s = 0; s < kPer; ++s) {
+            load_a(ra, a, (par ? 2 : 1) * kPer + s);
+            load_b<D2>(rb, b, 32 * s);
+            acc = mma6(ra, rb, acc);
+            if (par) {
+                load_a(ra, a, s);
+                load_b<D2>(rb, b + R2, 32 * s);
+                acc = mma6(ra, rb, acc);
+            }
+        }
+        const int i = 2 * col + par;
+        store_tile<D3>(bufB + i * R3, mt * 32, half, acc, w.b3, slope, 4 * p0 + i < (long long)l3 && i < 4 * T + 1, chk);
+    }
+    __syncthreads();
+
+    const int np = wave & 1, kh = wave >> 1;   // deconv5: wavefront = pair of position tiles x half of each run's channels
+    acc16 e5[2], o5[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) { e5[j] = zero16(); o5[j] = zero16(); }
+#pragma unroll 1
+    for (int run = 0; run < 2; ++run) {
+        {   // deconv4: wavefront = channel tile of the run x position tile, even and odd outputs
+            constexpr int kPer = D3 / 16;
+            const int mt = wave & 1, n0 = wave >> 1;
+            const u4v *a = (const u4v *)w.s4 + (size_t)(2 * run + mt) * 3 * kPer * 192 + lane;
+            const unsigned char *b = bufB + (n0 * 32 + col) * R3 + half * 16;
+            acc16 even = zero16(), odd = zero16();
+#pragma unroll
+            for (int s = 0; s < kPer; ++s) {
+                u4v a0[3], a1[3], a2[3], x0[3], x1[3];
+                load_a(a1, a, kPer + s);
+                load_a(a2, a, 2 * kPer + s);
+                load_a(a0, a, s);
+                load_b<D3>(x0, b, 32 * s);
+                load_b<D3>(x1, b + R3, 32 * s);
+                even = mma6(a1, x0, even);
+                odd = mma6(a2, x0, odd);
+                odd = mma6(a0, x1, odd);
+            }
+            if (run) __syncthreads();   // the previous run's outputs have been read
+            const int i = 2 * (n0 * 32 + col);
+            const float *bias = w.b4 + run * CH;
+            store_tile<CH>(bufA + i * R4, mt * 32, half, even, bias, slope, 8 * p0 + i < (long long)l4 && i < 8 * T + 1, chk);
+            store_tile<CH>(bufA + (i + 1) * R4, mt * 32, half, odd, bias, slope, 8 * p0 + i + 1 < (long long)l4 && i + 1 < 8 * T + 1, chk);
+        }
+        __syncthreads();
+        {   // deconv5, this run's channels
+            constexpr int kPer = D4 / 16;
+            const u4v *a = (const u4v *)w.s5 + lane;
+#pragma unroll
+            for (int q = 0; q < CH / 32; ++q) {
+                const int sl = kh * (CH / 32) + q, s = run * (CH / 16) + sl;   // step inside the run, and over all channels
+                u4v a0[3], a1[3], a2[3];
+                load_a(a1, a, kPer + s);
+                load_a(a2, a, 2 * kPer + s);
+                load_a(a0, a, s);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) {
+                    const unsigned char *b = bufA + ((np * 2 + j) * 32 + col) * R4 + half * 16;
+                    u4v x0[3], x1[3];
+                    load_b<CH>(x0, b, 32 * sl);
+                    load_b<CH>(x1, b + R4, 32 * sl);
+                    e5[j] = mma6(a1, x0, e5[j]);
+                    o5[j] = mma6(a2, x0, o5[j]);
+                    o5[j] = mma6(a0, x1, o5[j]);
+                }
+            }
+        }
+    }
+    __syncthreads();
+    // the two halves of the contraction meet: wavefront (np, kh) finishes tile 2 np + kh and hands the other one over
+    float *swap = (float *)bufA;
+    {
+        float *to = swap + (size_t)wave * 2048 + lane;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            to[r * 64] = kh ? e5[0][r] : e5[1][r];
+            to[1024 + r * 64] = kh ? o5[0][r] : o5[1][r];
+        }
+    }
+    __syncthreads();
+    float se = 0.f, so = 0.f;
+    {
+        const float *from = swap + (size_t)(np + 2 * (kh ^ 1)) * 2048 + lane;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int co = (r >> 2) * 8 + half * 4 + (r & 3);
+            const float bv = w.b5[co], wv = w.w6[co];
+            const float ye = (kh ? e5[1][r] : e5[0][r]) + from[r * 64] + bv;
+            const float yo = (kh ? o5[1][r] : o5[0][r]) + from[1024 + r * 64] + bv;
+            se = fmaf(wv, leaky_f(ye, slope), se);
+            so = fmaf(wv, leaky_f(yo, slope), so);
+        }
+    }
+    se += __shfl_xor(se, 32, 64);
+    so += __shfl_xor(so, 32, 64);
+    const int m = (np * 2 + kh) * 32 + col, i = 2 * m + half;   // lanes 0..31 store the even, lanes 32..63 the odd outputs
+    const bool mine = m < 8 * T && 16 * p0 + i < (long long)l5;
+    const float y = w.b6[0] + (half ? so : se);
+    if (mine) chk = fmaf(y, 0.f, chk);
+    if (!__syncthreads_or(chk != chk)) {
+        if (mine) out[16 * p0 + i] = y;
+        return;
+    }
+    const long long left = (long long)lz - p0;
+    plain_decoder<D0, D1, D2, D3, D4, D5>(z, out, w, (float *)bufA, p0, left < T ? (int)left : T, lz, l2, l3, l4, l5, slope);
+}
+
+// ---- launchers ---------------------------------------------------------------------------------------
+
+static bool is_layer(const LayerDev &l, int ci, int co, int ks, int st) {
+    return l.c_in == ci && l.c_out == co && l.ksize == ks && l.stride == st;
+}
+
+bool encoder_fused_covers(const LayerDev *l, int count) {
+    return count == 5 && is_layer(l[0], 1, 64, 3, 2) && is_layer(l[1], 64, 128, 3, 2) && is_layer(l[2], 128, 256, 3, 2) &&
+           is_layer(l[3], 256, 64, 3, 2) && is_layer(l[4], 64, 4, 1, 1);
+}
+
+bool decoder_fused_covers(const LayerDev *l, int count) {
+    return count == 6 && is_layer(l[0], 4, 4, 3, 1) && is_layer(l[1], 4, 32, 3, 2) && is_layer(l[2], 32, 64, 3, 2) &&
+           is_layer(l[3], 64, 128, 3, 2) && is_layer(l[4], 128, 32, 3, 2) && is_layer(l[5], 32, 1, 1, 1);
+}
+
+bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int count, const uint64_t *len, int batch, float slope,
+                          hipStream_t st) {
+    if (!encoder_fused_covers(l, count) || !l[1].ws || !l[2].ws || !l[3].ws) return false;
+    const uint32_t l4 = (uint32_t)len[4];
+    if (l4 == 0) return true;
+    EncoderDev w;
+    w.w1 = l[0].w; w.b1 = l[0].b;
+    w.w2 = l[1].w; w.b2 = l[1].b; w.s2 = l[1].ws;
+    w.w3 = l[2].w; w.b3 = l[2].b; w.s3 = l[2].ws;
+    w.w4 = l[3].w; w.b4 = l[3].b; w.s4 = l[3].ws;
+    w.w5 = l[4].w; w.b5 = l[4].b;
+    constexpr int P = 15;
+    hipLaunchKernelGGL((k_encoder_fused<64, 128, 256, 64, 4, P, 4>), dim3((l4 + P - 1) / P, batch), dim3(256), 0, st, x, out, w,
+                       (uint32_t)len[0], (uint32_t)len[1], (uint32_t)len[2], (uint32_t)len[3], l4, slope);
+    return true;
+}
+
+bool launch_decoder_fused(const float *z, float *out, const LayerDev *l, int count, uint64_t l_z, const uint64_t *len, int batch,
+                          float slope, hipStream_t st) {
+    if (!decoder_fused_covers(l, count) || !l[2].ws || !l[3].ws || !l[4].ws) return false;
+    if (len[4] == 0) return true;
+    DecoderDev w;
+    w.w1 = l[0].w; w.b1 = l[0].b;
+    w.w2 = l[1].w; w.b2 = l[1].b;
+    w.w3 = l[2].w; w.b3 = l[2].b; w.s3 = l[2].ws;
+    w.w4 = l[3].w; w.b4 = l[3].b; w.s4 = l[3].ws;
+    w.w5 = l[4].w; w.b5 = l[4].b; w.s5 = l[4].ws;
+    w.w6 = l[5].w; w.b6 = l[5].b;
+    constexpr int T = 15;
+    hipLaunchKernelGGL((k_decoder_fused<4, 4, 32, 64, 128, 32, T>), dim3(((uint32_t)l_z + T - 1) / T, batch), dim3(256), 0, st, z, out, w,
+                       (uint32_t)l_z, (uint32_t)len[1], (uint32_t)len[2], (uint32_t)len[3], (uint32_t)len[4], slope);
+    return true;
+}
+
+}  // namespace lgc

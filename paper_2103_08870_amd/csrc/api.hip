@@ -74,6 +74,7 @@ struct lgc_ae {
     std::vector<LayerDev> enc_dev, dec_dev;
     float *weights = nullptr;  // device copy of all weights and biases
     float *weights_t = nullptr;  // contraction-major copies for the layers that run on the matrix cores
+    uint16_t *weights_s = nullptr;  // copies as bf16 fragments in three parts for the stacks that run as one launch
 };
 
 static thread_local char g_err[256] = "";
@@ -669,9 +670,39 @@ extern "C" lgc_status lgc_ae_create(lgc_ae **out, int device, int n_enc, const l
             if (e == hipSuccess) e = hipGetLastError();
         }
     }
+    if (e == hipSuccess) {
+        // stacks that run as one launch: their deep layers' weights as bf16 fragments (as long as all are finite)
+        const bool fe = encoder_fused_covers(ae->enc_dev.data(), n_enc), fd = decoder_fused_covers(ae->dec_dev.data(), n_dec);
+        auto size = [](const LayerDev &l) { return (size_t)l.c_in * l.c_out * 3 * 3; };   // 3 taps, 3 parts
+        size_t s_total = 0;
+        if (fe) for (int l = 1; l <= 3; ++l) s_total += size(ae->enc_dev[l]);
+        if (fd) for (int l = 2; l <= 4; ++l) s_total += size(ae->dec_dev[l]);
+        if (s_total) {
+            e = hipMalloc((void **)&ae->weights_s, s_total * 2 + 4);
+            uint32_t *bad = (uint32_t *)(ae->weights_s + s_total), host_bad = 0;   // s_total is even
+            if (e == hipSuccess) e = hipMemset(bad, 0, 4);
+            size_t s_off = 0;
+            auto split = [&](LayerDev &l, bool transposed) {
+                launch_weights_split(l.w, ae->weights_s + s_off, l.c_in, l.c_out, transposed, bad, nullptr);
+                l.ws = ae->weights_s + s_off;
+                s_off += size(l);
+            };
+            if (e == hipSuccess) {
+                if (fe) for (int l = 1; l <= 3; ++l) split(ae->enc_dev[l], false);
+                if (fd) for (int l = 2; l <= 4; ++l) split(ae->dec_dev[l], true);
+                e = hipGetLastError();
+            }
+            if (e == hipSuccess) e = hipMemcpy(&host_bad, bad, 4, hipMemcpyDeviceToHost);
+            if (e == hipSuccess && host_bad) {
+                for (auto &l : ae->enc_dev) l.ws = nullptr;
+                for (auto &l : ae->dec_dev) l.ws = nullptr;
+            }
+        }
+    }
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         if (ae->weights_t) (void)hipFree(ae->weights_t);
+        if (ae->weights_s) (void)hipFree(ae->weights_s);
         (void)hipFree(ae->weights);
         delete ae;
         return fail(nullptr, LGC_EHIP, "copying autoencoder weights: %s", hipGetErrorString(e));
@@ -686,6 +717,7 @@ extern "C" void lgc_ae_destroy(lgc_ae *ae) {
     (void)hipDeviceSynchronize();
     if (ae->weights) (void)hipFree(ae->weights);
     if (ae->weights_t) (void)hipFree(ae->weights_t);
+    if (ae->weights_s) (void)hipFree(ae->weights_s);
     delete ae;
 }
 
@@ -794,6 +826,11 @@ static lgc_status run_encode(lgc_ctx *ctx, const lgc_ae *ae, const float *vals, 
     if (need > ctx->act_floats)
         return fail(ctx, LGC_EINVAL, "lgc_encode: activation scratch for k = %llu, batch = %d not reserved: call "
                                      "lgc_reserve(ctx, ae, k, batch, NULL) once beforehand", (unsigned long long)k, batch);
+    if (launch_encoder_fused(vals, latent, ae->enc_dev.data(), (int)nl, len.data(), batch, ae->slope, st)) {
+        hipError_t e1 = hipGetLastError();
+        if (e1 != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e1));
+        return LGC_OK;
+    }
     const float *cur = vals;
     // a layer never writes the buffer it reads: the activation buffer that is not `cur`
     auto other = [&](const float *c) { return c == ctx->act[0] ? ctx->act[1] : ctx->act[0]; };
@@ -886,6 +923,11 @@ static lgc_status run_decode(lgc_ctx *ctx, const lgc_ae *ae, const float *latent
     if (need > ctx->act_floats)
         return fail(ctx, LGC_EINVAL, "lgc_decode: activation scratch for k = %llu, batch = %d not reserved: call "
                                      "lgc_reserve(ctx, ae, k, batch, NULL) once beforehand", (unsigned long long)k, batch);
+    if (!innov && launch_decoder_fused(latent, rec, ae->dec_dev.data(), (int)nl, in_len, out_len.data(), batch, ae->slope, st)) {
+        hipError_t e1 = hipGetLastError();
+        if (e1 != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e1));
+        return LGC_OK;
+    }
     const float *cur = latent;
     // a layer never writes the buffer it reads: the activation buffer that is not `cur`
     auto other = [&](const float *c) { return c == ctx->act[0] ? ctx->act[1] : ctx->act[0]; };

@@ -175,6 +175,7 @@ struct LayerDev {
     int c_in, c_out, ksize, stride;
     const float *w, *b;         // device
     const float *wt = nullptr;  // device: weights in contraction-major order for the MFMA kernels, or null
+    const uint16_t *ws = nullptr;  // device: weights as bf16 fragments in three parts for the fused stacks, or null
 };
 void launch_conv1d(const float *in, float *out, const LayerDev &l, uint32_t l_in, uint32_t l_out,
                    int batch, bool act, float slope, hipStream_t st);
@@ -214,6 +215,16 @@ bool launch_convt3s2_mfma(const float *in, float *out, const LayerDev &l, uint32
 bool launch_convt3s2_mfma_head(const float *z, float *out, const LayerDev &h1, const LayerDev &h2, const LayerDev &l,
                                uint32_t l_z, uint32_t l_in, uint32_t l_out, int batch, bool act, float slope,
                                hipStream_t st);
+// ae_fused.hip: the whole stacks of Table I / Table II in one launch each; false = stack not covered (nothing
+// launched).  len: encoder: input length, then every layer's output length; decoder: every layer's output length.
+bool encoder_fused_covers(const LayerDev *l, int count);
+bool decoder_fused_covers(const LayerDev *l, int count);
+// *bad (device): incremented if a weight is not finite
+void launch_weights_split(const float *w, uint16_t *out, int c_in, int c_out, bool transposed, uint32_t *bad, hipStream_t st);
+bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int count, const uint64_t *len, int batch, float slope,
+                          hipStream_t st);
+bool launch_decoder_fused(const float *z, float *out, const LayerDev *l, int count, uint64_t l_z, const uint64_t *len, int batch,
+                          float slope, hipStream_t st);
 void launch_gather_at(float *v, float *u, uint64_t stride, uint32_t n, int batch, const uint32_t *idx, uint32_t k,
                       float *out, Stats *stats, hipStream_t st);
 void launch_average(const float *x, uint32_t len, int batch, float scale, float *out, hipStream_t st);

@@ -1,0 +1,107 @@
+"""The stacks of Table I / Table II as one launch each (three-part bf16 products in fp32 precision) against the oracle:
+lengths at the edges of a block's run of 15 latent positions (240 values), and inputs the split cannot represent."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2103_08870_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# Every layer rounds its sums to fp32 a few dozen times (2^-24 each, signs at random: about 2^-23 of the output's norm)
+# and the stacks have four deep layers.  A product left out of the split would show: m m' alone is 2^-18.
+REL_L2 = 4 * 2.0 ** -23
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2103_08870_amd import binding
+    binding.lib()
+    assert torch.cuda.is_available()
+    return binding
+
+
+def stacks(B, change=None):
+    enc, dec = synth.paper_ae()
+    host = [[t.numpy() for t in xs] for xs in synth.ae_weights(enc, dec, device="cpu")]
+    if change is not None:
+        host = [[np.ascontiguousarray(change(a, which)) for a in xs] for which, xs in enumerate(host)]
+    dev = [[torch.from_numpy(a).cuda() for a in xs] for xs in host]
+    return B.Autoencoder(enc, dec, *dev, slope=0.01), enc, dec, host
+
+
+def both_ways(B, oracle, ae, enc, dec, host, x, latent=None):
+    """(gpu latent, oracle's, gpu reconstruction of the oracle's latent, oracle's), per node stacked."""
+    batch, k = x.shape
+    ctx = B.Context(k, k, batch)
+    B.lgc_reserve(ctx, ae, k, batch)
+    lat = torch.full((batch, B.lgc_latent_len(ae, k)), 7.0, device="cuda")
+    rec = torch.full((batch, k), 7.0, device="cuda")
+    B.lgc_encode(ctx, ae, torch.from_numpy(x).cuda(), lat)
+    with np.errstate(all="ignore"):
+        ol = np.stack([oracle.encode(row, enc, host[0], host[1], slope=0.01) for row in x])
+    src = ol if latent is None else latent.reshape(ol.shape)
+    B.lgc_decode(ctx, ae, torch.from_numpy(np.ascontiguousarray(src.reshape(batch, -1))).cuda(), rec)
+    with np.errstate(all="ignore"):
+        orec = np.stack([oracle.decode(np.ascontiguousarray(z), k, enc, dec, host[2], host[3], slope=0.01) for z in src])
+    torch.cuda.synchronize()
+    ctx.close()
+    return lat.cpu().numpy(), ol.reshape(batch, -1), rec.cpu().numpy(), orec
+
+
+def assert_near(got, want, what):
+    assert (np.isnan(got) == np.isnan(want)).all() and (np.isinf(got) == np.isinf(want)).all(), what
+    assert (got[np.isinf(want)] == want[np.isinf(want)]).all(), what
+    ok = np.isfinite(want)
+    err = np.linalg.norm(got[ok].astype(np.float64) - want[ok]) / max(np.linalg.norm(want[ok].astype(np.float64)), 1e-300)
+    assert err <= REL_L2, (what, err)
+
+
+@pytest.mark.parametrize("k,batch", [(2, 1), (15, 1), (16, 3), (239, 1), (240, 2), (241, 1), (256, 1), (480, 1), (497, 3)])
+def test_lengths_at_the_edges_of_a_block(B, oracle, k, batch):
+    ae, enc, dec, host = stacks(B)
+    x = np.random.default_rng(k).laplace(0, 0.3, (batch, k)).astype(np.float32)
+    lat, ol, rec, orec = both_ways(B, oracle, ae, enc, dec, host, x)
+    assert_near(lat, ol, ("latent", k))
+    assert_near(rec, orec, ("reconstruction", k))
+    ae.close()
+
+
+# Positive weights: an Inf stays one Inf all the way (weights of both signs would turn it into NaN at once), so the
+# values that bf16 parts cannot carry have one right answer.  The largest finite values round to Inf in bf16.
+@pytest.mark.parametrize("special", [np.inf, np.nan, 3.4e38, 1e-30])
+def test_values_that_the_split_cannot_carry(B, oracle, special):
+    def change(a, which):
+        if which % 2:
+            return np.zeros_like(a) if special == 1e-30 else np.abs(a)   # biases
+        return np.abs(a) * np.float32(0.05)
+    ae, enc, dec, host = stacks(B, change)
+    k = 600
+    rng = np.random.default_rng(5)
+    x = np.abs(rng.normal(0, 1, (2, k))).astype(np.float32)
+    z = np.abs(rng.normal(0, 1, (2, 4 * 38))).astype(np.float32)
+    if special == 1e-30:
+        x *= np.float32(special); z *= np.float32(special)
+    else:
+        x[1, 300] = special
+        z[1, 2 * 38 + 20] = special
+    lat, ol, rec, orec = both_ways(B, oracle, ae, enc, dec, host, x, z)
+    assert_near(lat, ol, ("latent", special))
+    assert_near(rec, orec, ("reconstruction", special))
+    if not np.isfinite(special):
+        assert (~np.isfinite(ol)).any() and np.isfinite(ol[0]).all()   # the case is what it says
+    ae.close()
+
+
+def test_weights_that_are_not_finite(B, oracle):
+    # such a handle keeps to the fp32 kernels: NaN where the oracle has a NaN
+    def change(a, which):
+        if which == 0 and a.shape == (256, 128, 3):
+            a = a.copy(); a[7, 3, 1] = np.inf
+        return a
+    ae, enc, dec, host = stacks(B, change)
+    x = np.random.default_rng(1).normal(0, 1, (1, 100)).astype(np.float32)
+    lat, ol, rec, orec = both_ways(B, oracle, ae, enc, dec, host, x, np.ones((1, 4 * 7), np.float32))
+    assert_near(lat, ol, "latent")
+    assert_near(rec, orec, "reconstruction")
+    ae.close()
