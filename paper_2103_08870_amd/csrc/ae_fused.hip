@@ -13,11 +13,14 @@
 // cores run bf16 at 16 times the fp32 rate: 2.7 times fewer matrix-core cycles for the same precision (the sums are
 // rounded once per 16 products instead of once per 2, and come out slightly closer to the 64-bit result).
 // Measured against one fp32-MFMA launch per deep layer (ae_mfma.hip, which other stacks still use): 4 nodes x 25 600
-// values, encoder 79.3 -> 38.6 us, decoder 57.8 -> 21.5 us; 8 x 67 000, both together 468 -> 260 us; 1 x 1 023
-// (latency) 78.6 -> 37.0 us; relative error against 64 bits 1.2e-7 -> 1.0e-7 (latent), 2.9e-8 -> 2.7e-8.
-// The split is exact only for finite values; an Inf would meet products of both signs.  So every split carries
-// a check along, and a block that met an Inf or a NaN anywhere redoes its outputs in plain fp32 (plain_encoder /
-// plain_decoder), with the term order of the per-layer kernels.
+// values, encoder 79.4 -> 26.7 us (165 TFLOP/s of fp32 products), decoder 57.9 -> 21.4 us (126); 8 x 67 000, both
+// together 468 -> 228 us (163); 1 x 1 023 (latency) 79 -> 29 us.  Relative error against 64 bits, mean over sizes and
+// seeds: latent 1.16e-7 -> 1.02e-7, decoder 4.2e-8 -> 4.0e-8.  What bounds it: while a compute unit has blocks its
+// matrix cores are busy 63 % of the cycles (encoder) and 46 % (decoder) at a clock that drops to 1.9 GHz.
+// The split is exact only for finite values; an Inf would meet products of both signs.  Such a
+// value leaves a NaN among its parts, which makes every output it reaches a NaN, and a block with an output that is
+// not finite redoes its outputs in plain fp32 (plain_encoder / plain_decoder), with the term order of the
+// per-layer kernels.
 //
 // Operand layout of v_mfma_f32_32x32x16_bf16: lane l supplies A[i = l % 32][k = 8 (l / 32) + 0..7] and
 // B[k = 8 (l / 32) + 0..7][j = l % 32]; result r of 16 is C[i = 8 (r / 4) + 4 (l / 32) + r % 4][j = l % 32].  Here
@@ -43,29 +46,57 @@ namespace {
 
 __device__ __forceinline__ float leaky_f(float x, float slope) { return x > 0.f ? x : slope * x; }
 
-// Two values split into three bf16 pairs.  `chk` turns into a NaN if either is not finite (or rounds to Inf).
-__device__ __forceinline__ void split2(const float a, const float b, uint32_t &h, uint32_t &m, uint32_t &l, float &chk) {
+// Two values split into three bf16 pairs.  A value that is not finite, or rounds to Inf, leaves a NaN in m.
+__device__ __forceinline__ void split2(const float a, const float b, uint32_t &h, uint32_t &m, uint32_t &l) {
     h = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){a, b}, bf2));
-    const float ha = __uint_as_float(h << 16), hb = __uint_as_float(h & 0xffff0000u);
-    chk = fmaf(ha, 0.f, chk);
-    chk = fmaf(hb, 0.f, chk);
-    const float ra = a - ha, rb = b - hb;
+    const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
     m = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){ra, rb}, bf2));
     const float ma = __uint_as_float(m << 16), mb = __uint_as_float(m & 0xffff0000u);
     l = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){ra - ma, rb - mb}, bf2));
 }
 
-// acc += A B for one step of 16 input channels, both operands in three parts; the smallest products first
-__device__ __forceinline__ acc16 mma6(const u4v (&a)[3], const u4v (&b)[3], acc16 acc) {
-    const bf8 ah = __builtin_bit_cast(bf8, a[0]), am = __builtin_bit_cast(bf8, a[1]), al = __builtin_bit_cast(bf8, a[2]);
-    const bf8 bh = __builtin_bit_cast(bf8, b[0]), bm = __builtin_bit_cast(bf8, b[1]), bl = __builtin_bit_cast(bf8, b[2]);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bm, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(am, bh, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bm, acc, 0, 0, 0);
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc, 0, 0, 0);
-    return acc;
+// acc[i][j] + cross[i][j] += A[i] B[j] for one step of 16 input channels, both operands in three parts.  The five
+// products that hold an m or an l have sums of their own: rounded at their own, 2^8 times smaller size, they leave
+// the large sum one rounding per step instead of six.  The tiles are taken in turn, so that consecutive
+// instructions do not wait for each other's sums.
+template <int MT, int NT>
+__device__ __forceinline__ void mma6(acc16 (&acc)[MT][NT], acc16 (&cross)[MT][NT], const u4v (&a)[MT][3], const u4v (&b)[NT][3]) {
+    constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};   // parts h, m, l = 0, 1, 2
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) {
+                acc16 &c = q < 5 ? cross[i][j] : acc[i][j];
+                c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a[i][kA[q]]), __builtin_bit_cast(bf8, b[j][kB[q]]), c, 0, 0, 0);
+            }
+}
+
+// The even and the odd outputs of a transposed layer for one step: x0, x1 = inputs m, m + 1; a[t] = tap t
+__device__ __forceinline__ void mma6_up(acc16 &even, acc16 &odd, const u4v (&a)[3][3], const u4v (&x)[2][3]) {
+    constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};
+    auto mul = [](const u4v &p, const u4v &q, const acc16 &c) {
+        return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, p), __builtin_bit_cast(bf8, q), c, 0, 0, 0);
+    };
+#pragma unroll
+    for (int q = 0; q < 6; ++q) {
+        odd = mul(a[2][kA[q]], x[0][kB[q]], odd);
+        even = mul(a[1][kA[q]], x[0][kB[q]], even);
+        odd = mul(a[0][kA[q]], x[1][kB[q]], odd);
+    }
+}
+
+// A result tile that starts from the bias of its channels co0 + 8 (r / 4) + 4 half + r % 4
+__device__ __forceinline__ acc16 bias16(const float *__restrict__ bias, const int co0, const int half) {
+    acc16 z;
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+        const f4v b = *(const f4v *)(bias + co0 + 8 * g + 4 * half);
+#pragma unroll
+        for (int c = 0; c < 4; ++c) z[4 * g + c] = b[c];
+    }
+    return z;
 }
 
 __device__ __forceinline__ acc16 zero16() {
@@ -78,26 +109,25 @@ __device__ __forceinline__ acc16 zero16() {
 // Bytes of one position with C channels in the LDS: three parts, 16 bytes of padding.
 constexpr int row_bytes(int c) { return 6 * c + 16; }
 
-// One 32 x 32 result tile with bias and non-linearity into the LDS: `row` is the lane's position, channels
+// One 32 x 32 result tile with the non-linearity into the LDS: `row` is the lane's position, channels
 // co0 + 8 (r / 4) + 4 half + r % 4.  Positions that do not exist (valid false) hold zeros.
 template <int C>
 __device__ __forceinline__ void store_tile(unsigned char *row, const int co0, const int half, const acc16 &acc,
-                                           const float *__restrict__ bias, const float slope, const bool valid, float &chk) {
+                                           const float slope, const bool valid) {
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
         const int co = co0 + 8 * g + 4 * half;
-        const f4v b = *(const f4v *)(bias + co);
         float y[4];
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            y[c] = leaky_f(acc[4 * g + c] + b[c], slope);
+            y[c] = leaky_f(acc[4 * g + c], slope);
             y[c] = valid ? y[c] : 0.f;
         }
         u2v h, m, l;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             uint32_t x, z, w;
-            split2(y[2 * c], y[2 * c + 1], x, z, w, chk);
+            split2(y[2 * c], y[2 * c + 1], x, z, w);
             h[c] = x; m[c] = z; l[c] = w;
         }
         *(u2v *)(row + 2 * co) = h;
@@ -126,7 +156,8 @@ __global__ __launch_bounds__(256) void k_weights_split(const float *__restrict__
             x[c] = transposed ? w[((size_t)ci * c_out + co) * 3 + tap] : w[((size_t)co * c_in + ci) * 3 + tap];
         }
         uint32_t h, m, l;
-        split2(x[0], x[1], h, m, l, chk);
+        split2(x[0], x[1], h, m, l);
+        chk = fmaf(__uint_as_float(m << 16), 0.f, fmaf(__uint_as_float(m & 0xffff0000u), 0.f, chk));   // a NaN if a part is one
         *(uint32_t *)(o + e) = h;
         *(uint32_t *)(o + 512 + e) = m;
         *(uint32_t *)(o + 1024 + e) = l;
@@ -153,43 +184,62 @@ struct EncoderDev {
 
 namespace {
 
-// The K loop of one convolution for MT x NT tiles: steps [S0, S1) of 16 input channels, tap-major.  `b`: the LDS
-// rows of this lane's positions for tap 0; the odd positions lie `odd` bytes behind the even ones, so that a
-// stride-2 window (2i, 2i + 1, 2i + 2) is a read of row i of either half, and of row i + 1.  `a`: fragments of the first tile's
-// first step, this lane's 16 bytes; the tiles are a_tile (in 16-byte units) apart.  The fragments come from the L2:
-// DEPTH steps are kept in flight.
-template <int C, int MT, int NT, int S0, int S1, int DEPTH>
-__device__ __forceinline__ void conv_mma(acc16 (&acc)[MT][NT], const u4v *__restrict__ a, const int a_tile,
-                                         const unsigned char *const (&b)[NT], const int odd) {
-    constexpr int kPer = C / 16;   // steps per tap
-    u4v ra[DEPTH][MT][3];
+// The K loop of one convolution for MT x NT tiles: STEPS steps of 16 input channels from step s0 on, tap-major.  `b`:
+// the LDS rows of this lane's positions for tap 0; the odd positions lie `odd` bytes behind the even ones, so
+// that a stride-2 window (2i, 2i + 1, 2i + 2) is a read of row i of either half, and of row i + 1.  `a`: fragments
+// of the first tile's first step, this lane's 16 bytes; the tiles are a_tile (in 16-byte units) apart.  The
+// fragments come from the L2: AHEAD steps of them are kept in flight, the first ones from before the barrier that
+// the loop waits at, and the LDS reads run one step ahead.  The scheduling barriers keep it that way (left to
+// itself the compiler moves the loads down to their uses: conv4 then waits out the L2's latency in every step).
+template <int MT, int AHEAD>
+struct Fragments { u4v r[AHEAD + 1][MT][3]; };
+
+template <int MT, int AHEAD>
+__device__ __forceinline__ void fragments_start(Fragments<MT, AHEAD> &f, const u4v *__restrict__ a, const int a_tile) {
 #pragma unroll
-    for (int d = 0; d < DEPTH; ++d)
+    for (int d = 0; d < AHEAD; ++d)
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int p = 0; p < 3; ++p) ra[d][i][p] = a[i * a_tile + ((S0 + d) * 3 + p) * 64];
-#pragma unroll
-    for (int s = S0; s < S1; ++s) {
-        const int tap = s / kPer, at = 32 * (s % kPer);
-        u4v rb[NT][3];
+            for (int p = 0; p < 3; ++p) f.r[d][i][p] = a[i * a_tile + (d * 3 + p) * 64];
+    __builtin_amdgcn_sched_barrier(0);
+}
+
+template <int C, int MT, int NT, int S0, int STEPS, int AHEAD>
+__device__ __forceinline__ void conv_mma(acc16 (&acc)[MT][NT], Fragments<MT, AHEAD> &f, const u4v *__restrict__ a, const int a_tile,
+                                         const unsigned char *const (&b)[NT], const int odd) {
+    constexpr int kPer = C / 16;   // steps per tap
+    u4v rb[2][NT][3];
+    auto read_b = [&](u4v (&r)[NT][3], const int s) {
+        const int tap = s / kPer, at = (tap == 1 ? odd : (tap >> 1) * row_bytes(C)) + 32 * (s % kPer);
 #pragma unroll
         for (int j = 0; j < NT; ++j)
 #pragma unroll
-            for (int p = 0; p < 3; ++p)
-                rb[j][p] = *(const u4v *)(b[j] + (tap == 1 ? odd : (tap >> 1) * row_bytes(C)) + p * 2 * C + at);
-        const int d = (s - S0) % DEPTH;
+            for (int p = 0; p < 3; ++p) r[j][p] = *(const u4v *)(b[j] + p * 2 * C + at);
+    };
+    acc16 cross[MT][NT];
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int j = 0; j < NT; ++j) acc[i][j] = mma6(ra[d][i], rb[j], acc[i][j]);
-        if (s + DEPTH < S1) {
+        for (int j = 0; j < NT; ++j) cross[i][j] = zero16();
+    read_b(rb[0], S0);
+#pragma unroll
+    for (int s = 0; s < STEPS; ++s) {
+        if (s + AHEAD < STEPS) {
 #pragma unroll
             for (int i = 0; i < MT; ++i)
 #pragma unroll
-                for (int p = 0; p < 3; ++p) ra[d][i][p] = a[i * a_tile + ((s + DEPTH) * 3 + p) * 64];
+                for (int p = 0; p < 3; ++p) f.r[(s + AHEAD) % (AHEAD + 1)][i][p] = a[i * a_tile + ((s + AHEAD) * 3 + p) * 64];
         }
+        if (s + 1 < STEPS) read_b(rb[(s + 1) & 1], S0 + s + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        mma6<MT, NT>(acc, cross, f.r[s % (AHEAD + 1)], rb[s & 1]);
+        __builtin_amdgcn_sched_barrier(0);
     }
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[i][j] += cross[i][j];
 }
 
 // The latent positions [p0, p0 + count) in plain fp32, one after the other (buf: 2700 floats).
@@ -260,7 +310,6 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
     const long long p0 = (long long)blockIdx.x * P;
     x += (size_t)blockIdx.y * l0;
     out += (size_t)blockIdx.y * C5 * l4;
-    float chk = 0.f;
 
     for (int i = tid; i < 4 * N2 + 3; i += W * 64) {
         const long long e = 16 * p0 - 15 + i;
@@ -289,7 +338,7 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
             uint32_t a, b, d;
-            split2(y[2 * c], y[2 * c + 1], a, b, d, chk);
+            split2(y[2 * c], y[2 * c + 1], a, b, d);
             h[c] = a; m[c] = b; l[c] = d;
         }
         unsigned char *row = buf + ((i & 1) ? (N2 + 1) * R1 : 0) + (i >> 1) * R1 + o8 * 16;
@@ -297,42 +346,47 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
         *(u4v *)(row + 2 * C1) = m;
         *(u4v *)(row + 4 * C1) = l;
     }
-    __syncthreads();
 
     {   // conv2: C2 / 32 channel tiles x N2 / 32 position tiles
-        constexpr int kM = C2 / 32, kNW = W / kM, NT = N2 / 32 / kNW;
+        constexpr int kM = C2 / 32, kNW = W / kM, NT = N2 / 32 / kNW, kSteps = 3 * C1 / 16, kAhead = 2;
         static_assert(W % kM == 0 && (N2 / 32) % kNW == 0, "conv2 tiles");
         const int mt = wave / kNW, n0 = (wave % kNW) * NT;
+        const u4v *a = (const u4v *)w.s2 + (size_t)mt * kSteps * 192 + lane;
+        Fragments<1, kAhead> f;
+        fragments_start(f, a, 0);
         acc16 acc[1][NT];
         const unsigned char *b[NT];
 #pragma unroll
-        for (int j = 0; j < NT; ++j) { acc[0][j] = zero16(); b[j] = buf + ((n0 + j) * 32 + col) * R1 + half * 16; }
-        conv_mma<C1, 1, NT, 0, 3 * C1 / 16, 3>(acc, (const u4v *)w.s2 + (size_t)mt * (3 * C1 / 16) * 192 + lane, 0, b, (N2 + 1) * R1);
+        for (int j = 0; j < NT; ++j) { acc[0][j] = bias16(w.b2, mt * 32, half); b[j] = buf + ((n0 + j) * 32 + col) * R1 + half * 16; }
+        __syncthreads();
+        conv_mma<C1, 1, NT, 0, kSteps, kAhead>(acc, f, a, 0, b, (N2 + 1) * R1);
         __syncthreads();   // conv1's outputs have been read
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
             const int i = (n0 + j) * 32 + col;
             const long long q = 4 * p0 - 3 + i;
-            store_tile<C2>(buf + ((i & 1) ? (N3 + 1) * R2 : 0) + (i >> 1) * R2, mt * 32, half, acc[0][j], w.b2, slope,
-                           q >= 0 && q < (long long)l2 && i < N2 - 1, chk);
+            store_tile<C2>(buf + ((i & 1) ? (N3 + 1) * R2 : 0) + (i >> 1) * R2, mt * 32, half, acc[0][j], slope,
+                           q >= 0 && q < (long long)l2 && i < N2 - 1);
         }
     }
-    __syncthreads();
 
     {   // conv3
-        constexpr int kM = C3 / 32, kMW = kM < W ? kM : W, MT = kM / kMW, kNW = W / kMW, NT = N3 / 32 / kNW;
+        constexpr int kM = C3 / 32, kMW = kM < W ? kM : W, MT = kM / kMW, kNW = W / kMW, NT = N3 / 32 / kNW, kSteps = 3 * C2 / 16, kAhead = 1;
         static_assert(kM % kMW == 0 && W % kMW == 0 && (N3 / 32) % kNW == 0, "conv3 tiles");
         const int m0 = (wave / kNW) * MT, n0 = (wave % kNW) * NT;
+        const u4v *a = (const u4v *)w.s3 + (size_t)m0 * kSteps * 192 + lane;
+        Fragments<MT, kAhead> f;
+        fragments_start(f, a, kSteps * 192);
         acc16 acc[MT][NT];
         const unsigned char *b[NT];
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
             b[j] = buf + ((n0 + j) * 32 + col) * R2 + half * 16;
 #pragma unroll
-            for (int i = 0; i < MT; ++i) acc[i][j] = zero16();
+            for (int i = 0; i < MT; ++i) acc[i][j] = bias16(w.b3, (m0 + i) * 32, half);
         }
-        conv_mma<C2, MT, NT, 0, 3 * C2 / 16, 3>(acc, (const u4v *)w.s3 + (size_t)m0 * (3 * C2 / 16) * 192 + lane, (3 * C2 / 16) * 192, b,
-                                                (N3 + 1) * R2);
+        __syncthreads();
+        conv_mma<C2, MT, NT, 0, kSteps, kAhead>(acc, f, a, kSteps * 192, b, (N3 + 1) * R2);
         __syncthreads();
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
@@ -341,31 +395,33 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
             unsigned char *row = buf + ((i & 1) ? (N4 + 1) * R3 : 0) + (i >> 1) * R3;
 #pragma unroll
             for (int k = 0; k < MT; ++k)
-                store_tile<C3>(row, (m0 + k) * 32, half, acc[k][j], w.b3, slope, q >= 0 && q < (long long)l3 && i < N3 - 1, chk);
+                store_tile<C3>(row, (m0 + k) * 32, half, acc[k][j], slope, q >= 0 && q < (long long)l3 && i < N3 - 1);
         }
     }
-    __syncthreads();
 
     float *part = (float *)buf;                               // conv4's partial sums [kSplit][C4][33]
     float *red = part + kSplit * C4 * 33;                     // conv5's [W * 2][C5][32]
     static_assert(kBytes >= (kSplit * C4 * 33 + W * 2 * C5 * 32) * 4, "partial sums");
     {   // conv4: one position tile (of which N4 columns are used); the steps are shared out over kSplit wavefronts
-        constexpr int kSteps = 3 * C3 / 16 / kSplit;
+        constexpr int kSteps = 3 * C3 / 16 / kSplit, kAhead = 4;
         static_assert((3 * C3 / 16) % kSplit == 0, "conv4 steps");
         const int mt = wave / kSplit, ks = wave % kSplit;
+        const u4v *a = (const u4v *)w.s4 + (size_t)(mt * kSplit + ks) * kSteps * 192 + lane;
+        Fragments<1, kAhead> f;
+        fragments_start(f, a, 0);
         acc16 acc[1][1];
         acc[0][0] = zero16();
         const int c4 = col < N4 ? col : N4 - 1;
-        const u4v *a = (const u4v *)w.s4 + (size_t)mt * (3 * C3 / 16) * 192 + lane;
         const unsigned char *b[1] = {buf + c4 * R3 + half * 16};
         auto run = [&](auto k) {
-            constexpr int S = decltype(k)::value;
-            conv_mma<C3, 1, 1, S * kSteps, (S + 1) * kSteps, 4>(acc, a, 0, b, (N4 + 1) * R3);
+            constexpr int S = decltype(k)::value % kSplit;
+            conv_mma<C3, 1, 1, S * kSteps, kSteps, kAhead>(acc, f, a, 0, b, (N4 + 1) * R3);
         };
+        __syncthreads();
         if (ks == 0) run(std::integral_constant<int, 0>());    // wave-uniform
-        else if (ks == 1) run(std::integral_constant<int, 1 % kSplit>());
-        else if (ks == 2) run(std::integral_constant<int, 2 % kSplit>());
-        else run(std::integral_constant<int, 3 % kSplit>());
+        else if (ks == 1) run(std::integral_constant<int, 1>());
+        else if (ks == 2) run(std::integral_constant<int, 2>());
+        else run(std::integral_constant<int, 3>());
         __syncthreads();
 #pragma unroll
         for (int r = 0; r < 16; ++r)
@@ -399,9 +455,9 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
         z = w.b5[c];
 #pragma unroll
         for (int g = 0; g < W * 2; ++g) z += red[(g * C5 + c) * 32 + p];
-        chk = fmaf(z, 0.f, chk);
     }
-    if (!__syncthreads_or(chk != chk)) {
+    // a value that the split cannot carry, anywhere in the block, has made every output that it reaches a NaN
+    if (!__syncthreads_or(!(fabsf(z) < INFINITY))) {
         if (mine) out[(size_t)c * l4 + p0 + p] = z;
         return;
     }
@@ -512,7 +568,6 @@ __global__ __launch_bounds__(256) void k_decoder_fused(const float *__restrict__
     const long long p0 = (long long)blockIdx.x * T;
     z += (size_t)blockIdx.y * D0 * lz;
     out += (size_t)blockIdx.y * l5;
-    float chk = 0.f;
 
     for (int i = tid; i < D0 * (T + 3); i += 256) {
         const int c = i / (T + 3);
@@ -554,35 +609,43 @@ __global__ __launch_bounds__(256) void k_decoder_fused(const float *__restrict__
 #pragma unroll
         for (int c = 0; c < kCh; c += 2) {
             uint32_t h, m_, l;
-            split2(valid ? leaky_f(y[c], slope) : 0.f, valid ? leaky_f(y[c + 1], slope) : 0.f, h, m_, l, chk);
+            split2(valid ? leaky_f(y[c], slope) : 0.f, valid ? leaky_f(y[c + 1], slope) : 0.f, h, m_, l);
             *(uint32_t *)(row + 2 * c) = h;
             *(uint32_t *)(row + 2 * D2 + 2 * c) = m_;
             *(uint32_t *)(row + 4 * D2 + 2 * c) = l;
         }
     }
-    __syncthreads();
     {   // deconv3: wavefront = channel tile x (even or odd outputs)
         constexpr int kPer = D2 / 16;
         const int mt = wave & 1, par = wave >> 1;
         const u4v *a = (const u4v *)w.s3 + (size_t)mt * 3 * kPer * 192 + lane;
         const unsigned char *b = bufA + col * R2 + half * 16;
-        acc16 acc = zero16();
-        u4v ra[3], rb[3];
+        acc16 acc[1][1];
+        acc[0][0] = bias16(w.b3, mt * 32, half);
+        acc16 cross[1][1];
+        cross[0][0] = zero16();
+        u4v ra[2 * kPer][1][3];
 #pragma unroll
         for (int s = 0; s < kPer; ++s) {
-            load_a(ra, a, (par ? 2 : 1) * kPer + s);
-            load_b<D2>(rb, b, 32 * s);
-            acc = mma6(ra, rb, acc);
+            load_a(ra[s][0], a, (par ? 2 : 1) * kPer + s);
+            load_a(ra[kPer + s][0], a, s);   // of the odd outputs only
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        u4v rb[1][3];
+#pragma unroll
+        for (int s = 0; s < kPer; ++s) {
+            load_b<D2>(rb[0], b, 32 * s);
+            mma6<1, 1>(acc, cross, ra[s], rb);
             if (par) {
-                load_a(ra, a, s);
-                load_b<D2>(rb, b + R2, 32 * s);
-                acc = mma6(ra, rb, acc);
+                load_b<D2>(rb[0], b + R2, 32 * s);
+                mma6<1, 1>(acc, cross, ra[kPer + s], rb);
             }
         }
+        acc[0][0] += cross[0][0];
         const int i = 2 * col + par;
-        store_tile<D3>(bufB + i * R3, mt * 32, half, acc, w.b3, slope, 4 * p0 + i < (long long)l3 && i < 4 * T + 1, chk);
+        store_tile<D3>(bufB + i * R3, mt * 32, half, acc[0][0], slope, 4 * p0 + i < (long long)l3 && i < 4 * T + 1);
     }
-    __syncthreads();
 
     const int np = wave & 1, kh = wave >> 1;   // deconv5: wavefront = pair of position tiles x half of each run's channels
     acc16 e5[2], o5[2];
@@ -595,45 +658,58 @@ __global__ __launch_bounds__(256) void k_decoder_fused(const float *__restrict__
             const int mt = wave & 1, n0 = wave >> 1;
             const u4v *a = (const u4v *)w.s4 + (size_t)(2 * run + mt) * 3 * kPer * 192 + lane;
             const unsigned char *b = bufB + (n0 * 32 + col) * R3 + half * 16;
-            acc16 even = zero16(), odd = zero16();
+            u4v ra[2][3][3], rb[2][2][3];
+            auto fetch = [&](const int s) {
+#pragma unroll
+                for (int t = 0; t < 3; ++t) load_a(ra[s & 1][t], a, t * kPer + s);
+            };
+            auto read = [&](const int s) {
+                load_b<D3>(rb[s & 1][0], b, 32 * s);
+                load_b<D3>(rb[s & 1][1], b + R3, 32 * s);
+            };
+            fetch(0);
+            __builtin_amdgcn_sched_barrier(0);
+            acc16 even = bias16(w.b4 + run * CH, mt * 32, half), odd = even;
+            __syncthreads();   // deconv3's outputs are there; the previous run's of deconv4 have been read
+            read(0);
 #pragma unroll
             for (int s = 0; s < kPer; ++s) {
-                u4v a0[3], a1[3], a2[3], x0[3], x1[3];
-                load_a(a1, a, kPer + s);
-                load_a(a2, a, 2 * kPer + s);
-                load_a(a0, a, s);
-                load_b<D3>(x0, b, 32 * s);
-                load_b<D3>(x1, b + R3, 32 * s);
-                even = mma6(a1, x0, even);
-                odd = mma6(a2, x0, odd);
-                odd = mma6(a0, x1, odd);
+                if (s + 1 < kPer) { fetch(s + 1); read(s + 1); }
+                __builtin_amdgcn_sched_barrier(0);
+                mma6_up(even, odd, ra[s & 1], rb[s & 1]);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            if (run) __syncthreads();   // the previous run's outputs have been read
             const int i = 2 * (n0 * 32 + col);
-            const float *bias = w.b4 + run * CH;
-            store_tile<CH>(bufA + i * R4, mt * 32, half, even, bias, slope, 8 * p0 + i < (long long)l4 && i < 8 * T + 1, chk);
-            store_tile<CH>(bufA + (i + 1) * R4, mt * 32, half, odd, bias, slope, 8 * p0 + i + 1 < (long long)l4 && i + 1 < 8 * T + 1, chk);
+            store_tile<CH>(bufA + i * R4, mt * 32, half, even, slope, 8 * p0 + i < (long long)l4 && i < 8 * T + 1);
+            store_tile<CH>(bufA + (i + 1) * R4, mt * 32, half, odd, slope, 8 * p0 + i + 1 < (long long)l4 && i + 1 < 8 * T + 1);
         }
-        __syncthreads();
         {   // deconv5, this run's channels
-            constexpr int kPer = D4 / 16;
+            constexpr int kPer = D4 / 16, kSteps = CH / 32;
             const u4v *a = (const u4v *)w.s5 + lane;
+            u4v ra[2][3][3], rb[2][2][3];
+            const unsigned char *b = bufA + (np * 64 + col) * R4 + half * 16 + 32 * kh * kSteps;
+            auto fetch = [&](const int q) {
 #pragma unroll
-            for (int q = 0; q < CH / 32; ++q) {
-                const int sl = kh * (CH / 32) + q, s = run * (CH / 16) + sl;   // step inside the run, and over all channels
-                u4v a0[3], a1[3], a2[3];
-                load_a(a1, a, kPer + s);
-                load_a(a2, a, 2 * kPer + s);
-                load_a(a0, a, s);
+                for (int t = 0; t < 3; ++t) load_a(ra[q & 1][t], a, t * kPer + run * (CH / 16) + kh * kSteps + q);
+            };
+            auto read = [&](const int q, const int j) {
+                load_b<CH>(rb[j][0], b + j * 32 * R4, 32 * q);
+                load_b<CH>(rb[j][1], b + j * 32 * R4 + R4, 32 * q);
+            };
+            fetch(0);
+            __builtin_amdgcn_sched_barrier(0);
+            __syncthreads();
+            read(0, 0);
+#pragma unroll
+            for (int q = 0; q < kSteps; ++q) {
+                if (q + 1 < kSteps) fetch(q + 1);
 #pragma unroll
                 for (int j = 0; j < 2; ++j) {
-                    const unsigned char *b = bufA + ((np * 2 + j) * 32 + col) * R4 + half * 16;
-                    u4v x0[3], x1[3];
-                    load_b<CH>(x0, b, 32 * sl);
-                    load_b<CH>(x1, b + R4, 32 * sl);
-                    e5[j] = mma6(a1, x0, e5[j]);
-                    o5[j] = mma6(a2, x0, o5[j]);
-                    o5[j] = mma6(a0, x1, o5[j]);
+                    if (j == 0) read(q, 1);
+                    else if (q + 1 < kSteps) read(q + 1, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mma6_up(e5[j], o5[j], ra[q & 1], rb[j]);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
         }
@@ -668,8 +744,7 @@ __global__ __launch_bounds__(256) void k_decoder_fused(const float *__restrict__
     const int m = (np * 2 + kh) * 32 + col, i = 2 * m + half;   // lanes 0..31 store the even, lanes 32..63 the odd outputs
     const bool mine = m < 8 * T && 16 * p0 + i < (long long)l5;
     const float y = w.b6[0] + (half ? so : se);
-    if (mine) chk = fmaf(y, 0.f, chk);
-    if (!__syncthreads_or(chk != chk)) {
+    if (!__syncthreads_or(mine && !(fabsf(y) < INFINITY))) {
         if (mine) out[16 * p0 + i] = y;
         return;
     }
@@ -694,7 +769,7 @@ bool decoder_fused_covers(const LayerDev *l, int count) {
 }
 
 bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int count, const uint64_t *len, int batch, float slope,
-                          hipStream_t st) {
+                          int cus, hipStream_t st) {
     if (!encoder_fused_covers(l, count) || !l[1].ws || !l[2].ws || !l[3].ws) return false;
     const uint32_t l4 = (uint32_t)len[4];
     if (l4 == 0) return true;
@@ -704,9 +779,13 @@ bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int cou
     w.w3 = l[2].w; w.b3 = l[2].b; w.s3 = l[2].ws;
     w.w4 = l[3].w; w.b4 = l[3].b; w.s4 = l[3].ws;
     w.w5 = l[4].w; w.b5 = l[4].b;
-    constexpr int P = 15;
-    hipLaunchKernelGGL((k_encoder_fused<64, 128, 256, 64, 4, P, 4>), dim3((l4 + P - 1) / P, batch), dim3(256), 0, st, x, out, w,
-                       (uint32_t)len[0], (uint32_t)len[1], (uint32_t)len[2], (uint32_t)len[3], l4, slope);
+#define LGC_ENC(P, W) hipLaunchKernelGGL((k_encoder_fused<64, 128, 256, 64, 4, P, W>), dim3((l4 + P - 1) / P, batch), dim3(64 * W), 0, st, \
+                                         x, out, w, (uint32_t)len[0], (uint32_t)len[1], (uint32_t)len[2], (uint32_t)len[3], l4, slope)
+    // 31 positions per block stream the 1 MB of weights half as often as 15 do, and waste no half tile in conv4 (4 nodes
+    // x 25 600 values: 25.8 against 32.7 us, 8 x 67 000: 220 against 231); but while runs of 15 give every compute
+    // unit at most one block, the shorter chain of a block is what counts (1 x 1 023, both directions: 28.7 against 36.9 us).
+    if ((uint64_t)((l4 + 14) / 15) * batch <= (uint64_t)cus) LGC_ENC(15, 8); else LGC_ENC(31, 8);
+#undef LGC_ENC
     return true;
 }
 

@@ -826,7 +826,7 @@ static lgc_status run_encode(lgc_ctx *ctx, const lgc_ae *ae, const float *vals, 
     if (need > ctx->act_floats)
         return fail(ctx, LGC_EINVAL, "lgc_encode: activation scratch for k = %llu, batch = %d not reserved: call "
                                      "lgc_reserve(ctx, ae, k, batch, NULL) once beforehand", (unsigned long long)k, batch);
-    if (launch_encoder_fused(vals, latent, ae->enc_dev.data(), (int)nl, len.data(), batch, ae->slope, st)) {
+    if (launch_encoder_fused(vals, latent, ae->enc_dev.data(), (int)nl, len.data(), batch, ae->slope, ctx->cus, st)) {
         hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e1));
         return LGC_OK;

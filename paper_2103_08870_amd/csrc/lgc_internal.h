@@ -222,7 +222,7 @@ bool decoder_fused_covers(const LayerDev *l, int count);
 // *bad (device): incremented if a weight is not finite
 void launch_weights_split(const float *w, uint16_t *out, int c_in, int c_out, bool transposed, uint32_t *bad, hipStream_t st);
 bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int count, const uint64_t *len, int batch, float slope,
-                          hipStream_t st);
+                          int cus, hipStream_t st);
 bool launch_decoder_fused(const float *z, float *out, const LayerDev *l, int count, uint64_t l_z, const uint64_t *len, int batch,
                           float slope, hipStream_t st);
 void launch_gather_at(float *v, float *u, uint64_t stride, uint32_t n, int batch, const uint32_t *idx, uint32_t k,
