@@ -288,6 +288,9 @@ SelArgs make_args(lgc_ctx *c, const float *g, float *u, float *v, uint64_t n, ui
 
 constexpr int kMaxExactCalls = 64;   // most selections in a row that take the exact path outright after fall-backs were seen
 
+// Short vectors are selected exactly by kernels of their own, unless the exact radix path was asked for.
+bool takes_small_path(const lgc_ctx *ctx, uint64_t n, uint64_t k) { return ctx->opt_path != 1 && small_select_covers(n, k); }
+
 // accumulate (optional) + select; g == nullptr means selection only
 lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t n, int batch, uint64_t stride,
                       float m, uint64_t k, float *out_vals, uint32_t *out_idx, hipStream_t st) {
@@ -337,7 +340,13 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         a.notify_value = ctx->call_number;
     }
     ctx->cur ^= 1;  // this call uses the clean set and cleans the other one for the next call
-    if (fast) {
+    if (takes_small_path(ctx, n, k)) {
+        if (ctx->single_state) {   // no launch has cleared the scratch before this call: the first kernel does
+            a.next_state = (uint32_t *)ctx->scratch;
+            a.next_words = (uint32_t)(((char *)ctx->samples - (char *)ctx->scratch) / 4);
+        }
+        launch_small_select(a, batch, fused, vec, ctx->cus, st, fused ? profile_bracket(ctx) : Bracket());
+    } else if (fast) {
         launch_sample(a, batch, fused, vec, st);   // also clears the next call's state set
         launch_candidates(a, batch, fused, vec, st, profile_bracket(ctx));
         launch_gather(a, batch, st);
@@ -566,7 +575,8 @@ extern "C" lgc_status lgc_accumulate_topk_static(int device, const float *g, flo
     hipStream_t st = (hipStream_t)stream;
     // the array keeps the last call's contents: statistics and the state set start every call at zero
     // (a fill kernel, not a memset, so that the call can be recorded into a HIP graph)
-    if (k > 0) launch_clear((uint32_t *)sd->ptr, (uint32_t)(L.samples / 4), st);
+    // (the short vectors' first kernel does that itself)
+    if (k > 0 && !takes_small_path(&view, n, k)) launch_clear((uint32_t *)sd->ptr, (uint32_t)(L.samples / 4), st);
     return run_select(&view, g, u, v, n, batch, stride, momentum, k, out_vals, out_idx, st);
 }
 

@@ -1,11 +1,14 @@
-// Small device-side helpers shared by the selection kernels (gfx950, wave64).
+// Small helpers shared by the selection kernels (gfx950, wave64).
 #pragma once
+#include <hip/hip_ext.h>
+
 #include "lgc_internal.h"
 
 namespace lgc {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+typedef f4 f4u __attribute__((aligned(4)));   // 16-byte accesses at any 4-byte address (the hardware takes them)
 
 // ------------------------------------------------------------------ small helpers
 
@@ -68,6 +71,30 @@ __device__ inline void find_rank_bin(const uint32_t *hist, uint32_t rank, uint32
         }
     }
     __syncthreads();
+}
+
+// Exclusive prefix sum over a block of 1024 threads; `total` receives the sum.  tmp: 16 words.
+__device__ __forceinline__ uint32_t block_scan(const uint32_t x, uint32_t *tmp, uint32_t &total) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t incl = x;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const uint32_t y = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += y;
+    }
+    __syncthreads();
+    if (lane == 63) tmp[wave] = incl;
+    __syncthreads();
+    const uint32_t t = lane < 16 ? tmp[lane] : 0u;   // the sums over the wavefronts go over the lanes: fewer registers
+    total = wave_sum(t);
+    return incl - x + wave_sum(lane < wave ? t : 0u);
+}
+
+// An ordinary launch, or, with timing events, the launch form that stamps them itself.
+template <typename K, typename... Args>
+static void launch_timed(K kernel, dim3 grid, dim3 block, hipStream_t st, Bracket e, Args... args) {
+    if (e.start || e.stop) hipExtLaunchKernelGGL(kernel, grid, block, 0, st, e.start, e.stop, 0, args...);
+    else hipLaunchKernelGGL(kernel, grid, block, 0, st, args...);
 }
 
 }  // namespace lgc

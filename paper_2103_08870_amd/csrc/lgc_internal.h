@@ -164,6 +164,14 @@ void launch_candidates(const SelArgs &a, int batch, bool fused, bool vec, hipStr
 void launch_gather(const SelArgs &a, int batch, hipStream_t st);
 bool launch_output_from_candidates(const SelArgs &a, int batch, bool direct, bool vec, int cus, hipStream_t st);
 void launch_exact(const SelArgs &a, int batch, bool vec, int cus, hipStream_t st);
+// the candidates' bitmap straight to the output, one block per node (lists of up to kFinishList entries), with the exact
+// path standing by; report: a fast-path selection (statistics, carried thresholds)
+constexpr uint32_t kFinishList = 12288;
+constexpr uint32_t kFinishRows = 4096;
+void launch_finish_from_bitmap(const SelArgs &a, int batch, bool report, bool vec, int cus, hipStream_t st);
+// exact selection of short vectors (small.hip): accumulation (fused) and selection
+bool small_select_covers(uint64_t n, uint64_t k);
+void launch_small_select(const SelArgs &a, int batch, bool fused, bool vec, int cus, hipStream_t st, Bracket br = Bracket());
 // per-layer selection (segmented.hip)
 void launch_seg_estimate(const SelArgs &a, int batch, bool fused, bool vec, hipStream_t st);
 void launch_seg_select(const SelArgs &a, int batch, bool vec, hipStream_t st);

@@ -1,0 +1,127 @@
+// Exact top-k of short vectors (n < kMinFastN) without a sample: their first two launches (the third is
+// k_finish_or_exact, topk.hip).
+//
+// A short vector's selection is a chain of latencies, not of bytes: the radix select over several blocks
+// (k_exact, topk.hip) exchanges its histograms through the device five times, at 5-8 us each.  Here the pass that
+// touches every element (the accumulation, or the read of v) leaves a histogram of its 4096 keys per block; the
+// second launch adds those up, which fixes the leading 11 bits of T*, and flags the keys from there on; the third
+// lists them in one block's LDS and selects there.  Nothing crosses blocks but by the launches' ends.
+// Measured, accumulate + top-k of one node of 100 003 elements, k = 1 000, without a context: 44.5 us before (a
+// clearing launch, the accumulation, k_exact 38 us), 25.4 us now.  A single block that scans v for itself in
+// place of the last two launches took 31 us alone: reading and testing 400 KB is too much for one compute unit.
+#include "device_helpers.h"
+
+namespace lgc {
+
+constexpr uint32_t kSmallChunk = 4096;   // elements per block of the first launch
+constexpr int kSmallBins = 2048;         // key >> 20
+// the chunks' histograms lie where a sampled selection keeps its keys: two 16-bit counts per word
+static_assert((size_t)((kMinFastN + kSmallChunk - 1) / kSmallChunk) * (kSmallBins / 2) <= kSample, "room for the chunks' histograms");
+
+// u <- m u + g, v <- v + u (FUSED), the chunk's histogram, and the next call's state set cleared.  Four
+// elements per thread: the shortest chain.
+template <bool FUSED>
+__global__ __launch_bounds__(1024) void k_small_pass(SelArgs a) {
+    __shared__ uint32_t hist[kSmallBins];
+    const int node = blockIdx.y, tid = threadIdx.x;
+    {
+        const uint32_t gt = (blockIdx.y * gridDim.x + blockIdx.x) * 1024u + tid, nt = gridDim.x * gridDim.y * 1024u;
+        for (uint32_t i = gt; i < a.next_words; i += nt) a.next_state[i] = 0;
+    }
+    hist[tid] = 0; hist[tid + 1024] = 0;
+    const size_t off = (size_t)node * a.stride;
+    const uint32_t e = blockIdx.x * kSmallChunk + tid * 4;
+    float *v = a.v + off, *u = a.u + off;
+    const float *g = a.g + off;
+    f4 vv = {0.f, 0.f, 0.f, 0.f};
+    const uint32_t count = e >= a.n ? 0u : a.n - e < 4 ? a.n - e : 4u;
+    if (count == 4) {
+        vv = *(const f4u *)(v + e);
+        if (FUSED) {
+            f4 uu = *(const f4u *)(u + e);
+            const f4 gg = *(const f4u *)(g + e);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) { float x = uu[j], y = vv[j]; accum1(gg[j], x, y, a.momentum); uu[j] = x; vv[j] = y; }
+            *(f4u *)(u + e) = uu;
+            *(f4u *)(v + e) = vv;
+        }
+    } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if ((uint32_t)j < count) {
+                float y = v[e + j];
+                if (FUSED) {
+                    float x = u[e + j];
+                    accum1(g[e + j], x, y, a.momentum);
+                    u[e + j] = x; v[e + j] = y;
+                }
+                vv[j] = y;
+            }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        if ((uint32_t)j < count) atomicAdd(&hist[key_of(vv[j]) >> 20], 1u);
+    __syncthreads();
+    a.samples[(size_t)node * kSample + blockIdx.x * (kSmallBins / 2) + tid] = hist[2 * tid] | (hist[2 * tid + 1] << 16);
+}
+
+// The candidate bitmap and row counts (as k_candidates writes them) of the keys that share T*'s leading bits or lie above:
+// every block adds up the chunks' histograms for itself.  Wavefront w of a block takes 256 elements: part w % 4 of row w / 4.
+__global__ __launch_bounds__(1024) void k_small_flags(SelArgs a) {
+    __shared__ uint32_t hist[kSmallBins];
+    __shared__ uint32_t wave_tmp[16], res[2], row_sum[kSmallChunk / kRow];
+    const int node = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const uint32_t chunks = gridDim.x, e = blockIdx.x * kSmallChunk + tid * 4;
+    const float *v = a.v + (size_t)node * a.stride;
+    f4 x = {0.f, 0.f, 0.f, 0.f};
+    if (e < a.n && a.n - e >= 4) x = *(const f4u *)(v + e);
+    else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) if (e + j < a.n) x[j] = v[e + j];
+    }
+    const uint32_t *h = a.samples + (size_t)node * kSample + tid;
+    uint32_t lo = 0, hi = 0;
+    for (uint32_t c0 = 0; c0 < chunks; c0 += 16) {
+        uint32_t y[16];
+#pragma unroll
+        for (int c = 0; c < 16; ++c) y[c] = c0 + c < chunks ? h[(c0 + c) * (kSmallBins / 2)] : 0u;
+#pragma unroll
+        for (int c = 0; c < 16; ++c) { lo += y[c] & 0xffffu; hi += y[c] >> 16; }
+    }
+    hist[2 * tid] = lo; hist[2 * tid + 1] = hi;
+    if (tid < (int)(kSmallChunk / kRow)) row_sum[tid] = 0;
+    __syncthreads();
+    find_rank_bin<kSmallBins>(hist, a.k, wave_tmp, res);
+    const uint32_t least = res[0] << 20;   // (n >= k keys were counted: the bin exists)
+    const uint32_t row = blockIdx.x * (kSmallChunk / kRow) + (wave >> 2);
+    unsigned long long word = 0;
+    uint32_t count = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const unsigned long long m = __ballot(e + j < a.n && key_of(x[j]) >= least);
+        count += (uint32_t)__popcll(m);
+        if (lane == j) word = m;
+    }
+    const uint32_t nrows = (a.n + kRow - 1) / kRow;
+    if (row < nrows && lane < 4) a.bitmap[((size_t)node * a.rows + row) * kRowWords + (wave & 3) * 4 + lane] = word;
+    if (lane == 0) atomicAdd(&row_sum[wave >> 2], count);
+    __syncthreads();
+    if (tid < (int)(kSmallChunk / kRow)) {
+        const uint32_t r = blockIdx.x * (kSmallChunk / kRow) + tid;
+        if (r < nrows) a.row_count[(size_t)node * a.rows + r] = row_sum[tid];
+    }
+}
+
+// the finishing launch's list has to hold the selection and the keys that share T*'s leading bits
+bool small_select_covers(uint64_t n, uint64_t k) { return n < kMinFastN && k <= kFinishList / 3; }
+
+void launch_small_select(const SelArgs &a, int batch, bool fused, bool vec, int cus, hipStream_t st, Bracket br) {
+    const dim3 grid((a.n + kSmallChunk - 1) / kSmallChunk, batch);
+    if (fused) launch_timed(k_small_pass<true>, grid, dim3(1024), st, br, a);
+    else hipLaunchKernelGGL(k_small_pass<false>, grid, dim3(1024), 0, st, a);
+    hipLaunchKernelGGL(k_small_flags, grid, dim3(1024), 0, st, a);
+    launch_finish_from_bitmap(a, batch, false, vec, cus, st);
+}
+
+}  // namespace lgc

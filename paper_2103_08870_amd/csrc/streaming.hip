@@ -7,8 +7,6 @@
 // 1024 elements.  One wavefront per row, twelve 16-byte loads in flight before anything depends on them,
 // non-temporal loads and stores, no LDS, no barrier, no atomics, nothing shared between wavefronts.
 
-#include <hip/hip_ext.h>
-
 #include "device_helpers.h"
 
 namespace lgc {
@@ -100,13 +98,6 @@ static void for_each_share(uint32_t nrows, int batch, Bracket br, F launch) {
             if (b == batch - 1 && nrows - r <= per) e.stop = br.stop;
             launch((uint32_t)b, 1, r, nrows - r < per ? nrows : r + per, e);
         }
-}
-
-// An ordinary launch, or, with timing events, the launch form that stamps them itself.
-template <typename K, typename... Args>
-static void launch_timed(K kernel, dim3 grid, dim3 block, hipStream_t st, Bracket e, Args... args) {
-    if (e.start || e.stop) hipExtLaunchKernelGGL(kernel, grid, block, 0, st, e.start, e.stop, 0, args...);
-    else hipLaunchKernelGGL(kernel, grid, block, 0, st, args...);
 }
 
 void launch_accumulate(const float *g, float *u, float *v, uint32_t n, int batch, uint64_t stride,

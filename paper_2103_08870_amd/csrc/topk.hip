@@ -1100,6 +1100,186 @@ __global__ __launch_bounds__(1024) void k_output_or_exact(SelArgs a, uint32_t ou
     exact_tickets<VEC, 1024>(a, node, gridDim.y - out_blocks, hist, wave_tmp, res);
 }
 
+// From the candidates' bitmap to the output in ONE launch, for short lists: block 0 of a node (grid y) lists the flagged
+// elements in its LDS, in index order, finds T* among them and writes the selection; the blocks after it stand
+// by for the exact path and decide for themselves, from the row counts, whether they are needed.  k_gather and
+// k_output_or_exact do the same for longer lists with many blocks: two launches and a list that one writes to
+// memory for the other to read.
+__device__ __forceinline__ void finish_node(const SelArgs &a, const int node, const uint32_t total, const int report,
+                                            const uint32_t *offs /*[kFinishRows + 1]: list entries before each row*/, uint32_t *hist /*[kFineBins]*/,
+                                            uint32_t *wave_tmp /*[16]*/, uint32_t *res /*[2]*/) {
+    __shared__ uint32_t list_idx[kFinishList], list_val[kFinishList];
+    const int tid = threadIdx.x, lane = tid & 63;
+    Sel *s = a.sel + node;
+    const uint32_t nrows = (a.n + kRow - 1) / kRow;
+    float *v = a.v + (size_t)node * a.stride;
+    float *u = a.u ? a.u + (size_t)node * a.stride : nullptr;
+    // 16 lanes per row, lane 4 s + j holds word 4 s + j of it: element 256 s + 4 l + j is bit l.  In element order the
+    // bits of the four words of one s interleave.
+    const unsigned long long *bitmap = a.bitmap + (size_t)node * a.rows * kRowWords;
+    for (uint32_t base = 0; base < nrows; base += 256) {   // four rows per 16 lanes, their words in flight together
+        unsigned long long w[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const uint32_t r = base + t * 64 + (tid >> 4);
+            w[t] = r < nrows && offs[r + 1] != offs[r] ? bitmap[(size_t)r * kRowWords + (tid & 15)] : 0ull;
+        }
+#pragma unroll 1
+        for (int t = 0; t < 4; ++t) {
+            unsigned long long bits = t == 0 ? w[0] : t == 1 ? w[1] : t == 2 ? w[2] : w[3];
+            if (__ballot(bits != 0) == 0) continue;   // wave-uniform; no barrier in these loops
+            const uint32_t r = base + t * 64 + (tid >> 4), j = tid & 3u;
+            // the words of this s, and the flags of the earlier s of the row
+            unsigned long long x[4];
+            uint32_t mine = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                x[q] = ((unsigned long long)__shfl((uint32_t)(bits >> 32), (lane & ~3) | q, 64) << 32) | __shfl((uint32_t)bits, (lane & ~3) | q, 64);
+                mine += (uint32_t)__popcll(x[q]);
+            }
+            uint32_t before = r < nrows ? offs[r] : 0u;
+#pragma unroll
+            for (int q = 0; q < 3; ++q) { const uint32_t y = __shfl(mine, (lane & ~15) | (q * 4), 64); before += q < ((lane >> 2) & 3) ? y : 0u; }
+            while (bits) {
+                const int l = __ffsll(bits) - 1;
+                bits &= bits - 1;
+                const unsigned long long below = (1ull << l) - 1ull;
+                uint32_t at = before;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) at += (uint32_t)__popcll(x[q] & below) + ((uint32_t)q < j ? (uint32_t)(x[q] >> l) & 1u : 0u);
+                list_idx[at] = r * (uint32_t)kRow + ((lane >> 2) & 3) * 256u + 4u * l + j;   // at < total <= kFinishList
+            }
+        }
+    }
+    __syncthreads();
+    // the values, the largest and the smallest key
+    uint32_t most = 0;
+    uint32_t least = ~0u;
+#pragma unroll 1
+    for (uint32_t i0 = tid; i0 < total; i0 += 4096) {   // four reads in flight
+        uint32_t x[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) x[q] = i0 + q * 1024 < total ? __float_as_uint(v[list_idx[i0 + q * 1024]]) : 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (i0 + q * 1024 < total) {
+                list_val[i0 + q * 1024] = x[q];
+                const uint32_t key = x[q] & 0x7fffffffu;
+                most = key > most ? key : most; least = key < least ? key : least;
+            }
+    }
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) {
+        const uint32_t y = __shfl_xor(most, d, 64), z = __shfl_xor(least, d, 64);
+        most = y > most ? y : most; least = z < least ? z : least;
+    }
+    if (lane == 0) { hist[tid >> 6] = most; hist[16 + (tid >> 6)] = least; }
+    __syncthreads();
+    most = hist[lane & 15]; least = hist[16 + (lane & 15)];
+#pragma unroll
+    for (int d = 8; d >= 1; d >>= 1) {
+        const uint32_t y = __shfl_xor(most, d, 64), z = __shfl_xor(least, d, 64);
+        most = y > most ? y : most; least = z < least ? z : least;
+    }
+    // T*: digits of at most 12 bits of (key - least), as many as the keys' spread needs
+    uint32_t need = a.k, prefix = 0, ties = 0;
+    uint32_t bits = most > least ? 32u - (uint32_t)__clz(most - least) : 1u;   // of the largest difference
+    bits = __builtin_amdgcn_readfirstlane(bits);
+    uint32_t shift = bits;
+    while (shift) {                               // block-uniform
+        const uint32_t digit = shift < 12u ? shift : 12u, next = shift - digit;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kFineBins / 1024; ++i) hist[i * 1024 + tid] = 0;
+        __syncthreads();
+#pragma unroll 1
+        for (uint32_t i = tid; i < total; i += 1024) {
+            const uint32_t d = (list_val[i] & 0x7fffffffu) - least;
+            if ((uint32_t)((unsigned long long)d >> shift) == prefix) atomicAdd(&hist[(d >> next) & ((1u << digit) - 1u)], 1u);
+        }
+        __syncthreads();
+        find_rank_bin<kFineBins>(hist, need, wave_tmp, res);
+        need -= res[1];
+        ties = hist[res[0] & (kFineBins - 1)];
+        prefix = (prefix << digit) | res[0];
+        shift = next;
+    }
+    const uint32_t thr = least + prefix, quota = need;
+    if (tid == 0) {
+        if (report) report_outcome(a, node, s, true, thr, quota, total, s->t_est);
+        else carry_lapse(a, node);
+    }
+    // ordered output: kLen consecutive entries per thread
+    constexpr uint32_t kLen = kFinishList / 1024;
+    const uint32_t per = (total + 1023u) / 1024u, i0 = tid * per;
+    uint32_t gt = 0, eq = 0;
+#pragma unroll 1
+    for (uint32_t i = 0; i < per; ++i) {
+        const uint32_t key = i0 + i < total ? list_val[i0 + i] & 0x7fffffffu : 0u;
+        gt += i0 + i < total && key > thr; eq += i0 + i < total && key == thr;
+    }
+    static_assert(kLen * 1024 == kFinishList && kFinishList < (1u << 16), "both counts in one word");
+    uint32_t all;
+    const uint32_t pre = block_scan(gt | (eq << 16), wave_tmp, all);
+    if (tid == 0 && (all & 0xffffu) + (ties < quota ? ties : quota) != a.k) atomicAdd(&a.stats->errors, 1u);
+    uint32_t cg = pre & 0xffffu, ce = pre >> 16;
+    uint32_t *oidx = a.out_idx + (size_t)node * a.k;
+    float *oval = a.out_vals + (size_t)node * a.k;
+#pragma unroll 1
+    for (uint32_t i = i0; i < i0 + per && i < total; ++i) {
+        const uint32_t x = list_val[i], key = x & 0x7fffffffu, ix = list_idx[i];
+        const bool fg = key > thr, fe = key == thr;
+        if (fg || (fe && ce < quota)) {
+            const uint32_t o = cg + (ce < quota ? ce : quota);
+            if (o < a.k) { oidx[o] = ix; oval[o] = __uint_as_float(x); }
+            v[ix] = 0.0f;
+            if (u) u[ix] = 0.0f;
+        }
+        cg += fg; ce += fe;
+    }
+}
+
+template <bool VEC>
+__global__ __launch_bounds__(1024) void k_finish_or_exact(SelArgs a, int report) {
+    __shared__ uint32_t hist[kFineBins];
+    __shared__ uint32_t wave_tmp[16], res[2];
+    __shared__ uint32_t offs[kFinishRows + 1];
+    constexpr int kPer = kFinishRows / 1024;
+    const int node = blockIdx.x, tid = threadIdx.x;
+    const uint32_t nrows = (a.n + kRow - 1) / kRow;
+    const uint32_t *cnt = a.row_count + (size_t)node * a.rows;
+    uint32_t total;
+    {
+        uint32_t c[kPer], sum = 0;
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) { c[i] = (uint32_t)(tid * kPer + i) < nrows ? cnt[tid * kPer + i] : 0u; sum += c[i]; }
+        uint32_t at = block_scan(sum, wave_tmp, total);
+#pragma unroll
+        for (int i = 0; i < kPer; ++i) { offs[tid * kPer + i] = at; at += c[i]; }
+        if (tid == 1023) offs[kFinishRows] = at;
+    }
+    __syncthreads();
+    total = __builtin_amdgcn_readfirstlane(total);
+    const bool ok = total >= a.k && total <= kFinishList;   // the same for all the node's blocks
+    if (blockIdx.y != 0) {
+        if (!ok) exact_tickets<VEC, 1024>(a, node, gridDim.y - 1, hist, wave_tmp, res);
+        return;
+    }
+    if (tid == 0) a.sel[node].cand_total = total;
+    if (ok) finish_node(a, node, total, report, offs, hist, wave_tmp, res);
+    else if (tid == 0 && report) report_outcome(a, node, a.sel + node, false, 0, 0, total, a.sel[node].t_est);
+}
+
+void launch_finish_from_bitmap(const SelArgs &a, int batch, bool report, bool vec, int cus, hipStream_t st) {
+    const uint32_t chunks = (a.n + 16383u) / 16384u;
+    uint32_t standby = (uint32_t)(cus / batch);   // as in launch_output_from_candidates
+    if (standby > chunks) standby = chunks;
+    if (standby < 1) standby = 1;
+    const dim3 grid(batch, 1 + standby);
+    if (vec) hipLaunchKernelGGL(k_finish_or_exact<true>, grid, dim3(1024), 0, st, a, (int)report);
+    else hipLaunchKernelGGL(k_finish_or_exact<false>, grid, dim3(1024), 0, st, a, (int)report);
+}
+
 // Five launches: step 0..2: the radix pass of that digit (the digits before it are fixed again from their
 // finished histograms: a few microseconds, no exchange); step 3: T*, the tie quota and the counts of every
 // block's run; step 4: the ordered output.  The blocks need not be resident together, and their number is

@@ -1,0 +1,98 @@
+"""Exact top-k of short vectors (their own two launches) against the oracle: chunk and bitmap edges, ties through the cut,
+more keys sharing the threshold's leading bits than the LDS list holds, odd row starts, both callers."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2103_08870_amd import binding
+    binding.lib()
+    assert torch.cuda.is_available()
+    return binding
+
+
+def values(kind, rng, shape):
+    if kind == "normal":
+        return rng.normal(0, 1e-3, shape).astype(np.float32)
+    if kind == "few":        # seven magnitudes: every cut lies inside a tie, and the list overflows on long vectors
+        return (rng.integers(0, 7, shape) * rng.choice([-0.5, 0.5], shape)).astype(np.float32)
+    if kind == "narrow":     # all keys share their leading bits, none are equal by design
+        return (1.0 + rng.random(shape) * 0.1).astype(np.float32)
+    out = rng.normal(0, 1, shape).astype(np.float32)          # "special"
+    flat = out.reshape(-1)
+    for i, x in enumerate((np.inf, -np.inf, np.nan, 0.0, -0.0, 1e-42)):
+        flat[i::11 + i] = x
+    return out
+
+
+def same(t, a):
+    h = t.cpu().numpy()
+    nan = np.isnan(a)
+    return (np.isnan(h) == nan).all() and (h.view(np.uint32)[~nan] == a.view(np.uint32)[~nan]).all()
+
+
+@pytest.mark.parametrize("kind", ["normal", "few", "narrow", "special"])
+@pytest.mark.parametrize("n,k,batch,pad", [(1, 1, 1, 0), (3, 2, 3, 2), (4095, 4095 // 3, 2, 1), (4096, 1, 1, 0), (4097, 3072, 3, 0),
+                                           (32_767, 300, 2, 2), (32_768, 3072, 1, 0), (32_769, 33, 2, 3), (100_003, 1000, 2, 1),
+                                           (262_143, 2621, 1, 0), (262_143, 3073, 2, 1)])
+def test_short_vectors(B, oracle, kind, n, k, batch, pad):
+    rng = np.random.default_rng(n + k)
+    g, u, v = (values(kind, rng, (batch, n + pad)) for _ in range(3))
+    ctx = B.Context(n, k, batch)
+    with np.errstate(all="ignore"):
+        for b in range(batch):
+            oracle.accumulate(g[b, :n], un := u[b, :n].copy(), vn := v[b, :n].copy(), 0.9)
+            if b == 0:
+                eu, ev, ei, eo = [], [], [], []
+            vals, idx = oracle.topk(vn, un, k)
+            eu.append(un); ev.append(vn); ei.append(idx); eo.append(vals)
+    for call in ("context", "static", "pair", "radix"):
+        dg, du, dv = (torch.from_numpy(a).cuda()[:, :n] for a in (g, u, v))
+        ov = torch.zeros((batch, k), device="cuda")
+        oi = torch.zeros((batch, k), dtype=torch.int32, device="cuda")
+        if call == "static":
+            B.lgc_accumulate_topk_static(dg, du, dv, 0.9, k, ov, oi)
+        elif call == "pair":
+            B.lgc_accumulate(ctx, dg, du, dv, 0.9)
+            B.lgc_topk(ctx, dv, du, k, ov, oi)
+        else:
+            B.lgc_set_option(ctx, B.LGC_OPT_SELECT_PATH, 1 if call == "radix" else 0)
+            B.lgc_accumulate_topk(ctx, dg, du, dv, 0.9, k, ov, oi)
+        assert (oi.cpu().numpy().astype(np.uint32) == np.stack(ei)).all(), call
+        assert same(ov, np.stack(eo)) and same(dv, np.stack(ev)) and same(du, np.stack(eu)), call
+    assert B.lgc_stats(ctx)[2] == 0
+    ctx.close()
+
+
+def test_short_and_long_vectors_in_one_graph(B):
+    # two selections per replay on alternating scratch, one of them by the short vectors' kernels
+    gen = torch.Generator(device="cuda"); gen.manual_seed(3)
+    shapes = [(100_003, 100), (400_000, 400)]
+    ctx = B.Context(400_000, 400, 1)
+
+    def tensors():
+        gen.manual_seed(3)
+        return [[torch.randn(n, generator=gen, device="cuda") for _ in range(3)]
+                + [torch.zeros(k, device="cuda"), torch.zeros(k, dtype=torch.int32, device="cuda")] for n, k in shapes]
+
+    def step(ts, c):
+        for (n, k), (g, u, v, ov, oi) in zip(shapes, ts):
+            B.lgc_accumulate_topk(c, g, u, v, 0.9, k, ov, oi)
+
+    recorded, eager = tensors(), tensors()
+    other = B.Context(400_000, 400, 1)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step(recorded, ctx)
+    for _ in range(5):
+        graph.replay()
+        step(eager, other)
+        torch.cuda.synchronize()
+        for r, e in zip(recorded, eager):
+            assert all(torch.equal(x, y) for x, y in zip(r, e))
+    assert B.lgc_stats(ctx)[2] == 0 and B.lgc_stats(other)[2] == 0
+    ctx.close(); other.close()
