@@ -58,11 +58,11 @@ __device__ __forceinline__ void radix_pass(Each each, uint32_t &rank, uint32_t &
         __syncthreads();
         for (int i = tid; i < 1024; i += T) hist[i] = i < 256 ? sum : 0u;   // i < 256 only in the first trip: i == tid
         __syncthreads();
-        find_rank_bin<1024>(hist, rank, wave_tmp, res);
+        find_rank_bin<1024, T>(hist, rank, wave_tmp, res);
     } else if (PASS == 1) {
-        find_rank_bin<2048>(hist, rank, wave_tmp, res);
+        find_rank_bin<2048, T>(hist, rank, wave_tmp, res);
     } else {
-        find_rank_bin<4096>(hist, rank, wave_tmp, res);
+        find_rank_bin<4096, T>(hist, rank, wave_tmp, res);
     }
     const uint32_t digit = res[0] == 0xffffffffu ? 0u : res[0];
     const uint32_t more = res[1];
@@ -89,7 +89,7 @@ __device__ __forceinline__ uint32_t block_radix_select(Each each, uint32_t rank,
 // The kernel also clears the state set that the next call will use.
 template <bool FUSED, bool VEC>
 __global__ __launch_bounds__(1024) void k_seg_estimate(SelArgs a) {
-    __shared__ uint32_t hist[4096];
+    __shared__ __align__(16) uint32_t hist[4096];
     __shared__ uint32_t wave_tmp[16], res[2];
     const uint32_t l = blockIdx.x, tid = threadIdx.x;
     const int node = blockIdx.y;
@@ -315,7 +315,7 @@ __device__ __forceinline__ uint32_t select_in_block(const uint32_t *__restrict__
 // One block per (segment, node).
 template <bool VEC>
 __global__ __launch_bounds__(kSelThreads) void k_seg_select(SelArgs a) {
-    __shared__ uint32_t hist[4096];
+    __shared__ __align__(16) uint32_t hist[4096];
     __shared__ uint32_t wave_tmp[16], res[2], sh_g[16], sh_e[16];
     const uint32_t l = blockIdx.x;
     const int node = blockIdx.y;
@@ -397,7 +397,7 @@ template <bool VEC>
 __global__ __launch_bounds__(kSelThreads) void k_innovation(const float *__restrict__ vals, float *__restrict__ out,
                                                             uint32_t n, const uint32_t *__restrict__ seg_off,
                                                             const uint32_t *__restrict__ seg_k, Stats *stats) {
-    __shared__ uint32_t hist[4096];
+    __shared__ __align__(16) uint32_t hist[4096];
     __shared__ uint32_t wave_tmp[16], res[2], sh_g[16], sh_e[16];
     const uint32_t l = blockIdx.x;
     const uint32_t lo = seg_off[l], hi = seg_off[l + 1], k = seg_k[l];

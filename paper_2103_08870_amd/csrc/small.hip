@@ -22,7 +22,7 @@ static_assert((size_t)((kMinFastN + kSmallChunk - 1) / kSmallChunk) * (kSmallBin
 // elements per thread: the shortest chain.
 template <bool FUSED>
 __global__ __launch_bounds__(1024) void k_small_pass(SelArgs a) {
-    __shared__ uint32_t hist[kSmallBins];
+    __shared__ __align__(16) uint32_t hist[kSmallBins];
     const int node = blockIdx.y, tid = threadIdx.x;
     {
         const uint32_t gt = (blockIdx.y * gridDim.x + blockIdx.x) * 1024u + tid, nt = gridDim.x * gridDim.y * 1024u;
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(1024) void k_small_pass(SelArgs a) {
 // The candidate bitmap and row counts (as k_candidates writes them) of the keys that share T*'s leading bits or lie above:
 // every block adds up the chunks' histograms for itself.  Wavefront w of a block takes 256 elements: part w % 4 of row w / 4.
 __global__ __launch_bounds__(1024) void k_small_flags(SelArgs a) {
-    __shared__ uint32_t hist[kSmallBins];
+    __shared__ __align__(16) uint32_t hist[kSmallBins];
     __shared__ uint32_t wave_tmp[16], res[2], row_sum[kSmallChunk / kRow];
     const int node = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t chunks = gridDim.x, e = blockIdx.x * kSmallChunk + tid * 4;
@@ -92,7 +92,7 @@ __global__ __launch_bounds__(1024) void k_small_flags(SelArgs a) {
     hist[2 * tid] = lo; hist[2 * tid + 1] = hi;
     if (tid < (int)(kSmallChunk / kRow)) row_sum[tid] = 0;
     __syncthreads();
-    find_rank_bin<kSmallBins>(hist, a.k, wave_tmp, res);
+    find_rank_bin<kSmallBins, 1024>(hist, a.k, wave_tmp, res);
     const uint32_t least = res[0] << 20;   // (n >= k keys were counted: the bin exists)
     const uint32_t row = blockIdx.x * (kSmallChunk / kRow) + (wave >> 2);
     unsigned long long word = 0;

@@ -69,7 +69,7 @@ __device__ __forceinline__ uint32_t mix32(uint32_t h) {
 // The kernel also clears the state set that the next call will use.
 template <bool FUSED, bool VEC>
 __global__ __launch_bounds__(1024) void k_sample(SelArgs a) {
-    __shared__ uint32_t hist[kSampleBins];
+    __shared__ __align__(16) uint32_t hist[kSampleBins];
     __shared__ uint32_t wave_tmp[16], res[2];
     __shared__ uint32_t sh_last;
     const int node = blockIdx.y, tid = threadIdx.x;
@@ -141,7 +141,7 @@ __global__ __launch_bounds__(1024) void k_sample(SelArgs a) {
     for (int r = 0; r < (int)(kSample / 4 / 1024); ++r) x[r] = *(const u4 *)(smp + (r * 1024 + tid) * 4);
     for (int i = tid; i < kSampleBins; i += 1024) hist[i] = ld_agent32(&sh[i]);
     __syncthreads();
-    find_rank_bin<kSampleBins>(hist, a.rank, wave_tmp, res);
+    find_rank_bin<kSampleBins, 1024>(hist, a.rank, wave_tmp, res);
     const uint32_t b1 = res[0], need = a.rank - res[1];
     __syncthreads();
     if (b1 == 0xffffffffu) return;  // cannot happen (rank <= kSample); t_est stays 0: everything is a candidate
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(1024) void k_sample(SelArgs a) {
             if ((x[r][i] >> 20) == b1) atomicAdd(&hist[(x[r][i] >> 10) & 1023u], 1u);
     }
     __syncthreads();
-    find_rank_bin<1024>(hist, need, wave_tmp, res);
+    find_rank_bin<1024, 1024>(hist, need, wave_tmp, res);
     if (tid == 0) a.sel[node].t_est = (b1 << 20) | ((res[0] == 0xffffffffu ? 0u : res[0]) << 10);
 }
 
@@ -214,7 +214,7 @@ __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
     constexpr int kGatherRows = ROWS;
     constexpr int kPairs = (ROWS * kRowWords / 2 + THREADS - 1) / THREADS;   // pairs of bitmap words per thread
     static_assert(ROWS % 64 == 0 && ROWS <= THREADS && (ROWS & (ROWS - 1)) == 0, "rows per block");
-    __shared__ uint32_t hist[HIST ? kFineBins : 1];
+    __shared__ __align__(16) uint32_t hist[HIST ? kFineBins : 1];
     __shared__ unsigned long long rows_lds[kGatherRows * kRowWords];
     __shared__ uint32_t offs[kGatherRows];
     __shared__ uint32_t tmp[16];
@@ -258,12 +258,7 @@ __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
     if (HIST) for (int i = tid; i < kFineBins; i += THREADS) hist[i] = 0;
     const uint32_t before = block_sum<THREADS>(part, tmp);   // contains barriers: LDS is filled for all
     // exclusive scan of c over the first kGatherRows threads
-    uint32_t incl = c;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += y;
-    }
+    const uint32_t incl = wave_prefix(c);
     __syncthreads();
     if (lane == 63) tmp[wave] = incl;
     __syncthreads();
@@ -410,7 +405,7 @@ __device__ bool find_threshold(const SelArgs &a, int node, uint32_t total, uint3
     const uint32_t t_est = s->t_est;
     for (int i = tid; i < kFineBins; i += nt) hist[i] = a.fine_hist[node * kFineBins + i];
     __syncthreads();
-    find_rank_bin<kFineBins>(hist, a.k, wave_tmp, res);
+    find_rank_bin<kFineBins, 1024>(hist, a.k, wave_tmp, res);
     const uint32_t bin = res[0], need = a.k - res[1];
     __syncthreads();
     if (bin >= (uint32_t)kFineBins - 1) return false;
@@ -424,7 +419,7 @@ __device__ bool find_threshold(const SelArgs &a, int node, uint32_t total, uint3
         for (int i = tid; i < kFineBins; i += nt) hist[i] = a.level2_hist[node * kFineBins + i];
     }
     __syncthreads();
-    find_rank_bin<kFineBins>(hist, need, wave_tmp, res);
+    find_rank_bin<kFineBins, 1024>(hist, need, wave_tmp, res);
     thr = t_est + (bin << kFineShift) + res[0];
     quota = need - res[1];
     __syncthreads();
@@ -433,7 +428,7 @@ __device__ bool find_threshold(const SelArgs &a, int node, uint32_t total, uint3
 
 // Second-level histogram for long candidate lists: many blocks, each counts a slice.
 __global__ __launch_bounds__(1024) void k_select_level2(SelArgs a) {
-    __shared__ uint32_t hist[kFineBins];
+    __shared__ __align__(16) uint32_t hist[kFineBins];
     __shared__ uint32_t wave_tmp[16], res[2];
     const int node = blockIdx.y, tid = threadIdx.x;
     const Sel *s = a.sel + node;
@@ -442,7 +437,7 @@ __global__ __launch_bounds__(1024) void k_select_level2(SelArgs a) {
     const uint32_t t_est = s->t_est;
     for (int i = tid; i < kFineBins; i += 1024) hist[i] = a.fine_hist[node * kFineBins + i];
     __syncthreads();
-    find_rank_bin<kFineBins>(hist, a.k, wave_tmp, res);
+    find_rank_bin<kFineBins, 1024>(hist, a.k, wave_tmp, res);
     const uint32_t bin = res[0];
     __syncthreads();
     if (bin >= (uint32_t)kFineBins - 1) return;
@@ -503,7 +498,7 @@ __device__ __forceinline__ void output_direct(const SelArgs &a, const int node, 
 
     uint32_t thr = 0, quota = 0;
     if (ok) {   // uniform
-        find_rank_bin<kFineBins>(hist, a.k, wave_tmp, res);
+        find_rank_bin<kFineBins, 1024>(hist, a.k, wave_tmp, res);
         const uint32_t bin = res[0], need = a.k - res[1];
         __syncthreads();
         ok = bin < (uint32_t)kFineBins - 1;   // T* beyond the histogram's range: leave it to the exact path
@@ -526,7 +521,7 @@ __device__ __forceinline__ void output_direct(const SelArgs &a, const int node, 
                 for (int c = 0; c < 4; ++c) tally(x[c]);
             }
             __syncthreads();
-            find_rank_bin<kFineBins>(hist, need, wave_tmp, res);
+            find_rank_bin<kFineBins, 1024>(hist, need, wave_tmp, res);
             thr = t_est + (bin << kFineShift) + res[0];
             quota = need - res[1];
         }
@@ -756,7 +751,7 @@ __device__ __forceinline__ void emit_run(const SelArgs &a, const int node, const
 constexpr int kCountChunks = 4;   // chunks per block of k_count_chunks
 
 __global__ __launch_bounds__(1024) void k_count_chunks(SelArgs a) {
-    __shared__ uint32_t hist[kFineBins];
+    __shared__ __align__(16) uint32_t hist[kFineBins];
     __shared__ uint32_t wave_tmp[16], res[2];
     __shared__ uint32_t sh_gt[kCountChunks][16], sh_eq[kCountChunks][16];
     const int node = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -926,10 +921,11 @@ __device__ __forceinline__ void radix_count(const SelArgs &a, const int node, co
 
 // From a finished histogram of `pass` in LDS: the digit that holds the rank-th largest key, appended to prefix;
 // rank becomes the rank inside that digit's keys.  Block-wide.
+template <int THREADS>
 __device__ __forceinline__ void radix_digit(const int pass, const uint32_t *hist, uint32_t *wave_tmp, uint32_t *res,
                                             uint32_t &prefix, uint32_t &rank) {
-    if (pass == 0) find_rank_bin<kRadixBins>(hist, rank, wave_tmp, res);
-    else find_rank_bin<1024>(hist, rank, wave_tmp, res);
+    if (pass == 0) find_rank_bin<kRadixBins, THREADS>(hist, rank, wave_tmp, res);
+    else find_rank_bin<1024, THREADS>(hist, rank, wave_tmp, res);
     const uint32_t digit = res[0] == 0xffffffffu ? 0u : res[0];
     rank -= res[1];
     prefix = pass == 0 ? digit : ((prefix << 10) | digit);
@@ -945,7 +941,7 @@ __device__ __forceinline__ void radix_fix(const SelArgs &a, const int node, cons
     const uint32_t *gh = a.radix_hist + (node * 3 + pass) * kRadixBins;
     for (int i = tid; i < kRadixBins; i += THREADS) hist[i] = i < nb ? ld_agent32(&gh[i]) : 0u;
     __syncthreads();
-    radix_digit(pass, hist, wave_tmp, res, prefix, rank);
+    radix_digit<THREADS>(pass, hist, wave_tmp, res, prefix, rank);
 }
 
 // run number `run` of `nruns` in the ordered output: the chunks [run * per, (run + 1) * per) of the node
@@ -961,7 +957,7 @@ __device__ __forceinline__ void block_run(const SelArgs &a, const uint32_t run, 
 // One block of 1024 threads per node (grid (1, nodes)), everything in that block.
 template <bool VEC>
 __global__ __launch_bounds__(1024) void k_exact_block(SelArgs a) {
-    __shared__ uint32_t hist[kRadixBins];
+    __shared__ __align__(16) uint32_t hist[kRadixBins];
     __shared__ uint32_t wave_tmp[16], res[2];
     const int node = blockIdx.y, tid = threadIdx.x;
     Sel *s = a.sel + node;
@@ -976,7 +972,7 @@ __global__ __launch_bounds__(1024) void k_exact_block(SelArgs a) {
         __syncthreads();
         radix_tally<VEC, 1024>(v, a.n, tid, 1024u, pass, prefix, hist);
         __syncthreads();
-        radix_digit(pass, hist, wave_tmp, res, prefix, rank);
+        radix_digit<1024>(pass, hist, wave_tmp, res, prefix, rank);
     }
     // prefix is now the full key T*; rank the number of ties to take
     if (tid == 0) { s->thr = prefix; s->quota = rank; carry_lapse(a, node); }
@@ -1061,7 +1057,7 @@ __device__ __forceinline__ void exact_tickets(const SelArgs &a, const int node, 
 // Exact selection as one launch of its own: about one block of 1024 threads per compute unit, shared by the nodes.
 template <bool VEC>
 __global__ __launch_bounds__(1024) void k_exact(SelArgs a) {
-    __shared__ uint32_t hist[kRadixBins];
+    __shared__ __align__(16) uint32_t hist[kRadixBins];
     __shared__ uint32_t wave_tmp[16], res[2];
     const int node = blockIdx.y, tid = threadIdx.x;
     if (!a.force && a.sel[node].fast_ok) return;
@@ -1080,7 +1076,7 @@ __global__ __launch_bounds__(1024) void k_exact(SelArgs a) {
 // of its own for the fall-back costs 4.5 us per call even when it has nothing to do.
 template <bool VEC>
 __global__ __launch_bounds__(1024) void k_output_or_exact(SelArgs a, uint32_t out_blocks) {
-    __shared__ uint32_t hist[kFineBins];
+    __shared__ __align__(16) uint32_t hist[kFineBins];
     __shared__ uint32_t wave_tmp[16], res[2];
     // grid (nodes, blocks per node): blocks are handed out with x fastest, so every node's output blocks are on the
     // device before the first stand-by block (a compute unit holds one block of this kernel at a time)
@@ -1092,7 +1088,7 @@ __global__ __launch_bounds__(1024) void k_output_or_exact(SelArgs a, uint32_t ou
     if (ok) {   // the same for the whole block
         for (int i = tid; i < kFineBins; i += 1024) hist[i] = a.fine_hist[node * kFineBins + i];
         __syncthreads();
-        find_rank_bin<kFineBins>(hist, a.k, wave_tmp, res);
+        find_rank_bin<kFineBins, 1024>(hist, a.k, wave_tmp, res);
         ok = res[0] < (uint32_t)kFineBins - 1;
         __syncthreads();
     }
@@ -1198,7 +1194,7 @@ __device__ __forceinline__ void finish_node(const SelArgs &a, const int node, co
             if ((uint32_t)((unsigned long long)d >> shift) == prefix) atomicAdd(&hist[(d >> next) & ((1u << digit) - 1u)], 1u);
         }
         __syncthreads();
-        find_rank_bin<kFineBins>(hist, need, wave_tmp, res);
+        find_rank_bin<kFineBins, 1024>(hist, need, wave_tmp, res);
         need -= res[1];
         ties = hist[res[0] & (kFineBins - 1)];
         prefix = (prefix << digit) | res[0];
@@ -1241,7 +1237,7 @@ __device__ __forceinline__ void finish_node(const SelArgs &a, const int node, co
 
 template <bool VEC>
 __global__ __launch_bounds__(1024) void k_finish_or_exact(SelArgs a, int report) {
-    __shared__ uint32_t hist[kFineBins];
+    __shared__ __align__(16) uint32_t hist[kFineBins];
     __shared__ uint32_t wave_tmp[16], res[2];
     __shared__ uint32_t offs[kFinishRows + 1];
     constexpr int kPer = kFinishRows / 1024;
@@ -1286,7 +1282,7 @@ void launch_finish_from_bitmap(const SelArgs &a, int batch, bool report, bool ve
 // chosen for the passes over v alone.
 template <bool VEC>
 __global__ __launch_bounds__(kBlock) void k_exact_step(SelArgs a, int step) {
-    __shared__ uint32_t hist[kRadixBins];
+    __shared__ __align__(16) uint32_t hist[kRadixBins];
     __shared__ uint32_t wave_tmp[kWaves], res[2];
     const int node = blockIdx.y, tid = threadIdx.x;
     Sel *s = a.sel + node;
