@@ -34,6 +34,7 @@ struct lgc_ctx {
     uint32_t supers = 0;
     unsigned long long *bitmap = nullptr;
     uint32_t *cand_idx = nullptr, *cand_val = nullptr;
+    uint32_t *row_rec = nullptr;      // records of the rows with few candidates (an allocation of its own, or none)
     float *act[2] = {nullptr, nullptr};  // autoencoder activations (ping-pong), grown on demand
     size_t act_floats = 0;
     // per-layer selection: thresholds [max_batch][n_seg] and a candidate list of its own, grown on demand
@@ -281,6 +282,7 @@ SelArgs make_args(lgc_ctx *c, const float *g, float *u, float *v, uint64_t n, ui
     a.next_state = c->state[c->cur ^ 1]; a.next_words = c->single_state ? 0u : c->state_words;
     a.samples = c->samples; a.row_count = c->row_count; a.bitmap = c->bitmap;
     a.row_super = c->row_super; a.supers = c->supers;
+    a.row_rec = c->row_rec;
     a.cand_idx = c->cand_idx; a.cand_val = c->cand_val;
     a.out_vals = out_vals; a.out_idx = out_idx;
     return a;
@@ -291,36 +293,43 @@ constexpr int kMaxExactCalls = 64;   // most selections in a row that take the e
 // Short vectors are selected exactly by kernels of their own, unless the exact radix path was asked for.
 bool takes_small_path(const lgc_ctx *ctx, uint64_t n, uint64_t k) { return ctx->opt_path != 1 && small_select_covers(n, k); }
 
+// Short candidate lists of vectors that are not too long go from the bitmap to the output in one launch of one block
+// per node, with a third of the list to spare.
+bool takes_finish(uint64_t n, uint64_t k) {
+    return (n + kRow - 1) / kRow <= kFinishRows && 1.5 * expected_candidates((double)n, (double)k) + 2048.0 <= (double)kFinishList;
+}
+
 // accumulate (optional) + select; g == nullptr means selection only
 lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t n, int batch, uint64_t stride,
                       float m, uint64_t k, float *out_vals, uint32_t *out_idx, hipStream_t st) {
     const bool fused = g != nullptr;
-    const bool vec = aligned(v, 16) && (!u || aligned(u, 16)) && (!g || aligned(g, 16)) &&
-                     (batch == 1 || stride % 4 == 0);
     if (k == 0) {
         if (fused) {
-            launch_accumulate(g, u, v, (uint32_t)n, batch, stride, m, vec, st, profile_bracket(ctx));
+            launch_accumulate(g, u, v, (uint32_t)n, batch, stride, m, st, profile_bracket(ctx));
         }
         return LGC_OK;
     }
     SelArgs a = make_args(ctx, g, u, v, n, stride, m, k, out_vals, out_idx);
+    const bool finishes_in_one = takes_finish(n, k);
     {   // a carried threshold aims at 1.5 k candidates, or at what a sample would give where that is fewer (large k)
         const double sampled = expected_candidates((double)n, (double)k) / (double)k;
         a.carry_target = (float)log2(sampled < 1.5 ? sampled : 1.5);
         // and is offered only if it is expected to flag no more than 2.2 k, and no more than the list holds with
         // a third of the margin to spare (log scale)
-        const double room = 0.75 * log2((double)ctx->cap / (double)k);
+        const double holds = finishes_in_one ? std::min((double)ctx->cap, (double)kFinishList) : (double)ctx->cap;
+        const double room = 0.75 * log2(holds / (double)k);
         a.carry_most = (float)(room < log2(2.2) ? room : log2(2.2));
     }
     ctx->last_seg = nullptr;
+    bool small = takes_small_path(ctx, n, k);
     bool fast = ctx->opt_path != 1 && n >= kMinFastN;
     if (fast) {
         a.rank = choose_rank((uint32_t)n, (uint32_t)k);
         fast = a.rank <= kSample / 4 &&
                1.5 * expected_candidates((double)n, (double)k) + 4096.0 <= (double)ctx->cap;
     }
-    if (fast && ctx->opt_path == 0 && ctx->fell_back_host) {
-        // data on which the fast path keeps failing (very many equal magnitudes around the k-th largest): reaching
+    if ((fast || small) && ctx->opt_path == 0 && ctx->fell_back_host) {
+        // data on which the fast path (or the short vectors' own) keeps failing (very many equal magnitudes around the k-th largest): reaching
         // the exact path through the failed fast path costs nearly twice what taking it outright does.  Each newly
         // seen fall-back doubles the number of selections that take the exact path outright before the fast path is
         // tried again (1, 2, 4, ... 64); a fast-path success seen after the last fall-back resets it.
@@ -333,34 +342,40 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         } else if ((int32_t)(served - fell_back) > 0) {
             ctx->penalty = 0;
         }
-        if (ctx->exact_calls_left > 0) { --ctx->exact_calls_left; fast = false; }
+        if (ctx->exact_calls_left > 0) { --ctx->exact_calls_left; fast = small = false; }
     }
-    if (fast) {
+    // the rows' records: where one block per node reads them, and for long candidate lists (one node of 2^28 elements, 1 %:
+    // gather 142 -> 55 us); in between, what the gather saves its reads of v had saved the output's stores
+    // to the same lines (4 nodes x 25.6 M, 0.1 %: gather 17 -> 12 us, the whole call no faster)
+    const bool long_list = expected_candidates((double)n, (double)k) > 131072.0;
+    if (!finishes_in_one && !long_list) a.row_rec = nullptr;
+    if (fast || small) {
         if (++ctx->call_number == 0) ctx->call_number = 1;
         a.notify_value = ctx->call_number;
     }
     ctx->cur ^= 1;  // this call uses the clean set and cleans the other one for the next call
-    if (takes_small_path(ctx, n, k)) {
+    if (small) {
         if (ctx->single_state) {   // no launch has cleared the scratch before this call: the first kernel does
             a.next_state = (uint32_t *)ctx->scratch;
             a.next_words = (uint32_t)(((char *)ctx->samples - (char *)ctx->scratch) / 4);
         }
-        launch_small_select(a, batch, fused, vec, ctx->cus, st, fused ? profile_bracket(ctx) : Bracket());
+        launch_small_select(a, batch, fused, ctx->cus, st, fused ? profile_bracket(ctx) : Bracket());
     } else if (fast) {
-        launch_sample(a, batch, fused, vec, st);   // also clears the next call's state set
-        launch_candidates(a, batch, fused, vec, st, profile_bracket(ctx));
-        launch_gather(a, batch, st);
+        launch_sample(a, batch, fused, st);   // also clears the next call's state set
+        launch_candidates(a, batch, fused, st, profile_bracket(ctx));
+        if (finishes_in_one) launch_finish_from_bitmap(a, batch, true, ctx->cus, st);
+        else launch_gather(a, batch, st);
         a.force = 0;
         // the exact path as fall-back, for nodes the fast path hands back: with short candidate lists it rides in
         // the output launch, otherwise one launch of its own that nearly always has nothing to do
-        if (!launch_output_from_candidates(a, batch, expected_candidates((double)n, (double)k) <= 131072.0, vec, ctx->cus, st))
-            launch_exact(a, batch, vec, ctx->cus, st);
+        if (!finishes_in_one && !launch_output_from_candidates(a, batch, !long_list, ctx->cus, st))
+            launch_exact(a, batch, ctx->cus, st);
     } else {
         if (fused) {
-            launch_accumulate(g, u, v, (uint32_t)n, batch, stride, m, vec, st, profile_bracket(ctx));
+            launch_accumulate(g, u, v, (uint32_t)n, batch, stride, m, st, profile_bracket(ctx));
         }
         a.force = 1;   // exact path chosen outright (as five launches when the input is long); it also clears the next call's state set
-        launch_exact(a, batch, vec, ctx->cus, st);
+        launch_exact(a, batch, ctx->cus, st);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e));
@@ -409,6 +424,10 @@ extern "C" lgc_status lgc_create(lgc_ctx **out, int device, uint64_t max_n, uint
         return fail(nullptr, LGC_EHIP, "hipMemset: %s", hipGetErrorString(e));
     }
     bind_scratch(c, block, L);
+    // The rows' records spare the kernels after the streaming pass a search and scattered reads.  Without them (they
+    // take a quarter byte per element, at most 4 GB are asked for) the selection works the way without.
+    const size_t rec_bytes = (size_t)max_batch * L.rows * kRecordWords * 4;
+    if (rec_bytes <= ((size_t)4 << 30) && hipMalloc((void **)&c->row_rec, rec_bytes) != hipSuccess) c->row_rec = nullptr;
     // the pinned words of the automatic path choice; without them (allocation refused) the choice is simply not adaptive
     void *pinned = nullptr, *pinned_dev = nullptr;
     if (hipHostMalloc(&pinned, 64, hipHostMallocMapped) == hipSuccess) {
@@ -436,6 +455,7 @@ extern "C" void lgc_destroy(lgc_ctx *ctx) {
     if (ctx->seg_cand) (void)hipFree(ctx->seg_cand);
     if (ctx->seg_row_prefix) (void)hipFree(ctx->seg_row_prefix);
     if (ctx->scratch) (void)hipFree(ctx->scratch);
+    if (ctx->row_rec) (void)hipFree(ctx->row_rec);
     if (ctx->fell_back_host) (void)hipHostFree(ctx->fell_back_host);
     delete ctx;
 }
@@ -572,6 +592,9 @@ extern "C" lgc_status lgc_accumulate_topk_static(int device, const float *g, flo
     view.cus = sd->cus;
     view.single_state = true;
     bind_scratch(&view, sd->ptr, L);
+    // the rows' records, where the array has room for them
+    const size_t rec_bytes = (size_t)batch * L.rows * kRecordWords * 4;
+    if (rec_bytes <= kStaticScratchBytes - L.bytes) view.row_rec = (uint32_t *)(sd->ptr + L.bytes);
     hipStream_t st = (hipStream_t)stream;
     // the array keeps the last call's contents: statistics and the state set start every call at zero
     // (a fill kernel, not a memset, so that the call can be recorded into a HIP graph)
@@ -1000,8 +1023,7 @@ extern "C" lgc_status lgc_innovation(lgc_ctx *ctx, const lgc_segments *seg, cons
     if (!aligned(vals, 4) || !aligned(out, 4)) return fail(ctx, LGC_EINVAL, "pointer not 4-byte aligned");
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return fail(ctx, LGC_EHIP, "cannot select device %d", ctx->device);
-    const bool vec = aligned(vals, 16) && (batch == 1 || seg->n % 4 == 0);
-    launch_innovation(vals, out, (uint32_t)seg->n, batch, seg->n_seg, seg->off, seg->k, vec, ctx->stats,
+    launch_innovation(vals, out, (uint32_t)seg->n, batch, seg->n_seg, seg->off, seg->k, ctx->stats,
                       (hipStream_t)stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e));
@@ -1179,16 +1201,15 @@ static lgc_status run_segmented(lgc_ctx *ctx, const lgc_segments *seg, const flo
     if (!guard.ok) return fail(ctx, LGC_EHIP, "cannot select device %d", ctx->device);
     hipStream_t st = (hipStream_t)stream;
     const bool fused = g != nullptr;
-    const bool vec = aligned(v, 16) && (!u || aligned(u, 16)) && (!g || aligned(g, 16)) &&
-                     (batch == 1 || stride % 4 == 0);
     if (seg->total_k == 0) {
-        if (fused) launch_accumulate(g, u, v, (uint32_t)seg->n, batch, stride, m, vec, st);
+        if (fused) launch_accumulate(g, u, v, (uint32_t)seg->n, batch, stride, m, st);
         return LGC_OK;
     }
     if (!seg_scratch_fits(ctx, seg))
         return fail(ctx, LGC_EINVAL, "per-layer selection: scratch for this segment plan not reserved: call "
                                      "lgc_reserve(ctx, NULL, 0, 0, seg) once beforehand");
     SelArgs a = make_args(ctx, g, u, v, seg->n, stride, m, seg->total_k, out_vals, out_idx);
+    a.row_rec = nullptr;   // (the layers' candidates go through the list as they are)
     a.n_seg = seg->n_seg; a.seg_off = seg->off; a.seg_k = seg->k; a.seg_out = seg->out; a.seg_rank = seg->rank;
     a.row_seg = seg->row_seg; a.seg_t = ctx->seg_t; a.row_prefix = ctx->seg_row_prefix;
     a.cap = seg->cap;
@@ -1203,16 +1224,16 @@ static lgc_status run_segmented(lgc_ctx *ctx, const lgc_segments *seg, const flo
     ctx->last_seg = seg; ctx->last_seg_k = seg->total_k;
     ctx->cur ^= 1;  // this call uses the clean set and cleans the other one for the next call
     if (seg->n_sampled) {
-        launch_seg_estimate(a, batch, fused, vec, st);   // also clears the next call's state set
-        launch_candidates(a, batch, fused, vec, st, profile_bracket(ctx));
+        launch_seg_estimate(a, batch, fused, st);   // also clears the next call's state set
+        launch_candidates(a, batch, fused, st, profile_bracket(ctx));
         launch_gather(a, batch, st);
     } else {
         launch_clear(a.next_state, a.next_words, st);
         if (fused) {
-            launch_accumulate(g, u, v, (uint32_t)seg->n, batch, stride, m, vec, st, profile_bracket(ctx));
+            launch_accumulate(g, u, v, (uint32_t)seg->n, batch, stride, m, st, profile_bracket(ctx));
         }
     }
-    launch_seg_select(a, batch, vec, st);
+    launch_seg_select(a, batch, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e));
     return LGC_OK;
@@ -1246,8 +1267,7 @@ static lgc_status gather_common(lgc_ctx *ctx, const float *g, float *u, float *v
     if (!guard.ok) return fail(ctx, LGC_EHIP, "cannot select device %d", ctx->device);
     hipStream_t st = (hipStream_t)stream;
     if (g) {
-        const bool vec = aligned(v, 16) && aligned(u, 16) && aligned(g, 16) && (batch == 1 || stride % 4 == 0);
-        launch_accumulate(g, u, v, (uint32_t)n, batch, stride, momentum, vec, st, profile_bracket(ctx));
+        launch_accumulate(g, u, v, (uint32_t)n, batch, stride, momentum, st, profile_bracket(ctx));
     }
     launch_gather_at(v, u, stride, (uint32_t)n, batch, idx, (uint32_t)k, out_vals, ctx->stats, st);
     hipError_t e = hipGetLastError();

@@ -8,7 +8,9 @@ namespace lgc {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-typedef f4 f4u __attribute__((aligned(4)));   // 16-byte accesses at any 4-byte address (the hardware takes them)
+// 16-byte accesses at any 4-byte address (the hardware takes them)
+typedef f4 f4u __attribute__((aligned(4)));
+typedef u4 u4u __attribute__((aligned(4)));
 
 // ------------------------------------------------------------------ small helpers
 

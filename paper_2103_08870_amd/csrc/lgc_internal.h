@@ -32,6 +32,10 @@ constexpr int kRadixBins = 2048;
 // word 4s+j, bit l  <->  element  row*1024 + 256 s + 4 l + j   (s, j in 0..3, l = lane)
 constexpr int kRow = 1024;
 constexpr int kRowWords = 16;
+// record of a row that holds 1 .. kRecord candidates: their values, then their positions in the row (16 bits each), in
+// index order; 256 bytes apart, of which 192 are used
+constexpr int kRecord = 32;
+constexpr int kRecordWords = 64;
 constexpr uint32_t kSuperRows = 8192;           // rows per group whose candidates are summed ahead of the gather
 
 // The streaming kernels are launched over at most this many rows (a little over 2 GB of g, u, v
@@ -134,6 +138,7 @@ struct SelArgs {
     uint32_t *row_super;      // [batch][supers] candidates per group of kSuperRows rows (vectors of more than one group)
     uint32_t supers;           // groups per node in row_super; 0: the gather adds up the row counts themselves
     unsigned long long *bitmap;  // [batch][rows][kRowWords]
+    uint32_t *row_rec;           // [batch][rows][kRecordWords]  records of the rows with few candidates (null: none are kept)
     uint32_t *cand_idx;       // [batch][cap]  gathered, index-ordered
     uint32_t *cand_val;
     float *out_vals;          // [batch][k]
@@ -157,26 +162,26 @@ struct Bracket {
     hipEvent_t start = nullptr, stop = nullptr;
 };
 void launch_accumulate(const float *g, float *u, float *v, uint32_t n, int batch, uint64_t stride,
-                       float momentum, bool vec, hipStream_t st, Bracket br = Bracket());
+                       float momentum, hipStream_t st, Bracket br = Bracket());
 void launch_clear(uint32_t *words, uint32_t count, hipStream_t st);
-void launch_sample(const SelArgs &a, int batch, bool fused, bool vec, hipStream_t st);
-void launch_candidates(const SelArgs &a, int batch, bool fused, bool vec, hipStream_t st, Bracket br = Bracket());
+void launch_sample(const SelArgs &a, int batch, bool fused, hipStream_t st);
+void launch_candidates(const SelArgs &a, int batch, bool fused, hipStream_t st, Bracket br = Bracket());
 void launch_gather(const SelArgs &a, int batch, hipStream_t st);
-bool launch_output_from_candidates(const SelArgs &a, int batch, bool direct, bool vec, int cus, hipStream_t st);
-void launch_exact(const SelArgs &a, int batch, bool vec, int cus, hipStream_t st);
+bool launch_output_from_candidates(const SelArgs &a, int batch, bool direct, int cus, hipStream_t st);
+void launch_exact(const SelArgs &a, int batch, int cus, hipStream_t st);
 // the candidates' bitmap straight to the output, one block per node (lists of up to kFinishList entries), with the exact
 // path standing by; report: a fast-path selection (statistics, carried thresholds)
 constexpr uint32_t kFinishList = 12288;
 constexpr uint32_t kFinishRows = 4096;
-void launch_finish_from_bitmap(const SelArgs &a, int batch, bool report, bool vec, int cus, hipStream_t st);
+void launch_finish_from_bitmap(const SelArgs &a, int batch, bool report, int cus, hipStream_t st);
 // exact selection of short vectors (small.hip): accumulation (fused) and selection
 bool small_select_covers(uint64_t n, uint64_t k);
-void launch_small_select(const SelArgs &a, int batch, bool fused, bool vec, int cus, hipStream_t st, Bracket br = Bracket());
+void launch_small_select(const SelArgs &a, int batch, bool fused, int cus, hipStream_t st, Bracket br = Bracket());
 // per-layer selection (segmented.hip)
-void launch_seg_estimate(const SelArgs &a, int batch, bool fused, bool vec, hipStream_t st);
-void launch_seg_select(const SelArgs &a, int batch, bool vec, hipStream_t st);
+void launch_seg_estimate(const SelArgs &a, int batch, bool fused, hipStream_t st);
+void launch_seg_select(const SelArgs &a, int batch, hipStream_t st);
 void launch_innovation(const float *vals, float *out, uint32_t n, int batch, uint32_t n_seg, const uint32_t *seg_off,
-                       const uint32_t *seg_k, bool vec, Stats *stats, hipStream_t st);
+                       const uint32_t *seg_k, Stats *stats, hipStream_t st);
 
 // autoencoder.hip
 struct LayerDev {

@@ -87,7 +87,7 @@ __device__ __forceinline__ uint32_t block_radix_select(Each each, uint32_t rank,
 // One block per (segment, node).  Direct segments publish 0xffffffff ("flag nothing").
 // The keys that the accumulation WILL produce are sampled when FUSED (v + (m*u + g), not stored).
 // The kernel also clears the state set that the next call will use.
-template <bool FUSED, bool VEC>
+template <bool FUSED>
 __global__ __launch_bounds__(1024) void k_seg_estimate(SelArgs a) {
     __shared__ __align__(16) uint32_t hist[4096];
     __shared__ uint32_t wave_tmp[16], res[2];
@@ -126,12 +126,12 @@ __global__ __launch_bounds__(1024) void k_seg_estimate(SelArgs a) {
     if (!active) {
 #pragma unroll
         for (int j = 0; j < 16; ++j) keys[j] = 0;
-    } else if (VEC) {
+    } else {
         f4 vv[4], uu[4], gg[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            vv[q] = *(const f4 *)(a.v + off + q * 4);
-            if (FUSED) { uu[q] = *(const f4 *)(a.u + off + q * 4); gg[q] = *(const f4 *)(a.g + off + q * 4); }
+            vv[q] = *(const f4u *)(a.v + off + q * 4);
+            if (FUSED) { uu[q] = *(const f4u *)(a.u + off + q * 4); gg[q] = *(const f4u *)(a.g + off + q * 4); }
         }
 #pragma unroll
         for (int q = 0; q < 4; ++q)
@@ -141,13 +141,6 @@ __global__ __launch_bounds__(1024) void k_seg_estimate(SelArgs a) {
                 if (FUSED) accum1(gg[q][j], x, y, a.momentum);
                 keys[q * 4 + j] = key_of(y);
             }
-    } else {
-#pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            float y = a.v[off + j];
-            if (FUSED) { float x = a.u[off + j]; accum1(a.g[off + j], x, y, a.momentum); }
-            keys[j] = key_of(y);
-        }
     }
     // the order statistic to 2^-11 relative resolution (exponent and 11 mantissa bits), rounded down: a threshold
     // needs no more, and a lower one only flags a few more candidates (3 % where the counts are steepest)
@@ -163,22 +156,17 @@ __global__ __launch_bounds__(1024) void k_seg_estimate(SelArgs a) {
     if (tid == 0) *out = prefix << 12;
 }
 
-void launch_seg_estimate(const SelArgs &a, int batch, bool fused, bool vec, hipStream_t st) {
+void launch_seg_estimate(const SelArgs &a, int batch, bool fused, hipStream_t st) {
     dim3 grid(a.n_seg, batch);
-    if (fused) {
-        if (vec) hipLaunchKernelGGL((k_seg_estimate<true, true>), grid, dim3(1024), 0, st, a);
-        else hipLaunchKernelGGL((k_seg_estimate<true, false>), grid, dim3(1024), 0, st, a);
-    } else {
-        if (vec) hipLaunchKernelGGL((k_seg_estimate<false, true>), grid, dim3(1024), 0, st, a);
-        else hipLaunchKernelGGL((k_seg_estimate<false, false>), grid, dim3(1024), 0, st, a);
-    }
+    if (fused) hipLaunchKernelGGL(k_seg_estimate<true>, grid, dim3(1024), 0, st, a);
+    else hipLaunchKernelGGL(k_seg_estimate<false>, grid, dim3(1024), 0, st, a);
 }
 
 // ------------------------------------------------------------------ exact selection inside one segment
 
 // The block's source: `bits` holds raw fp32 patterns at positions [begin, end); the position of
 // entry p in the node's vector is pos[p] (candidate list) or p itself (pos == nullptr: the
-// source is v).  ALIGNED: bits + (begin & ~3) is 16-byte aligned (vector loads).
+// source is v).
 // A long source is read four times (three digit passes and the output pass; it stays in the L2
 // after the first) in rolled loops: unrolling those for 64 K entries was an order of magnitude
 // slower (instruction fetch).
@@ -189,7 +177,7 @@ constexpr int kSelThreads = 512;          // most segments and candidate runs ar
 // of the source gets dense[p] = its value if kept, +0 otherwise (the innovation component).
 // SMALL: the source spans at most kSelKeep rounds (16 K entries from begin & ~3 on): it is read once
 // and kept in registers for all four sweeps (the layers' candidate runs and the small layers).
-template <bool ALIGNED, bool DENSE, bool SMALL>
+template <bool DENSE, bool SMALL>
 __device__ __forceinline__ uint32_t select_in_block(const uint32_t *__restrict__ bits, const uint32_t *__restrict__ pos,
                                                 const uint32_t begin, const uint32_t end, const uint32_t k,
                                                 float *__restrict__ v, float *__restrict__ u,
@@ -207,8 +195,8 @@ __device__ __forceinline__ uint32_t select_in_block(const uint32_t *__restrict__
         u4 x = {0u, 0u, 0u, 0u};
         if (g < groups) {
             const uint32_t p = a0 + (g << 2);
-            if (ALIGNED && p + 4 <= end) {
-                x = *(const u4 *)(bits + p);                 // entries below `begin` are masked by position later
+            if (p + 4 <= end) {
+                x = *(const u4u *)(bits + p);                 // entries below `begin` are masked by position later
             } else {
 #pragma unroll
                 for (int c = 0; c < 4; ++c)
@@ -313,7 +301,6 @@ __device__ __forceinline__ uint32_t select_in_block(const uint32_t *__restrict__
 }
 
 // One block per (segment, node).
-template <bool VEC>
 __global__ __launch_bounds__(kSelThreads) void k_seg_select(SelArgs a) {
     __shared__ __align__(16) uint32_t hist[4096];
     __shared__ uint32_t wave_tmp[16], res[2], sh_g[16], sh_e[16];
@@ -371,14 +358,14 @@ __global__ __launch_bounds__(kSelThreads) void k_seg_select(SelArgs a) {
     uint32_t thr;
     if (from_list) {
         if (p1 - (p0 & ~3u) <= kSmall)
-            thr = select_in_block<true, false, true>(cval, cidx, p0, p1, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
+            thr = select_in_block<false, true>(cval, cidx, p0, p1, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
         else
-            thr = select_in_block<true, false, false>(cval, cidx, p0, p1, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
+            thr = select_in_block<false, false>(cval, cidx, p0, p1, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
     } else {
         if (hi - (lo & ~3u) <= kSmall)
-            thr = select_in_block<VEC, false, true>((const uint32_t *)v, nullptr, lo, hi, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
+            thr = select_in_block<false, true>((const uint32_t *)v, nullptr, lo, hi, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
         else
-            thr = select_in_block<VEC, false, false>((const uint32_t *)v, nullptr, lo, hi, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
+            thr = select_in_block<false, false>((const uint32_t *)v, nullptr, lo, hi, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
     }
     // sampled layers: the record of this layer's exact thresholds, and its offer to the next selection
     if (a.seg_carry && a.seg_rank[l] != 0 && threadIdx.x == 0) {
@@ -393,7 +380,6 @@ __global__ __launch_bounds__(kSelThreads) void k_seg_select(SelArgs a) {
 // Innovation component (Alg. 1: threshold_inv, mask_inv; Sec. IV-C): per segment of the vector of
 // selected values the k_l largest magnitudes stay, everything else becomes +0.  The input is not
 // modified.  One block per (segment, node).
-template <bool VEC>
 __global__ __launch_bounds__(kSelThreads) void k_innovation(const float *__restrict__ vals, float *__restrict__ out,
                                                             uint32_t n, const uint32_t *__restrict__ seg_off,
                                                             const uint32_t *__restrict__ seg_k, Stats *stats) {
@@ -408,24 +394,22 @@ __global__ __launch_bounds__(kSelThreads) void k_innovation(const float *__restr
         return;
     }
     if (hi - (lo & ~3u) <= (uint32_t)kSelKeep * kSelThreads * 4u)
-        select_in_block<VEC, true, true>((const uint32_t *)src, nullptr, lo, hi, k, nullptr, nullptr, nullptr, nullptr, dst, stats,
+        select_in_block<true, true>((const uint32_t *)src, nullptr, lo, hi, k, nullptr, nullptr, nullptr, nullptr, dst, stats,
                                          hist, wave_tmp, res, sh_g, sh_e);
     else
-        select_in_block<VEC, true, false>((const uint32_t *)src, nullptr, lo, hi, k, nullptr, nullptr, nullptr, nullptr, dst, stats,
+        select_in_block<true, false>((const uint32_t *)src, nullptr, lo, hi, k, nullptr, nullptr, nullptr, nullptr, dst, stats,
                                           hist, wave_tmp, res, sh_g, sh_e);
 }
 
 void launch_innovation(const float *vals, float *out, uint32_t n, int batch, uint32_t n_seg, const uint32_t *seg_off,
-                       const uint32_t *seg_k, bool vec, Stats *stats, hipStream_t st) {
+                       const uint32_t *seg_k, Stats *stats, hipStream_t st) {
     dim3 grid(n_seg, batch);
-    if (vec) hipLaunchKernelGGL(k_innovation<true>, grid, dim3(kSelThreads), 0, st, vals, out, n, seg_off, seg_k, stats);
-    else hipLaunchKernelGGL(k_innovation<false>, grid, dim3(kSelThreads), 0, st, vals, out, n, seg_off, seg_k, stats);
+    hipLaunchKernelGGL(k_innovation, grid, dim3(kSelThreads), 0, st, vals, out, n, seg_off, seg_k, stats);
 }
 
-void launch_seg_select(const SelArgs &a, int batch, bool vec, hipStream_t st) {
+void launch_seg_select(const SelArgs &a, int batch, hipStream_t st) {
     dim3 grid(a.n_seg, batch);
-    if (vec) hipLaunchKernelGGL(k_seg_select<true>, grid, dim3(kSelThreads), 0, st, a);
-    else hipLaunchKernelGGL(k_seg_select<false>, grid, dim3(kSelThreads), 0, st, a);
+    hipLaunchKernelGGL(k_seg_select, grid, dim3(kSelThreads), 0, st, a);
 }
 
 }  // namespace lgc

@@ -7,7 +7,7 @@
 // second launch adds those up, which fixes the leading 11 bits of T*, and flags the keys from there on; the third
 // lists them in one block's LDS and selects there.  Nothing crosses blocks but by the launches' ends.
 // Measured, accumulate + top-k of one node of 100 003 elements, k = 1 000, without a context: 44.5 us before (a
-// clearing launch, the accumulation, k_exact 38 us), 25.4 us now.  A single block that scans v for itself in
+// clearing launch, the accumulation, k_exact 38 us), 21.3 us now.  A single block that scans v for itself in
 // place of the last two launches took 31 us alone: reading and testing 400 KB is too much for one compute unit.
 #include "device_helpers.h"
 
@@ -66,11 +66,13 @@ __global__ __launch_bounds__(1024) void k_small_pass(SelArgs a) {
     a.samples[(size_t)node * kSample + blockIdx.x * (kSmallBins / 2) + tid] = hist[2 * tid] | (hist[2 * tid + 1] << 16);
 }
 
-// The candidate bitmap and row counts (as k_candidates writes them) of the keys that share T*'s leading bits or lie above:
+// The candidate bitmap, row counts and records (as k_candidates writes them) of the keys that share T*'s leading bits or lie above:
 // every block adds up the chunks' histograms for itself.  Wavefront w of a block takes 256 elements: part w % 4 of row w / 4.
 __global__ __launch_bounds__(1024) void k_small_flags(SelArgs a) {
     __shared__ __align__(16) uint32_t hist[kSmallBins];
-    __shared__ uint32_t wave_tmp[16], res[2], row_sum[kSmallChunk / kRow];
+    __shared__ uint32_t wave_tmp[16], res[2];
+    constexpr int kRowsHere = kSmallChunk / kRow;
+    __shared__ uint32_t part_sum[kRowsHere][4], rec[kRowsHere][kRecordWords];
     const int node = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const uint32_t chunks = gridDim.x, e = blockIdx.x * kSmallChunk + tid * 4;
     const float *v = a.v + (size_t)node * a.stride;
@@ -90,38 +92,52 @@ __global__ __launch_bounds__(1024) void k_small_flags(SelArgs a) {
         for (int c = 0; c < 16; ++c) { lo += y[c] & 0xffffu; hi += y[c] >> 16; }
     }
     hist[2 * tid] = lo; hist[2 * tid + 1] = hi;
-    if (tid < (int)(kSmallChunk / kRow)) row_sum[tid] = 0;
     __syncthreads();
     find_rank_bin<kSmallBins, 1024>(hist, a.k, wave_tmp, res);
     const uint32_t least = res[0] << 20;   // (n >= k keys were counted: the bin exists)
-    const uint32_t row = blockIdx.x * (kSmallChunk / kRow) + (wave >> 2);
+    const int local = wave >> 2, part = wave & 3;
+    const uint32_t row = blockIdx.x * kRowsHere + local, nrows = (a.n + kRow - 1) / kRow;
     unsigned long long word = 0;
-    uint32_t count = 0;
+    bool f[4];
+    uint32_t count = 0, mine = 0;      // flags of the wavefront, of its lower lanes
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const unsigned long long m = __ballot(e + j < a.n && key_of(x[j]) >= least);
+        f[j] = e + j < a.n && key_of(x[j]) >= least;
+        const unsigned long long m = __ballot(f[j]);
         count += (uint32_t)__popcll(m);
+        mine += lanes_below(m);
         if (lane == j) word = m;
     }
-    const uint32_t nrows = (a.n + kRow - 1) / kRow;
-    if (row < nrows && lane < 4) a.bitmap[((size_t)node * a.rows + row) * kRowWords + (wave & 3) * 4 + lane] = word;
-    if (lane == 0) atomicAdd(&row_sum[wave >> 2], count);
+    if (row < nrows && lane < 4) a.bitmap[((size_t)node * a.rows + row) * kRowWords + part * 4 + lane] = word;
+    if (lane == 0) part_sum[local][part] = count;
     __syncthreads();
-    if (tid < (int)(kSmallChunk / kRow)) {
-        const uint32_t r = blockIdx.x * (kSmallChunk / kRow) + tid;
-        if (r < nrows) a.row_count[(size_t)node * a.rows + r] = row_sum[tid];
+    uint32_t total = 0;
+#pragma unroll
+    for (int p = 0; p < 4; ++p) { mine += p < part ? part_sum[local][p] : 0u; total += part_sum[local][p]; }
+    if (total <= (uint32_t)kRecord) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (f[j]) {
+                rec[local][mine] = __float_as_uint(x[j]);
+                ((uint16_t *)(rec[local] + kRecord))[mine] = (uint16_t)(part * 256 + lane * 4 + j);
+                ++mine;
+            }
     }
+    if (row < nrows && part == 0 && lane == 0) a.row_count[(size_t)node * a.rows + row] = total;
+    __syncthreads();
+    if (a.row_rec && row < nrows && part == 0 && lane < kRecord + kRecord / 2)   // (rows with more hold nothing of use)
+        a.row_rec[((size_t)node * a.rows + row) * kRecordWords + lane] = rec[local][lane];
 }
 
 // the finishing launch's list has to hold the selection and the keys that share T*'s leading bits
 bool small_select_covers(uint64_t n, uint64_t k) { return n < kMinFastN && k <= kFinishList / 3; }
 
-void launch_small_select(const SelArgs &a, int batch, bool fused, bool vec, int cus, hipStream_t st, Bracket br) {
+void launch_small_select(const SelArgs &a, int batch, bool fused, int cus, hipStream_t st, Bracket br) {
     const dim3 grid((a.n + kSmallChunk - 1) / kSmallChunk, batch);
     if (fused) launch_timed(k_small_pass<true>, grid, dim3(1024), st, br, a);
     else hipLaunchKernelGGL(k_small_pass<false>, grid, dim3(1024), 0, st, a);
     hipLaunchKernelGGL(k_small_flags, grid, dim3(1024), 0, st, a);
-    launch_finish_from_bitmap(a, batch, false, vec, cus, st);
+    launch_finish_from_bitmap(a, batch, false, cus, st);
 }
 
 }  // namespace lgc

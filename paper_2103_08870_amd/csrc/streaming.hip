@@ -5,7 +5,7 @@
 // and, in the candidate pass, the flags "key(v) >= t_est" (key = bits(v) & 0x7fffffff) that the selection
 // kernels (topk.hip, segmented.hip) work from: one bit per element in a dense bitmap, one count per row of
 // 1024 elements.  One wavefront per row, twelve 16-byte loads in flight before anything depends on them,
-// non-temporal loads and stores, no LDS, no barrier, no atomics, nothing shared between wavefronts.
+// non-temporal loads and stores, no barrier, no atomics, nothing shared between wavefronts.
 
 #include "device_helpers.h"
 
@@ -25,18 +25,18 @@ __device__ __forceinline__ void full_row(const float *__restrict__ g, float *__r
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
         if (FUSED) {
-            gg[s] = __builtin_nontemporal_load((const f4 *)(g + s * 256));
-            uu[s] = __builtin_nontemporal_load((const f4 *)(u + s * 256));
+            gg[s] = __builtin_nontemporal_load((const f4u *)(g + s * 256));
+            uu[s] = __builtin_nontemporal_load((const f4u *)(u + s * 256));
         }
-        vv[s] = __builtin_nontemporal_load((const f4 *)(v + s * 256));
+        vv[s] = __builtin_nontemporal_load((const f4u *)(v + s * 256));
     }
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
         if (FUSED) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) { float x = uu[s][j], y = vv[s][j]; accum1(gg[s][j], x, y, m); uu[s][j] = x; vv[s][j] = y; }
-            __builtin_nontemporal_store(uu[s], (f4 *)(u + s * 256));
-            __builtin_nontemporal_store(vv[s], (f4 *)(v + s * 256));
+            __builtin_nontemporal_store(uu[s], (f4u *)(u + s * 256));
+            __builtin_nontemporal_store(vv[s], (f4u *)(v + s * 256));
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) bits[s][j] = __float_as_uint(vv[s][j]);
@@ -47,7 +47,6 @@ __device__ __forceinline__ void full_row(const float *__restrict__ g, float *__r
 
 // Same traversal as the candidate pass below: one wavefront per row of 1024 elements,
 // all twelve 16-byte loads of a row in flight before anything depends on them, non-temporal.
-template <bool VEC>
 __global__ __launch_bounds__(kBlock) void k_accumulate(const float *__restrict__ g, float *__restrict__ u,
                                                        float *__restrict__ v, uint32_t n, uint64_t stride,
                                                        float m) {
@@ -58,7 +57,7 @@ __global__ __launch_bounds__(kBlock) void k_accumulate(const float *__restrict__
     for (uint32_t r = blockIdx.x * kWaves + wave; r < nrows; r += gridDim.x * kWaves) {
         const uint32_t row = r * (uint32_t)kRow;
         const uint32_t end = (n - row > (uint32_t)kRow) ? row + kRow : n;
-        if (VEC && row + 1024 <= end) {
+        if (row + 1024 <= end) {
             uint32_t bits[4][4];
             full_row<true>(g + row + lane * 4, u + row + lane * 4, v + row + lane * 4, m, bits);
         } else {
@@ -101,15 +100,14 @@ static void for_each_share(uint32_t nrows, int batch, Bracket br, F launch) {
 }
 
 void launch_accumulate(const float *g, float *u, float *v, uint32_t n, int batch, uint64_t stride,
-                       float momentum, bool vec, hipStream_t st, Bracket br) {
+                       float momentum, hipStream_t st, Bracket br) {
     const uint32_t nrows = (n + kRow - 1) / kRow;
     for_each_share(nrows, batch, br, [&](uint32_t node0, int nodes, uint32_t r0, uint32_t r1, Bracket e) {
-        // a share is passed as shifted pointers and its own length (row ranges keep 16-byte alignment)
+        // a share is passed as shifted pointers and its own length 
         const size_t off = (size_t)node0 * stride + (size_t)r0 * kRow;
         const uint32_t len = (r1 == nrows ? n : r1 * (uint32_t)kRow) - r0 * (uint32_t)kRow;
         dim3 grid((r1 - r0 + kWaves - 1) / kWaves, nodes);
-        if (vec) launch_timed(k_accumulate<true>, grid, dim3(kBlock), st, e, g + off, u + off, v + off, len, stride, momentum);
-        else launch_timed(k_accumulate<false>, grid, dim3(kBlock), st, e, g + off, u + off, v + off, len, stride, momentum);
+        launch_timed(k_accumulate, grid, dim3(kBlock), st, e, g + off, u + off, v + off, len, stride, momentum);
     });
 }
 
@@ -118,12 +116,15 @@ void launch_accumulate(const float *g, float *u, float *v, uint32_t n, int batch
 // FUSED: reads g,u,v, writes u,v (the accumulation) and classifies the new v; otherwise reads v.
 // One wavefront per row of 1024 elements.  The flags "key >= t_est" of the row go out as one
 // full 128-byte line of the candidate bitmap (dense, coalesced: no partial-line writes), the
-// row's candidate count as one word.  No barrier, no LDS, no atomics, nothing shared.
+// row's candidate count as one word.  REC: and the candidates of a row that holds a few (up to kRecord) as one
+// record: their values and positions, so that the kernels after this one neither search the bitmap nor read v again at
+// scattered places.  No barrier, no atomics, nothing shared (a wavefront puts its record together in its own part of the LDS).
 // SEG: per-layer selection; the threshold of an element is that of its segment (a.seg_t, one per
 // node and segment; 0xffffffff flags nothing).  a.row_seg names the segment of a row's first
 // element, with bit 31 set when the row runs into further segments.
-template <bool FUSED, bool VEC, bool SEG>
+template <bool FUSED, bool SEG, bool REC>
 __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
+    __shared__ uint32_t record_lds[REC ? kWaves : 1][kRecordWords];
     const int node = a.node0 + blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const size_t off = (size_t)node * a.stride;
     const float *__restrict__ g = a.g + off;
@@ -158,22 +159,22 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
                 }
             }
         }
-        if (VEC && row + 1024 <= end) {
+        if (row + 1024 <= end) {
             full_row<FUSED>(g + row + lane * 4, u + row + lane * 4, v + row + lane * 4, m, bits);
         } else {
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const uint32_t e0 = row + s * 256 + lane * 4;
                 f4 vv = {0.f, 0.f, 0.f, 0.f};
-                if (VEC && e0 + 3 < end) {
-                    vv = *(const f4 *)(v + e0);
+                if (e0 + 3 < end) {
+                    vv = *(const f4u *)(v + e0);
                     if (FUSED) {
-                        const f4 gg = *(const f4 *)(g + e0);
-                        f4 uu = *(const f4 *)(u + e0);
+                        const f4 gg = *(const f4u *)(g + e0);
+                        f4 uu = *(const f4u *)(u + e0);
 #pragma unroll
                         for (int j = 0; j < 4; ++j) { float x = uu[j], y = vv[j]; accum1(gg[j], x, y, m); uu[j] = x; vv[j] = y; }
-                        *(f4 *)(u + e0) = uu;
-                        *(f4 *)(v + e0) = vv;
+                        *(f4u *)(u + e0) = uu;
+                        *(f4u *)(v + e0) = vv;
                     }
                 } else {
                     for (int j = 0; j < 4; ++j) if (e0 + j < end) {
@@ -192,12 +193,14 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
         }
         // 16 flag words of the row; lane i < 16 ends up holding word i
         uint32_t lo = 0, hi = 0, count = 0;
+        unsigned long long flags[4][4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t e = row + s * 256 + lane * 4 + j;
                 const unsigned long long mk = __ballot(e < end && (bits[s][j] & 0x7fffffffu) >= (SEG ? thr[s][j] : t_est));
+                flags[s][j] = mk;
                 count += (uint32_t)__popcll(mk);
                 const bool mine = lane == s * 4 + j;
                 lo = mine ? (uint32_t)mk : lo;
@@ -206,24 +209,43 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
         }
         if (lane < kRowWords) bitmap[(size_t)r * kRowWords + lane] = ((unsigned long long)hi << 32) | lo;
         if (lane == 0) row_count[r] = count;
+        // the row's record, put together in the LDS and stored as whole lines (wave-uniform condition)
+        if (REC && count != 0 && count <= (uint32_t)kRecord) {
+            uint32_t *rec = record_lds[wave];
+            uint32_t at = 0;
+#pragma unroll
+            for (int s = 0; s < 4; ++s) {
+                if ((flags[s][0] | flags[s][1] | flags[s][2] | flags[s][3]) != 0) {
+                    uint32_t mine = at;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) { mine += lanes_below(flags[s][j]); at += (uint32_t)__popcll(flags[s][j]); }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if ((flags[s][j] >> lane) & 1u) {
+                            rec[mine] = bits[s][j];
+                            ((uint16_t *)(rec + kRecord))[mine] = (uint16_t)(s * 256 + lane * 4 + j);
+                            ++mine;
+                        }
+                    }
+                }
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (lane < kRecord + kRecord / 2) a.row_rec[((size_t)node * a.rows + r) * kRecordWords + lane] = rec[lane];
+        }
     }
 }
 
-void launch_candidates(const SelArgs &args, int batch, bool fused, bool vec, hipStream_t st, Bracket br) {
+void launch_candidates(const SelArgs &args, int batch, bool fused, hipStream_t st, Bracket br) {
     const uint32_t nrows = (args.n + kRow - 1) / kRow;
     const bool seg = args.seg_t != nullptr;
     for_each_share(nrows, batch, br, [&](uint32_t node0, int nodes, uint32_t r0, uint32_t r1, Bracket e) {
         SelArgs a = args;
         a.node0 = node0; a.row_begin = r0; a.row_end = r1;
         dim3 grid((r1 - r0 + kWaves - 1) / kWaves, nodes);
-#define LGC_CAND(F, V, S) launch_timed(k_candidates<F, V, S>, grid, dim3(kBlock), st, e, a)
-        if (seg) {
-            if (fused) { if (vec) LGC_CAND(true, true, true); else LGC_CAND(true, false, true); }
-            else       { if (vec) LGC_CAND(false, true, true); else LGC_CAND(false, false, true); }
-        } else {
-            if (fused) { if (vec) LGC_CAND(true, true, false); else LGC_CAND(true, false, false); }
-            else       { if (vec) LGC_CAND(false, true, false); else LGC_CAND(false, false, false); }
-        }
+#define LGC_CAND(F, S, R) launch_timed(k_candidates<F, S, R>, grid, dim3(kBlock), st, e, a)
+        if (seg) { if (fused) LGC_CAND(true, true, false); else LGC_CAND(false, true, false); }
+        else if (a.row_rec) { if (fused) LGC_CAND(true, false, true); else LGC_CAND(false, false, true); }
+        else { if (fused) LGC_CAND(true, false, false); else LGC_CAND(false, false, false); }
 #undef LGC_CAND
     });
 }

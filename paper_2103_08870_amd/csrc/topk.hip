@@ -67,7 +67,7 @@ __device__ __forceinline__ uint32_t mix32(uint32_t h) {
 // A node whose record of carried thresholds offers a candidate threshold for this very selection (same shape, the
 // selection right after the one that wrote it) takes that one and samples nothing.
 // The kernel also clears the state set that the next call will use.
-template <bool FUSED, bool VEC>
+template <bool FUSED>
 __global__ __launch_bounds__(1024) void k_sample(SelArgs a) {
     __shared__ __align__(16) uint32_t hist[kSampleBins];
     __shared__ uint32_t wave_tmp[16], res[2];
@@ -103,16 +103,8 @@ __global__ __launch_bounds__(1024) void k_sample(SelArgs a) {
     __syncthreads();
     u4 keys;
     f4 vv, uu = {0.f, 0.f, 0.f, 0.f}, gg = {0.f, 0.f, 0.f, 0.f};
-    if (VEC) {
-        vv = *(const f4 *)(a.v + off + e);
-        if (FUSED) { uu = *(const f4 *)(a.u + off + e); gg = *(const f4 *)(a.g + off + e); }
-    } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            vv[i] = a.v[off + e + i];
-            if (FUSED) { uu[i] = a.u[off + e + i]; gg[i] = a.g[off + e + i]; }
-        }
-    }
+    vv = *(const f4u *)(a.v + off + e);
+    if (FUSED) { uu = *(const f4u *)(a.u + off + e); gg = *(const f4u *)(a.g + off + e); }
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         float x = uu[i], y = vv[i];
@@ -158,15 +150,10 @@ __global__ __launch_bounds__(1024) void k_sample(SelArgs a) {
     if (tid == 0) a.sel[node].t_est = (b1 << 20) | ((res[0] == 0xffffffffu ? 0u : res[0]) << 10);
 }
 
-void launch_sample(const SelArgs &a, int batch, bool fused, bool vec, hipStream_t st) {
+void launch_sample(const SelArgs &a, int batch, bool fused, hipStream_t st) {
     dim3 grid(kSampleGroups / 1024, batch);
-    if (fused) {
-        if (vec) hipLaunchKernelGGL((k_sample<true, true>), grid, dim3(1024), 0, st, a);
-        else hipLaunchKernelGGL((k_sample<true, false>), grid, dim3(1024), 0, st, a);
-    } else {
-        if (vec) hipLaunchKernelGGL((k_sample<false, true>), grid, dim3(1024), 0, st, a);
-        else hipLaunchKernelGGL((k_sample<false, false>), grid, dim3(1024), 0, st, a);
-    }
+    if (fused) hipLaunchKernelGGL(k_sample<true>, grid, dim3(1024), 0, st, a);
+    else hipLaunchKernelGGL(k_sample<false>, grid, dim3(1024), 0, st, a);
 }
 
 // ------------------------------------------------------------------ gather of the candidates
@@ -184,7 +171,8 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t x, uint32_t *tmp /*[16]*/
 }
 
 // ROWS bitmap rows per block of THREADS threads.  Lists the candidates of its rows, in index
-// order, behind those of all earlier rows of the node: position, and value re-read from v.
+// order, behind those of all earlier rows of the node: position and value, from the row's record or, for a row
+// with more candidates than a record holds, from the bitmap and v.
 // Counts them in the fine histogram of d = key - t_est (bins of 2^12, last bin open-ended) and
 // adds the block's count to the node's total.  The block's part of the bitmap is staged in LDS;
 // the work is balanced over the threads by output position (binary search of the owning row,
@@ -207,6 +195,37 @@ __global__ __launch_bounds__(1024) void k_row_sums(SelArgs a) {
     }
     const uint32_t total = block_sum<1024>(part, tmp);
     if (threadIdx.x == 0) a.row_super[(size_t)blockIdx.y * a.supers + blockIdx.x] = total;
+}
+
+// The i-th flagged element of a row of the bitmap, in element order (s, lane, j).
+__device__ __forceinline__ uint32_t row_element(const unsigned long long *w, uint32_t i) {
+    unsigned long long w0 = 0, w1 = 0, w2 = 0, w3 = 0;
+    uint32_t sub = 0;
+    bool found = false;
+#pragma unroll
+    for (int sr = 0; sr < 4; ++sr) {
+        const unsigned long long x0 = w[4 * sr], x1 = w[4 * sr + 1], x2 = w[4 * sr + 2], x3 = w[4 * sr + 3];
+        const uint32_t cs = (uint32_t)(__popcll(x0) + __popcll(x1) + __popcll(x2) + __popcll(x3));
+        if (!found) {
+            if (i < cs) { found = true; sub = sr; w0 = x0; w1 = x1; w2 = x2; w3 = x3; }
+            else i -= cs;
+        }
+    }
+    // largest l such that the lanes below l hold at most i flags: lane l holds candidate i
+    uint32_t l = 0;
+#pragma unroll
+    for (int step = 32; step >= 1; step >>= 1) {
+        const unsigned long long below = (1ull << (l + step)) - 1ull;   // lanes 0 .. l+step-1
+        const uint32_t cb = (uint32_t)(__popcll(w0 & below) + __popcll(w1 & below) + __popcll(w2 & below) + __popcll(w3 & below));
+        if (cb <= i) l += step;
+    }
+    const unsigned long long below = (1ull << l) - 1ull;
+    uint32_t rem = i - (uint32_t)(__popcll(w0 & below) + __popcll(w1 & below) + __popcll(w2 & below) + __popcll(w3 & below));
+    const uint32_t b0 = (uint32_t)(w0 >> l) & 1u, b1 = (uint32_t)(w1 >> l) & 1u, b2 = (uint32_t)(w2 >> l) & 1u;
+    uint32_t j;
+    if (b0 && rem == 0) j = 0;
+    else { rem -= b0; if (b1 && rem == 0) j = 1; else { rem -= b1; j = (b2 && rem == 0) ? 2 : 3; } }
+    return sub * 256 + l * 4 + j;
 }
 
 template <bool HIST, int ROWS, int THREADS>
@@ -277,36 +296,16 @@ __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
 #pragma unroll
         for (int step = kGatherRows / 2; step >= 1; step >>= 1)
             if (offs[r + step] <= p) r += step;
-        uint32_t i = p - offs[r];   // the i-th candidate of row r, in element order (s, lane, j)
-        const unsigned long long *w = rows_lds + r * kRowWords;
-        unsigned long long w0 = 0, w1 = 0, w2 = 0, w3 = 0;
-        uint32_t sub = 0;
-        bool found = false;
-#pragma unroll
-        for (int sr = 0; sr < 4; ++sr) {
-            const unsigned long long x0 = w[4 * sr], x1 = w[4 * sr + 1], x2 = w[4 * sr + 2], x3 = w[4 * sr + 3];
-            const uint32_t cs = (uint32_t)(__popcll(x0) + __popcll(x1) + __popcll(x2) + __popcll(x3));
-            if (!found) {
-                if (i < cs) { found = true; sub = sr; w0 = x0; w1 = x1; w2 = x2; w3 = x3; }
-                else i -= cs;
-            }
+        const uint32_t i = p - offs[r];   // the i-th candidate of row r
+        uint32_t ix, vb;
+        if (a.row_rec && (r + 1 < (uint32_t)kGatherRows ? offs[r + 1] : block_total) - offs[r] <= (uint32_t)kRecord) {
+            const uint32_t *rec = a.row_rec + ((size_t)node * a.rows + first + r) * kRecordWords;
+            vb = rec[i];
+            ix = (first + r) * (uint32_t)kRow + ((const uint16_t *)(rec + kRecord))[i];
+        } else {
+            ix = (first + r) * (uint32_t)kRow + row_element(rows_lds + r * kRowWords, i);
+            vb = ix < a.n ? __float_as_uint(v[ix]) : 0u;
         }
-        // largest l such that the lanes below l hold at most i flags: lane l holds candidate i
-        uint32_t l = 0;
-#pragma unroll
-        for (int step = 32; step >= 1; step >>= 1) {
-            const unsigned long long below = (1ull << (l + step)) - 1ull;   // lanes 0 .. l+step-1
-            const uint32_t cb = (uint32_t)(__popcll(w0 & below) + __popcll(w1 & below) + __popcll(w2 & below) + __popcll(w3 & below));
-            if (cb <= i) l += step;
-        }
-        const unsigned long long below = (1ull << l) - 1ull;
-        uint32_t rem = i - (uint32_t)(__popcll(w0 & below) + __popcll(w1 & below) + __popcll(w2 & below) + __popcll(w3 & below));
-        const uint32_t b0 = (uint32_t)(w0 >> l) & 1u, b1 = (uint32_t)(w1 >> l) & 1u, b2 = (uint32_t)(w2 >> l) & 1u;
-        uint32_t j;
-        if (b0 && rem == 0) j = 0;
-        else { rem -= b0; if (b1 && rem == 0) j = 1; else { rem -= b1; j = (b2 && rem == 0) ? 2 : 3; } }
-        const uint32_t ix = (first + r) * (uint32_t)kRow + sub * 256 + l * 4 + j;
-        const uint32_t vb = ix < a.n ? __float_as_uint(v[ix]) : 0u;
         const uint32_t q = before + p;
         if (q < a.cap) { cidx[q] = ix; cval[q] = vb; }
         if (HIST) {
@@ -597,7 +596,7 @@ __device__ __forceinline__ void output_direct(const SelArgs &a, const int node, 
 // (and u), reading v itself.  Every block of the node (THREADS threads) owns a run of consecutive chunks of
 // 16 * THREADS elements: kRows rows of 4 * THREADS, four consecutive elements per thread and row.
 // load_chunk: the value bits of this thread's 16 elements of a chunk and their flags (bit r*4+j).
-template <bool VEC, int THREADS>
+template <int THREADS>
 __device__ __forceinline__ void load_chunk(const float *__restrict__ v, const uint32_t base, const uint32_t n,
                                            const uint32_t thr, uint32_t (&bits)[kRows][4], uint32_t &gtm, uint32_t &eqm) {
     const int tid = threadIdx.x;
@@ -606,7 +605,7 @@ __device__ __forceinline__ void load_chunk(const float *__restrict__ v, const ui
     for (int r = 0; r < kRows; ++r) {
         const uint32_t e0 = base + r * (THREADS * 4) + tid * 4;
         f4 vv = {0.f, 0.f, 0.f, 0.f};
-        if (VEC && e0 + 3 < n) vv = *(const f4 *)(v + e0);
+        if (e0 + 3 < n) vv = *(const f4u *)(v + e0);
         else { for (int j = 0; j < 4; ++j) if (e0 + j < n) vv[j] = v[e0 + j]; }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -622,7 +621,7 @@ __device__ __forceinline__ void load_chunk(const float *__restrict__ v, const ui
 // count_run: the counts of "greater" and "equal" over run number `run` of the node, stored as
 // totals[run] = greater << 32 | equal.  emit_run (once all runs are counted): the counts of the runs before
 // this one place the run in the output; the run is then written chunk by chunk with a running offset.
-template <bool VEC, int THREADS>
+template <int THREADS>
 __device__ __forceinline__ void count_run(const SelArgs &a, const int node, const uint32_t thr,
                                           const uint32_t c_lo, const uint32_t c_hi, const uint32_t run) {
     constexpr int W = THREADS / 64;
@@ -632,7 +631,7 @@ __device__ __forceinline__ void count_run(const SelArgs &a, const int node, cons
     uint32_t g = 0, e = 0;
     for (uint32_t chunk = c_lo; chunk < c_hi; ++chunk) {
         uint32_t bits[kRows][4], gtm, eqm;
-        load_chunk<VEC, THREADS>(v, chunk * (uint32_t)(16 * THREADS), a.n, thr, bits, gtm, eqm);
+        load_chunk<THREADS>(v, chunk * (uint32_t)(16 * THREADS), a.n, thr, bits, gtm, eqm);
         g += (uint32_t)__popc(gtm); e += (uint32_t)__popc(eqm);
     }
     g = wave_sum(g); e = wave_sum(e);
@@ -645,7 +644,7 @@ __device__ __forceinline__ void count_run(const SelArgs &a, const int node, cons
     }
 }
 
-template <bool VEC, int THREADS>
+template <int THREADS>
 __device__ __forceinline__ void emit_run(const SelArgs &a, const int node, const uint32_t thr, const uint32_t quota,
                                          const uint32_t c_lo, const uint32_t c_hi, const uint32_t nchunks,
                                          const uint32_t run) {
@@ -676,7 +675,7 @@ __device__ __forceinline__ void emit_run(const SelArgs &a, const int node, const
     for (uint32_t chunk = c_lo; chunk < c_hi; ++chunk) {   // c_lo, c_hi: the same for the whole block
         const uint32_t base = chunk * (uint32_t)(16 * THREADS);
         uint32_t bits[kRows][4], gtm, eqm;
-        load_chunk<VEC, THREADS>(v, base, a.n, thr, bits, gtm, eqm);
+        load_chunk<THREADS>(v, base, a.n, thr, bits, gtm, eqm);
         // position of my flagged elements inside the chunk, in index order (row, wave, lane, j)
         uint32_t lane_gt[kRows], lane_eq[kRows];
         __syncthreads();   // the previous chunk's readers of sh_gt / sh_eq are done
@@ -873,7 +872,7 @@ __global__ __launch_bounds__(1024) void k_emit_scanned(SelArgs a) {
 //    outright on long vectors; the kernel boundaries are the only exchange between blocks.
 
 // counts digit `pass` of the keys whose higher digits equal `prefix` into hist (LDS), this block's share of v
-template <bool VEC, int THREADS>
+template <int THREADS>
 __device__ __forceinline__ void radix_tally(const float *__restrict__ v, const uint32_t n, const uint32_t first,
                                             const uint32_t nthreads, const int pass, const uint32_t prefix,
                                             uint32_t *hist) {
@@ -882,31 +881,28 @@ __device__ __forceinline__ void radix_tally(const float *__restrict__ v, const u
         else if (pass == 1) { if ((key >> 20) == prefix) atomicAdd(&hist[(key >> 10) & 1023u], 1u); }
         else { if ((key >> 10) == prefix) atomicAdd(&hist[key & 1023u], 1u); }
     };
-    if (VEC) {
-        const uint32_t n4 = n >> 2;
-        for (uint32_t i = first; i < n4; i += 4 * nthreads) {   // four 16-byte loads in flight per thread
-            f4 vv[4];
+    const uint32_t n4 = n >> 2;
+    for (uint32_t i = first; i < n4; i += 4 * nthreads) {   // four 16-byte loads in flight per thread
+        f4 vv[4];
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const uint32_t ii = i + r * nthreads;   // < 2^29 + 2^22: no wrap
-                vv[r] = ii < n4 ? ((const f4 *)v)[ii] : (f4){0.f, 0.f, 0.f, 0.f};
-            }
+        for (int r = 0; r < 4; ++r) {
+            const uint32_t ii = i + r * nthreads;   // < 2^29 + 2^22: no wrap
+            vv[r] = (f4){0.f, 0.f, 0.f, 0.f};
+            if (ii < n4) vv[r] = ((const f4u *)v)[ii];
+        }
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                if (i + r * nthreads < n4) {
-                    count(key_of(vv[r].x)); count(key_of(vv[r].y)); count(key_of(vv[r].z)); count(key_of(vv[r].w));
-                }
+        for (int r = 0; r < 4; ++r) {
+            if (i + r * nthreads < n4) {
+                count(key_of(vv[r].x)); count(key_of(vv[r].y)); count(key_of(vv[r].z)); count(key_of(vv[r].w));
             }
         }
-        for (uint32_t i = (n4 << 2) + first; i < n; i += nthreads) count(key_of(v[i]));
-    } else {
-        for (uint32_t i = first; i < n; i += nthreads) count(key_of(v[i]));
     }
+    for (uint32_t i = (n4 << 2) + first; i < n; i += nthreads) count(key_of(v[i]));
 }
 
 // One pass over share `run` of `nruns` of the node's v: the histogram of digit `pass` among the keys whose
 // higher digits equal `prefix`, counted in LDS and added to the node's histogram of that pass.
-template <bool VEC, int THREADS>
+template <int THREADS>
 __device__ __forceinline__ void radix_count(const SelArgs &a, const int node, const int pass, const uint32_t prefix,
                                             uint32_t *hist /*[kRadixBins]*/, const uint32_t run, const uint32_t nruns) {
     const int tid = threadIdx.x;
@@ -914,7 +910,7 @@ __device__ __forceinline__ void radix_count(const SelArgs &a, const int node, co
     uint32_t *gh = a.radix_hist + (node * 3 + pass) * kRadixBins;
     for (int i = tid; i < nb; i += THREADS) hist[i] = 0;
     __syncthreads();
-    radix_tally<VEC, THREADS>(a.v + (size_t)node * a.stride, a.n, run * THREADS + tid, nruns * THREADS, pass, prefix, hist);
+    radix_tally<THREADS>(a.v + (size_t)node * a.stride, a.n, run * THREADS + tid, nruns * THREADS, pass, prefix, hist);
     __syncthreads();
     for (int i = tid; i < nb; i += THREADS) { const uint32_t h = hist[i]; if (h) atomicAdd(&gh[i], h); }
 }
@@ -955,7 +951,6 @@ __device__ __forceinline__ void block_run(const SelArgs &a, const uint32_t run, 
 }
 
 // One block of 1024 threads per node (grid (1, nodes)), everything in that block.
-template <bool VEC>
 __global__ __launch_bounds__(1024) void k_exact_block(SelArgs a) {
     __shared__ __align__(16) uint32_t hist[kRadixBins];
     __shared__ uint32_t wave_tmp[16], res[2];
@@ -970,14 +965,14 @@ __global__ __launch_bounds__(1024) void k_exact_block(SelArgs a) {
     for (int pass = 0; pass < 3; ++pass) {
         for (int i = tid; i < kRadixBins; i += 1024) hist[i] = 0;
         __syncthreads();
-        radix_tally<VEC, 1024>(v, a.n, tid, 1024u, pass, prefix, hist);
+        radix_tally<1024>(v, a.n, tid, 1024u, pass, prefix, hist);
         __syncthreads();
         radix_digit<1024>(pass, hist, wave_tmp, res, prefix, rank);
     }
     // prefix is now the full key T*; rank the number of ties to take
     if (tid == 0) { s->thr = prefix; s->quota = rank; carry_lapse(a, node); }
     const uint32_t nchunks = (a.n + 16383u) / 16384u;
-    emit_run<VEC, 1024>(a, node, prefix, rank, 0u, nchunks, nchunks, 0u);
+    emit_run<1024>(a, node, prefix, rank, 0u, nchunks, nchunks, 0u);
 }
 
 // The same phases in one launch of several blocks per node, for the fast path's fall-back on long vectors (it
@@ -1019,7 +1014,7 @@ __device__ __forceinline__ void phase_done(Ctr *c, const int phase) {
 }
 
 // The ticket loop of one block; `shares` = shares per phase = blocks of the node that run this loop.
-template <bool VEC, int THREADS>
+template <int THREADS>
 __device__ __forceinline__ void exact_tickets(const SelArgs &a, const int node, const uint32_t shares, uint32_t *hist /*[kRadixBins]*/,
                                               uint32_t *wave_tmp /*[THREADS / 64]*/, uint32_t *res /*[2]*/) {
     __shared__ uint32_t sh_ticket;
@@ -1039,15 +1034,15 @@ __device__ __forceinline__ void exact_tickets(const SelArgs &a, const int node, 
         if (phase > 0 && !phase_wait(a, c, phase - 1, shares)) return;   // a wait expired somewhere: give up, lgc_stats reports it
         for (; fixed < (phase < 3 ? phase : 3); ++fixed) radix_fix<THREADS>(a, node, fixed, hist, wave_tmp, res, prefix, rank);
         if (phase < 3) {
-            radix_count<VEC, THREADS>(a, node, phase, prefix, hist, run, shares);
+            radix_count<THREADS>(a, node, phase, prefix, hist, run, shares);
         } else {
             uint32_t c_lo, c_hi, nchunks;
             block_run<THREADS>(a, run, shares, c_lo, c_hi, nchunks);
             if (phase == 3) {
                 if (run == 0 && tid == 0) { s->thr = prefix; s->quota = rank; carry_lapse(a, node); }   // prefix is the full key T*, rank the ties to take
-                count_run<VEC, THREADS>(a, node, prefix, c_lo, c_hi, run);
+                count_run<THREADS>(a, node, prefix, c_lo, c_hi, run);
             } else {
-                emit_run<VEC, THREADS>(a, node, prefix, rank, c_lo, c_hi, nchunks, run);
+                emit_run<THREADS>(a, node, prefix, rank, c_lo, c_hi, nchunks, run);
             }
         }
         phase_done(c, phase);
@@ -1055,7 +1050,6 @@ __device__ __forceinline__ void exact_tickets(const SelArgs &a, const int node, 
 }
 
 // Exact selection as one launch of its own: about one block of 1024 threads per compute unit, shared by the nodes.
-template <bool VEC>
 __global__ __launch_bounds__(1024) void k_exact(SelArgs a) {
     __shared__ __align__(16) uint32_t hist[kRadixBins];
     __shared__ uint32_t wave_tmp[16], res[2];
@@ -1065,7 +1059,7 @@ __global__ __launch_bounds__(1024) void k_exact(SelArgs a) {
         const uint32_t gtid = blockIdx.x * 1024u + tid, nthreads = gridDim.x * 1024u, all = gridDim.y * nthreads;
         for (uint32_t i = blockIdx.y * nthreads + gtid; i < a.next_words; i += all) a.next_state[i] = 0;
     }
-    exact_tickets<VEC, 1024>(a, node, gridDim.x, hist, wave_tmp, res);
+    exact_tickets<1024>(a, node, gridDim.x, hist, wave_tmp, res);
 }
 
 // Output for short candidate lists and the fall-back in ONE launch: blocks 0 .. out_blocks - 1 of a node (grid y)
@@ -1074,7 +1068,6 @@ __global__ __launch_bounds__(1024) void k_exact(SelArgs a) {
 // (the same test they make: enough candidates, none lost, T* inside the histogram's range) and leaves if so,
 // which is nearly always and costs them one block-wide search; otherwise they run the ticket loop.  A launch
 // of its own for the fall-back costs 4.5 us per call even when it has nothing to do.
-template <bool VEC>
 __global__ __launch_bounds__(1024) void k_output_or_exact(SelArgs a, uint32_t out_blocks) {
     __shared__ __align__(16) uint32_t hist[kFineBins];
     __shared__ uint32_t wave_tmp[16], res[2];
@@ -1093,16 +1086,22 @@ __global__ __launch_bounds__(1024) void k_output_or_exact(SelArgs a, uint32_t ou
         __syncthreads();
     }
     if (ok) return;
-    exact_tickets<VEC, 1024>(a, node, gridDim.y - out_blocks, hist, wave_tmp, res);
+    exact_tickets<1024>(a, node, gridDim.y - out_blocks, hist, wave_tmp, res);
 }
 
 // From the candidates' bitmap to the output in ONE launch, for short lists: block 0 of a node (grid y) lists the flagged
 // elements in its LDS, in index order, finds T* among them and writes the selection; the blocks after it stand
 // by for the exact path and decide for themselves, from the row counts, whether they are needed.  k_gather and
 // k_output_or_exact do the same for longer lists with many blocks: two launches and a list that one writes to
-// memory for the other to read.
+// memory for the other to read.  What it costs is one block's chain: 2 us for the row counts, 1 us per 1024 entries
+// for rows and records, 1.3 us per digit, 2.5 us for the ordered output.  All loops are kept rolled: code that runs once per
+// launch is fetched as it runs, and four entries per thread side by side took 1.5 times as long.
+// Measured against the two launches: one node of 2^20 elements, k = 1 024: 10.4 us against 17; 3 x 3.33 M, k = 3 333: 20 against 22.6.
+constexpr int kFinishBins = 8192;
+static_assert(kFinishBins >= kRadixBins, "the exact path counts in the same words");
+
 __device__ __forceinline__ void finish_node(const SelArgs &a, const int node, const uint32_t total, const int report,
-                                            const uint32_t *offs /*[kFinishRows + 1]: list entries before each row*/, uint32_t *hist /*[kFineBins]*/,
+                                            const uint32_t *offs /*[kFinishRows + 1]: list entries before each row*/, uint32_t *hist /*[kFinishBins]*/,
                                             uint32_t *wave_tmp /*[16]*/, uint32_t *res /*[2]*/) {
     __shared__ uint32_t list_idx[kFinishList], list_val[kFinishList];
     const int tid = threadIdx.x, lane = tid & 63;
@@ -1110,59 +1109,29 @@ __device__ __forceinline__ void finish_node(const SelArgs &a, const int node, co
     const uint32_t nrows = (a.n + kRow - 1) / kRow;
     float *v = a.v + (size_t)node * a.stride;
     float *u = a.u ? a.u + (size_t)node * a.stride : nullptr;
-    // 16 lanes per row, lane 4 s + j holds word 4 s + j of it: element 256 s + 4 l + j is bit l.  In element order the
-    // bits of the four words of one s interleave.
     const unsigned long long *bitmap = a.bitmap + (size_t)node * a.rows * kRowWords;
-    for (uint32_t base = 0; base < nrows; base += 256) {   // four rows per 16 lanes, their words in flight together
-        unsigned long long w[4];
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const uint32_t r = base + t * 64 + (tid >> 4);
-            w[t] = r < nrows && offs[r + 1] != offs[r] ? bitmap[(size_t)r * kRowWords + (tid & 15)] : 0ull;
-        }
+    uint32_t half = 1;                            // the search below starts at half of a power of two >= nrows
+    while (half * 2 < nrows) half *= 2;
+    uint32_t most = 0, least = ~0u;
 #pragma unroll 1
-        for (int t = 0; t < 4; ++t) {
-            unsigned long long bits = t == 0 ? w[0] : t == 1 ? w[1] : t == 2 ? w[2] : w[3];
-            if (__ballot(bits != 0) == 0) continue;   // wave-uniform; no barrier in these loops
-            const uint32_t r = base + t * 64 + (tid >> 4), j = tid & 3u;
-            // the words of this s, and the flags of the earlier s of the row
-            unsigned long long x[4];
-            uint32_t mine = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                x[q] = ((unsigned long long)__shfl((uint32_t)(bits >> 32), (lane & ~3) | q, 64) << 32) | __shfl((uint32_t)bits, (lane & ~3) | q, 64);
-                mine += (uint32_t)__popcll(x[q]);
-            }
-            uint32_t before = r < nrows ? offs[r] : 0u;
-#pragma unroll
-            for (int q = 0; q < 3; ++q) { const uint32_t y = __shfl(mine, (lane & ~15) | (q * 4), 64); before += q < ((lane >> 2) & 3) ? y : 0u; }
-            while (bits) {
-                const int l = __ffsll(bits) - 1;
-                bits &= bits - 1;
-                const unsigned long long below = (1ull << l) - 1ull;
-                uint32_t at = before;
-#pragma unroll
-                for (int q = 0; q < 4; ++q) at += (uint32_t)__popcll(x[q] & below) + ((uint32_t)q < j ? (uint32_t)(x[q] >> l) & 1u : 0u);
-                list_idx[at] = r * (uint32_t)kRow + ((lane >> 2) & 3) * 256u + 4u * l + j;   // at < total <= kFinishList
-            }
-        }
-    }
-    __syncthreads();
-    // the values, the largest and the smallest key
-    uint32_t most = 0;
-    uint32_t least = ~0u;
+    for (uint32_t p = tid; p < total; p += 1024) {
+        uint32_t r = 0;                           // last row with offs[r] <= p: it holds entry p
 #pragma unroll 1
-    for (uint32_t i0 = tid; i0 < total; i0 += 4096) {   // four reads in flight
-        uint32_t x[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) x[q] = i0 + q * 1024 < total ? __float_as_uint(v[list_idx[i0 + q * 1024]]) : 0u;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (i0 + q * 1024 < total) {
-                list_val[i0 + q * 1024] = x[q];
-                const uint32_t key = x[q] & 0x7fffffffu;
-                most = key > most ? key : most; least = key < least ? key : least;
-            }
+        for (uint32_t step = half; step >= 1; step >>= 1)
+            if (r + step < nrows && offs[r + step] <= p) r += step;
+        const uint32_t i = p - offs[r];
+        uint32_t ix, x;
+        if (a.row_rec && offs[r + 1] - offs[r] <= (uint32_t)kRecord) {
+            const uint32_t *rec = a.row_rec + ((size_t)node * a.rows + r) * kRecordWords;
+            x = rec[i];
+            ix = r * (uint32_t)kRow + ((const uint16_t *)(rec + kRecord))[i];
+        } else {
+            ix = r * (uint32_t)kRow + row_element(bitmap + (size_t)r * kRowWords, i);
+            x = ix < a.n ? __float_as_uint(v[ix]) : 0u;
+        }
+        list_idx[p] = ix; list_val[p] = x;
+        const uint32_t key = x & 0x7fffffffu;
+        most = key > most ? key : most; least = key < least ? key : least;
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
@@ -1177,16 +1146,16 @@ __device__ __forceinline__ void finish_node(const SelArgs &a, const int node, co
         const uint32_t y = __shfl_xor(most, d, 64), z = __shfl_xor(least, d, 64);
         most = y > most ? y : most; least = z < least ? z : least;
     }
-    // T*: digits of at most 12 bits of (key - least), as many as the keys' spread needs
+    // T*: digits of at most 13 bits of (key - least), as many as the keys' spread needs (two, mostly)
     uint32_t need = a.k, prefix = 0, ties = 0;
     uint32_t bits = most > least ? 32u - (uint32_t)__clz(most - least) : 1u;   // of the largest difference
     bits = __builtin_amdgcn_readfirstlane(bits);
     uint32_t shift = bits;
     while (shift) {                               // block-uniform
-        const uint32_t digit = shift < 12u ? shift : 12u, next = shift - digit;
+        const uint32_t digit = shift < 13u ? shift : 13u, next = shift - digit;
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < kFineBins / 1024; ++i) hist[i * 1024 + tid] = 0;
+        for (int i = 0; i < kFinishBins / 1024; ++i) hist[i * 1024 + tid] = 0;
         __syncthreads();
 #pragma unroll 1
         for (uint32_t i = tid; i < total; i += 1024) {
@@ -1194,16 +1163,19 @@ __device__ __forceinline__ void finish_node(const SelArgs &a, const int node, co
             if ((uint32_t)((unsigned long long)d >> shift) == prefix) atomicAdd(&hist[(d >> next) & ((1u << digit) - 1u)], 1u);
         }
         __syncthreads();
-        find_rank_bin<kFineBins, 1024>(hist, need, wave_tmp, res);
+        find_rank_bin<kFinishBins, 1024>(hist, need, wave_tmp, res);
         need -= res[1];
-        ties = hist[res[0] & (kFineBins - 1)];
+        ties = hist[res[0] & (kFinishBins - 1)];
         prefix = (prefix << digit) | res[0];
         shift = next;
     }
     const uint32_t thr = least + prefix, quota = need;
     if (tid == 0) {
         if (report) report_outcome(a, node, s, true, thr, quota, total, s->t_est);
-        else carry_lapse(a, node);
+        else {   // short vectors: one node speaks for those served (256 stores to host memory would take 25 us)
+            carry_lapse(a, node);
+            if (a.notify && node == 0) st_system32(a.notify + 1, a.notify_value);
+        }
     }
     // ordered output: kLen consecutive entries per thread
     constexpr uint32_t kLen = kFinishList / 1024;
@@ -1235,9 +1207,8 @@ __device__ __forceinline__ void finish_node(const SelArgs &a, const int node, co
     }
 }
 
-template <bool VEC>
 __global__ __launch_bounds__(1024) void k_finish_or_exact(SelArgs a, int report) {
-    __shared__ __align__(16) uint32_t hist[kFineBins];
+    __shared__ __align__(16) uint32_t hist[kFinishBins];
     __shared__ uint32_t wave_tmp[16], res[2];
     __shared__ uint32_t offs[kFinishRows + 1];
     constexpr int kPer = kFinishRows / 1024;
@@ -1258,29 +1229,30 @@ __global__ __launch_bounds__(1024) void k_finish_or_exact(SelArgs a, int report)
     total = __builtin_amdgcn_readfirstlane(total);
     const bool ok = total >= a.k && total <= kFinishList;   // the same for all the node's blocks
     if (blockIdx.y != 0) {
-        if (!ok) exact_tickets<VEC, 1024>(a, node, gridDim.y - 1, hist, wave_tmp, res);
+        if (!ok) exact_tickets<1024>(a, node, gridDim.y - 1, hist, wave_tmp, res);
         return;
     }
     if (tid == 0) a.sel[node].cand_total = total;
     if (ok) finish_node(a, node, total, report, offs, hist, wave_tmp, res);
-    else if (tid == 0 && report) report_outcome(a, node, a.sel + node, false, 0, 0, total, a.sel[node].t_est);
+    else if (tid == 0) {
+        if (report) report_outcome(a, node, a.sel + node, false, 0, 0, total, a.sel[node].t_est);
+        else if (a.notify) st_system32(a.notify, a.notify_value);
+    }
 }
 
-void launch_finish_from_bitmap(const SelArgs &a, int batch, bool report, bool vec, int cus, hipStream_t st) {
+void launch_finish_from_bitmap(const SelArgs &a, int batch, bool report, int cus, hipStream_t st) {
     const uint32_t chunks = (a.n + 16383u) / 16384u;
     uint32_t standby = (uint32_t)(cus / batch);   // as in launch_output_from_candidates
     if (standby > chunks) standby = chunks;
     if (standby < 1) standby = 1;
     const dim3 grid(batch, 1 + standby);
-    if (vec) hipLaunchKernelGGL(k_finish_or_exact<true>, grid, dim3(1024), 0, st, a, (int)report);
-    else hipLaunchKernelGGL(k_finish_or_exact<false>, grid, dim3(1024), 0, st, a, (int)report);
+    hipLaunchKernelGGL(k_finish_or_exact, grid, dim3(1024), 0, st, a, (int)report);
 }
 
 // Five launches: step 0..2: the radix pass of that digit (the digits before it are fixed again from their
 // finished histograms: a few microseconds, no exchange); step 3: T*, the tie quota and the counts of every
 // block's run; step 4: the ordered output.  The blocks need not be resident together, and their number is
 // chosen for the passes over v alone.
-template <bool VEC>
 __global__ __launch_bounds__(kBlock) void k_exact_step(SelArgs a, int step) {
     __shared__ __align__(16) uint32_t hist[kRadixBins];
     __shared__ uint32_t wave_tmp[kWaves], res[2];
@@ -1293,23 +1265,23 @@ __global__ __launch_bounds__(kBlock) void k_exact_step(SelArgs a, int step) {
     uint32_t c_lo, c_hi, nchunks;
     block_run<kBlock>(a, blockIdx.x, gridDim.x, c_lo, c_hi, nchunks);
     if (step == 4) {
-        emit_run<VEC, kBlock>(a, node, s->thr, s->quota, c_lo, c_hi, nchunks, blockIdx.x);
+        emit_run<kBlock>(a, node, s->thr, s->quota, c_lo, c_hi, nchunks, blockIdx.x);
         return;
     }
     uint32_t prefix = 0, rank = a.k;
     for (int pass = 0; pass < (step < 3 ? step : 3); ++pass) radix_fix<kBlock>(a, node, pass, hist, wave_tmp, res, prefix, rank);
     if (step < 3) {
-        radix_count<VEC, kBlock>(a, node, step, prefix, hist, blockIdx.x, gridDim.x);
+        radix_count<kBlock>(a, node, step, prefix, hist, blockIdx.x, gridDim.x);
         return;
     }
     if (blockIdx.x == 0 && tid == 0) { s->thr = prefix; s->quota = rank; carry_lapse(a, node); }
-    count_run<VEC, kBlock>(a, node, prefix, c_lo, c_hi, blockIdx.x);
+    count_run<kBlock>(a, node, prefix, c_lo, c_hi, blockIdx.x);
 }
 
 constexpr uint64_t kStepMinElems = 1ull << 20;   // forced exact selection of this many elements (all nodes) and more: five launches
 constexpr uint32_t kBlockMaxElems = 1u << 15;    // vectors up to this length: one block per node does everything
 
-void launch_exact(const SelArgs &a, int batch, bool vec, int cus, hipStream_t st) {
+void launch_exact(const SelArgs &a, int batch, int cus, hipStream_t st) {
     const uint32_t chunks = (a.n + kChunk - 1) / kChunk;
     if (a.force && (uint64_t)a.n * batch >= kStepMinElems) {
         // five launches: about four blocks per compute unit in all (fewer make a block's share of a pass long,
@@ -1319,14 +1291,12 @@ void launch_exact(const SelArgs &a, int batch, bool vec, int cus, hipStream_t st
         if (per_node < 1) per_node = 1;
         dim3 grid2(per_node, batch);
         for (int step = 0; step < 5; ++step) {
-            if (vec) hipLaunchKernelGGL(k_exact_step<true>, grid2, dim3(kBlock), 0, st, a, step);
-            else hipLaunchKernelGGL(k_exact_step<false>, grid2, dim3(kBlock), 0, st, a, step);
+            hipLaunchKernelGGL(k_exact_step, grid2, dim3(kBlock), 0, st, a, step);
         }
         return;
     }
     if (a.n <= kBlockMaxElems) {
-        if (vec) hipLaunchKernelGGL(k_exact_block<true>, dim3(1, batch), dim3(1024), 0, st, a);
-        else hipLaunchKernelGGL(k_exact_block<false>, dim3(1, batch), dim3(1024), 0, st, a);
+        hipLaunchKernelGGL(k_exact_block, dim3(1, batch), dim3(1024), 0, st, a);
         return;
     }
     // one launch, about one block of 1024 threads per compute unit shared by the nodes: each block more makes the
@@ -1336,14 +1306,13 @@ void launch_exact(const SelArgs &a, int batch, bool vec, int cus, hipStream_t st
     if (per_node > shares_max) per_node = shares_max;
     if (per_node < 1) per_node = 1;
     dim3 grid(per_node, batch);
-    if (vec) hipLaunchKernelGGL(k_exact<true>, grid, dim3(1024), 0, st, a);
-    else hipLaunchKernelGGL(k_exact<false>, grid, dim3(1024), 0, st, a);
+    hipLaunchKernelGGL(k_exact, grid, dim3(1024), 0, st, a);
 }
 
 // direct = true: short candidate lists (each block reads the whole list; the fall-back rides in the same
 // launch); false: long lists (second-level histogram by many blocks, counts per chunk, output).  Returns
 // whether the fall-back to the exact path is part of what was launched.
-bool launch_output_from_candidates(const SelArgs &a, int batch, bool direct, bool vec, int cus, hipStream_t st) {
+bool launch_output_from_candidates(const SelArgs &a, int batch, bool direct, int cus, hipStream_t st) {
     if (direct) {
         const uint32_t out_blocks = (a.cap + 4095) / 4096;
         // stand-by blocks of 1024 threads, about one per compute unit shared by the nodes, as in the stand-alone
@@ -1356,8 +1325,7 @@ bool launch_output_from_candidates(const SelArgs &a, int batch, bool direct, boo
         if (standby > chunks) standby = chunks;
         if (standby < 1) standby = 1;
         const dim3 grid(batch, out_blocks + standby);
-        if (vec) hipLaunchKernelGGL(k_output_or_exact<true>, grid, dim3(1024), 0, st, a, out_blocks);
-        else hipLaunchKernelGGL(k_output_or_exact<false>, grid, dim3(1024), 0, st, a, out_blocks);
+        hipLaunchKernelGGL(k_output_or_exact, grid, dim3(1024), 0, st, a, out_blocks);
         return true;
     }
     uint32_t blocks = (a.cap + 16383) / 16384;

@@ -96,3 +96,32 @@ def test_short_and_long_vectors_in_one_graph(B):
             assert all(torch.equal(x, y) for x, y in zip(r, e))
     assert B.lgc_stats(ctx)[2] == 0 and B.lgc_stats(other)[2] == 0
     ctx.close(); other.close()
+
+
+# Rows (1024 elements) whose candidates fill a record exactly, exceed it by one, or fill the row; vectors at the limits of
+# the one-launch finish (4096 rows) and a list long enough for the kernels of the dense selections.
+@pytest.mark.parametrize("n,k", [(300_001, 1500), (4_194_304, 2500), (4_194_305, 2500), (5_000_003, 200_000)])
+def test_rows_at_the_limits_of_a_record(B, oracle, n, k):
+    rng = np.random.default_rng(n)
+    v = rng.normal(0, 1e-3, (2, n + 1)).astype(np.float32)
+    rows = n // 1024
+    for b in range(2):
+        for i, m in enumerate((1, 31, 32, 33, 40, 64, 1024, 32)):
+            r = (i * 37 + b) % rows
+            at = r * 1024 + rng.permutation(1024)[:m]
+            v[b, at] = rng.choice([-1.0, 1.0], m) * (1.0 + rng.random(m))
+    g, u = np.zeros_like(v), rng.normal(0, 1e-4, v.shape).astype(np.float32)
+    ctx = B.Context(n, k, 2)
+    dg, du, dv = (torch.from_numpy(a).cuda()[:, :n] for a in (g, u, v))
+    ov, oi = torch.zeros((2, k), device="cuda"), torch.zeros((2, k), dtype=torch.int32, device="cuda")
+    for _ in range(2):
+        B.lgc_accumulate_topk(ctx, dg, du, dv, 0.9, k, ov, oi)
+        for b in range(2):
+            un, vn = u[b, :n].copy(), v[b, :n].copy()
+            oracle.accumulate(g[b, :n].copy(), un, vn, 0.9)
+            vals, idx = oracle.topk(vn, un, k)
+            u[b, :n], v[b, :n] = un, vn
+            assert (oi[b].cpu().numpy().astype(np.uint32) == idx).all() and same(ov[b], vals)
+        assert same(dv, v[:, :n]) and same(du, u[:, :n])
+    assert B.lgc_stats(ctx)[2] == 0
+    ctx.close()
