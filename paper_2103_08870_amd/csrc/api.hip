@@ -293,10 +293,12 @@ constexpr int kMaxExactCalls = 64;   // most selections in a row that take the e
 // Short vectors are selected exactly by kernels of their own, unless the exact radix path was asked for.
 bool takes_small_path(const lgc_ctx *ctx, uint64_t n, uint64_t k) { return ctx->opt_path != 1 && small_select_covers(n, k); }
 
-// Short candidate lists of vectors that are not too long go from the bitmap to the output in one launch of one block
-// per node, with a third of the list to spare.
+// Short candidate lists of vectors that are not too long go from the bitmap to the output in one launch of one block per
+// node.  The line: one block takes 1.3 us per 1024 entries that many blocks take side by side (3 x 3.33 M elements,
+// 6 200 expected, accumulation and selection: 69.2 us in one launch, 65.1 us in two; 2^20 elements, 1 900
+// expected: 10.4 us against 17 for the launches themselves).
 bool takes_finish(uint64_t n, uint64_t k) {
-    return (n + kRow - 1) / kRow <= kFinishRows && 1.5 * expected_candidates((double)n, (double)k) + 2048.0 <= (double)kFinishList;
+    return (n + kRow - 1) / kRow <= kFinishRows && expected_candidates((double)n, (double)k) <= 4096.0;
 }
 
 // accumulate (optional) + select; g == nullptr means selection only
@@ -344,11 +346,12 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         }
         if (ctx->exact_calls_left > 0) { --ctx->exact_calls_left; fast = small = false; }
     }
-    // the rows' records: where one block per node reads them, and for long candidate lists (one node of 2^28 elements, 1 %:
-    // gather 142 -> 55 us); in between, what the gather saves its reads of v had saved the output's stores
-    // to the same lines (4 nodes x 25.6 M, 0.1 %: gather 17 -> 12 us, the whole call no faster)
+    // The rows' records: where one block per node reads them; for long candidate lists (one node of 2^28 elements, 1 %:
+    // gather 142 -> 55 us); and where v stays in the 256 MB memory-side cache (3 x 3.33 M: 64.4 -> 63.6 us per call).
+    // In between, what the gather saves in reads of v the output pays: its zeros then go to lines that nothing has
+    // fetched (8 x 44.5 M, 0.1 %: 1325 us without, 1339 with; 4 x 25.6 M: 384.2, 385.0).
     const bool long_list = expected_candidates((double)n, (double)k) > 131072.0;
-    if (!finishes_in_one && !long_list) a.row_rec = nullptr;
+    if (!finishes_in_one && !long_list && n * (uint64_t)batch > (1ull << 25)) a.row_rec = nullptr;
     if (fast || small) {
         if (++ctx->call_number == 0) ctx->call_number = 1;
         a.notify_value = ctx->call_number;

@@ -135,7 +135,8 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
     const float m = a.momentum;
     unsigned long long *bitmap = a.bitmap + (size_t)node * a.rows * kRowWords;
     uint32_t *row_count = a.row_count + (size_t)node * a.rows;
-    for (uint32_t r = a.row_begin + blockIdx.x * kWaves + wave; r < a.row_end; r += gridDim.x * kWaves) {
+    const uint32_t r = a.row_begin + blockIdx.x * kWaves + wave;   // one row per wavefront (the launcher's grid)
+    if (r < a.row_end) {
         const uint32_t row = r * (uint32_t)kRow;
         const uint32_t end = (a.n - row > (uint32_t)kRow) ? row + kRow : a.n;
         uint32_t bits[4][4];
@@ -202,9 +203,10 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
                 const unsigned long long mk = __ballot(e < end && (bits[s][j] & 0x7fffffffu) >= (SEG ? thr[s][j] : t_est));
                 flags[s][j] = mk;
                 count += (uint32_t)__popcll(mk);
-                const bool mine = lane == s * 4 + j;
-                lo = mine ? (uint32_t)mk : lo;
-                hi = mine ? (uint32_t)(mk >> 32) : hi;
+                // (a choice by lane number takes three instructions and, hoisted, 32 scalar registers: 72 -> 68 vector registers
+                // without records, 92 -> 70 with; 8 x 44.5 M elements, whole step: 1336 -> 1325 us)
+                asm("v_writelane_b32 %0, %1, %2" : "+v"(lo) : "s"((uint32_t)mk), "n"(s * 4 + j));
+                asm("v_writelane_b32 %0, %1, %2" : "+v"(hi) : "s"((uint32_t)(mk >> 32)), "n"(s * 4 + j));
             }
         }
         if (lane < kRowWords) bitmap[(size_t)r * kRowWords + lane] = ((unsigned long long)hi << 32) | lo;
