@@ -339,6 +339,8 @@ lgc_status lgc_reserve(lgc_ctx *ctx, const lgc_ae *ae /* nullable */, uint64_t k
  *       HIP graph keeps the choice made when it was recorded.
  *   1 = always the exact radix path.
  *   2 = always the fast path first, whatever happened before.
+ * For fewer than 2^18 elements the fast path (k up to 4096) counts every element's
+ * magnitude instead of sampling; larger k takes the exact radix path.
  * What the switch is for: where very many magnitudes are equal around the k-th
  * largest, as in quantised gradients, no threshold separates about k elements,
  * and reaching the exact path through the failed fast path costs more than

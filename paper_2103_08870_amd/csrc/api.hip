@@ -346,12 +346,17 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         }
         if (ctx->exact_calls_left > 0) { --ctx->exact_calls_left; fast = small = false; }
     }
-    // The rows' records: where one block per node reads them; for long candidate lists (one node of 2^28 elements, 1 %:
-    // gather 142 -> 55 us); and where v stays in the 256 MB memory-side cache (3 x 3.33 M: 64.4 -> 63.6 us per call).
-    // In between, what the gather saves in reads of v the output pays: its zeros then go to lines that nothing has
-    // fetched (8 x 44.5 M, 0.1 %: 1325 us without, 1339 with; 4 x 25.6 M: 384.2, 385.0).
-    const bool long_list = expected_candidates((double)n, (double)k) > 131072.0;
-    if (!finishes_in_one && !long_list && n * (uint64_t)batch > (1ull << 25)) a.row_rec = nullptr;
+    // The rows' records: where one block per node reads them; for candidate lists whose lines of v (128 bytes each) are
+    // more than the 256 MB memory-side cache holds (one node of 2^28 elements, 1 %: gather 142 -> 55 us); and for short
+    // lists where all of v stays in that cache (3 x 3.33 M: 64.4 -> 63.6 us per call).  In between, what the gather saves in reads of v the
+    // output pays: its zeros then go to lines that nothing has fetched.  Whole step without / with records: 8 x 44.5 M,
+    // 0.1 %: 1325 / 1339 us; 4 x 25.6 M, 0.1 %: 384.2 / 385.0; 67 M, 0.8 %: 322 / 330; 2^28, 0.4 %: 1111 / 1128,
+    // 0.7 % (2.4 M candidates): 1262 / 1268, 1 % (3.4 M): 1404 / 1380;
+    // and a long list under the cache's size in a short vector, 20 M, 1 %: 138 / 140.5.
+    const double listed = expected_candidates((double)n, (double)k);
+    const bool long_list = listed > 131072.0;
+    const bool v_stays = !long_list && n * (uint64_t)batch <= (1ull << 25);
+    if (!finishes_in_one && !v_stays && listed * batch < 2097152.0) a.row_rec = nullptr;
     if (fast || small) {
         if (++ctx->call_number == 0) ctx->call_number = 1;
         a.notify_value = ctx->call_number;

@@ -100,7 +100,7 @@ def test_short_and_long_vectors_in_one_graph(B):
 
 # Rows (1024 elements) whose candidates fill a record exactly, exceed it by one, or fill the row; vectors at the limits of
 # the one-launch finish (4096 rows) and a list long enough for the kernels of the dense selections.
-@pytest.mark.parametrize("n,k", [(300_001, 1500), (4_194_304, 2500), (4_194_305, 2500), (5_000_003, 200_000)])
+@pytest.mark.parametrize("n,k", [(300_001, 1000), (4_194_304, 1000), (4_194_305, 1000), (5_000_003, 50_000), (5_000_003, 200_000)])
 def test_rows_at_the_limits_of_a_record(B, oracle, n, k):
     rng = np.random.default_rng(n)
     v = rng.normal(0, 1e-3, (2, n + 1)).astype(np.float32)
