@@ -338,7 +338,7 @@ def main():
     ratio_index = args.ratio_index % len(w.ks)
     traffic, traffic_source = measured_traffic(w.cfg, ratio_index, args.selection, args.pattern)
     roofline = {"bound": "hbm", "achieved": None, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": None,
-                "traffic": traffic, "traffic_source": traffic_source, "kernel": f"lgc::k_candidates<true, true, {'false' if seg is None else 'true'}> (fused accumulate + candidate bitmap, all nodes in one launch)",
+                "traffic": traffic, "traffic_source": traffic_source, "kernel": f"lgc::k_candidates<true, {'false' if seg is None else 'true'}, ..> (fused accumulate + candidate bitmap, all nodes in one launch)",
                 "algorithmic_bytes_per_launch": ALGO_BYTES_PER_ELEM * K * n}
     if kern_launches:
         # ps: one streaming launch per step covers all K nodes; rar: the selecting node's launch and
@@ -350,7 +350,7 @@ def main():
                         launches=kern_launches,
                         algorithmic_bytes_per_launch=ALGO_BYTES_PER_ELEM * K * n * args.steps // kern_launches)
         if args.pattern == "rar":
-            roofline.update(kernel="lgc::k_candidates<true, true, false> (selecting node) + lgc::k_accumulate<true> "
+            roofline.update(kernel="lgc::k_candidates<true, false, ..> (selecting node) + lgc::k_accumulate "
                                    "(other nodes): the streaming launches of one step")
 
     if plain is not None:
