@@ -113,6 +113,11 @@ void launch_accumulate(const float *g, float *u, float *v, uint32_t n, int batch
 
 // ------------------------------------------------------------------ candidate pass (the streaming kernel)
 
+// x with lane `lane` replaced by the wave-uniform value.  (A choice by lane number takes three instructions and, hoisted,
+// 32 scalar registers: 72 -> 68 vector registers without records, 92 -> 70 with; 8 x 44.5 M elements, whole step: 1333 -> 1322 us.)  It is the compiler's own instruction and not inline assembly because it reads scalar registers that a compare
+// has just written: the compiler puts the wait states in between that the hardware does not supply.
+__device__ uint32_t write_lane(uint32_t value, uint32_t lane, uint32_t x) __asm("llvm.amdgcn.writelane.i32");
+
 // FUSED: reads g,u,v, writes u,v (the accumulation) and classifies the new v; otherwise reads v.
 // One wavefront per row of 1024 elements.  The flags "key >= t_est" of the row go out as one
 // full 128-byte line of the candidate bitmap (dense, coalesced: no partial-line writes), the
@@ -203,10 +208,8 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
                 const unsigned long long mk = __ballot(e < end && (bits[s][j] & 0x7fffffffu) >= (SEG ? thr[s][j] : t_est));
                 flags[s][j] = mk;
                 count += (uint32_t)__popcll(mk);
-                // (a choice by lane number takes three instructions and, hoisted, 32 scalar registers: 72 -> 68 vector registers
-                // without records, 92 -> 70 with; 8 x 44.5 M elements, whole step: 1336 -> 1325 us)
-                asm("v_writelane_b32 %0, %1, %2" : "+v"(lo) : "s"((uint32_t)mk), "n"(s * 4 + j));
-                asm("v_writelane_b32 %0, %1, %2" : "+v"(hi) : "s"((uint32_t)(mk >> 32)), "n"(s * 4 + j));
+                lo = write_lane((uint32_t)mk, s * 4 + j, lo);
+                hi = write_lane((uint32_t)(mk >> 32), s * 4 + j, hi);
             }
         }
         if (lane < kRowWords) bitmap[(size_t)r * kRowWords + lane] = ((unsigned long long)hi << 32) | lo;

@@ -1,0 +1,68 @@
+"""The gfx950 assembly of every kernel, as the library's build flags make it: wait states the hardware does not supply."""
+import os
+import re
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
+
+from paper_2103_08870_amd import build
+
+# gfx940 and later: a vector instruction that reads a scalar register needs two wait states after the vector
+# instruction that wrote it.  The compiler inserts them between its own instructions, but not into inline assembly.
+WAIT_STATES = 2
+TWO_RESULTS = ("v_add_co", "v_addc_co", "v_sub_co", "v_subb_co", "v_subrev_co", "v_subbrev_co", "v_div_scale", "v_mad_u64_u32", "v_mad_i64_i32")
+
+
+def assembly(source):
+    cmd = [build._hipcc()] + build.FLAGS + ["--cuda-device-only", "-S", os.path.join(build.CSRC, source), "-o", "-"]
+    r = subprocess.run(cmd, capture_output=True, text=True, timeout=300)
+    assert r.returncode == 0, r.stderr
+    return r.stdout
+
+
+def scalar_registers(operand):
+    if operand in ("vcc", "vcc_lo", "vcc_hi"):
+        return {"vcc": {"vcc_lo", "vcc_hi"}}.get(operand, {operand})
+    m = re.fullmatch(r"-?\|?s(\d+)\|?", operand)
+    if m:
+        return {int(m.group(1))}
+    m = re.fullmatch(r"s\[(\d+):(\d+)\]", operand)
+    return set(range(int(m.group(1)), int(m.group(2)) + 1)) if m else set()
+
+
+def short_waits(text):
+    """Lines of `text` that read a scalar register too soon after a vector instruction wrote it."""
+    found, clock, written = [], 0, {}
+    for number, line in enumerate(text.splitlines(), 1):
+        words = line.split(";")[0].strip().split(None, 1)
+        if not words or words[0].startswith(".") or words[0].endswith(":") or "=" in words[0]:
+            continue
+        name, operands = words[0], [o.strip() for o in words[1].split(",")] if len(words) > 1 else []
+        if name.startswith("v_"):
+            results = 2 if name.startswith(TWO_RESULTS) else 1
+            for o in operands[results:]:
+                if any(clock - written.get(r, -99) < WAIT_STATES + 1 for r in scalar_registers(o)):
+                    found.append((number, line.strip()))
+        results = operands[:2 if name.startswith(TWO_RESULTS) else 1]
+        for o in results:
+            for r in scalar_registers(o):
+                if name.startswith("v_"):
+                    written[r] = clock
+                else:
+                    written.pop(r, None)
+        clock += int(operands[0]) + 1 if name == "s_nop" else 1
+    return found
+
+
+def test_the_check_sees_a_short_wait():
+    assert short_waits("v_cmp_ne_u32_e64 s[0:1], 0, v0\nv_writelane_b32 v20, s0, 14\n") == [(2, "v_writelane_b32 v20, s0, 14")]
+    assert short_waits("v_cmp_ne_u32_e32 vcc, 0, v0\ns_mov_b32 s4, s5\nv_cndmask_b32_e32 v1, v2, v3, vcc\n")
+    assert not short_waits("v_cmp_ne_u32_e64 s[0:1], 0, v0\ns_nop 1\nv_writelane_b32 v20, s1, 14\n")
+    assert not short_waits("v_cmp_ne_u32_e64 s[0:1], 0, v0\ns_mov_b32 s0, s5\nv_mov_b32_e32 v20, s0\n")
+
+
+def test_scalar_registers_written_by_vector_instructions_are_waited_for():
+    with ThreadPoolExecutor(max_workers=8) as ex:
+        listings = dict(zip(build.SOURCES, ex.map(assembly, build.SOURCES)))
+    for source, text in listings.items():
+        assert source == "api.hip" or text.count("v_cmp") > 0   # (the host side has no kernels)
+        assert short_waits(text) == [], source
