@@ -181,7 +181,10 @@ uint64_t lgc_latent_len(const lgc_ae *ae, uint64_t k);
  * fp32 arithmetic with fp32 accumulation.  k == 0 is a no-op.
  * Stacks other than two kernel-3 / stride-2 layers of up to 16 channels keep
  * their intermediate tensors in the context's activation scratch, which must
- * have been reserved (lgc_reserve); the call itself never allocates. */
+ * have been reserved (lgc_reserve); the call itself never allocates.  The
+ * stacks of Table I / Table II run as one launch that keeps them on chip, and
+ * use the reserved scratch only in place (latent overlapping vals, in
+ * lgc_decode rec overlapping latent) or if a weight is not finite. */
 lgc_status lgc_encode(lgc_ctx *ctx, const lgc_ae *ae, const float *vals, uint64_t k, int batch,
                       float *latent, void *stream);
 
@@ -310,8 +313,7 @@ lgc_status lgc_average(lgc_ctx *ctx, const float *x, uint64_t len, int batch, fl
  *   ae  (nullable): the activation buffers lgc_encode / lgc_decode /
  *        lgc_decode_innovation need with this autoencoder for inputs of up to
  *        k values per node and up to `batch` nodes (the largest intermediate
- *        tensor of either stack, twice; nothing for stacks that run as one
- *        launch);
+ *        tensor of either stack, twice);
  *   seg (nullable): the per-layer thresholds and the candidate list of
  *        lgc_topk_segmented / lgc_accumulate_topk_segmented with this plan.
  * A later reservation only ever grows the buffers, so one call per

@@ -841,6 +841,12 @@ static lgc_status check_ae_call(lgc_ctx *ctx, const lgc_ae *ae, const void *a, c
     return LGC_OK;
 }
 
+// Do two ranges of floats overlap?  The blocks of a stack that runs as one launch store outputs while others still read
+// inputs, so a call in place takes one launch per layer, of which the last reads activation scratch only.
+static bool overlap(const float *a, uint64_t na, const float *b, uint64_t nb) {
+    return (uintptr_t)a < (uintptr_t)(b + nb) && (uintptr_t)b < (uintptr_t)(a + na);
+}
+
 static lgc_status run_encode(lgc_ctx *ctx, const lgc_ae *ae, const float *vals, uint64_t k, int batch,
                              float *latent, void *stream) {
     lgc_status s = check_ae_call(ctx, ae, vals, latent, k, batch);
@@ -867,7 +873,8 @@ static lgc_status run_encode(lgc_ctx *ctx, const lgc_ae *ae, const float *vals, 
     if (need > ctx->act_floats)
         return fail(ctx, LGC_EINVAL, "lgc_encode: activation scratch for k = %llu, batch = %d not reserved: call "
                                      "lgc_reserve(ctx, ae, k, batch, NULL) once beforehand", (unsigned long long)k, batch);
-    if (launch_encoder_fused(vals, latent, ae->enc_dev.data(), (int)nl, len.data(), batch, ae->slope, ctx->cus, st)) {
+    if (!overlap(vals, k * batch, latent, (uint64_t)batch * ae->enc[nl - 1].c_out * len[nl]) &&
+        launch_encoder_fused(vals, latent, ae->enc_dev.data(), (int)nl, len.data(), batch, ae->slope, ctx->cus, st)) {
         hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e1));
         return LGC_OK;
@@ -964,7 +971,8 @@ static lgc_status run_decode(lgc_ctx *ctx, const lgc_ae *ae, const float *latent
     if (need > ctx->act_floats)
         return fail(ctx, LGC_EINVAL, "lgc_decode: activation scratch for k = %llu, batch = %d not reserved: call "
                                      "lgc_reserve(ctx, ae, k, batch, NULL) once beforehand", (unsigned long long)k, batch);
-    if (!innov && launch_decoder_fused(latent, rec, ae->dec_dev.data(), (int)nl, in_len, out_len.data(), batch, ae->slope, st)) {
+    if (!innov && !overlap(latent, (uint64_t)batch * ae->dec[0].c_in * in_len, rec, k * batch) &&
+        launch_decoder_fused(latent, rec, ae->dec_dev.data(), (int)nl, in_len, out_len.data(), batch, ae->slope, st)) {
         hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e1));
         return LGC_OK;

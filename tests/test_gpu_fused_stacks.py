@@ -105,3 +105,22 @@ def test_weights_that_are_not_finite(B, oracle):
     assert_near(lat, ol, "latent")
     assert_near(rec, orec, "reconstruction")
     ae.close()
+
+
+@pytest.mark.parametrize("k,batch", [(600, 2), (20_000, 4)])
+def test_in_place(B, oracle, k, batch):
+    # the output over the input: every value of it is stored after the last read of what it replaces
+    ae, enc, dec, host = stacks(B)
+    x = np.random.default_rng(k).laplace(0, 0.3, (batch, k)).astype(np.float32)
+    ctx = B.Context(k, k, batch)
+    B.lgc_reserve(ctx, ae, k, batch)
+    length = B.lgc_latent_len(ae, k)
+    buf = torch.from_numpy(x).cuda()
+    lat = buf.view(-1)[:batch * length].view(batch, length)
+    B.lgc_encode(ctx, ae, buf, lat)
+    ol = np.stack([oracle.encode(row, enc, host[0], host[1], slope=0.01) for row in x])
+    assert_near(lat.cpu().numpy(), ol.reshape(batch, -1), "latent")
+    B.lgc_decode(ctx, ae, lat, buf)
+    orec = np.stack([oracle.decode(z, k, enc, dec, host[2], host[3], slope=0.01) for z in ol])
+    assert_near(buf.cpu().numpy(), orec, "reconstruction")
+    ctx.close(); ae.close()

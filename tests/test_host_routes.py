@@ -1,0 +1,108 @@
+"""What the library's host side launches and allocates for a call, read from a HIP runtime that only records
+(recording_hip.cpp): no GPU, no tensor, any size."""
+import ctypes as C
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+if ROOT not in sys.path:
+    sys.path.insert(0, ROOT)
+
+u64, p = C.c_uint64, C.c_void_p
+PAPER = ([(1, 64, 3, 2), (64, 128, 3, 2), (128, 256, 3, 2), (256, 64, 3, 2), (64, 4, 1, 1)],
+         [(4, 4, 3, 1), (4, 32, 3, 2), (32, 64, 3, 2), (64, 128, 3, 2), (128, 32, 3, 2), (32, 1, 1, 1)])
+
+
+class Layer(C.Structure):
+    _fields_ = [("c_in", C.c_int32), ("c_out", C.c_int32), ("ksize", C.c_int32), ("stride", C.c_int32)]
+
+
+class Host:
+    """The library over the recording runtime."""
+
+    def __init__(self, fake, library):
+        self.fake, self.lib = C.CDLL(fake, mode=C.RTLD_GLOBAL), C.CDLL(library)
+        self.fake.recorded.restype = C.c_char_p
+
+    def log(self):
+        """[("malloc", bytes) or ("launch", kernel, grid)] since the last call."""
+        out = []
+        for line in self.fake.recorded().decode().splitlines():
+            what, *rest = line.split()
+            if what == "malloc":
+                out.append((what, int(rest[0])))
+            else:   # _ZN3lgc15k_encoder_fusedI...: the name is as long as its number says
+                digits = rest[0][rest[0].index("lgc") + 3:]
+                n = "".join(c for c in digits[:3] if c.isdigit())
+                out.append((what, digits[len(n):len(n) + int(n)], [int(x) for x in rest[1:]]))
+        return out
+
+    def kernels(self):
+        return [x[1] for x in self.log() if x[0] == "launch"]
+
+    def ctx(self, max_n, max_k, batch):
+        h = p()
+        assert self.lib.lgc_create(C.byref(h), 0, u64(max_n), u64(max_k), batch) == 0
+        return h
+
+    def autoencoder(self, enc, dec):
+        weights = (p * 64)(*[1 << 40] * 64)
+        h = p()
+        assert self.lib.lgc_ae_create(C.byref(h), 0, len(enc), (Layer * len(enc))(*enc), len(dec), (Layer * len(dec))(*dec), C.c_float(0.01),
+                                      weights, weights, weights, weights) == 0
+        return h
+
+    def encode(self, ctx, ae, vals, k, batch, latent):
+        return self.lib.lgc_encode(ctx, ae, p(vals), u64(k), batch, p(latent), None)
+
+    def decode(self, ctx, ae, latent, k, batch, rec):
+        return self.lib.lgc_decode(ctx, ae, p(latent), u64(k), batch, p(rec), None)
+
+
+def paper_stacks_in_place(h):
+    k, batch = 1000, 2
+    ctx, ae = h.ctx(k, k, batch), h.autoencoder(*PAPER)
+    assert h.lib.lgc_reserve(ctx, ae, u64(k), batch, None) == 0
+    latent = 4 * batch * 4 * 63             # bytes: 4 channels of 63 positions
+    at = 1 << 30
+    out = {}
+    h.log()
+    for name, offset in (("apart", 4 * k * batch), ("same", 0), ("last", 4 * k * batch - 4), ("before", -latent), ("into", 4 - latent)):
+        assert h.encode(ctx, ae, at, k, batch, at + offset) == 0
+        out["encode " + name] = h.kernels()
+    for name, offset in (("apart", latent), ("same", 0), ("last", latent - 4), ("before", -4 * k * batch), ("into", 4 - 4 * k * batch)):
+        assert h.decode(ctx, ae, at, k, batch, at + offset) == 0
+        out["decode " + name] = h.kernels()
+    return out
+
+
+@pytest.fixture(scope="module")
+def answers(tmp_path_factory):
+    """Every scenario (a function above, by name), run in one process of its own."""
+    from paper_2103_08870_amd import build
+    library = build.build(force=False)
+    fake = str(tmp_path_factory.mktemp("hip") / "librecording_hip.so")
+    r = subprocess.run([build._hipcc(), "-O1", "-std=c++17", "-shared", "-fPIC", "--offload-arch=gfx950", os.path.join(HERE, "recording_hip.cpp"), "-o", fake],
+                       capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), fake, library], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
+    return json.loads(r.stdout)
+
+
+def test_paper_stacks_in_place_go_layer_by_layer(answers):
+    # a stack in one launch writes outputs while other blocks still read inputs; the last of several launches does not
+    for name, kernels in answers["paper_stacks_in_place"].items():
+        fused = kernels in (["k_encoder_fused"], ["k_decoder_fused"])
+        assert fused == (name.split()[1] in ("apart", "before")), (name, kernels)
+        assert fused or len(kernels) >= 3, (name, kernels)
+
+
+if __name__ == "__main__":
+    host = Host(sys.argv[1], sys.argv[2])
+    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place,)}))
