@@ -19,8 +19,9 @@
 // matrix cores are busy 63 % of the cycles (encoder) and 46 % (decoder) at a clock that drops to 1.9 GHz.
 // The split is exact only for finite values; an Inf would meet products of both signs.  Such a
 // value leaves a NaN among its parts, which makes every output it reaches a NaN, and a block with an output that is
-// not finite redoes its outputs in plain fp32 (plain_encoder / plain_decoder), with the term order of the
-// per-layer kernels.
+// not finite redoes its outputs in plain fp32 on the fp32 matrix cores.  Every block doing so: 4 nodes x 25 600 values,
+// encoder 32 -> 96 us, decoder 26 -> 53 us; 8 x 67 000: 146 -> 467 and 92 -> 231 us (one fp32-MFMA launch per layer:
+// 83, 59, 270 and 194 us; one position after the other on the vector units: 3.3, 1.6, 16 and 8 ms).
 //
 // Operand layout of v_mfma_f32_32x32x16_bf16: lane l supplies A[i = l % 32][k = 8 (l / 32) + 0..7] and
 // B[k = 8 (l / 32) + 0..7][j = l % 32]; result r of 16 is C[i = 8 (r / 4) + 4 (l / 32) + r % 4][j = l % 32].  Here
@@ -242,49 +243,60 @@ __device__ __forceinline__ void conv_mma(acc16 (&acc)[MT][NT], Fragments<MT, AHE
         for (int j = 0; j < NT; ++j) acc[i][j] += cross[i][j];
 }
 
-// The latent positions [p0, p0 + count) in plain fp32, one after the other (buf: 2700 floats).
-template <int C1, int C2, int C3, int C4, int C5>
-__device__ __forceinline__ void plain_encoder(const float *x, float *out, const EncoderDev &w, float *buf, const long long p0,
-                                           const int count, const long long l0, const long long l1, const long long l2,
-                                           const long long l3, const long long l4, const float slope) {
-    float *h1 = buf, *h2 = h1 + 15 * C1, *h3 = h2 + 7 * C2, *h4 = h3 + 3 * C3;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    auto layer = [&](const float *in, float *o, const float *wt, const float *bias, int c_in, int c_out, int n, long long q0, long long len) {
-        for (int i = tid; i < n * c_out; i += nt) {
-            const int j = i / c_out, co = i % c_out;
-            float a = bias[co];
-#pragma unroll 1
-            for (int ci = 0; ci < c_in; ++ci)
-                for (int t = 0; t < 3; ++t) a = fmaf(wt[((size_t)co * c_in + ci) * 3 + t], in[(2 * j + t) * c_in + ci], a);
-            o[i] = q0 + j >= 0 && q0 + j < len ? leaky_f(a, slope) : 0.f;
-        }
-        __syncthreads();
-    };
-#pragma unroll 1
-    for (int r = 0; r < count; ++r) {
-        const long long p = p0 + r;
-        for (int i = tid; i < 15 * C1; i += nt) {
-            const int j = i / C1, co = i % C1;
-            const long long q = 8 * p - 7 + j;
-            float a = w.b1[co];
-            for (int t = 0; t < 3; ++t) {
-                const long long e = 2 * q - 1 + t;
-                a = fmaf(w.w1[co * 3 + t], e >= 0 && e < l0 ? x[e] : 0.f, a);
-            }
-            h1[i] = q >= 0 && q < l1 ? leaky_f(a, slope) : 0.f;
-        }
-        __syncthreads();
-        layer(h1, h2, w.w2, w.b2, C1, C2, 7, 4 * p - 3, l2);
-        layer(h2, h3, w.w3, w.b3, C2, C3, 3, 2 * p - 1, l3);
-        layer(h3, h4, w.w4, w.b4, C3, C4, 1, p, l4);
-        if (tid < C5) {
-            float a = w.b5[tid];
-#pragma unroll 1
-            for (int ci = 0; ci < C4; ++ci) a = fmaf(w.w5[tid * C4 + ci], h4[ci], a);
-            out[(size_t)tid * l4 + p] = a;
-        }
-        __syncthreads();
+// The redo in plain fp32, for blocks with a value that the split cannot carry: the same tiles and windows on the fp32 matrix
+// cores (v_mfma_f32_32x32x2_f32: lane l supplies A[i = l % 32][k = l / 32] and B[k = l / 32][j = l % 32], results as above),
+// activations as rows of fp32 in the same LDS.  A lane's half takes four of eight channels in turn, so that its operands are 16-byte reads.
+__device__ __forceinline__ acc16 mma_fp32(const float a, const float b, const acc16 &c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
+}
+
+constexpr int row_floats(int c) { return c + 4; }
+
+// acc += one tile: w = the lane's output channel [CI][3], b = its row for tap 0, `odd` floats before the odd positions',
+// both from the half's first channel on
+template <int CI>
+__device__ __forceinline__ void conv_fp32(acc16 &acc, const float *__restrict__ w, const float *b, const int odd) {
+#pragma unroll 2
+    for (int c = 0; c < CI; c += 8) {
+        const f4v x[3] = {*(const f4v *)(b + c), *(const f4v *)(b + odd + c), *(const f4v *)(b + row_floats(CI) + c)};
+        f4v y[3];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) y[t] = *(const f4v *)(w + 3 * c + 4 * t);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int t = 0; t < 3; ++t) acc = mma_fp32(y[(3 * e + t) / 4][(3 * e + t) % 4], x[t][e], acc);
     }
+}
+
+// One kernel-3 / stride-2 layer for N positions from q0 on, in place in buf; W wavefronts share the tiles out.  The outputs:
+// even positions, then (after N / 2 + 1 rows) odd ones.
+template <int CI, int CO, int N, int W>
+__device__ __forceinline__ void layer_fp32(float *buf, const float *__restrict__ wt, const float *__restrict__ bias, const int wave,
+                                           const long long q0, const long long len, const float slope) {
+    constexpr int kTiles = (CO / 32) * ((N + 31) / 32), kMine = (kTiles + W - 1) / W, R = row_floats(CI), S = row_floats(CO);
+    const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+    acc16 acc[kMine];
+#pragma unroll
+    for (int m = 0; m < kMine; ++m) {
+        const int tile = wave + m * W, co0 = tile % (CO / 32) * 32, i = tile / (CO / 32) * 32 + col;
+        if (tile < kTiles) {                       // wave-uniform
+            acc[m] = bias16(bias, co0, half);
+            conv_fp32<CI>(acc[m], wt + (size_t)(co0 + col) * CI * 3 + 12 * half, buf + (i < N ? i : N - 1) * R + 4 * half, (N + 1) * R);
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < kMine; ++m) {
+        const int tile = wave + m * W, co0 = tile % (CO / 32) * 32, i = tile / (CO / 32) * 32 + col;
+        if (tile < kTiles && i < N) {
+            float *row = buf + ((i & 1) ? (N / 2 + 1) * S : 0) + (i >> 1) * S + co0 + 4 * half;
+            const bool valid = q0 + i >= 0 && q0 + i < len;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) row[8 * (r >> 2) + (r & 3)] = valid ? leaky_f(acc[m][r], slope) : 0.f;
+        }
+    }
+    __syncthreads();
 }
 
 }  // namespace
@@ -302,7 +314,8 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
     constexpr int kBytes = kBytes1 > kBytes2 ? (kBytes1 > kBytes3 ? kBytes1 : kBytes3) : (kBytes2 > kBytes3 ? kBytes2 : kBytes3);
     constexpr int kSplit = W / (C4 / 32);                 // conv4: wavefronts that share a tile, each a run of its steps
     static_assert(C1 % 16 == 0 && C2 % 32 == 0 && C3 % 32 == 0 && C4 % 32 == 0 && N3 % 32 == 0 && N4 <= 32 && C5 <= 4, "tiles");
-    static_assert(kBytes >= (15 * C1 + 7 * C2 + 3 * C3 + C4) * 4, "plain_encoder's buffer");
+    static_assert(row_floats(C1) * 4 <= R1 && row_floats(C2) * 4 <= R2 && row_floats(C3) * 4 <= R3 && 2 * (N4 / 2 + 1) * row_floats(C4) * 4 <= kBytes,
+                  "rows of fp32 take no more room");
     __shared__ __align__(16) unsigned char buf[kBytes];
     __shared__ float xs[4 * N2 + 4];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -317,23 +330,28 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
     }
     __syncthreads();
 
-    // conv1: a wavefront takes 64 positions x 8 channels at a time (weights wave-uniform)
+    // conv1: a wavefront takes 64 positions x 8 channels at a time (weights wave-uniform); put(position, group of 8 channels, values)
+    auto conv1 = [&](auto put) {
 #pragma unroll 1
-    for (int unit = wave; unit < (C1 / 8) * (2 * N2 / 64); unit += W) {
-        const int o8 = unit % (C1 / 8), i = (unit / (C1 / 8)) * 64 + lane;
-        const long long q = 8 * p0 - 7 + i;
-        const bool valid = q >= 0 && q < (long long)l1;
-        const float x0 = xs[2 * i], x1 = xs[2 * i + 1], x2 = xs[2 * i + 2];
-        float y[8];
+        for (int unit = wave; unit < (C1 / 8) * (2 * N2 / 64); unit += W) {
+            const int o8 = unit % (C1 / 8), i = (unit / (C1 / 8)) * 64 + lane;
+            const long long q = 8 * p0 - 7 + i;
+            const uint32_t valid = q >= 0 && q < (long long)l1 ? ~0u : 0u;   // (a mask: a choice becomes a branch around the loads of every channel)
+            const float x0 = xs[2 * i], x1 = xs[2 * i + 1], x2 = xs[2 * i + 2];
+            float y[8];
 #pragma unroll
-        for (int c = 0; c < 8; ++c) {
-            const float *wc = w.w1 + (o8 * 8 + c) * 3;
-            float a = w.b1[o8 * 8 + c];
-            a = fmaf(wc[0], x0, a);
-            a = fmaf(wc[1], x1, a);
-            a = fmaf(wc[2], x2, a);
-            y[c] = valid ? leaky_f(a, slope) : 0.f;
+            for (int c = 0; c < 8; ++c) {
+                const float *wc = w.w1 + (o8 * 8 + c) * 3;
+                float a = w.b1[o8 * 8 + c];
+                a = fmaf(wc[0], x0, a);
+                a = fmaf(wc[1], x1, a);
+                a = fmaf(wc[2], x2, a);
+                y[c] = __uint_as_float(__float_as_uint(leaky_f(a, slope)) & valid);
+            }
+            put(i, o8, y);
         }
+    };
+    conv1([&](const int i, const int o8, const float (&y)[8]) {
         u4v h, m, l;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -345,7 +363,7 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
         *(u4v *)row = h;
         *(u4v *)(row + 2 * C1) = m;
         *(u4v *)(row + 4 * C1) = l;
-    }
+    });
 
     {   // conv2: C2 / 32 channel tiles x N2 / 32 position tiles
         constexpr int kM = C2 / 32, kNW = W / kM, NT = N2 / 32 / kNW, kSteps = 3 * C1 / 16, kAhead = 2;
@@ -461,8 +479,22 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
         if (mine) out[(size_t)c * l4 + p0 + p] = z;
         return;
     }
-    const long long left = (long long)l4 - p0;
-    plain_encoder<C1, C2, C3, C4, C5>(x, out, w, (float *)buf, p0, left < P ? (int)left : P, l0, l1, l2, l3, l4, slope);
+    float *f = (float *)buf;
+    conv1([&](const int i, const int o8, const float (&y)[8]) {
+        float *row = f + ((i & 1) ? (N2 + 1) * row_floats(C1) : 0) + (i >> 1) * row_floats(C1) + o8 * 8;
+        *(f4v *)row = (f4v){y[0], y[1], y[2], y[3]};
+        *(f4v *)(row + 4) = (f4v){y[4], y[5], y[6], y[7]};
+    });
+    __syncthreads();
+    layer_fp32<C1, C2, N2, W>(f, w.w2, w.b2, wave, 4 * p0 - 3, l2, slope);
+    layer_fp32<C2, C3, N3, W>(f, w.w3, w.b3, wave, 2 * p0 - 1, l3, slope);
+    layer_fp32<C3, C4, N4, W>(f, w.w4, w.b4, wave, p0, l4, slope);
+    if (mine) {
+        const float *row = f + ((p & 1) ? (N4 / 2 + 1) * row_floats(C4) : 0) + (p >> 1) * row_floats(C4);
+        z = w.b5[c];
+        for (int ci = 0; ci < C4; ++ci) z = fmaf(w.w5[c * C4 + ci], row[ci], z);
+        out[(size_t)c * l4 + p0 + p] = z;
+    }
 }
 
 // ---- decoder ---------------------------------------------------------------------------------------
@@ -490,67 +522,37 @@ __device__ __forceinline__ void load_b(u4v (&r)[3], const unsigned char *b, cons
     for (int p = 0; p < 3; ++p) r[p] = *(const u4v *)(b + p * 2 * C + at);
 }
 
-// The outputs of the latent positions [p0, p0 + count) in plain fp32, one position after the other.
-template <int D0, int D1, int D2, int D3, int D4, int D5>
-__device__ __forceinline__ void plain_decoder(const float *z, float *out, const DecoderDev &w, float *buf, const long long p0,
-                                           const int count, const long long lz, const long long l2, const long long l3,
-                                           const long long l4, const long long l5, const float slope) {
-    float *h1 = buf, *h2 = h1 + 2 * D1, *h3 = h2 + 3 * D2, *h4 = h3 + 5 * D3, *h5 = h4 + 9 * D4;
-    const int tid = threadIdx.x, nt = blockDim.x;
-    // n outputs from 2 m0 on, inputs from m0 on
-    auto layer = [&](const float *in, float *o, const float *wt, const float *bias, int c_in, int c_out, int n, long long q0, long long len) {
-        for (int i = tid; i < n * c_out; i += nt) {
-            const int j = i / c_out, co = i % c_out, m = j >> 1;
-            float a = bias[co];
+// The even and the odd outputs of a transposed layer in plain fp32, CI input channels from row b (the lane's input m; m + 1
+// lies R floats on): w = the lane's output channel of [CI][CO][3], both from the half's first channel on
+template <int CI, int CO, int R>
+__device__ __forceinline__ void up_fp32(acc16 &even, acc16 &odd, const float *__restrict__ w, const float *b) {
 #pragma unroll 1
-            for (int ci = 0; ci < c_in; ++ci) {
-                const float *wc = wt + ((size_t)ci * c_out + co) * 3;
-                if (j & 1) {
-                    a = fmaf(wc[0], in[(m + 1) * c_in + ci], a);
-                    a = fmaf(wc[2], in[m * c_in + ci], a);
-                } else {
-                    a = fmaf(wc[1], in[m * c_in + ci], a);
-                }
-            }
-            o[i] = q0 + j < len ? leaky_f(a, slope) : 0.f;
+    for (int c = 0; c < CI; c += 8) {
+        const f4v x0 = *(const f4v *)(b + c), x1 = *(const f4v *)(b + R + c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const float *wc = w + (size_t)(c + e) * CO * 3;
+            odd = mma_fp32(wc[2], x0[e], odd);
+            even = mma_fp32(wc[1], x0[e], even);
+            odd = mma_fp32(wc[0], x1[e], odd);
         }
-        __syncthreads();
-    };
-#pragma unroll 1
-    for (int r = 0; r < count; ++r) {
-        const long long p = p0 + r;
-        for (int i = tid; i < 2 * D1; i += nt) {
-            const int j = i / D1, co = i % D1;
-            float a = w.b1[co];
-            for (int ci = 0; ci < D0; ++ci)
-                for (int t = 0; t < 3; ++t) {
-                    const long long e = p + j + 1 - t;
-                    a = fmaf(w.w1[(ci * D1 + co) * 3 + t], e >= 0 && e < lz ? z[(size_t)ci * lz + e] : 0.f, a);
-                }
-            h1[i] = p + j < lz ? leaky_f(a, slope) : 0.f;
-        }
-        __syncthreads();
-        layer(h1, h2, w.w2, w.b2, D1, D2, 3, 2 * p, l2);
-        layer(h2, h3, w.w3, w.b3, D2, D3, 5, 4 * p, l3);
-        layer(h3, h4, w.w4, w.b4, D3, D4, 9, 8 * p, l4);
-        layer(h4, h5, w.w5, w.b5, D4, D5, 16, 16 * p, l5);
-        if (tid < 16 && 16 * p + tid < l5) {
-            float a = w.b6[0];
-#pragma unroll 1
-            for (int ci = 0; ci < D5; ++ci) a = fmaf(w.w6[ci], h5[tid * D5 + ci], a);
-            out[16 * p + tid] = a;
-        }
-        __syncthreads();
     }
+}
+
+// One result tile with the non-linearity as fp32: `row` is the lane's position
+__device__ __forceinline__ void store_fp32(float *row, const int co0, const int half, const acc16 &acc, const float slope, const bool valid) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) row[co0 + 8 * (r >> 2) + 4 * half + (r & 3)] = valid ? leaky_f(acc[r], slope) : 0.f;
 }
 
 }  // namespace
 
 // T latent positions per block of four wavefronts.  Local numbering from 1, 2, 4, 8 and 16 p0 on: T + 1 outputs of
 // deconv1, 2T + 1 of deconv2, 4T + 1 of deconv3, 8T + 1 of deconv4 and 16T of deconv5.  deconv4's outputs are made
-// and consumed in two runs of D4 / 2 channels, so that two blocks fit a compute unit's LDS.
+// and consumed in two runs of D4 / 2 channels, so that two blocks fit a compute unit's LDS, and its registers: the bound
+// of two wavefronts per SIMD keeps the redo from taking more.
 template <int D0, int D1, int D2, int D3, int D4, int D5, int T>
-__global__ __launch_bounds__(256) void k_decoder_fused(const float *__restrict__ z, float *__restrict__ out, DecoderDev w,
+__global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restrict__ z, float *__restrict__ out, DecoderDev w,
                                                        uint32_t lz, uint32_t l2, uint32_t l3, uint32_t l4, uint32_t l5,
                                                        float slope) {
     constexpr int M3 = 2 * (T + 1), M4 = 4 * (T + 1), M5 = 8 * (T + 1);   // tile widths: input positions of deconv3, 4, 5
@@ -559,7 +561,7 @@ __global__ __launch_bounds__(256) void k_decoder_fused(const float *__restrict__
     constexpr int kBytesA = (M5 + 1) * R4, kBytesB = (M4 + 1) * R3;
     static_assert(M3 == 32 && M4 == 64 && M5 == 128 && D2 % 16 == 0 && D3 == 64 && CH == 64 && D5 == 32, "tiles");
     static_assert((M3 + 1) * R2 <= kBytesA && 4 * 2 * 1024 * 4 <= kBytesA, "region A");
-    static_assert((2 * D1 + 3 * D2 + 5 * D3 + 9 * D4 + 16 * D5) * 4 <= kBytesA, "plain_decoder's buffer");
+    static_assert(row_floats(D2) * 4 <= R2 && row_floats(D3) * 4 <= R3 && row_floats(CH) * 4 <= R4, "rows of fp32 take no more room");
     __shared__ __align__(16) unsigned char bufA[kBytesA];   // deconv2's outputs, then deconv4's run by run
     __shared__ __align__(16) unsigned char bufB[kBytesB];   // deconv3's outputs
     __shared__ float zs[D0 * (T + 3)], h1[D1 * (T + 1)];
@@ -588,11 +590,10 @@ __global__ __launch_bounds__(256) void k_decoder_fused(const float *__restrict__
         h1[i] = p0 + j < (long long)lz ? leaky_f(a, slope) : 0.f;
     }
     __syncthreads();
-    {   // deconv2: thread = position x group of D2 / 8 channels
-        constexpr int kCh = D2 / 8;
+    constexpr int kCh = D2 / 8;
+    auto deconv2 = [&](float (&y)[kCh]) {   // thread = position x group of D2 / 8 channels
         const int j = tid & 31, cg = tid >> 5, m = j >> 1;
         const bool odd = j & 1, valid = 2 * p0 + j < (long long)l2 && j < 2 * T + 1;
-        float y[kCh];
 #pragma unroll
         for (int c = 0; c < kCh; ++c) y[c] = w.b2[cg * kCh + c];
 #pragma unroll
@@ -605,11 +606,17 @@ __global__ __launch_bounds__(256) void k_decoder_fused(const float *__restrict__
                 y[c] = odd ? o : e;
             }
         }
-        unsigned char *row = bufA + j * R2 + cg * kCh * 2;
+#pragma unroll
+        for (int c = 0; c < kCh; ++c) y[c] = valid ? leaky_f(y[c], slope) : 0.f;
+    };
+    {
+        float y[kCh];
+        deconv2(y);
+        unsigned char *row = bufA + (tid & 31) * R2 + (tid >> 5) * kCh * 2;
 #pragma unroll
         for (int c = 0; c < kCh; c += 2) {
             uint32_t h, m_, l;
-            split2(valid ? leaky_f(y[c], slope) : 0.f, valid ? leaky_f(y[c + 1], slope) : 0.f, h, m_, l);
+            split2(y[c], y[c + 1], h, m_, l);
             *(uint32_t *)(row + 2 * c) = h;
             *(uint32_t *)(row + 2 * D2 + 2 * c) = m_;
             *(uint32_t *)(row + 4 * D2 + 2 * c) = l;
@@ -748,8 +755,46 @@ __global__ __launch_bounds__(256) void k_decoder_fused(const float *__restrict__
         if (mine) out[16 * p0 + i] = y;
         return;
     }
-    const long long left = (long long)lz - p0;
-    plain_decoder<D0, D1, D2, D3, D4, D5>(z, out, w, (float *)bufA, p0, left < T ? (int)left : T, lz, l2, l3, l4, l5, slope);
+    float *fa = (float *)bufA, *fb = (float *)bufB;
+    int hf = half;
+    asm("" : "+v"(hf));   // the same number, unknown to the compiler: the values loaded above are not kept in registers for the redo
+    {
+        float y[kCh];
+        deconv2(y);
+#pragma unroll
+        for (int c = 0; c < kCh; ++c) fa[(tid & 31) * row_floats(D2) + (tid >> 5) * kCh + c] = y[c];
+    }
+    __syncthreads();
+    if (wave < D3 / 32) {   // deconv3: wavefront = channel tile
+        acc16 even = bias16(w.b3, wave * 32, hf), odd = even;
+        up_fp32<D2, D3, row_floats(D2)>(even, odd, w.w3 + (4 * hf * D3 + wave * 32 + col) * 3, fa + col * row_floats(D2) + 4 * hf);
+        const int j = 2 * col;
+        store_fp32(fb + j * row_floats(D3), wave * 32, hf, even, slope, 4 * p0 + j < (long long)l3 && j < 4 * T + 1);
+        store_fp32(fb + (j + 1) * row_floats(D3), wave * 32, hf, odd, slope, 4 * p0 + j + 1 < (long long)l3 && j + 1 < 4 * T + 1);
+    }
+    acc16 e = bias16(w.b5, 0, hf), o = e;   // deconv5: wavefront = position tile
+#pragma unroll 1
+    for (int run = 0; run < 2; ++run) {
+        const int co0 = run * CH + (wave & 1) * 32, m0 = (wave >> 1) * 32 + col, j = 2 * m0;   // deconv4: channel tile x position tile
+        acc16 even = bias16(w.b4, co0, hf), odd = even;
+        __syncthreads();
+        up_fp32<D3, D4, row_floats(D3)>(even, odd, w.w4 + (4 * hf * D4 + co0 + col) * 3, fb + m0 * row_floats(D3) + 4 * hf);
+        store_fp32(fa + j * row_floats(CH), (wave & 1) * 32, hf, even, slope, 8 * p0 + j < (long long)l4 && j < 8 * T + 1);
+        store_fp32(fa + (j + 1) * row_floats(CH), (wave & 1) * 32, hf, odd, slope, 8 * p0 + j + 1 < (long long)l4 && j + 1 < 8 * T + 1);
+        __syncthreads();
+        up_fp32<CH, D5, row_floats(CH)>(e, o, w.w5 + ((run * CH + 4 * hf) * D5 + col) * 3, fa + (wave * 32 + col) * row_floats(CH) + 4 * hf);
+    }
+    se = 0.f; so = 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const float wv = w.w6[(r >> 2) * 8 + hf * 4 + (r & 3)];
+        se = fmaf(wv, leaky_f(e[r], slope), se);
+        so = fmaf(wv, leaky_f(o[r], slope), so);
+    }
+    se += __shfl_xor(se, 32, 64);
+    so += __shfl_xor(so, 32, 64);
+    const int m1 = wave * 32 + col, i1 = 2 * m1 + hf;
+    if (m1 < 8 * T && 16 * p0 + i1 < (long long)l5) out[16 * p0 + i1] = w.b6[0] + (hf ? so : se);
 }
 
 // ---- launchers ---------------------------------------------------------------------------------------

@@ -1,5 +1,5 @@
 """The stacks of Table I / Table II as one launch each (three-part bf16 products in fp32 precision) against the oracle:
-lengths at the edges of a block's run of 15 latent positions (240 values), and inputs the split cannot represent."""
+lengths at the edges of a block's run of 15 or 31 latent positions (240, 496 values), inputs the split cannot represent, calls in place."""
 import numpy as np
 import pytest
 import torch
@@ -57,7 +57,9 @@ def assert_near(got, want, what):
     assert err <= REL_L2, (what, err)
 
 
-@pytest.mark.parametrize("k,batch", [(2, 1), (15, 1), (16, 3), (239, 1), (240, 2), (241, 1), (256, 1), (480, 1), (497, 3)])
+# the last three take 31 positions per block: a last block of 31, of 1 and of 2 positions
+@pytest.mark.parametrize("k,batch", [(2, 1), (15, 1), (16, 3), (239, 1), (240, 2), (241, 1), (256, 1), (480, 1), (497, 3),
+                                     (496 * 20, 7), (496 * 20 + 1, 7), (496 * 20 + 17, 7)])
 def test_lengths_at_the_edges_of_a_block(B, oracle, k, batch):
     ae, enc, dec, host = stacks(B)
     x = np.random.default_rng(k).laplace(0, 0.3, (batch, k)).astype(np.float32)
@@ -68,29 +70,62 @@ def test_lengths_at_the_edges_of_a_block(B, oracle, k, batch):
 
 
 # Positive weights: an Inf stays one Inf all the way (weights of both signs would turn it into NaN at once), so the
-# values that bf16 parts cannot carry have one right answer.  The largest finite values round to Inf in bf16.
+# values that bf16 parts cannot carry have one right answer.  The largest finite values round to Inf in bf16.  Blocks of
+# 15 latent positions (600 values), and of 31 where there are enough of them (7 nodes x 10 000); the values sit inside a
+# block, where two blocks' windows overlap, and in the last, partly filled block.
+@pytest.mark.parametrize("k,batch", [(600, 2), (10_000, 7)])
 @pytest.mark.parametrize("special", [np.inf, np.nan, 3.4e38, 1e-30])
-def test_values_that_the_split_cannot_carry(B, oracle, special):
+def test_values_that_the_split_cannot_carry(B, oracle, special, k, batch):
     def change(a, which):
         if which % 2:
             return np.zeros_like(a) if special == 1e-30 else np.abs(a)   # biases
         return np.abs(a) * np.float32(0.05)
     ae, enc, dec, host = stacks(B, change)
-    k = 600
     rng = np.random.default_rng(5)
-    x = np.abs(rng.normal(0, 1, (2, k))).astype(np.float32)
-    z = np.abs(rng.normal(0, 1, (2, 4 * 38))).astype(np.float32)
+    length = -(-k // 16)
+    x = np.abs(rng.normal(0, 1, (batch, k))).astype(np.float32)
+    z = np.abs(rng.normal(0, 1, (batch, 4, length))).astype(np.float32)
     if special == 1e-30:
         x *= np.float32(special); z *= np.float32(special)
     else:
-        x[1, 300] = special
-        z[1, 2 * 38 + 20] = special
+        x[1, [300, k - 1]] = special
+        z[1, 2, [20, length - 1]] = special
+        if batch > 2:
+            x[3, [16 * 31 * 3 - 8, 16 * 31 * 7]] = special
+            z[3, 0, [15 * 4, 15 * 9 - 1]] = special
     lat, ol, rec, orec = both_ways(B, oracle, ae, enc, dec, host, x, z)
     assert_near(lat, ol, ("latent", special))
     assert_near(rec, orec, ("reconstruction", special))
     if not np.isfinite(special):
         assert (~np.isfinite(ol)).any() and np.isfinite(ol[0]).all()   # the case is what it says
     ae.close()
+
+
+def test_values_that_are_not_finite_cost_no_more_than_fp32(B):
+    # the redo runs on the matrix cores (measured: 3 times the ordinary call where every block redoes); position by
+    # position on the vector units it took 100 times as long
+    k, batch = 25_600, 4
+    ae, _, _, _ = stacks(B)
+    ctx = B.Context(k, k, batch)
+    B.lgc_reserve(ctx, ae, k, batch)
+    lat, rec = torch.empty((batch, B.lgc_latent_len(ae, k)), device="cuda"), torch.empty((batch, k), device="cuda")
+
+    def milliseconds(x):
+        start, stop = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        for timed in (False, True):
+            if timed:
+                start.record()
+            for _ in range(20):
+                B.lgc_encode(ctx, ae, x, lat)
+                B.lgc_decode(ctx, ae, lat, rec)
+        stop.record()
+        torch.cuda.synchronize()
+        return start.elapsed_time(stop)
+
+    usual = milliseconds(torch.full((batch, k), 0.5, device="cuda"))
+    nan = milliseconds(torch.full((batch, k), float("nan"), device="cuda"))
+    assert torch.isnan(rec).all() and nan < 12 * usual, (nan, usual)
+    ctx.close(); ae.close()
 
 
 def test_weights_that_are_not_finite(B, oracle):
