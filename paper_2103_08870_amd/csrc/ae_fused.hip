@@ -11,11 +11,13 @@
 //   x w = h h' + (h m' + m h') + (m m' + h l' + l h') + terms below 2^-26 |x w|
 // so six bf16 products, exact in the fp32 accumulators' input, take the place of one fp32 product.  The matrix
 // cores run bf16 at 16 times the fp32 rate: 2.7 times fewer matrix-core cycles for the same precision (the sums are
-// rounded once per 16 products instead of once per 2, and come out slightly closer to the 64-bit result).
+// rounded once per 16 products instead of once per 2).  The last layer of each stack adds its few products per output
+// in 64 bits: the cost cannot be told from none (4 x 25 600: 26.0 us either way), and in 32 bits those sums were over half of the latent's error.
 // Measured against one fp32-MFMA launch per deep layer (ae_mfma.hip, which other stacks still use): 4 nodes x 25 600
 // values, encoder 79.4 -> 26.7 us (165 TFLOP/s of fp32 products), decoder 57.9 -> 21.4 us (126); 8 x 67 000, both
-// together 468 -> 228 us (163); 1 x 1 023 (latency) 79 -> 29 us.  Relative error against 64 bits, mean over sizes and
-// seeds: latent 1.16e-7 -> 1.02e-7, decoder 4.2e-8 -> 4.0e-8.  What bounds it: while a compute unit has blocks its
+// together 468 -> 228 us (163); 1 x 1 023 (latency) 79 -> 29 us.  Relative error against 64 bits, six
+// sizes from 1 x 500 to 8 x 67 000 x six seeds, mean (least to largest): latent 1.15e-7 (0.87 to 1.46) -> 0.41e-7 (0.34 to 0.51; 0.99e-7
+// with the last sums in 32 bits), decoder 3.86e-8 (2.96 to 5.54) -> 3.46e-8 (2.81 to 4.93; 3.73e-8): lower at every size with every seed.  What bounds it: while a compute unit has blocks its
 // matrix cores are busy 63 % of the cycles (encoder) and 46 % (decoder) at a clock that drops to 1.9 GHz.
 // The split is exact only for finite values; an Inf would meet products of both signs.  Such a
 // value leaves a NaN among its parts, which makes every output it reaches a NaN, and a block with an output that is
@@ -418,8 +420,8 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
     }
 
     float *part = (float *)buf;                               // conv4's partial sums [kSplit][C4][33]
-    float *red = part + kSplit * C4 * 33;                     // conv5's [W * 2][C5][32]
-    static_assert(kBytes >= (kSplit * C4 * 33 + W * 2 * C5 * 32) * 4, "partial sums");
+    double *red = (double *)(part + kSplit * C4 * 33);         // conv5's [W * 2][C5][32]
+    static_assert(kSplit * C4 * 33 % 2 == 0 && kBytes >= kSplit * C4 * 33 * 4 + W * 2 * C5 * 32 * 8, "partial sums");
     {   // conv4: one position tile (of which N4 columns are used); the steps are shared out over kSplit wavefronts
         constexpr int kSteps = 3 * C3 / 16 / kSplit, kAhead = 4;
         static_assert((3 * C3 / 16) % kSplit == 0, "conv4 steps");
@@ -449,9 +451,9 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
     {   // conv4's sums, bias and non-linearity; conv5's sums over this thread's channels
         constexpr int kGroups = W * 2, kCh = C4 / kGroups;
         const int p = tid & 31, cg = tid >> 5;
-        float t[C5];
+        double t[C5];
 #pragma unroll
-        for (int c = 0; c < C5; ++c) t[c] = 0.f;
+        for (int c = 0; c < C5; ++c) t[c] = 0.;
 #pragma unroll
         for (int i = 0; i < kCh; ++i) {
             const int co = cg * kCh + i;
@@ -460,7 +462,7 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
             for (int s = 1; s < kSplit; ++s) y += part[(s * C4 + co) * 33 + p];
             y = leaky_f(y + w.b4[co], slope);
 #pragma unroll
-            for (int c = 0; c < C5; ++c) t[c] = fmaf(w.w5[c * C4 + co], y, t[c]);
+            for (int c = 0; c < C5; ++c) t[c] = fma((double)w.w5[c * C4 + co], (double)y, t[c]);
         }
 #pragma unroll
         for (int c = 0; c < C5; ++c) red[(cg * C5 + c) * 32 + p] = t[c];
@@ -470,9 +472,10 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
     const bool mine = c < C5 && p < P && p0 + p < (long long)l4;
     float z = 0.f;
     if (mine) {
-        z = w.b5[c];
+        double sum = w.b5[c];
 #pragma unroll
-        for (int g = 0; g < W * 2; ++g) z += red[(g * C5 + c) * 32 + p];
+        for (int g = 0; g < W * 2; ++g) sum += red[(g * C5 + c) * 32 + p];
+        z = (float)sum;
     }
     // a value that the split cannot carry, anywhere in the block, has made every output that it reaches a NaN
     if (!__syncthreads_or(!(fabsf(z) < INFINITY))) {
@@ -733,7 +736,7 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
         }
     }
     __syncthreads();
-    float se = 0.f, so = 0.f;
+    double se = 0., so = 0.;
     {
         const float *from = swap + (size_t)(np + 2 * (kh ^ 1)) * 2048 + lane;
 #pragma unroll
@@ -742,15 +745,15 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
             const float bv = w.b5[co], wv = w.w6[co];
             const float ye = (kh ? e5[1][r] : e5[0][r]) + from[r * 64] + bv;
             const float yo = (kh ? o5[1][r] : o5[0][r]) + from[1024 + r * 64] + bv;
-            se = fmaf(wv, leaky_f(ye, slope), se);
-            so = fmaf(wv, leaky_f(yo, slope), so);
+            se = fma((double)wv, (double)leaky_f(ye, slope), se);
+            so = fma((double)wv, (double)leaky_f(yo, slope), so);
         }
     }
     se += __shfl_xor(se, 32, 64);
     so += __shfl_xor(so, 32, 64);
     const int m = (np * 2 + kh) * 32 + col, i = 2 * m + half;   // lanes 0..31 store the even, lanes 32..63 the odd outputs
     const bool mine = m < 8 * T && 16 * p0 + i < (long long)l5;
-    const float y = w.b6[0] + (half ? so : se);
+    const float y = (float)(w.b6[0] + (half ? so : se));
     if (!__syncthreads_or(mine && !(fabsf(y) < INFINITY))) {
         if (mine) out[16 * p0 + i] = y;
         return;
@@ -784,17 +787,17 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
         __syncthreads();
         up_fp32<CH, D5, row_floats(CH)>(e, o, w.w5 + ((run * CH + 4 * hf) * D5 + col) * 3, fa + (wave * 32 + col) * row_floats(CH) + 4 * hf);
     }
-    se = 0.f; so = 0.f;
+    se = 0.; so = 0.;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const float wv = w.w6[(r >> 2) * 8 + hf * 4 + (r & 3)];
-        se = fmaf(wv, leaky_f(e[r], slope), se);
-        so = fmaf(wv, leaky_f(o[r], slope), so);
+        se = fma((double)wv, (double)leaky_f(e[r], slope), se);
+        so = fma((double)wv, (double)leaky_f(o[r], slope), so);
     }
     se += __shfl_xor(se, 32, 64);
     so += __shfl_xor(so, 32, 64);
     const int m1 = wave * 32 + col, i1 = 2 * m1 + hf;
-    if (m1 < 8 * T && 16 * p0 + i1 < (long long)l5) out[16 * p0 + i1] = w.b6[0] + (hf ? so : se);
+    if (m1 < 8 * T && 16 * p0 + i1 < (long long)l5) out[16 * p0 + i1] = (float)(w.b6[0] + (hf ? so : se));
 }
 
 // ---- launchers ---------------------------------------------------------------------------------------

@@ -69,6 +69,47 @@ def test_lengths_at_the_edges_of_a_block(B, oracle, k, batch):
     ae.close()
 
 
+# The one-launch stacks may not be further from the 64-bit result than one fp32 launch per layer was.  The bounds are what those
+# kernels measured for the same weights and values (error of the latent, of the reconstruction, in 1e-8, seeds 0 to 3).
+FP32 = {1_023: ((14.31, 3.74), (9.44, 2.28), (11.37, 7.27), (10.05, 3.30)),
+        25_600: ((20.24, 3.64), (11.31, 2.19), (12.99, 7.49), (11.45, 3.26))}
+
+
+@pytest.mark.parametrize("k,batch", [(1_023, 1), (25_600, 4)])
+def test_error_against_64_bits(B, k, batch):
+    enc, dec = synth.paper_ae()
+    slope, errors = 0.01, []
+    for seed in range(4):
+        w = [[t.cuda() for t in xs] for xs in synth.ae_weights(enc, dec, device="cpu", seed=seed)]
+        gen = torch.Generator(device="cuda"); gen.manual_seed(seed)
+        x = torch.randn((batch, k), generator=gen, device="cuda") * 0.3
+        ae, ctx = B.Autoencoder(enc, dec, *w, slope=slope), B.Context(k, k, batch)
+        B.lgc_reserve(ctx, ae, k, batch)
+        lat, rec = torch.empty((batch, B.lgc_latent_len(ae, k)), device="cuda"), torch.empty((batch, k), device="cuda")
+        B.lgc_encode(ctx, ae, x, lat)
+        B.lgc_decode(ctx, ae, lat, rec)
+        w = [[t.double().cpu() for t in xs] for xs in w]
+        h, lens = x.double().cpu()[:, None], []
+        for i, (_, _, ks, st) in enumerate(enc):
+            lens.append(h.shape[2])
+            h = torch.nn.functional.conv1d(h, w[0][i], w[1][i], stride=st, padding=(ks - 1) // 2)
+            h = h if i + 1 == len(enc) else torch.nn.functional.leaky_relu(h, slope)
+        got = lat.double().cpu()
+        e_lat = ((got - h.flatten(1)).norm() / h.norm()).item()
+        h = got.view(h.shape)
+        lens = [n for n, (_, _, _, st) in zip(lens, enc) if st == 2]
+        for i, (_, _, ks, st) in enumerate(dec):
+            n = lens.pop() if st == 2 else h.shape[2]
+            pad = (ks - 1) // 2
+            h = torch.nn.functional.conv_transpose1d(h, w[2][i], w[3][i], stride=st, padding=pad,
+                                                     output_padding=n - ((h.shape[2] - 1) * st + ks - 2 * pad))
+            h = h if i + 1 == len(dec) else torch.nn.functional.leaky_relu(h, slope)
+        errors.append((e_lat, ((rec.double().cpu() - h[:, 0]).norm() / h.norm()).item()))
+        ctx.close(); ae.close()
+    for got, bound in zip(errors, FP32[k]):
+        assert got[0] < bound[0] * 1e-8 and got[1] < bound[1] * 1e-8, (errors, FP32[k])
+
+
 # Positive weights: an Inf stays one Inf all the way (weights of both signs would turn it into NaN at once), so the
 # values that bf16 parts cannot carry have one right answer.  The largest finite values round to Inf in bf16.  Blocks of
 # 15 latent positions (600 values), and of 31 where there are enough of them (7 nodes x 10 000); the values sit inside a
