@@ -20,8 +20,11 @@
 // with the last sums in 32 bits), decoder 3.86e-8 (2.96 to 5.54) -> 3.46e-8 (2.81 to 4.93; 3.73e-8): lower at every size with every seed.  What bounds it: while a compute unit has blocks its
 // matrix cores are busy 63 % of the cycles (encoder) and 46 % (decoder) at a clock that drops to 1.9 GHz.
 // The split is exact only for finite values; an Inf would meet products of both signs.  Such a
-// value leaves a NaN among its parts, which makes every output it reaches a NaN, and a block with an output that is
-// not finite redoes its outputs in plain fp32 on the fp32 matrix cores.  Every block doing so: 4 nodes x 25 600 values,
+// value (or one that rounds to Inf) leaves a NaN among its parts, which makes every output it reaches a NaN.  And it is exact only while the
+// parts are normal numbers: these matrix instructions take smaller ones for zero, so parts below 2^-126 are lost.  What that can
+// do to an output has a bound that the weights give (fused_limits).  A block with an output that is not finite, or is small enough
+// for the bound to matter, redoes its outputs in plain fp32 on the fp32 matrix cores, which keep small numbers (inputs of about 1e-33, no
+// biases: the reconstruction is 5.7e-7 off; 9.4e-4 without the redo, 7.3e-7 with fp32 launches).  Every block doing so: 4 nodes x 25 600 values,
 // encoder 32 -> 96 us, decoder 26 -> 53 us; 8 x 67 000: 146 -> 467 and 92 -> 231 us (one fp32-MFMA launch per layer:
 // 83, 59, 270 and 194 us; one position after the other on the vector units: 3.3, 1.6, 16 and 8 ms).
 //
@@ -31,6 +34,8 @@
 // order when the handle is created (fragments of 1 KB, a step's three parts one after the other), activations are
 // kept in the LDS position by position, [h | m | l][channels], so that every operand is one 16-byte read per lane.  Rows are
 // padded by 16 bytes: eight neighbouring positions then start in eight different groups of banks.
+#include <math.h>
+
 #include <type_traits>
 
 #include "lgc_internal.h"
@@ -49,7 +54,7 @@ namespace {
 
 __device__ __forceinline__ float leaky_f(float x, float slope) { return x > 0.f ? x : slope * x; }
 
-// Two values split into three bf16 pairs.  A value that is not finite, or rounds to Inf, leaves a NaN in m.
+// Two values split into three bf16 pairs.  A value that is not finite leaves a NaN in m, one that rounds to Inf an Inf in m and a NaN in l.
 __device__ __forceinline__ void split2(const float a, const float b, uint32_t &h, uint32_t &m, uint32_t &l) {
     h = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){a, b}, bf2));
     const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
@@ -168,11 +173,41 @@ __global__ __launch_bounds__(256) void k_weights_split(const float *__restrict__
     if (chk != chk) atomicAdd(bad, 1u);
 }
 
+// *most = the largest magnitude (bits) of w, from zero on
+__global__ __launch_bounds__(256) void k_most(const float *__restrict__ w, int count, uint32_t *most) {
+    uint32_t m = 0;
+    for (int i = blockIdx.x * 256 + threadIdx.x; i < count; i += gridDim.x * 256) { const uint32_t x = __float_as_uint(w[i]) & 0x7fffffffu; m = x > m ? x : m; }
+    atomicMax(most, m);
+}
+
 }  // namespace
 
 void launch_weights_split(const float *w, uint16_t *out, int c_in, int c_out, bool transposed, uint32_t *bad, hipStream_t st) {
     const int total = (c_out / 32) * 3 * (c_in / 16) * 64;
     hipLaunchKernelGGL(k_weights_split, dim3((total + 255) / 256), dim3(256), 0, st, w, out, c_in, c_out, (int)transposed, bad);
+}
+
+void launch_most(const float *w, int count, uint32_t *most, hipStream_t st) {
+    hipLaunchKernelGGL(k_most, dim3((count + 2047) / 2048), dim3(256), 0, st, w, count, most);
+}
+
+// How far an output can be off because numbers below 2^-126 count as zero in the split's products: a stored value loses up to
+// two parts, a product of up to 6 terms per input is off by as many such numbers, and a layer passes on what comes in times
+// its largest weight times its inputs per output (and the slope, if that enlarges).  An output 2^24 times as large does not
+// feel it.  Weights lose parts too: a layer whose largest one is 2^25 times 2^-126 loses no more than
+// rounding would.
+bool fused_limits(const LayerDev *l, int split, const float *most, bool transposed, float slope, bool no_bias, FusedLimits &out) {
+    const double tiny = ldexp(1.0, -126), steep = fmax(1.0, fabs((double)slope));
+    double off = 0.0;
+    for (int i = 0; i < split; ++i) {
+        if (most[i] != 0.f && most[i] < ldexpf(1.f, -101)) return false;
+        const double inputs = (transposed ? 2.0 : 3.0) * l[i].c_in;
+        off = steep * inputs * (most[i] * (off + 2 * tiny) + 6 * tiny);
+    }
+    off *= (double)most[split] * l[split].c_in;
+    out.least = (float)ldexp(off, 24);
+    out.no_bias = no_bias;
+    return out.least <= ldexpf(1.f, -40);   // (also no NaN: weights so large that usual outputs would all be redone)
 }
 
 // ---- encoder ---------------------------------------------------------------------------------------
@@ -183,6 +218,7 @@ struct EncoderDev {
     const float *w2, *w3, *w4, *b2, *b3, *b4;   // [c_out][c_in][3]
     const uint16_t *s2, *s3, *s4;               // the same as bf16 fragments
     const float *w5, *b5;                       // [C5][C4][1]
+    FusedLimits limits;
 };
 
 namespace {
@@ -255,19 +291,24 @@ __device__ __forceinline__ acc16 mma_fp32(const float a, const float b, const ac
 constexpr int row_floats(int c) { return c + 4; }
 
 // acc += one tile: w = the lane's output channel [CI][3], b = its row for tap 0, `odd` floats before the odd positions',
-// both from the half's first channel on
+// both from the half's first channel on.  Sums of 96 products are added up: one running sum of 768 is off twice as far.
 template <int CI>
 __device__ __forceinline__ void conv_fp32(acc16 &acc, const float *__restrict__ w, const float *b, const int odd) {
+#pragma unroll 1
+    for (int c0 = 0; c0 < CI; c0 += 32) {
+        acc16 sum = zero16();
 #pragma unroll 2
-    for (int c = 0; c < CI; c += 8) {
-        const f4v x[3] = {*(const f4v *)(b + c), *(const f4v *)(b + odd + c), *(const f4v *)(b + row_floats(CI) + c)};
-        f4v y[3];
+        for (int c = c0; c < c0 + 32; c += 8) {
+            const f4v x[3] = {*(const f4v *)(b + c), *(const f4v *)(b + odd + c), *(const f4v *)(b + row_floats(CI) + c)};
+            f4v y[3];
 #pragma unroll
-        for (int t = 0; t < 3; ++t) y[t] = *(const f4v *)(w + 3 * c + 4 * t);
+            for (int t = 0; t < 3; ++t) y[t] = *(const f4v *)(w + 3 * c + 4 * t);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
+            for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int t = 0; t < 3; ++t) acc = mma_fp32(y[(3 * e + t) / 4][(3 * e + t) % 4], x[t][e], acc);
+                for (int t = 0; t < 3; ++t) sum = mma_fp32(y[(3 * e + t) / 4][(3 * e + t) % 4], x[t][e], sum);
+        }
+        acc += sum;
     }
 }
 
@@ -477,8 +518,13 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
         for (int g = 0; g < W * 2; ++g) sum += red[(g * C5 + c) * 32 + p];
         z = (float)sum;
     }
-    // a value that the split cannot carry, anywhere in the block, has made every output that it reaches a NaN
-    if (!__syncthreads_or(!(fabsf(z) < INFINITY))) {
+    bool redo = __syncthreads_or(mine && !(fabsf(z) >= w.limits.least && fabsf(z) < INFINITY));
+    if (redo && w.limits.no_bias) {   // nothing but zeros gives zeros
+        bool any = false;
+        for (int i = tid; i < 4 * N2 + 3; i += W * 64) any = any || xs[i] != 0.f;
+        redo = __syncthreads_or(any);
+    }
+    if (!redo) {
         if (mine) out[(size_t)c * l4 + p0 + p] = z;
         return;
     }
@@ -494,9 +540,9 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
     layer_fp32<C3, C4, N4, W>(f, w.w4, w.b4, wave, p0, l4, slope);
     if (mine) {
         const float *row = f + ((p & 1) ? (N4 / 2 + 1) * row_floats(C4) : 0) + (p >> 1) * row_floats(C4);
-        z = w.b5[c];
-        for (int ci = 0; ci < C4; ++ci) z = fmaf(w.w5[c * C4 + ci], row[ci], z);
-        out[(size_t)c * l4 + p0 + p] = z;
+        double sum = w.b5[c];
+        for (int ci = 0; ci < C4; ++ci) sum = fma((double)w.w5[c * C4 + ci], (double)row[ci], sum);
+        out[(size_t)c * l4 + p0 + p] = (float)sum;
     }
 }
 
@@ -509,6 +555,7 @@ struct DecoderDev {
     const float *w1, *w2, *w3, *w4, *w5, *w6;   // [c_in][c_out][3]; w6 [D5]
     const float *b1, *b2, *b3, *b4, *b5, *b6;
     const uint16_t *s3, *s4, *s5;               // the deep layers as bf16 fragments
+    FusedLimits limits;
 };
 
 namespace {
@@ -754,7 +801,12 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
     const int m = (np * 2 + kh) * 32 + col, i = 2 * m + half;   // lanes 0..31 store the even, lanes 32..63 the odd outputs
     const bool mine = m < 8 * T && 16 * p0 + i < (long long)l5;
     const float y = (float)(w.b6[0] + (half ? so : se));
-    if (!__syncthreads_or(mine && !(fabsf(y) < INFINITY))) {
+    bool redo = __syncthreads_or(mine && !(fabsf(y) >= w.limits.least && fabsf(y) < INFINITY));
+    if (redo && w.limits.no_bias) {   // nothing but zeros gives zeros
+        redo = __syncthreads_or(tid < D0 * (T + 3) && zs[tid] != 0.f);
+        static_assert(D0 * (T + 3) <= 256, "one value per thread");
+    }
+    if (!redo) {
         if (mine) out[16 * p0 + i] = y;
         return;
     }
@@ -817,7 +869,7 @@ bool decoder_fused_covers(const LayerDev *l, int count) {
 }
 
 bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int count, const uint64_t *len, int batch, float slope,
-                          int cus, hipStream_t st) {
+                          const FusedLimits &limits, int cus, hipStream_t st) {
     if (!encoder_fused_covers(l, count) || !l[1].ws || !l[2].ws || !l[3].ws) return false;
     const uint32_t l4 = (uint32_t)len[4];
     if (l4 == 0) return true;
@@ -827,6 +879,7 @@ bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int cou
     w.w3 = l[2].w; w.b3 = l[2].b; w.s3 = l[2].ws;
     w.w4 = l[3].w; w.b4 = l[3].b; w.s4 = l[3].ws;
     w.w5 = l[4].w; w.b5 = l[4].b;
+    w.limits = limits;
 #define LGC_ENC(P, W) hipLaunchKernelGGL((k_encoder_fused<64, 128, 256, 64, 4, P, W>), dim3((l4 + P - 1) / P, batch), dim3(64 * W), 0, st, \
                                          x, out, w, (uint32_t)len[0], (uint32_t)len[1], (uint32_t)len[2], (uint32_t)len[3], l4, slope)
     // 31 positions per block stream the 1 MB of weights half as often as 15 do, and waste no half tile in conv4 (4 nodes
@@ -838,7 +891,7 @@ bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int cou
 }
 
 bool launch_decoder_fused(const float *z, float *out, const LayerDev *l, int count, uint64_t l_z, const uint64_t *len, int batch,
-                          float slope, hipStream_t st) {
+                          float slope, const FusedLimits &limits, hipStream_t st) {
     if (!decoder_fused_covers(l, count) || !l[2].ws || !l[3].ws || !l[4].ws) return false;
     if (len[4] == 0) return true;
     DecoderDev w;
@@ -848,6 +901,7 @@ bool launch_decoder_fused(const float *z, float *out, const LayerDev *l, int cou
     w.w4 = l[3].w; w.b4 = l[3].b; w.s4 = l[3].ws;
     w.w5 = l[4].w; w.b5 = l[4].b; w.s5 = l[4].ws;
     w.w6 = l[5].w; w.b6 = l[5].b;
+    w.limits = limits;
     constexpr int T = 15;
     hipLaunchKernelGGL((k_decoder_fused<4, 4, 32, 64, 128, 32, T>), dim3(((uint32_t)l_z + T - 1) / T, batch), dim3(256), 0, st, z, out, w,
                        (uint32_t)l_z, (uint32_t)len[1], (uint32_t)len[2], (uint32_t)len[3], (uint32_t)len[4], slope);

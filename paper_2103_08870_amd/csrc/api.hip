@@ -76,6 +76,7 @@ struct lgc_ae {
     float *weights = nullptr;  // device copy of all weights and biases
     float *weights_t = nullptr;  // contraction-major copies for the layers that run on the matrix cores
     uint16_t *weights_s = nullptr;  // copies as bf16 fragments in three parts for the stacks that run as one launch
+    FusedLimits enc_limits, dec_limits;   // of those stacks
 };
 
 static thread_local char g_err[256] = "";
@@ -712,32 +713,45 @@ extern "C" lgc_status lgc_ae_create(lgc_ae **out, int device, int n_enc, const l
         }
     }
     if (e == hipSuccess) {
-        // stacks that run as one launch: their deep layers' weights as bf16 fragments (as long as all are finite)
+        // stacks that run as one launch: three deep layers' weights as bf16 fragments (as long as all are finite and in range)
         const bool fe = encoder_fused_covers(ae->enc_dev.data(), n_enc), fd = decoder_fused_covers(ae->dec_dev.data(), n_dec);
         auto size = [](const LayerDev &l) { return (size_t)l.c_in * l.c_out * 3 * 3; };   // 3 taps, 3 parts
         size_t s_total = 0;
         if (fe) for (int l = 1; l <= 3; ++l) s_total += size(ae->enc_dev[l]);
         if (fd) for (int l = 2; l <= 4; ++l) s_total += size(ae->dec_dev[l]);
         if (s_total) {
-            e = hipMalloc((void **)&ae->weights_s, s_total * 2 + 4);
-            uint32_t *bad = (uint32_t *)(ae->weights_s + s_total), host_bad = 0;   // s_total is even
-            if (e == hipSuccess) e = hipMemset(bad, 0, 4);
+            // per stack: weights that are not finite; largest magnitudes of the deep layers, the last layer, all biases
+            constexpr int kWords = 6;
+            uint32_t host[2][kWords] = {};
+            e = hipMalloc((void **)&ae->weights_s, s_total * 2 + sizeof host);
+            uint32_t *words = (uint32_t *)(ae->weights_s + s_total);   // s_total is even
+            if (e == hipSuccess) e = hipMemset(words, 0, sizeof host);
             size_t s_off = 0;
-            auto split = [&](LayerDev &l, bool transposed) {
-                launch_weights_split(l.w, ae->weights_s + s_off, l.c_in, l.c_out, transposed, bad, nullptr);
-                l.ws = ae->weights_s + s_off;
-                s_off += size(l);
+            auto prepare = [&](std::vector<LayerDev> &ls, int first, bool transposed, uint32_t *w) {
+                for (int i = 0; i < 4; ++i) {
+                    LayerDev &l = ls[first + i];
+                    launch_most(l.w, l.c_in * l.c_out * l.ksize, w + 1 + i, nullptr);
+                    if (i == 3) break;
+                    launch_weights_split(l.w, ae->weights_s + s_off, l.c_in, l.c_out, transposed, w, nullptr);
+                    l.ws = ae->weights_s + s_off;
+                    s_off += size(l);
+                }
+                for (auto &l : ls) launch_most(l.b, l.c_out, w + 5, nullptr);
             };
             if (e == hipSuccess) {
-                if (fe) for (int l = 1; l <= 3; ++l) split(ae->enc_dev[l], false);
-                if (fd) for (int l = 2; l <= 4; ++l) split(ae->dec_dev[l], true);
+                if (fe) prepare(ae->enc_dev, 1, false, words);
+                if (fd) prepare(ae->dec_dev, 2, true, words + kWords);
                 e = hipGetLastError();
             }
-            if (e == hipSuccess) e = hipMemcpy(&host_bad, bad, 4, hipMemcpyDeviceToHost);
-            if (e == hipSuccess && host_bad) {
-                for (auto &l : ae->enc_dev) l.ws = nullptr;
-                for (auto &l : ae->dec_dev) l.ws = nullptr;
-            }
+            if (e == hipSuccess) e = hipMemcpy(host, words, sizeof host, hipMemcpyDeviceToHost);
+            auto settle = [&](std::vector<LayerDev> &ls, int first, bool transposed, const uint32_t *w, FusedLimits &limits) {
+                float most[4];
+                memcpy(most, w + 1, sizeof most);
+                if (w[0] || !fused_limits(ls.data() + first, 3, most, transposed, slope, w[5] == 0, limits))
+                    for (auto &l : ls) l.ws = nullptr;
+            };
+            if (e == hipSuccess && fe) settle(ae->enc_dev, 1, false, host[0], ae->enc_limits);
+            if (e == hipSuccess && fd) settle(ae->dec_dev, 2, true, host[1], ae->dec_limits);
         }
     }
     if (e == hipSuccess) e = hipDeviceSynchronize();
@@ -874,7 +888,7 @@ static lgc_status run_encode(lgc_ctx *ctx, const lgc_ae *ae, const float *vals, 
         return fail(ctx, LGC_EINVAL, "lgc_encode: activation scratch for k = %llu, batch = %d not reserved: call "
                                      "lgc_reserve(ctx, ae, k, batch, NULL) once beforehand", (unsigned long long)k, batch);
     if (!overlap(vals, k * batch, latent, (uint64_t)batch * ae->enc[nl - 1].c_out * len[nl]) &&
-        launch_encoder_fused(vals, latent, ae->enc_dev.data(), (int)nl, len.data(), batch, ae->slope, ctx->cus, st)) {
+        launch_encoder_fused(vals, latent, ae->enc_dev.data(), (int)nl, len.data(), batch, ae->slope, ae->enc_limits, ctx->cus, st)) {
         hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e1));
         return LGC_OK;
@@ -972,7 +986,7 @@ static lgc_status run_decode(lgc_ctx *ctx, const lgc_ae *ae, const float *latent
         return fail(ctx, LGC_EINVAL, "lgc_decode: activation scratch for k = %llu, batch = %d not reserved: call "
                                      "lgc_reserve(ctx, ae, k, batch, NULL) once beforehand", (unsigned long long)k, batch);
     if (!innov && !overlap(latent, (uint64_t)batch * ae->dec[0].c_in * in_len, rec, k * batch) &&
-        launch_decoder_fused(latent, rec, ae->dec_dev.data(), (int)nl, in_len, out_len.data(), batch, ae->slope, st)) {
+        launch_decoder_fused(latent, rec, ae->dec_dev.data(), (int)nl, in_len, out_len.data(), batch, ae->slope, ae->dec_limits, st)) {
         hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e1));
         return LGC_OK;

@@ -113,20 +113,21 @@ def test_error_against_64_bits(B, k, batch):
 # Positive weights: an Inf stays one Inf all the way (weights of both signs would turn it into NaN at once), so the
 # values that bf16 parts cannot carry have one right answer.  The largest finite values round to Inf in bf16.  Blocks of
 # 15 latent positions (600 values), and of 31 where there are enough of them (7 nodes x 10 000); the values sit inside a
-# block, where two blocks' windows overlap, and in the last, partly filled block.
+# block, where two blocks' windows overlap, and in the last, partly filled block.  At 1e-33 the split's low parts, and their products,
+# are below the least normal number (the reconstruction, about 3e-38, is just above it); no biases, which would hide it.
 @pytest.mark.parametrize("k,batch", [(600, 2), (10_000, 7)])
-@pytest.mark.parametrize("special", [np.inf, np.nan, 3.4e38, 1e-30])
+@pytest.mark.parametrize("special", [np.inf, np.nan, 3.4e38, 1e-30, 1e-33, 0.0])
 def test_values_that_the_split_cannot_carry(B, oracle, special, k, batch):
     def change(a, which):
         if which % 2:
-            return np.zeros_like(a) if special == 1e-30 else np.abs(a)   # biases
+            return np.zeros_like(a) if special < 1 else np.abs(a)   # biases
         return np.abs(a) * np.float32(0.05)
     ae, enc, dec, host = stacks(B, change)
     rng = np.random.default_rng(5)
     length = -(-k // 16)
     x = np.abs(rng.normal(0, 1, (batch, k))).astype(np.float32)
     z = np.abs(rng.normal(0, 1, (batch, 4, length))).astype(np.float32)
-    if special == 1e-30:
+    if special < 1:
         x *= np.float32(special); z *= np.float32(special)
     else:
         x[1, [300, k - 1]] = special
@@ -169,14 +170,23 @@ def test_values_that_are_not_finite_cost_no_more_than_fp32(B):
     ctx.close(); ae.close()
 
 
-def test_weights_that_are_not_finite(B, oracle):
-    # such a handle keeps to the fp32 kernels: NaN where the oracle has a NaN
+@pytest.mark.parametrize("factor", [np.inf, 1e6, 1e-36])
+def test_weights_that_the_split_cannot_carry(B, oracle, factor):
+    # such a handle keeps to the fp32 kernels: one Inf (NaN where the oracle has a NaN), deep layers so large that what the split
+    # loses of small numbers could show, a layer of weights near the least normal number (nothing else may cover what it gives);
+    # positive ones, so that sums do not cancel
     def change(a, which):
-        if which == 0 and a.shape == (256, 128, 3):
-            a = a.copy(); a[7, 3, 1] = np.inf
+        a = a.copy() if factor == np.inf else np.abs(a)
+        if factor == np.inf:
+            if a.shape == (256, 128, 3):
+                a[7, 3, 1] = np.inf
+        elif factor == 1e-36:
+            a *= np.float32(factor if a.shape in ((128, 64, 3), (32, 64, 3)) else 1e3 if a.ndim == 3 else 0)
+        elif a.ndim == 3 and min(a.shape[:2]) >= 32:
+            a *= np.float32(factor)
         return a
     ae, enc, dec, host = stacks(B, change)
-    x = np.random.default_rng(1).normal(0, 1, (1, 100)).astype(np.float32)
+    x = np.random.default_rng(1).uniform(0, 1, (1, 100)).astype(np.float32)
     lat, ol, rec, orec = both_ways(B, oracle, ae, enc, dec, host, x, np.ones((1, 4 * 7), np.float32))
     assert_near(lat, ol, "latent")
     assert_near(rec, orec, "reconstruction")
