@@ -34,7 +34,8 @@ struct lgc_ctx {
     uint32_t supers = 0;
     unsigned long long *bitmap = nullptr;
     uint32_t *cand_idx = nullptr, *cand_val = nullptr;
-    uint32_t *row_rec = nullptr;      // records of the rows with few candidates (an allocation of its own, or none)
+    uint32_t *row_rec = nullptr;      // records of the rows with few candidates (an allocation of its own, or none), room for rec_rows of them
+    uint64_t rec_rows = 0;
     float *act[2] = {nullptr, nullptr};  // autoencoder activations (ping-pong), grown on demand
     size_t act_floats = 0;
     // per-layer selection: thresholds [max_batch][n_seg] and a candidate list of its own, grown on demand
@@ -283,7 +284,7 @@ SelArgs make_args(lgc_ctx *c, const float *g, float *u, float *v, uint64_t n, ui
     a.next_state = c->state[c->cur ^ 1]; a.next_words = c->single_state ? 0u : c->state_words;
     a.samples = c->samples; a.row_count = c->row_count; a.bitmap = c->bitmap;
     a.row_super = c->row_super; a.supers = c->supers;
-    a.row_rec = c->row_rec;
+    a.row_rec = c->row_rec; a.rec_stride = (a.n + kRow - 1) / kRow;
     a.cand_idx = c->cand_idx; a.cand_val = c->cand_val;
     a.out_vals = out_vals; a.out_idx = out_idx;
     return a;
@@ -300,6 +301,31 @@ bool takes_small_path(const lgc_ctx *ctx, uint64_t n, uint64_t k) { return ctx->
 // expected: 10.4 us against 17 for the launches themselves).
 bool takes_finish(uint64_t n, uint64_t k) {
     return (n + kRow - 1) / kRow <= kFinishRows && expected_candidates((double)n, (double)k) <= 4096.0;
+}
+
+// The rows' records: where one block per node reads them; for candidate lists whose lines of v (128 bytes each) are
+// more than the 256 MB memory-side cache holds; and for short lists where all of v stays in that cache.  In between, what
+// the gather saves in reads of v the output pays: its zeros then go to lines that nothing has fetched.
+// Whole step without / with records, us.  Long lists: 2^28, 0.4 %: 1111 / 1128, 0.6 % (2.13 M candidates): 1196 / 1203, 0.7 % (2.44 M):
+// 1262 / 1268 and, another day, 1249 / 1246, 0.75 % (2.59 M): 1272 / 1265, 0.8 %: 1297 / 1290, 1 %: 1390 / 1364 (gather 142 -> 55); 8 x 44.5 M, 0.6 %
+// (2.83 M): 1608 / 1599, 0.8 %: 1727 / 1699; 2^27, 1.8 % (2.85 M): 769 / 765.
+// Short lists: 3 x 3.33 M, 0.1 %: 70.7 / 68.2; 16 M: 86.0 / 82.8; 4 x 6 M: 116.3 / 114.5; 4 x 8 M: 142.5 / 140.8; then under 1 %
+// (4 x 9.5 M: 163.5 / 162.9; 64 M: 250.2 / 249.6) and turning: 4 x 25.6 M: 384.2 / 385.0; 8 x 44.5 M: 1325 / 1339.
+// A long list under the cache's size in a short vector, 20 M, 1 %: 138 / 140.5; 67 M, 0.8 %: 322 / 330.
+constexpr double kRecordsFromList = 2.5e6;             // candidates of all nodes
+constexpr uint64_t kRecordsUpToElems = 1ull << 25;     // elements of all nodes
+bool takes_records(uint64_t n, uint64_t k, int batch) {
+    const double listed = expected_candidates((double)n, (double)k);
+    return takes_finish(n, k) || (listed <= 131072.0 && n * (uint64_t)batch <= kRecordsUpToElems) || listed * batch >= kRecordsFromList;
+}
+
+// Rows that takes_records can ask records for in calls of up to this size (a quarter byte per element; none beyond 4 GB)
+uint64_t record_rows(uint64_t max_n, uint64_t max_k, int max_batch) {
+    const uint64_t rows = (max_n + kRow - 1) / kRow, B = (uint64_t)max_batch, all = B * rows;
+    const uint64_t some = std::min(all, std::max(B * std::min<uint64_t>(rows, kFinishRows), kRecordsUpToElems / kRow + B));
+    const bool dense = expected_candidates((double)max_n, (double)max_k) * max_batch >= kRecordsFromList;
+    const uint64_t need = dense ? all : some;
+    return need * kRecordWords * 4 <= (4ull << 30) ? need : some * kRecordWords * 4 <= (4ull << 30) ? some : 0;
 }
 
 // accumulate (optional) + select; g == nullptr means selection only
@@ -347,17 +373,8 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         }
         if (ctx->exact_calls_left > 0) { --ctx->exact_calls_left; fast = small = false; }
     }
-    // The rows' records: where one block per node reads them; for candidate lists whose lines of v (128 bytes each) are
-    // more than the 256 MB memory-side cache holds (one node of 2^28 elements, 1 %: gather 142 -> 55 us); and for short
-    // lists where all of v stays in that cache (3 x 3.33 M: 64.4 -> 63.6 us per call).  In between, what the gather saves in reads of v the
-    // output pays: its zeros then go to lines that nothing has fetched.  Whole step without / with records: 8 x 44.5 M,
-    // 0.1 %: 1325 / 1339 us; 4 x 25.6 M, 0.1 %: 384.2 / 385.0; 67 M, 0.8 %: 322 / 330; 2^28, 0.4 %: 1111 / 1128,
-    // 0.7 % (2.4 M candidates): 1262 / 1268, 1 % (3.4 M): 1404 / 1380;
-    // and a long list under the cache's size in a short vector, 20 M, 1 %: 138 / 140.5.
-    const double listed = expected_candidates((double)n, (double)k);
-    const bool long_list = listed > 131072.0;
-    const bool v_stays = !long_list && n * (uint64_t)batch <= (1ull << 25);
-    if (!finishes_in_one && !v_stays && listed * batch < 2097152.0) a.row_rec = nullptr;
+    const bool long_list = expected_candidates((double)n, (double)k) > 131072.0;
+    if (!takes_records(n, k, batch) || (uint64_t)batch * a.rec_stride > ctx->rec_rows) a.row_rec = nullptr;
     if (fast || small) {
         if (++ctx->call_number == 0) ctx->call_number = 1;
         a.notify_value = ctx->call_number;
@@ -433,10 +450,10 @@ extern "C" lgc_status lgc_create(lgc_ctx **out, int device, uint64_t max_n, uint
         return fail(nullptr, LGC_EHIP, "hipMemset: %s", hipGetErrorString(e));
     }
     bind_scratch(c, block, L);
-    // The rows' records spare the kernels after the streaming pass a search and scattered reads.  Without them (they
-    // take a quarter byte per element, at most 4 GB are asked for) the selection works the way without.
-    const size_t rec_bytes = (size_t)max_batch * L.rows * kRecordWords * 4;
-    if (rec_bytes <= ((size_t)4 << 30) && hipMalloc((void **)&c->row_rec, rec_bytes) != hipSuccess) c->row_rec = nullptr;
+    // The rows' records spare the kernels after the streaming pass a search and scattered reads.  Without them (allocation
+    // refused) the selection works the way without.
+    c->rec_rows = record_rows(max_n, max_k, max_batch);
+    if (c->rec_rows && hipMalloc((void **)&c->row_rec, c->rec_rows * kRecordWords * 4) != hipSuccess) { c->row_rec = nullptr; c->rec_rows = 0; }
     // the pinned words of the automatic path choice; without them (allocation refused) the choice is simply not adaptive
     void *pinned = nullptr, *pinned_dev = nullptr;
     if (hipHostMalloc(&pinned, 64, hipHostMallocMapped) == hipSuccess) {
@@ -602,8 +619,8 @@ extern "C" lgc_status lgc_accumulate_topk_static(int device, const float *g, flo
     view.single_state = true;
     bind_scratch(&view, sd->ptr, L);
     // the rows' records, where the array has room for them
-    const size_t rec_bytes = (size_t)batch * L.rows * kRecordWords * 4;
-    if (rec_bytes <= kStaticScratchBytes - L.bytes) view.row_rec = (uint32_t *)(sd->ptr + L.bytes);
+    view.row_rec = (uint32_t *)(sd->ptr + L.bytes);
+    view.rec_rows = (kStaticScratchBytes - L.bytes) / (kRecordWords * 4);
     hipStream_t st = (hipStream_t)stream;
     // the array keeps the last call's contents: statistics and the state set start every call at zero
     // (a fill kernel, not a memset, so that the call can be recorded into a HIP graph)

@@ -138,7 +138,8 @@ struct SelArgs {
     uint32_t *row_super;      // [batch][supers] candidates per group of kSuperRows rows (vectors of more than one group)
     uint32_t supers;           // groups per node in row_super; 0: the gather adds up the row counts themselves
     unsigned long long *bitmap;  // [batch][rows][kRowWords]
-    uint32_t *row_rec;           // [batch][rows][kRecordWords]  records of the rows with few candidates (null: none are kept)
+    uint32_t *row_rec;           // [batch][rec_stride][kRecordWords]  records of the rows with few candidates (null: none are kept)
+    uint32_t rec_stride;         // rows of the call's vectors
     uint32_t *cand_idx;       // [batch][cap]  gathered, index-ordered
     uint32_t *cand_val;
     float *out_vals;          // [batch][k]

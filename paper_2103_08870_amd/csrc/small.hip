@@ -126,7 +126,7 @@ __global__ __launch_bounds__(1024) void k_small_flags(SelArgs a) {
     if (row < nrows && part == 0 && lane == 0) a.row_count[(size_t)node * a.rows + row] = total;
     __syncthreads();
     if (a.row_rec && row < nrows && part == 0 && lane < kRecord + kRecord / 2)   // (rows with more hold nothing of use)
-        a.row_rec[((size_t)node * a.rows + row) * kRecordWords + lane] = rec[local][lane];
+        a.row_rec[((size_t)node * a.rec_stride + row) * kRecordWords + lane] = rec[local][lane];
 }
 
 // the finishing launch's list has to hold the selection and the keys that share T*'s leading bits

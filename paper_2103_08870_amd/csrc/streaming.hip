@@ -235,7 +235,7 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            if (lane < kRecord + kRecord / 2) a.row_rec[((size_t)node * a.rows + r) * kRecordWords + lane] = rec[lane];
+            if (lane < kRecord + kRecord / 2) a.row_rec[((size_t)node * a.rec_stride + r) * kRecordWords + lane] = rec[lane];
         }
     }
 }

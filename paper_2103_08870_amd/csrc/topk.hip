@@ -299,7 +299,7 @@ __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
         const uint32_t i = p - offs[r];   // the i-th candidate of row r
         uint32_t ix, vb;
         if (a.row_rec && (r + 1 < (uint32_t)kGatherRows ? offs[r + 1] : block_total) - offs[r] <= (uint32_t)kRecord) {
-            const uint32_t *rec = a.row_rec + ((size_t)node * a.rows + first + r) * kRecordWords;
+            const uint32_t *rec = a.row_rec + ((size_t)node * a.rec_stride + first + r) * kRecordWords;
             vb = rec[i];
             ix = (first + r) * (uint32_t)kRow + ((const uint16_t *)(rec + kRecord))[i];
         } else {
@@ -1122,7 +1122,7 @@ __device__ __forceinline__ void finish_node(const SelArgs &a, const int node, co
         const uint32_t i = p - offs[r];
         uint32_t ix, x;
         if (a.row_rec && offs[r + 1] - offs[r] <= (uint32_t)kRecord) {
-            const uint32_t *rec = a.row_rec + ((size_t)node * a.rows + r) * kRecordWords;
+            const uint32_t *rec = a.row_rec + ((size_t)node * a.rec_stride + r) * kRecordWords;
             x = rec[i];
             ix = r * (uint32_t)kRow + ((const uint16_t *)(rec + kRecord))[i];
         } else {

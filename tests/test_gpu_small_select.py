@@ -98,6 +98,27 @@ def test_short_and_long_vectors_in_one_graph(B):
     ctx.close(); other.close()
 
 
+# Records are laid out by the call's rows: several nodes in a context for longer vectors, with few, finishing and dense lists
+@pytest.mark.parametrize("n,k,batch,max_n,max_k", [(50_001, 500, 3, 5_000_000, 20_000), (1_100_000, 1100, 3, 5_000_000, 20_000),
+                                                   (2_000_003, 12_000, 3, 5_000_000, 20_000), (30_000_001, 900_000, 3, 40_000_000, 1_200_000)])
+def test_records_in_a_larger_context(B, n, k, batch, max_n, max_k):
+    gen = torch.Generator(device="cuda"); gen.manual_seed(n)
+    ctx, own = B.Context(max_n, max_k, batch + 1), B.Context(n, k, batch)
+    start = [torch.randn((batch, n), generator=gen, device="cuda") for _ in range(3)]
+    results = []
+    for c, path in ((ctx, 0), (own, 0), (own, 1)):
+        B.lgc_set_option(c, B.LGC_OPT_SELECT_PATH, path)
+        g, u, v = (t.clone() for t in start)
+        ov, oi = torch.zeros((batch, k), device="cuda"), torch.zeros((batch, k), dtype=torch.int32, device="cuda")
+        for _ in range(2):
+            B.lgc_accumulate_topk(c, g, u, v, 0.9, k, ov, oi)
+        results.append((u, v, ov, oi))
+        assert B.lgc_stats(c)[1:] == (0, 0)          # nothing fell back: the records were read
+    for other in results[1:]:
+        assert all(torch.equal(x, y) for x, y in zip(results[0], other))
+    ctx.close(); own.close()
+
+
 # Rows (1024 elements) whose candidates fill a record exactly, exceed it by one, or fill the row; vectors at the limits of
 # the one-launch finish (4096 rows) and a list long enough for the kernels of the dense selections.
 @pytest.mark.parametrize("n,k", [(300_001, 1000), (4_194_304, 1000), (4_194_305, 1000), (5_000_003, 50_000), (5_000_003, 200_000)])

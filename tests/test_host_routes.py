@@ -32,7 +32,8 @@ class Host:
     def log(self):
         """[("malloc", bytes) or ("launch", kernel, grid)] since the last call."""
         out = []
-        for line in self.fake.recorded().decode().splitlines():
+        self.raw = self.fake.recorded().decode()
+        for line in self.raw.splitlines():
             what, *rest = line.split()
             if what == "malloc":
                 out.append((what, int(rest[0])))
@@ -44,6 +45,13 @@ class Host:
 
     def kernels(self):
         return [x[1] for x in self.log() if x[0] == "launch"]
+
+    def topk(self, ctx, n, k, batch):
+        """The template arguments of the streaming pass of one accumulation and selection."""
+        self.log()
+        assert self.lib.lgc_accumulate_topk(ctx, p(1 << 40), p(1 << 41), p(1 << 42), u64(n), batch, u64(n), C.c_float(0.9), u64(k), p(1 << 43), p(1 << 43), None) == 0
+        names = [line.split()[1] for line in self.raw.splitlines() if "k_candidates" in line] if self.log() else []
+        return names
 
     def ctx(self, max_n, max_k, batch):
         h = p()
@@ -81,6 +89,26 @@ def paper_stacks_in_place(h):
     return out
 
 
+RECORDS = [  # elements, kept, nodes; whether the rows keep records: measured sizes on either side of each line of the rule
+    (1 << 20, 1024, 1, True), (3_333_331, 3333, 3, True), (16_000_000, 16_000, 1, True), (8_000_000, 8000, 4, True), (8_500_000, 8500, 4, False),
+    (25_600_000, 25_600, 4, False), (44_500_000, 44_500, 8, False), (1 << 28, 1_610_612, 1, False), (1 << 28, 1_879_048, 1, False),
+    (1 << 28, 2_147_483, 1, True), (1 << 28, 2_684_354, 1, True), (44_500_000, 445_000, 8, True), (67_000_000, 536_000, 1, False)]
+
+
+def records(h):
+    out = []
+    for n, k, batch, _ in RECORDS:
+        h.log()
+        ctx = h.ctx(n, k, batch)
+        taken = [x[1] for x in h.log() if x[0] == "malloc"]
+        passes = h.topk(ctx, n, k, batch)
+        h.lib.lgc_destroy(ctx)
+        out.append([taken, sorted(set(passes))])
+    big = h.ctx(1 << 28, 2_684_354, 2)      # one context for all: what fits a call does not depend on the context's own rows
+    out.append([h.topk(big, n, k, batch) for n, k, batch in ((1 << 28, 2_684_354, 2), (1 << 28, 2_684_354, 1), (16_000_000, 16_000, 2), (16_000_000, 16_000, 1))])
+    return out
+
+
 @pytest.fixture(scope="module")
 def answers(tmp_path_factory):
     """Every scenario (a function above, by name), run in one process of its own."""
@@ -103,6 +131,17 @@ def test_paper_stacks_in_place_go_layer_by_layer(answers):
         assert fused or len(kernels) >= 3, (name, kernels)
 
 
+def test_records_are_kept_and_allocated_where_the_rule_asks_for_them(answers):
+    *single, shared = answers["records"]
+    for (n, k, batch, wanted), (taken, passes) in zip(RECORDS, single):
+        assert passes and all(("ELb1EEEv" in x) == wanted for x in passes), (n, k, batch, passes)
+        rows, room = -(-n // 1024) * batch, sum(taken[1:]) / 256
+        # room for what a call within the context's limits can keep records of: no more than 32 K rows and one per node (2^25
+        # elements in all), or 4096 rows per node, unless the lists are dense
+        assert room >= rows if wanted else room <= min(rows, max(2 ** 15 + batch, 4096 * batch)), (n, k, batch, taken)
+    assert [all("ELb1EEEv" in x for x in passes) for passes in shared] == [True, True, True, True]
+
+
 if __name__ == "__main__":
     host = Host(sys.argv[1], sys.argv[2])
-    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place,)}))
+    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place, records)}))
