@@ -343,7 +343,8 @@ lgc_status lgc_reserve(lgc_ctx *ctx, const lgc_ae *ae /* nullable */, uint64_t k
  *   1 = always the exact radix path.
  *   2 = always the fast path first, whatever happened before.
  * For fewer than 2^18 elements the fast path (k up to 4096) counts every element's
- * magnitude instead of sampling; larger k takes the exact radix path.
+ * magnitude instead of sampling (and is not counted by lgc_stats); larger k takes
+ * the exact radix path.
  * What the switch is for: where very many magnitudes are equal around the k-th
  * largest, as in quantised gradients, no threshold separates about k elements,
  * and reaching the exact path through the failed fast path costs more than
@@ -385,8 +386,9 @@ lgc_status lgc_set_option(lgc_ctx *ctx, lgc_option opt, int64_t value);
  * to the exact path on the device (one selection = one node in lgc_topk /
  * lgc_accumulate_topk, one sampled layer of one node in the per-layer calls),
  * and the device-side error count (bounded waits that expired; positions out
- * of range or out of order in lgc_scatter / lgc_gather).  Returns LGC_EDEVICE
- * if errors != 0. */
+ * of range or out of order in lgc_scatter / lgc_gather).  Selections of fewer
+ * than 2^18 elements, and those that take the exact path outright, are counted
+ * by neither of the first two.  Returns LGC_EDEVICE if errors != 0. */
 lgc_status lgc_stats(lgc_ctx *ctx, uint64_t *fast, uint64_t *fallback, uint64_t *errors);
 
 /* Synchronises and reports the selections (nodes) since the last call of this
