@@ -4,17 +4,46 @@
 // A short vector's selection is a chain of latencies, not of bytes: the radix select over several blocks
 // (k_exact, topk.hip) exchanges its histograms through the device five times, at 5-8 us each.  Here the pass that
 // touches every element (the accumulation, or the read of v) leaves a histogram of its 4096 keys per block; the
-// second launch adds those up, which fixes the leading 11 bits of T*, and flags the keys from there on; the third
+// second launch adds those up, which finds T*'s bin, and flags the keys from there on; the third
 // lists them in one block's LDS and selects there.  Nothing crosses blocks but by the launches' ends.
 // Measured, accumulate + top-k of one node of 100 003 elements, k = 1 000, without a context: 44.5 us before (a
-// clearing launch, the accumulation, k_exact 38 us), 21.3 us now.  A single block that scans v for itself in
+// clearing launch, the accumulation, k_exact 38 us), 20.4 us now.  A single block that scans v for itself in
 // place of the last two launches took 31 us alone: reading and testing 400 KB is too much for one compute unit.
 #include "device_helpers.h"
 
 namespace lgc {
 
 constexpr uint32_t kSmallChunk = 4096;   // elements per block of the first launch
-constexpr int kSmallBins = 2048;         // key >> 20
+constexpr int kSmallBins = 2048;
+
+// The bins: octaves cut into 32 parts from 2^-27 to 2^8, into 8 from 2^-60 and up to 2^73, whole beyond.  What shares T*'s bin
+// is listed and finished by one block: in a run in progress the residuals lie close below T*, and with 8 parts throughout (key >> 20)
+// up to 21 000 of 262 143 elements did (k = 2 621; the list overflows at 12 288), with 32 parts 7 000.  Accumulate + top-k in such a
+// run without a context, us, radix path / 8 parts / 32 parts: 262 143, k = 2 621: 46.9 / 55.8 / 30.9; k = 262: 45.0 / 31.1 / 20.2; 100 003, k = 4 000:
+// 45.8 / 52.8 / 36.9; k = 1 000: 44.9 / 31.6 / 21.2; 20 000, k = 200: 35.6 / 15.6 / 15.7.
+struct SmallZone { uint32_t octave, shift, bin; };
+constexpr SmallZone kSmallZones[] = {{0, 23, 0}, {67, 20, 67}, {100, 18, 67 + 33 * 8}, {135, 20, 331 + 35 * 32}, {200, 23, 1451 + 65 * 8}};
+static_assert(kSmallZones[4].bin + 56 <= kSmallBins, "bins");
+
+__device__ __forceinline__ uint32_t small_bin(const uint32_t key) {
+    uint32_t bin = key >> 23;
+#pragma unroll
+    for (int z = 1; z < 5; ++z) {
+        const uint32_t first = kSmallZones[z].octave << 23;
+        bin = key >= first ? kSmallZones[z].bin + ((key - first) >> kSmallZones[z].shift) : bin;
+    }
+    return bin;
+}
+
+// the least key of a bin
+__device__ __forceinline__ uint32_t small_bin_key(const uint32_t bin) {
+    uint32_t key = bin << 23;
+#pragma unroll
+    for (int z = 1; z < 5; ++z)
+        key = bin >= kSmallZones[z].bin ? (kSmallZones[z].octave << 23) + ((bin - kSmallZones[z].bin) << kSmallZones[z].shift) : key;
+    return key;
+}
+
 // the chunks' histograms lie where a sampled selection keeps its keys: two 16-bit counts per word
 static_assert((size_t)((kMinFastN + kSmallChunk - 1) / kSmallChunk) * (kSmallBins / 2) <= kSample, "room for the chunks' histograms");
 
@@ -61,12 +90,12 @@ __global__ __launch_bounds__(1024) void k_small_pass(SelArgs a) {
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < 4; ++j)
-        if ((uint32_t)j < count) atomicAdd(&hist[key_of(vv[j]) >> 20], 1u);
+        if ((uint32_t)j < count) atomicAdd(&hist[small_bin(key_of(vv[j]))], 1u);
     __syncthreads();
     a.samples[(size_t)node * kSample + blockIdx.x * (kSmallBins / 2) + tid] = hist[2 * tid] | (hist[2 * tid + 1] << 16);
 }
 
-// The candidate bitmap, row counts and records (as k_candidates writes them) of the keys that share T*'s leading bits or lie above:
+// The candidate bitmap, row counts and records (as k_candidates writes them) of the keys in T*'s bin or above:
 // every block adds up the chunks' histograms for itself.  Wavefront w of a block takes 256 elements: part w % 4 of row w / 4.
 __global__ __launch_bounds__(1024) void k_small_flags(SelArgs a) {
     __shared__ __align__(16) uint32_t hist[kSmallBins];
@@ -94,7 +123,7 @@ __global__ __launch_bounds__(1024) void k_small_flags(SelArgs a) {
     hist[2 * tid] = lo; hist[2 * tid + 1] = hi;
     __syncthreads();
     find_rank_bin<kSmallBins, 1024>(hist, a.k, wave_tmp, res);
-    const uint32_t least = res[0] << 20;   // (n >= k keys were counted: the bin exists)
+    const uint32_t least = small_bin_key(res[0]);   // (n >= k keys were counted: the bin exists)
     const int local = wave >> 2, part = wave & 3;
     const uint32_t row = blockIdx.x * kRowsHere + local, nrows = (a.n + kRow - 1) / kRow;
     unsigned long long word = 0;
@@ -129,7 +158,7 @@ __global__ __launch_bounds__(1024) void k_small_flags(SelArgs a) {
         a.row_rec[((size_t)node * a.rec_stride + row) * kRecordWords + lane] = rec[local][lane];
 }
 
-// the finishing launch's list has to hold the selection and the keys that share T*'s leading bits
+// the finishing launch's list has to hold the selection and the keys that share T*'s bin
 bool small_select_covers(uint64_t n, uint64_t k) { return n < kMinFastN && k <= kFinishList / 3; }
 
 void launch_small_select(const SelArgs &a, int batch, bool fused, int cus, hipStream_t st, Bracket br) {
