@@ -335,6 +335,9 @@ lgc_status lgc_reserve(lgc_ctx *ctx, const lgc_ae *ae /* nullable */, uint64_t k
  *       selections of the context before it tries the fast path again: 1
  *       after the first fall-back, twice as many after each further one, 64
  *       at most, and from 1 again once the fast path has served a selection.
+ *       (Short candidate lists go through one launch that holds 12 288 entries;
+ *       a context with room for more first takes the launches that use it, for
+ *       64 selections, when that one falls back.)
  *       It sees the outcomes without any synchronisation: each selection
  *       stores its number to one of two pinned host words, which the host
  *       reads when it queues the next selection, so the switch comes some

@@ -55,6 +55,11 @@ struct lgc_ctx {
     uint32_t *fell_back_host = nullptr, *fell_back_dev = nullptr;
     uint32_t call_number = 0, fell_back_seen = 0;
     int exact_calls_left = 0, penalty = 0;
+    // The one-launch finish holds shorter lists than a context with a large capacity: after a fall-back of it such a context
+    // goes through the many-block launches for some calls.  Bit i: the call i numbers ago was one.
+    uint64_t spare_finishes = 0;
+    uint32_t spare_fell_back = 0;
+    int many_block_calls_left = 0;
     std::vector<hipEvent_t> ev;  // pairs: start, stop
     size_t ev_used = 0;
     char err[256] = {0};
@@ -290,6 +295,7 @@ SelArgs make_args(lgc_ctx *c, const float *g, float *u, float *v, uint64_t n, ui
     return a;
 }
 
+constexpr int kManyBlockCalls = 64;  // selections between the tries of the one-launch finish after it fell back where longer lists are held
 constexpr int kMaxExactCalls = 64;   // most selections in a row that take the exact path outright after fall-backs were seen
 
 // Short vectors are selected exactly by kernels of their own, unless the exact radix path was asked for.
@@ -339,7 +345,26 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         return LGC_OK;
     }
     SelArgs a = make_args(ctx, g, u, v, n, stride, m, k, out_vals, out_idx);
-    const bool finishes_in_one = takes_finish(n, k);
+    ctx->last_seg = nullptr;
+    bool small = takes_small_path(ctx, n, k);
+    bool fast = ctx->opt_path != 1 && n >= kMinFastN;
+    if (fast) {
+        a.rank = choose_rank((uint32_t)n, (uint32_t)k);
+        fast = a.rank <= kSample / 4 &&
+               1.5 * expected_candidates((double)n, (double)k) + 4096.0 <= (double)ctx->cap;
+    }
+    bool finishes_in_one = takes_finish(n, k);
+    // Lists beyond what the one-launch finish holds but within the context's capacity (many equal magnitudes around the k-th
+    // largest, in a context for longer vectors: 4 M elements, k = 1 000, 20 000 of them equal: 57 us through many blocks, 105 falling back)
+    const bool spare_finish = fast && finishes_in_one && ctx->cap > kFinishList;
+    const uint32_t fell_back = ctx->fell_back_host ? ((volatile uint32_t *)ctx->fell_back_host)[0] : 0u;
+    const uint32_t age = ctx->call_number - fell_back;
+    const bool by_finish = fell_back != 0 && age < 64 && (ctx->spare_finishes >> age & 1u);
+    if (by_finish && fell_back != ctx->spare_fell_back) {
+        ctx->spare_fell_back = fell_back;
+        ctx->many_block_calls_left = kManyBlockCalls;
+    }
+    if (spare_finish && ctx->many_block_calls_left > 0) { --ctx->many_block_calls_left; finishes_in_one = false; }
     {   // a carried threshold aims at 1.5 k candidates, or at what a sample would give where that is fewer (large k)
         const double sampled = expected_candidates((double)n, (double)k) / (double)k;
         a.carry_target = (float)log2(sampled < 1.5 ? sampled : 1.5);
@@ -349,25 +374,18 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         const double room = 0.75 * log2(holds / (double)k);
         a.carry_most = (float)(room < log2(2.2) ? room : log2(2.2));
     }
-    ctx->last_seg = nullptr;
-    bool small = takes_small_path(ctx, n, k);
-    bool fast = ctx->opt_path != 1 && n >= kMinFastN;
-    if (fast) {
-        a.rank = choose_rank((uint32_t)n, (uint32_t)k);
-        fast = a.rank <= kSample / 4 &&
-               1.5 * expected_candidates((double)n, (double)k) + 4096.0 <= (double)ctx->cap;
-    }
     if ((fast || small) && ctx->opt_path == 0 && ctx->fell_back_host) {
         // data on which the fast path (or the short vectors' own) keeps failing (very many equal magnitudes around the k-th largest): reaching
         // the exact path through the failed fast path costs nearly twice what taking it outright does.  Each newly
         // seen fall-back doubles the number of selections that take the exact path outright before the fast path is
         // tried again (1, 2, 4, ... 64); a fast-path success seen after the last fall-back resets it.
-        const uint32_t fell_back = ((volatile uint32_t *)ctx->fell_back_host)[0];
         const uint32_t served = ((volatile uint32_t *)ctx->fell_back_host)[1];
         if (fell_back != ctx->fell_back_seen) {
             ctx->fell_back_seen = fell_back;
-            ctx->penalty = ctx->penalty ? (ctx->penalty * 2 > kMaxExactCalls ? kMaxExactCalls : ctx->penalty * 2) : 1;
-            ctx->exact_calls_left = ctx->penalty;
+            if (!by_finish) {
+                ctx->penalty = ctx->penalty ? (ctx->penalty * 2 > kMaxExactCalls ? kMaxExactCalls : ctx->penalty * 2) : 1;
+                ctx->exact_calls_left = ctx->penalty;
+            }
         } else if ((int32_t)(served - fell_back) > 0) {
             ctx->penalty = 0;
         }
@@ -378,6 +396,7 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
     if (fast || small) {
         if (++ctx->call_number == 0) ctx->call_number = 1;
         a.notify_value = ctx->call_number;
+        ctx->spare_finishes = ctx->spare_finishes << 1 | (uint64_t)(spare_finish && finishes_in_one && fast);
     }
     ctx->cur ^= 1;  // this call uses the clean set and cleans the other one for the next call
     if (small) {

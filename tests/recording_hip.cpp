@@ -53,7 +53,8 @@ hipError_t hipMalloc(void **p, size_t bytes) {
     return hipSuccess;
 }
 hipError_t hipFree(void *) { return hipSuccess; }
-hipError_t hipHostMalloc(void **p, size_t bytes, unsigned) { *p = calloc(1, bytes); return *p ? hipSuccess : hipErrorOutOfMemory; }
+void *pinned;   // the last pinned allocation
+hipError_t hipHostMalloc(void **p, size_t bytes, unsigned) { *p = pinned = calloc(1, bytes); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipHostGetDevicePointer(void **d, void *h, unsigned) { *d = h; return hipSuccess; }
 hipError_t hipGetSymbolAddress(void **p, const void *) { *p = static_array; return hipSuccess; }

@@ -109,6 +109,28 @@ def records(h):
     return out
 
 
+def fall_backs_of_the_one_launch_finish(h):
+    """Kernels of selections on a context, the first of which reports a fall-back; the same with every selection that goes
+    through the one-launch finish reporting one."""
+    out = {}
+    for name, max_n, max_k, every in (("larger", 25_600_000, 25_600, False), ("own", 1 << 20, 1000, False), ("larger, each", 25_600_000, 25_600, True)):
+        ctx = h.ctx(max_n, max_k, 1)
+        words = C.cast(p.in_dll(h.fake, "pinned"), C.POINTER(C.c_uint32))
+        seen, reported, numbered = [], False, 0
+        for _ in range(140):
+            h.topk(ctx, 1 << 20, 1000, 1)
+            kernel = "finish" if "k_finish_or_exact" in h.raw else "many" if "k_output_or_exact" in h.raw else "exact"
+            numbered += kernel != "exact"            # selections that take the exact path outright report nothing and have no number
+            if kernel == "finish" and (every or not reported):
+                words[0], reported = numbered, True
+            elif kernel != "exact":
+                words[1] = numbered
+            seen.append(kernel)
+        out[name] = seen
+        h.lib.lgc_destroy(ctx)
+    return out
+
+
 @pytest.fixture(scope="module")
 def answers(tmp_path_factory):
     """Every scenario (a function above, by name), run in one process of its own."""
@@ -142,6 +164,14 @@ def test_records_are_kept_and_allocated_where_the_rule_asks_for_them(answers):
     assert [all("ELb1EEEv" in x for x in passes) for passes in shared] == [True, True, True, True]
 
 
+def test_fall_backs_of_the_one_launch_finish(answers):
+    got = answers["fall_backs_of_the_one_launch_finish"]
+    # a context that holds longer lists uses them; one of the selection's own size holds no more and takes the exact path once
+    assert got["larger"] == ["finish"] + ["many"] * 64 + ["finish"] * 75
+    assert got["own"] == ["finish", "exact"] + ["finish"] * 138
+    assert got["larger, each"] == (["finish"] + ["many"] * 64) * 2 + ["finish"] + ["many"] * 9
+
+
 if __name__ == "__main__":
     host = Host(sys.argv[1], sys.argv[2])
-    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place, records)}))
+    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place, records, fall_backs_of_the_one_launch_finish)}))
