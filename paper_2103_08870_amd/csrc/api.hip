@@ -302,9 +302,10 @@ constexpr int kMaxExactCalls = 64;   // most selections in a row that take the e
 bool takes_small_path(const lgc_ctx *ctx, uint64_t n, uint64_t k) { return ctx->opt_path != 1 && small_select_covers(n, k); }
 
 // Short candidate lists of vectors that are not too long go from the bitmap to the output in one launch of one block per
-// node.  The line: one block takes 1.3 us per 1024 entries that many blocks take side by side (3 x 3.33 M elements,
-// 6 200 expected, accumulation and selection: 69.2 us in one launch, 65.1 us in two; 2^20 elements, 1 900
-// expected: 10.4 us against 17 for the launches themselves).
+// node.  The line: one block takes 1.3 us per 1024 entries that many blocks take side by side, which from about 4 500 expected
+// entries on is more than a launch.  Whole step, us, one launch / many blocks: 2^20 elements, 1 920 expected: 26.8 / 29.8, 3 454: 32.0 / 32.9,
+// 4 443: 35.1 / 34.0, 5 646: 38.8 / 34.5; 4 M, 2 036: 34.1 / 37.5, 3 804: 39.1 / 40.4, 4 887: 41.9 / 42.1, 6 056: 45.0 / 43.0;
+// 3 and 8 nodes alike (8 x 4 M, 3 804: 141.0 / 142.7, 6 056: 146.9 / 145.2).
 bool takes_finish(uint64_t n, uint64_t k) {
     return (n + kRow - 1) / kRow <= kFinishRows && expected_candidates((double)n, (double)k) <= 4096.0;
 }
