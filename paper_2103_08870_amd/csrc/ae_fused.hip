@@ -11,22 +11,26 @@
 //   x w = h h' + (h m' + m h') + (m m' + h l' + l h') + terms below 2^-26 |x w|
 // so six bf16 products, exact in the fp32 accumulators' input, take the place of one fp32 product.  The matrix
 // cores run bf16 at 16 times the fp32 rate: 2.7 times fewer matrix-core cycles for the same precision (the sums are
-// rounded once per 16 products instead of once per 2).  The last layer of each stack adds its few products per output
-// in 64 bits: the cost cannot be told from none (4 x 25 600: 26.0 us either way), and in 32 bits those sums were over half of the latent's error.
+// rounded once per 16 products instead of once per 2).  The last layer of each stack adds its few products per output in
+// 64 bits: the cost cannot be told from none (4 x 25 600: 26.0 us either way), and in 32 bits those sums were over half
+// of the latent's error.
 // Measured against one fp32-MFMA launch per deep layer (ae_mfma.hip, which other stacks still use): 4 nodes x 25 600
-// values, encoder 79.4 -> 26.7 us (165 TFLOP/s of fp32 products), decoder 57.9 -> 21.4 us (126); 8 x 67 000, both
-// together 468 -> 228 us (163); 1 x 1 023 (latency) 79 -> 29 us.  Relative error against 64 bits, six
-// sizes from 1 x 500 to 8 x 67 000 x six seeds, mean (least to largest): latent 1.15e-7 (0.87 to 1.46) -> 0.41e-7 (0.34 to 0.51; 0.99e-7
-// with the last sums in 32 bits), decoder 3.86e-8 (2.96 to 5.54) -> 3.46e-8 (2.81 to 4.93; 3.73e-8): lower at every size with every seed.  What bounds it: while a compute unit has blocks its
-// matrix cores are busy 63 % of the cycles (encoder) and 46 % (decoder) at a clock that drops to 1.9 GHz.
-// The split is exact only for finite values; an Inf would meet products of both signs.  Such a
-// value (or one that rounds to Inf) leaves a NaN among its parts, which makes every output it reaches a NaN.  And it is exact only while the
-// parts are normal numbers: these matrix instructions take smaller ones for zero, so parts below 2^-126 are lost.  What that can
-// do to an output has a bound that the weights give (fused_limits).  A block with an output that is not finite, or is small enough
-// for the bound to matter, redoes its outputs in plain fp32 on the fp32 matrix cores, which keep small numbers (inputs of about 1e-33, no
-// biases: the reconstruction is 5.7e-7 off; 9.4e-4 without the redo, 7.3e-7 with fp32 launches).  Every block doing so: 4 nodes x 25 600 values,
-// encoder 32 -> 96 us, decoder 26 -> 53 us; 8 x 67 000: 146 -> 467 and 92 -> 231 us (one fp32-MFMA launch per layer:
-// 83, 59, 270 and 194 us; one position after the other on the vector units: 3.3, 1.6, 16 and 8 ms).
+// values, encoder 79.4 -> 26.8 us (165 TFLOP/s of fp32 products), decoder 58.0 -> 21.3 us (126); 8 x 67 000, both
+// together 468 -> 230 us (162); 1 x 1 023 (latency) 79 -> 29 us.  Relative error against 64 bits, six sizes from 1 x 500 to
+// 8 x 67 000 x six seeds, mean (least to largest): latent 1.15e-7 (0.87 to 1.46) -> 0.41e-7 (0.34 to 0.51; 0.99e-7 with the
+// last sums in 32 bits), decoder 3.86e-8 (2.96 to 5.54) -> 3.46e-8 (2.81 to 4.93; 3.73e-8): lower at every size with every
+// seed.  What bounds it: while a compute unit has blocks its matrix cores are busy 54-57 % of the cycles (encoder) and
+// 39-44 % (decoder).
+//
+// The split is exact only for finite values; an Inf would meet products of both signs.  Such a value (or one that rounds
+// to Inf) leaves a NaN among its parts, which makes every output it reaches a NaN.  And it is exact only while the parts
+// are normal numbers: these matrix instructions take smaller ones for zero, so parts below 2^-126 are lost.  What that can
+// do to an output has a bound that the weights give (fused_limits).  A block with an output that is not finite, or is
+// small enough for the bound to matter, redoes its outputs in plain fp32 on the fp32 matrix cores, which keep small numbers
+// (inputs of about 1e-33, no biases: the reconstruction is 5.7e-7 off; 9.4e-4 without the redo, 7.3e-7 with fp32
+// launches).  Every block doing so: 4 nodes x 25 600 values, encoder 32 -> 95 us, decoder 26 -> 53 us; 8 x 67 000: 141 -> 466
+// and 89 -> 232 us (one fp32-MFMA launch per layer: 83, 59, 270 and 194 us; one position after the other on the vector
+// units: 3.3, 1.6, 16 and 8 ms).
 //
 // Operand layout of v_mfma_f32_32x32x16_bf16: lane l supplies A[i = l % 32][k = 8 (l / 32) + 0..7] and
 // B[k = 8 (l / 32) + 0..7][j = l % 32]; result r of 16 is C[i = 8 (r / 4) + 4 (l / 32) + r % 4][j = l % 32].  Here
