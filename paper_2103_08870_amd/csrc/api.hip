@@ -30,8 +30,7 @@ struct lgc_ctx {
     int cur = 0;                      // set the next call will use (it is clean)
     int cus = 1;                      // compute units of the device
     uint32_t rows = 0, status_cand_stride = 0, status_exact_stride = 0;
-    uint32_t *samples = nullptr, *row_count = nullptr, *row_super = nullptr;
-    uint32_t supers = 0;
+    uint32_t *samples = nullptr, *row_count = nullptr;
     unsigned long long *bitmap = nullptr;
     uint32_t *cand_idx = nullptr, *cand_val = nullptr;
     uint32_t *row_rec = nullptr;      // records of the rows with few candidates (an allocation of its own, or none), room for rec_rows of them
@@ -214,8 +213,8 @@ StateLayout state_layout(int max_batch, uint32_t status_cand_stride, uint32_t st
 // device memory.  Everything before `samples` (statistics, carried thresholds, state sets) must start at zero.
 struct ScratchLayout {
     bool ok = false;
-    uint32_t cap = 0, rows = 0, supers = 0, status_cand_stride = 0, status_exact_stride = 0, state_words = 0;
-    size_t stats = 0, carry = 0, state[2] = {0, 0}, samples = 0, row_count = 0, row_super = 0, bitmap = 0, cand_idx = 0, cand_val = 0;
+    uint32_t cap = 0, rows = 0, status_cand_stride = 0, status_exact_stride = 0, state_words = 0;
+    size_t stats = 0, carry = 0, state[2] = {0, 0}, samples = 0, row_count = 0, bitmap = 0, cand_idx = 0, cand_val = 0;
     size_t bytes = 0;
 };
 
@@ -228,7 +227,6 @@ ScratchLayout scratch_layout(uint64_t max_n, uint64_t max_k, int max_batch, bool
     const StateLayout L = state_layout(max_batch, s.status_cand_stride, s.status_exact_stride);
     if (L.words >= (1ull << 31)) return s;
     s.state_words = (uint32_t)L.words;
-    s.supers = (s.rows + kSuperRows - 1) / kSuperRows;
     const size_t B = (size_t)max_batch, A = 256;
     size_t off = 0;
     auto carve = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, A); return o; };
@@ -238,7 +236,6 @@ ScratchLayout scratch_layout(uint64_t max_n, uint64_t max_k, int max_batch, bool
     s.state[1] = two_state_sets ? carve(L.words * 4) : s.state[0];
     s.samples = carve(B * kSample * 4);
     s.row_count = carve(B * s.rows * 4);
-    s.row_super = carve(B * s.supers * 4);
     s.bitmap = carve(B * (size_t)s.rows * kRowWords * 8);
     s.cand_idx = carve(B * (size_t)s.cap * 4);
     s.cand_val = carve(B * (size_t)s.cap * 4);
@@ -250,7 +247,7 @@ ScratchLayout scratch_layout(uint64_t max_n, uint64_t max_k, int max_batch, bool
 void bind_scratch(lgc_ctx *c, void *base_ptr, const ScratchLayout &s) {
     char *base = (char *)base_ptr;
     c->scratch = base_ptr;
-    c->cap = s.cap; c->rows = s.rows; c->supers = s.supers;
+    c->cap = s.cap; c->rows = s.rows;
     c->status_cand_stride = s.status_cand_stride; c->status_exact_stride = s.status_exact_stride;
     c->state_words = s.state_words;
     c->stats = (Stats *)(base + s.stats);
@@ -259,7 +256,6 @@ void bind_scratch(lgc_ctx *c, void *base_ptr, const ScratchLayout &s) {
     c->state[1] = (uint32_t *)(base + s.state[1]);
     c->samples = (uint32_t *)(base + s.samples);
     c->row_count = (uint32_t *)(base + s.row_count);
-    c->row_super = (uint32_t *)(base + s.row_super);
     c->bitmap = (unsigned long long *)(base + s.bitmap);
     c->cand_idx = (uint32_t *)(base + s.cand_idx);
     c->cand_val = (uint32_t *)(base + s.cand_val);
@@ -288,7 +284,6 @@ SelArgs make_args(lgc_ctx *c, const float *g, float *u, float *v, uint64_t n, ui
     a.status_exact = (unsigned long long *)(cur + L.status_exact);
     a.next_state = c->state[c->cur ^ 1]; a.next_words = c->single_state ? 0u : c->state_words;
     a.samples = c->samples; a.row_count = c->row_count; a.bitmap = c->bitmap;
-    a.row_super = c->row_super; a.supers = c->supers;
     a.row_rec = c->row_rec; a.rec_stride = (a.n + kRow - 1) / kRow;
     a.cand_idx = c->cand_idx; a.cand_val = c->cand_val;
     a.out_vals = out_vals; a.out_idx = out_idx;

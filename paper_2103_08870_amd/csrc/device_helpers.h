@@ -103,6 +103,12 @@ __device__ __forceinline__ uint32_t block_scan(const uint32_t x, uint32_t *tmp, 
     return incl - x + wave_sum(lane < wave ? t : 0u);
 }
 
+// Candidates per kGroupRows rows of a node, in long vectors.  They lie where the exact path keeps its runs' counts: by the
+// time a node falls back the gather has read them, and each 4096 elements have two words there.
+__device__ __forceinline__ uint32_t *group_counts(const SelArgs &a, const int node) {
+    return (uint32_t *)(a.status_exact + (size_t)node * a.status_exact_stride);
+}
+
 // An ordinary launch, or, with timing events, the launch form that stamps them itself.
 template <typename K, typename... Args>
 static void launch_timed(K kernel, dim3 grid, dim3 block, hipStream_t st, Bracket e, Args... args) {

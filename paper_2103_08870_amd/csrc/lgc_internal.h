@@ -36,7 +36,7 @@ constexpr int kRowWords = 16;
 // index order; 256 bytes apart, of which 192 are used
 constexpr int kRecord = 32;
 constexpr int kRecordWords = 64;
-constexpr uint32_t kSuperRows = 8192;           // rows per group whose candidates are summed ahead of the gather
+constexpr int kGroupRows = 128;                 // rows per block of the gather, whose candidates are summed ahead of it in long vectors
 
 // The streaming kernels are launched over at most this many rows (a little over 2 GB of g, u, v
 // traffic; the ResNet50-sized workload, 4 x 25 000 rows, is one launch): measured on MI355X,
@@ -135,8 +135,8 @@ struct SelArgs {
     // bulk scratch
     uint32_t *samples;        // [batch][kSample]
     uint32_t *row_count;      // [batch][rows]  candidates per row
-    uint32_t *row_super;      // [batch][supers] candidates per group of kSuperRows rows (vectors of more than one group)
-    uint32_t supers;           // groups per node in row_super; 0: the gather adds up the row counts themselves
+    int groups_counted;       // 1: the candidates of every kGroupRows rows are summed by a launch of its own (group_counts, device_helpers.h)
+    int sparse_bitmap;        // 1: the lines of rows without candidates are not written
     unsigned long long *bitmap;  // [batch][rows][kRowWords]
     uint32_t *row_rec;           // [batch][rec_stride][kRecordWords]  records of the rows with few candidates (null: none are kept)
     uint32_t rec_stride;         // rows of the call's vectors

@@ -177,24 +177,16 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t x, uint32_t *tmp /*[16]*/
 // adds the block's count to the node's total.  The block's part of the bitmap is staged in LDS;
 // the work is balanced over the threads by output position (binary search of the owning row,
 // then of the bit inside the row), whatever the spread of the candidates.
-// Long vectors (a.supers != 0): the candidates of every kSuperRows rows are summed by a kernel of their own, so
-// that a gather block adds up at most kSuperRows row counts (and a few sums) to find its place
-// instead of all the counts before it, which at 2^28 elements was most of the gather's time.
-
-__global__ __launch_bounds__(1024) void k_row_sums(SelArgs a) {
-    __shared__ uint32_t tmp[16];
-    const uint32_t nrows = (a.n + kRow - 1) / kRow;
-    const uint32_t *cnt = a.row_count + (size_t)blockIdx.y * a.rows;
-    const uint32_t lo = blockIdx.x * kSuperRows;
-    uint32_t part = 0;
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {   // rows per node are a multiple of 4 in the scratch; rows past nrows are not read
-        const uint32_t i0 = lo + (r * 1024 + threadIdx.x) * 4;
-        if (i0 + 3 < nrows) { const u4 x = *(const u4 *)(cnt + i0); part += x[0] + x[1] + x[2] + x[3]; }
-        else for (uint32_t i = i0; i < nrows; ++i) part += cnt[i];
-    }
-    const uint32_t total = block_sum<1024>(part, tmp);
-    if (threadIdx.x == 0) a.row_super[(size_t)blockIdx.y * a.supers + blockIdx.x] = total;
+// Long vectors (a.groups_counted): the candidates of every block's rows are summed by a kernel of their own, one wavefront each, so that a
+// block adds up the sums before its own instead of all the row counts.
+__global__ __launch_bounds__(1024) void k_group_counts(SelArgs a) {
+    const int node = blockIdx.y, lane = threadIdx.x & 63;
+    const uint32_t nrows = (a.n + kRow - 1) / kRow, g = blockIdx.x * 16 + (threadIdx.x >> 6), r = g * kGroupRows + 2 * lane;
+    static_assert(kGroupRows == 2 * 64, "two rows per lane");
+    if (g * kGroupRows >= nrows) return;
+    const uint32_t *cnt = a.row_count + (size_t)node * a.rows;
+    const uint32_t x = wave_sum((r < nrows ? cnt[r] : 0u) + (r + 1 < nrows ? cnt[r + 1] : 0u));
+    if (lane == 0) group_counts(a, node)[g] = x;
 }
 
 // The i-th flagged element of a row of the bitmap, in element order (s, lane, j).
@@ -247,6 +239,7 @@ __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
     const float *v = a.v + (size_t)node * a.stride;
     uint32_t *cidx = a.cand_idx + (size_t)node * a.cap, *cval = a.cand_val + (size_t)node * a.cap;
 
+    if (HIST && a.groups_counted && group_counts(a, node)[blockIdx.x] == 0) return;   // nothing to list (block-uniform)
     // all independent loads first: my row's count, my slice of the bitmap, the counts before the block
     const uint32_t c = (uint32_t)tid < mine ? cnt[first + tid] : 0u;
     ulonglong2 bm[kPairs];
@@ -256,11 +249,12 @@ __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
         bm[q] = (w2 * 2 < mine * kRowWords) ? *(const ulonglong2 *)(bitmap + (size_t)w2 * 2) : ulonglong2{0ull, 0ull};
     }
     const uint32_t t_est = HIST ? s->t_est : 0u;
-    // candidates before the block: whole groups of kSuperRows rows (summed beforehand when the
-    // vector has more than one group), then the rows of the block's own group
-    const uint32_t group = a.supers ? first / kSuperRows : 0u;
-    uint32_t part = (uint32_t)tid < group ? a.row_super[(size_t)node * a.supers + tid] : 0u;
-    for (uint32_t i0 = group * kSuperRows + tid * 4; i0 < first; i0 += 4 * THREADS * 4) {   // first and the row stride are multiples of 4
+    // candidates before the block
+    uint32_t part = 0;
+    if (a.groups_counted) {
+        const uint32_t *sums = group_counts(a, node);
+        for (uint32_t i = tid; i < blockIdx.x; i += THREADS) part += sums[i];
+    } else for (uint32_t i0 = tid * 4; i0 < first; i0 += 4 * THREADS * 4) {   // first and the row stride are multiples of 4
         u4 x[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) x[r] = (i0 + r * 4 * THREADS < first) ? *(const u4 *)(cnt + i0 + r * 4 * THREADS) : (u4){0u, 0u, 0u, 0u};
@@ -320,6 +314,8 @@ __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
     }
 }
 
+constexpr uint32_t kGroupsCountedFrom = 32 * 1024;
+
 template <int ROWS, int THREADS>
 static void launch_gather_shape(const SelArgs &g, uint32_t nrows, int batch, hipStream_t st) {
     const dim3 grid((nrows + ROWS - 1) / ROWS, batch);
@@ -328,19 +324,17 @@ static void launch_gather_shape(const SelArgs &g, uint32_t nrows, int batch, hip
     else hipLaunchKernelGGL((k_gather<true, ROWS, THREADS>), grid, dim3(THREADS), 0, st, g);
 }
 
-void launch_gather(const SelArgs &a, int batch, hipStream_t st) {
-    const uint32_t nrows = (a.n + kRow - 1) / kRow;
-    // the sums per group pay for their launch from about 32 K rows on (measured: at 25 K rows the gather
-    // gains 0.5 us from them, at 256 K rows 17 us)
-    SelArgs g = a;
-    if (nrows > 4 * kSuperRows)
-        hipLaunchKernelGGL(k_row_sums, dim3((nrows + kSuperRows - 1) / kSuperRows, batch), dim3(1024), 0, st, g);
-    else
-        g.supers = 0;
+void launch_gather(const SelArgs &args, int batch, hipStream_t st) {
+    SelArgs a = args;
+    const uint32_t nrows = (a.n + kRow - 1) / kRow, groups = (nrows + kGroupRows - 1) / kGroupRows;
+    // The sums pay for their launch from about 32 K rows on: 8 x 43.5 K rows, whole step without / with them and the early end of blocks
+    // without candidates: 1318 / 1305 us, 4 x 39 K 601 / 594, 1 x 254 K (0.1 %) 943 / 934; 4 x 25 K rows 382.9 / 383.6, by layers 409 / 411.
+    a.groups_counted = nrows > kGroupsCountedFrom;
+    if (a.groups_counted) hipLaunchKernelGGL(k_group_counts, dim3((groups + 15) / 16, batch), dim3(1024), 0, st, a);
     // 128 rows per block of 1024 threads; measured on the ResNet50-sized workload (4 nodes): 64 rows x 512
     // threads 18.0 us, 64 x 1024 20.2, 128 x 512 19.8, 64 x 256 21.5, this shape 18.2 (the same within noise:
     // what the kernel costs is its chain of dependent memory round trips, not the search work of its busiest block)
-    launch_gather_shape<128, 1024>(g, nrows, batch, st);
+    launch_gather_shape<kGroupRows, 1024>(a, nrows, batch, st);
 }
 
 // Adds, for every candidate i < total that passes `member`, one count to hist[digit(d)], where
