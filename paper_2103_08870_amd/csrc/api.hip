@@ -284,7 +284,7 @@ SelArgs make_args(lgc_ctx *c, const float *g, float *u, float *v, uint64_t n, ui
     a.status_exact = (unsigned long long *)(cur + L.status_exact);
     a.next_state = c->state[c->cur ^ 1]; a.next_words = c->single_state ? 0u : c->state_words;
     a.samples = c->samples; a.row_count = c->row_count; a.bitmap = c->bitmap;
-    a.row_rec = c->row_rec; a.rec_stride = (a.n + kRow - 1) / kRow;
+    a.row_rec = c->row_rec; a.rec_stride = (a.n + kRow - 1) / kRow; a.rec_most = kRecord;
     a.cand_idx = c->cand_idx; a.cand_val = c->cand_val;
     a.out_vals = out_vals; a.out_idx = out_idx;
     return a;
@@ -389,6 +389,14 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
     }
     const bool long_list = expected_candidates((double)n, (double)k) > 131072.0;
     if (!takes_records(n, k, batch) || (uint64_t)batch * a.rec_stride > ctx->rec_rows) a.row_rec = nullptr;
+    // Long lists with records: the pass itself can write the zeros of what it takes for selected, from a threshold that the sample or
+    // the carried one puts where T* is expected; the output then touches u and v where that was wrong only (2^28 elements, 1 %: output 212 -> 47 us, the
+    // scatter after it 146 -> 119, the pass 884 -> 897, whole step 1387 -> 1220).  Whether it pays for a node its previous selection says (topk.hip).
+    if (fast && fused && long_list && a.row_rec && a.carry) {
+        a.zero_early = 1; a.rec_most = kZeroRecord;
+        const double rk = (double)k * (double)kSample / (double)n;
+        a.rank_zero = rk < 1.0 ? 1u : (uint32_t)(rk + 0.5);
+    }
     if (fast || small) {
         if (++ctx->call_number == 0) ctx->call_number = 1;
         a.notify_value = ctx->call_number;
@@ -405,7 +413,7 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         launch_sample(a, batch, fused, st);   // also clears the next call's state set
         launch_candidates(a, batch, fused, st, profile_bracket(ctx));
         if (finishes_in_one) launch_finish_from_bitmap(a, batch, true, ctx->cus, st);
-        else launch_gather(a, batch, st);
+        else launch_gather(a, batch, ctx->cus, st);
         a.force = 0;
         // the exact path as fall-back, for nodes the fast path hands back: with short candidate lists it rides in
         // the output launch, otherwise one launch of its own that nearly always has nothing to do
@@ -1288,7 +1296,7 @@ static lgc_status run_segmented(lgc_ctx *ctx, const lgc_segments *seg, const flo
     if (seg->n_sampled) {
         launch_seg_estimate(a, batch, fused, st);   // also clears the next call's state set
         launch_candidates(a, batch, fused, st, profile_bracket(ctx));
-        launch_gather(a, batch, st);
+        launch_gather(a, batch, ctx->cus, st);
     } else {
         launch_clear(a.next_state, a.next_words, st);
         if (fused) {

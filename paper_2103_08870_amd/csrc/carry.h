@@ -26,7 +26,7 @@ __device__ __forceinline__ void carry_update(Carry *c, const uint32_t n, const u
     const bool same = !fresh && c->n == n && c->k == k;     // the record is the previous selection's, of this shape
     const bool follows = same && c->len > 0;
     const float l1 = c->log2_t[0], l2 = c->log2_t[1];
-    uint32_t len = 0, next = 0, fails = same ? c->fails : 0u, held = same ? c->held : 0u;
+    uint32_t len = 0, next = 0, next_t = 0, fails = same ? c->fails : 0u, held = same ? c->held : 0u;
     if (carried) {
         if (!ok) { fails = fails < 5 ? fails + 1 : 5u; held = 0; }
         else if (++held >= 64) { fails = fails ? fails - 1 : 0u; held = 0; }
@@ -44,13 +44,13 @@ __device__ __forceinline__ void carry_update(Carry *c, const uint32_t n, const u
             const float gap = fmaxf(fminf(fmaxf(target / slope, 0.25f * used), 4.f * used), 4.f * miss);
             if (gap <= 0.25f && gap * slope <= most) {
                 const uint32_t t = __float_as_uint(exp2f(2.f * l0 - l1 - gap));
-                if (t >= kMinNormal && t < kInf) next = t;
+                if (t >= kMinNormal && t < kInf) { next = t; next_t = __float_as_uint(exp2f(2.f * l0 - l1)); }
             }
         }
     }
     c->n = n; c->k = k; c->len = len;
     c->log2_t[0] = l0; c->log2_t[1] = l1; c->log2_t[2] = l2;
-    c->next_t_est = next; c->fails = fails; c->held = held; c->miss = miss;
+    c->next_t_est = next; c->next_t = next_t; c->fails = fails; c->held = held; c->miss = miss;
 }
 
 }  // namespace lgc

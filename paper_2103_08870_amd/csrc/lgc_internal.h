@@ -36,6 +36,9 @@ constexpr int kRowWords = 16;
 // index order; 256 bytes apart, of which 192 are used
 constexpr int kRecord = 32;
 constexpr int kRecordWords = 64;
+// where the pass zeroes what it takes for selected (SelArgs::zero_early), records hold fewer candidates, and their u after the positions
+constexpr int kZeroRecord = 24;
+static_assert(2 * kZeroRecord + kZeroRecord / 2 <= kRecordWords && kRecord + kRecord / 2 <= kRecordWords, "a record");
 constexpr int kGroupRows = 128;                 // rows per block of the gather, whose candidates are summed ahead of it in long vectors
 
 // The streaming kernels are launched over at most this many rows (a little over 2 GB of g, u, v
@@ -54,7 +57,10 @@ struct Sel {
     uint32_t quota;       // how many elements with key == T* are taken (lowest indices first)
     uint32_t fast_ok;     // 1: the fast path produced this node's output
     uint32_t carried;     // 1: t_est was carried over from earlier selections, not sampled
-    uint32_t pad[10];
+    uint32_t t_zero;      // zero_early: the pass zeroes the elements with key >= t_zero (>= t_est; ~0: none) of the rows that keep a record
+    uint32_t recorded;    // zeros: candidates of the rows with up to kZeroRecord, and rows with more (atomic adds in the gather kernel only)
+    uint32_t crowded;
+    uint32_t pad[7];
 };
 static_assert(sizeof(Sel) == 64, "Sel is one 64-byte record");
 
@@ -91,7 +97,9 @@ struct Carry {
     uint32_t held;        // carried selections that held since `fails` last changed
     float miss;           // how far T* lay from the trend of the two selections before it (log2), largest of the
                           // recent selections: each selection's own miss, or 0.85 of the value before
-    uint32_t pad[5];
+    uint32_t next_t;      // T* (key) that the offer was made from: what the next selection's is expected to be
+    uint32_t zeros_pay;   // few of the selection's rows held more candidates than a record: the pass may zero what it takes for selected
+    uint32_t pad[3];
 };
 static_assert(sizeof(Carry) == 64, "Carry is one 64-byte record");
 
@@ -140,6 +148,10 @@ struct SelArgs {
     unsigned long long *bitmap;  // [batch][rows][kRowWords]
     uint32_t *row_rec;           // [batch][rec_stride][kRecordWords]  records of the rows with few candidates (null: none are kept)
     uint32_t rec_stride;         // rows of the call's vectors
+    uint32_t rec_most;           // candidates that a record holds: kRecord, or kZeroRecord
+    int zero_early;              // 1: the pass writes zeros in the place of the elements of u and v that it takes for selected; what
+                                 // is not selected after all is written back (bit 31 of a listed position: zeroed by the pass)
+    uint32_t rank_zero;          // rank of the sample's order statistic from which on it does
     uint32_t *cand_idx;       // [batch][cap]  gathered, index-ordered
     uint32_t *cand_val;
     float *out_vals;          // [batch][k]
@@ -167,7 +179,7 @@ void launch_accumulate(const float *g, float *u, float *v, uint32_t n, int batch
 void launch_clear(uint32_t *words, uint32_t count, hipStream_t st);
 void launch_sample(const SelArgs &a, int batch, bool fused, hipStream_t st);
 void launch_candidates(const SelArgs &a, int batch, bool fused, hipStream_t st, Bracket br = Bracket());
-void launch_gather(const SelArgs &a, int batch, hipStream_t st);
+void launch_gather(const SelArgs &a, int batch, int cus, hipStream_t st);
 bool launch_output_from_candidates(const SelArgs &a, int batch, bool direct, int cus, hipStream_t st);
 void launch_exact(const SelArgs &a, int batch, int cus, hipStream_t st);
 // the candidates' bitmap straight to the output, one block per node (lists of up to kFinishList entries), with the exact

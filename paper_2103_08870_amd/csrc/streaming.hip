@@ -18,9 +18,11 @@ namespace lgc {
 // is touched once per call, so all loads and stores are non-temporal: on this part that alone
 // lifts the fused kernel from about 60 % to 72-77 % of the HBM peak (and the plain read of v in
 // the selection-only form likewise; the few candidates' values are read again by the gather).
-template <bool FUSED>
+// ZERO: elements with key >= t_zero are stored as zeros; bits, ubits: what v and u would have been.
+template <bool FUSED, bool ZERO>
 __device__ __forceinline__ void full_row(const float *__restrict__ g, float *__restrict__ u, float *__restrict__ v,
-                                         const float m, uint32_t (&bits)[4][4]) {
+                                         const float m, uint32_t (&bits)[4][4], const uint32_t t_zero, uint32_t (&ubits)[4][4]) {
+    static_assert(FUSED || !ZERO, "a pass that writes");
     f4 gg[4], uu[4], vv[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -35,11 +37,21 @@ __device__ __forceinline__ void full_row(const float *__restrict__ g, float *__r
         if (FUSED) {
 #pragma unroll
             for (int j = 0; j < 4; ++j) { float x = uu[s][j], y = vv[s][j]; accum1(gg[s][j], x, y, m); uu[s][j] = x; vv[s][j] = y; }
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            bits[s][j] = __float_as_uint(vv[s][j]);
+            if (ZERO) {
+                ubits[s][j] = __float_as_uint(uu[s][j]);
+                const bool zero = (bits[s][j] & 0x7fffffffu) >= t_zero;
+                vv[s][j] = zero ? 0.f : vv[s][j];
+                uu[s][j] = zero ? 0.f : uu[s][j];
+            }
+        }
+        if (FUSED) {
             __builtin_nontemporal_store(uu[s], (f4u *)(u + s * 256));
             __builtin_nontemporal_store(vv[s], (f4u *)(v + s * 256));
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) bits[s][j] = __float_as_uint(vv[s][j]);
     }
 }
 
@@ -58,8 +70,8 @@ __global__ __launch_bounds__(kBlock) void k_accumulate(const float *__restrict__
         const uint32_t row = r * (uint32_t)kRow;
         const uint32_t end = (n - row > (uint32_t)kRow) ? row + kRow : n;
         if (row + 1024 <= end) {
-            uint32_t bits[4][4];
-            full_row<true>(g + row + lane * 4, u + row + lane * 4, v + row + lane * 4, m, bits);
+            uint32_t bits[4][4], ubits[4][4];
+            full_row<true, false>(g + row + lane * 4, u + row + lane * 4, v + row + lane * 4, m, bits, 0u, ubits);
         } else {
             for (uint32_t e = row + lane; e < end; e += 64) {
                 float uu = u[e], vv = v[e];
@@ -127,7 +139,9 @@ __device__ uint32_t write_lane(uint32_t value, uint32_t lane, uint32_t x) __asm(
 // SEG: per-layer selection; the threshold of an element is that of its segment (a.seg_t, one per
 // node and segment; 0xffffffff flags nothing).  a.row_seg names the segment of a row's first
 // element, with bit 31 set when the row runs into further segments.
-template <bool FUSED, bool SEG, bool REC>
+// ZERO (with REC; a.zero_early): elements with key >= t_zero, which are taken for selected, go out as zeros in u and v, and the
+// record keeps their u as well; a row with more candidates than that record holds is written as it is after all.
+template <bool FUSED, bool SEG, bool ZERO, bool REC>
 __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
     __shared__ uint32_t record_lds[REC ? kWaves : 1][kRecordWords];
     const int node = a.node0 + blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -135,7 +149,9 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
     const float *__restrict__ g = a.g + off;
     float *__restrict__ u = a.u + off;
     float *__restrict__ v = a.v + off;
-    const uint32_t t_est = SEG ? 0u : a.sel[node].t_est;
+    static_assert(!ZERO || (FUSED && REC && !SEG), "zeros need records");
+    constexpr uint32_t kMost = ZERO ? kZeroRecord : kRecord;   // candidates that a record holds
+    const uint32_t t_est = SEG ? 0u : a.sel[node].t_est, t_zero = ZERO ? a.sel[node].t_zero : 0u;
     const uint32_t *seg_t = SEG ? a.seg_t + (size_t)node * a.n_seg : nullptr;
     const float m = a.momentum;
     unsigned long long *bitmap = a.bitmap + (size_t)node * a.rows * kRowWords;
@@ -144,7 +160,7 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
     if (r < a.row_end) {
         const uint32_t row = r * (uint32_t)kRow;
         const uint32_t end = (a.n - row > (uint32_t)kRow) ? row + kRow : a.n;
-        uint32_t bits[4][4];
+        uint32_t bits[4][4], ubits[4][4];
         uint32_t thr[4][4];
         if (SEG) {
             const uint32_t rs = a.row_seg[r];
@@ -166,17 +182,17 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
             }
         }
         if (row + 1024 <= end) {
-            full_row<FUSED>(g + row + lane * 4, u + row + lane * 4, v + row + lane * 4, m, bits);
+            full_row<FUSED, ZERO>(g + row + lane * 4, u + row + lane * 4, v + row + lane * 4, m, bits, t_zero, ubits);
         } else {
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
                 const uint32_t e0 = row + s * 256 + lane * 4;
-                f4 vv = {0.f, 0.f, 0.f, 0.f};
+                f4 vv = {0.f, 0.f, 0.f, 0.f}, uu = {0.f, 0.f, 0.f, 0.f};
                 if (e0 + 3 < end) {
                     vv = *(const f4u *)(v + e0);
                     if (FUSED) {
                         const f4 gg = *(const f4u *)(g + e0);
-                        f4 uu = *(const f4u *)(u + e0);
+                        uu = *(const f4u *)(u + e0);
 #pragma unroll
                         for (int j = 0; j < 4; ++j) { float x = uu[j], y = vv[j]; accum1(gg[j], x, y, m); uu[j] = x; vv[j] = y; }
                         *(f4u *)(u + e0) = uu;
@@ -189,12 +205,13 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
                             float x = u[e0 + j];
                             accum1(g[e0 + j], x, y, m);
                             u[e0 + j] = x; v[e0 + j] = y;
+                            uu[j] = x;
                         }
                         vv[j] = y;
                     }
                 }
 #pragma unroll
-                for (int j = 0; j < 4; ++j) bits[s][j] = __float_as_uint(vv[j]);
+                for (int j = 0; j < 4; ++j) { bits[s][j] = __float_as_uint(vv[j]); if (ZERO) ubits[s][j] = __float_as_uint(uu[j]); }
             }
         }
         // 16 flag words of the row; lane i < 16 ends up holding word i
@@ -215,7 +232,27 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
         if (lane < kRowWords && (count != 0 || !a.sparse_bitmap)) bitmap[(size_t)r * kRowWords + lane] = ((unsigned long long)hi << 32) | lo;
         if (lane == 0) row_count[r] = count;
         // the row's record, put together in the LDS and stored as whole lines (wave-uniform condition)
-        if (REC && count != 0 && count <= (uint32_t)kRecord) {
+        if (ZERO) {   // (wave-uniform conditions)
+            const bool whole = row + 1024 <= end;
+            if (whole && count > kMost && t_zero != ~0u) {   // no record: what has gone out as zeros is written after all
+#pragma unroll
+                for (int s = 0; s < 4; ++s) {
+                    const uint32_t e0 = row + s * 256 + lane * 4;
+                    *(u4u *)(u + e0) = (u4){ubits[s][0], ubits[s][1], ubits[s][2], ubits[s][3]};
+                    *(u4u *)(v + e0) = (u4){bits[s][0], bits[s][1], bits[s][2], bits[s][3]};
+                }
+            } else if (!whole && count <= kMost) { // the vector's last, shorter row has gone out as it is
+#pragma unroll
+                for (int s = 0; s < 4; ++s)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (((flags[s][j] >> lane) & 1u) && (bits[s][j] & 0x7fffffffu) >= t_zero) {
+                            u[row + s * 256 + lane * 4 + j] = 0.f;
+                            v[row + s * 256 + lane * 4 + j] = 0.f;
+                        }
+            }
+        }
+        if (REC && count != 0 && count <= kMost) {
             uint32_t *rec = record_lds[wave];
             uint32_t at = 0;
 #pragma unroll
@@ -228,14 +265,15 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
                     for (int j = 0; j < 4; ++j) {
                         if ((flags[s][j] >> lane) & 1u) {
                             rec[mine] = bits[s][j];
-                            ((uint16_t *)(rec + kRecord))[mine] = (uint16_t)(s * 256 + lane * 4 + j);
+                            ((uint16_t *)(rec + kMost))[mine] = (uint16_t)(s * 256 + lane * 4 + j);
+                            if (ZERO) rec[kMost + kMost / 2 + mine] = ubits[s][j];
                             ++mine;
                         }
                     }
                 }
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            if (lane < kRecord + kRecord / 2) a.row_rec[((size_t)node * a.rec_stride + r) * kRecordWords + lane] = rec[lane];
+            if (lane < (int)(ZERO ? 2 * kMost + kMost / 2 : kMost + kMost / 2)) a.row_rec[((size_t)node * a.rec_stride + r) * kRecordWords + lane] = rec[lane];
         }
     }
 }
@@ -251,10 +289,11 @@ void launch_candidates(const SelArgs &args, int batch, bool fused, hipStream_t s
         a.sparse_bitmap = (uint64_t)nrows * batch > kRowsPerLaunch;
         a.node0 = node0; a.row_begin = r0; a.row_end = r1;
         dim3 grid((r1 - r0 + kWaves - 1) / kWaves, nodes);
-#define LGC_CAND(F, S, R) launch_timed(k_candidates<F, S, R>, grid, dim3(kBlock), st, e, a)
-        if (seg) { if (fused) LGC_CAND(true, true, false); else LGC_CAND(false, true, false); }
-        else if (a.row_rec) { if (fused) LGC_CAND(true, false, true); else LGC_CAND(false, false, true); }
-        else { if (fused) LGC_CAND(true, false, false); else LGC_CAND(false, false, false); }
+#define LGC_CAND(F, S, Z, R) launch_timed(k_candidates<F, S, Z, R>, grid, dim3(kBlock), st, e, a)
+        if (seg) { if (fused) LGC_CAND(true, true, false, false); else LGC_CAND(false, true, false, false); }
+        else if (a.zero_early) LGC_CAND(true, false, true, true);
+        else if (a.row_rec) { if (fused) LGC_CAND(true, false, false, true); else LGC_CAND(false, false, false, true); }
+        else { if (fused) LGC_CAND(true, false, false, false); else LGC_CAND(false, false, false, false); }
 #undef LGC_CAND
     });
 }

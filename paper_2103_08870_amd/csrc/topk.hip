@@ -81,7 +81,10 @@ __global__ __launch_bounds__(1024) void k_sample(SelArgs a) {
         const Carry *c = a.carry + node;
         const uint32_t t = c->next_t_est;
         if (t != 0 && c->n == a.n && c->k == a.k) {
-            if (blockIdx.x == 0 && tid == 0) { a.sel[node].t_est = t; a.sel[node].carried = 1; atomicAdd(&a.stats->carried, 1u); }
+            if (blockIdx.x == 0 && tid == 0) {
+                a.sel[node].t_est = t; a.sel[node].carried = 1; atomicAdd(&a.stats->carried, 1u);
+                a.sel[node].t_zero = !c->zeros_pay ? ~0u : c->next_t > t ? c->next_t : t;
+            }
             return;
         }
     }
@@ -136,18 +139,37 @@ __global__ __launch_bounds__(1024) void k_sample(SelArgs a) {
     find_rank_bin<kSampleBins, 1024>(hist, a.rank, wave_tmp, res);
     const uint32_t b1 = res[0], need = a.rank - res[1];
     __syncthreads();
-    if (b1 == 0xffffffffu) return;  // cannot happen (rank <= kSample); t_est stays 0: everything is a candidate
-    hist[tid] = 0;
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < (int)(kSample / 4 / 1024); ++r) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if ((x[r][i] >> 20) == b1) atomicAdd(&hist[(x[r][i] >> 10) & 1023u], 1u);
+    if (b1 == 0xffffffffu) { if (tid == 0) a.sel[node].t_zero = ~0u; return; }  // cannot happen (rank <= kSample); t_est stays 0: everything is a candidate
+    uint32_t b2 = 0, need2 = 0;
+    // (the record is the previous selection's, of this shape)
+    const bool zeros = a.zero_early && a.carry && a.carry[node].len > 0 && a.carry[node].n == a.n && a.carry[node].k == a.k && a.carry[node].zeros_pay;
+    if (zeros) {
+        find_rank_bin<kSampleBins, 1024>(hist, a.rank_zero, wave_tmp, res);
+        b2 = res[0]; need2 = a.rank_zero - res[1];
+        __syncthreads();
     }
-    __syncthreads();
-    find_rank_bin<1024, 1024>(hist, need, wave_tmp, res);
-    if (tid == 0) a.sel[node].t_est = (b1 << 20) | ((res[0] == 0xffffffffu ? 0u : res[0]) << 10);
+    // the key, 2^-13 resolution, of the need-th largest of the sampled keys of first-level bin `bin`
+    auto refine = [&](const uint32_t bin, const uint32_t rank) -> uint32_t {
+        hist[tid] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < (int)(kSample / 4 / 1024); ++r) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if ((x[r][i] >> 20) == bin) atomicAdd(&hist[(x[r][i] >> 10) & 1023u], 1u);
+        }
+        __syncthreads();
+        find_rank_bin<1024, 1024>(hist, rank, wave_tmp, res);
+        return (bin << 20) | ((res[0] == 0xffffffffu ? 0u : res[0]) << 10);
+    };
+    const uint32_t t = refine(b1, need);
+    if (tid == 0) a.sel[node].t_est = t;
+    uint32_t t2 = ~0u;
+    if (zeros) {   // (rank_zero <= rank: t_zero >= t_est)
+        __syncthreads();
+        t2 = refine(b2, need2);
+    }
+    if (tid == 0) a.sel[node].t_zero = t2;
 }
 
 void launch_sample(const SelArgs &a, int batch, bool fused, hipStream_t st) {
@@ -157,6 +179,8 @@ void launch_sample(const SelArgs &a, int batch, bool fused, hipStream_t st) {
 }
 
 // ------------------------------------------------------------------ gather of the candidates
+
+constexpr uint32_t kZeroed = 0x80000000u;   // of a listed position (n < 2^31): the pass has written zeros there
 
 template <int THREADS>
 __device__ __forceinline__ uint32_t block_sum(uint32_t x, uint32_t *tmp /*[16]*/) {
@@ -239,7 +263,6 @@ __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
     const float *v = a.v + (size_t)node * a.stride;
     uint32_t *cidx = a.cand_idx + (size_t)node * a.cap, *cval = a.cand_val + (size_t)node * a.cap;
 
-    if (HIST && a.groups_counted && group_counts(a, node)[blockIdx.x] == 0) return;   // nothing to list (block-uniform)
     // all independent loads first: my row's count, my slice of the bitmap, the counts before the block
     const uint32_t c = (uint32_t)tid < mine ? cnt[first + tid] : 0u;
     ulonglong2 bm[kPairs];
@@ -314,6 +337,124 @@ __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
     }
 }
 
+// For the next selection's zeros from the pass (a.zero_early), what they would save and cost: a lane's row holds c candidates
+__device__ __forceinline__ void count_crowded(Sel *s, const uint32_t c) {
+    const uint32_t held = wave_sum(c <= (uint32_t)kZeroRecord ? c : 0u), crowded = (uint32_t)__popcll(__ballot(c > (uint32_t)kZeroRecord));
+    if ((threadIdx.x & 63) == 0) {
+        if (held) atomicAdd(&s->recorded, held);
+        if (crowded) atomicAdd(&s->crowded, crowded);
+    }
+}
+
+// The same for the flat selection of long vectors (a.groups_counted), with the work cut where the candidates are, not where the
+// rows are: a piece is up to T candidates of one group of kGroupRows rows, one per thread, and the node's blocks take the pieces in turn.
+// Groups without candidates cost nothing, and where the candidates cluster no block is left with a multiple of the others' work.
+// us, a block per group (with the row counts summed per 8192 rows, its launch included) / pieces: 8 x 44.5 M at 0.1 % 44.8 / 28.6;
+// 2^28, 1 %, spread evenly 58.6 / 39.5; 260 M, 0.85 %, in clusters 80.2 / 75.9; 4 x 60 M, 1 %, in clusters 72.8 / 64.4.
+template <int T>
+__global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
+    constexpr int W = T / 64, kPairs = kGroupRows * kRowWords / 2 / T;   // wavefronts; pairs of bitmap words per thread
+    __shared__ __align__(16) uint32_t hist[kFineBins];
+    __shared__ unsigned long long rows_lds[kGroupRows * kRowWords];
+    __shared__ uint32_t offs[kGroupRows];
+    __shared__ uint32_t tmp[2 * W], piece[4];
+    static_assert(kGroupRows == 128 && kPairs * 2 * T == kGroupRows * kRowWords && W >= 2, "two wavefronts' rows");
+    const int node = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    Sel *s = a.sel + node;
+    const uint32_t nrows = (a.n + kRow - 1) / kRow, groups = (nrows + kGroupRows - 1) / kGroupRows;
+    const uint32_t *cnt = a.row_count + (size_t)node * a.rows, *sums = group_counts(a, node);
+    const float *v = a.v + (size_t)node * a.stride;
+    uint32_t *cidx = a.cand_idx + (size_t)node * a.cap, *cval = a.cand_val + (size_t)node * a.cap;
+    const uint32_t t_est = s->t_est, t_zero = a.zero_early ? s->t_zero : ~0u;
+
+    // this thread's run of groups: its candidates and pieces, and those before it
+    const uint32_t per = (groups + T - 1) / T, g0 = tid * per;
+    uint32_t c = 0, w = 0;
+    for (uint32_t i = 0; i < per; ++i) {
+        const uint32_t x = g0 + i < groups ? sums[g0 + i] : 0u;
+        c += x; w += (x + T - 1) / T;
+    }
+    for (int i = tid; i < kFineBins; i += T) hist[i] = 0;
+    const uint32_t c_incl = wave_prefix(c), w_incl = wave_prefix(w);
+    if (lane == 63) { tmp[wave] = c_incl; tmp[W + wave] = w_incl; }
+    __syncthreads();
+    const uint32_t cw = lane < W ? tmp[lane] : 0u, ww = lane < W ? tmp[W + lane] : 0u;
+    const uint32_t c_before = c_incl - c + wave_sum(lane < wave ? cw : 0u), w_before = w_incl - w + wave_sum(lane < wave ? ww : 0u);
+    const uint32_t pieces = wave_sum(ww), total = wave_sum(cw);
+    if (blockIdx.x == 0 && tid == 0) s->cand_total = total;
+
+    for (uint32_t p = blockIdx.x; p < pieces; p += gridDim.x) {   // block-uniform, from scalar registers
+        __syncthreads();   // the previous piece's readers are done
+        if (w_before <= p && p - w_before < w) {
+            uint32_t g = g0, at = c_before, j = p - w_before, x = c;
+            if (per > 1) {
+                for (;; ++g) {   // (ends within the run: it holds the piece)
+                    x = sums[g];
+                    const uint32_t here = (x + T - 1) / T;
+                    if (j < here) break;
+                    j -= here; at += x;
+                }
+            }
+            piece[0] = g; piece[1] = j * T; piece[2] = x; piece[3] = at;
+        }
+        __syncthreads();
+        const uint32_t first = piece[0] * kGroupRows, q = piece[1] + tid, all = piece[2], before = piece[3];
+        const uint32_t mine = nrows - first < (uint32_t)kGroupRows ? nrows - first : (uint32_t)kGroupRows;
+        const uint32_t rc = (uint32_t)tid < mine ? cnt[first + tid] : 0u;
+        const unsigned long long *bitmap = a.bitmap + ((size_t)node * a.rows + first) * kRowWords;
+        if (!a.row_rec) {   // (the words of rows without candidates may be whatever was there: nobody looks at them)
+            ulonglong2 bm[kPairs];
+#pragma unroll
+            for (int i = 0; i < kPairs; ++i) {
+                const uint32_t at = (i * T + tid) * 2;
+                bm[i] = at < mine * kRowWords ? *(const ulonglong2 *)(bitmap + at) : ulonglong2{0ull, 0ull};
+            }
+#pragma unroll
+            for (int i = 0; i < kPairs; ++i) { rows_lds[(i * T + tid) * 2] = bm[i].x; rows_lds[(i * T + tid) * 2 + 1] = bm[i].y; }
+        }
+        if (wave < kGroupRows / 64) {
+            const uint32_t incl = wave_prefix(rc);
+            offs[tid] = incl - rc;
+            if (lane == 63) tmp[wave] = incl;
+            if (a.zero_early && piece[1] == 0) count_crowded(s, rc);
+        }
+        __syncthreads();
+        if (q < all) {
+            // last row r with start(r) <= q: it is the one that holds candidate q of the group
+            const uint32_t half = tmp[0];
+            auto start = [&](uint32_t r) { return offs[r] + (r < 64 ? 0u : half); };
+            uint32_t r = 0;
+#pragma unroll
+            for (int step = kGroupRows / 2; step >= 1; step >>= 1)
+                if (start(r + step) <= q) r += step;
+            const uint32_t i = q - start(r);   // the i-th candidate of row r
+            uint32_t ix, vb;
+            if (a.row_rec && (r + 1 < (uint32_t)kGroupRows ? start(r + 1) : all) - start(r) <= a.rec_most) {
+                const uint32_t *rec = a.row_rec + ((size_t)node * a.rec_stride + first + r) * kRecordWords;
+                vb = rec[i];
+                ix = (first + r) * (uint32_t)kRow + ((const uint16_t *)(rec + a.rec_most))[i];
+                if ((vb & 0x7fffffffu) >= t_zero) ix |= kZeroed;
+            } else {
+                ix = (first + r) * (uint32_t)kRow + row_element(a.row_rec ? bitmap + (size_t)r * kRowWords : rows_lds + r * kRowWords, i);
+                vb = ix < a.n ? __float_as_uint(v[ix]) : 0u;
+            }
+            if (before + q < a.cap) { cidx[before + q] = ix; cval[before + q] = vb; }
+            const uint32_t d = ((vb & 0x7fffffffu) - t_est) >> kFineShift;
+            atomicAdd(&hist[d < (uint32_t)kFineBins - 1 ? d : (uint32_t)kFineBins - 1], 1u);
+        }
+    }
+    __syncthreads();
+    uint32_t *fine = a.fine_hist + node * kFineBins;
+    for (int i = tid; i < kFineBins; i += T) { const uint32_t h = hist[i]; if (h) atomicAdd(&fine[i], h); }
+}
+
+template <int T>
+static void launch_gather_pieces(const SelArgs &a, uint32_t groups, int batch, int cus, hipStream_t st) {
+    // 2048 threads per compute unit, shared by the nodes; no more blocks than there can be pieces
+    const uint32_t most = groups + a.cap / T, fill = (uint32_t)((2048 / T * cus + batch - 1) / batch);
+    hipLaunchKernelGGL(k_gather_pieces<T>, dim3(fill < most ? fill : most, batch), dim3(T), 0, st, a);
+}
+
 constexpr uint32_t kGroupsCountedFrom = 32 * 1024;
 
 template <int ROWS, int THREADS>
@@ -324,13 +465,22 @@ static void launch_gather_shape(const SelArgs &g, uint32_t nrows, int batch, hip
     else hipLaunchKernelGGL((k_gather<true, ROWS, THREADS>), grid, dim3(THREADS), 0, st, g);
 }
 
-void launch_gather(const SelArgs &args, int batch, hipStream_t st) {
+void launch_gather(const SelArgs &args, int batch, int cus, hipStream_t st) {
     SelArgs a = args;
     const uint32_t nrows = (a.n + kRow - 1) / kRow, groups = (nrows + kGroupRows - 1) / kGroupRows;
-    // The sums pay for their launch from about 32 K rows on: 8 x 43.5 K rows, whole step without / with them and the early end of blocks
-    // without candidates: 1318 / 1305 us, 4 x 39 K 601 / 594, 1 x 254 K (0.1 %) 943 / 934; 4 x 25 K rows 382.9 / 383.6, by layers 409 / 411.
-    a.groups_counted = nrows > kGroupsCountedFrom;
+    // Records with zeros from the pass are read by pieces at any length (8 x 30 M, 1 %, block per group / pieces: 1231 / 1222 us).
+    // The sums pay for their launch from about 32 K rows on: 8 x 43.5 K rows, whole step without / with them and the
+    // pieces: 1318 / 1303 us, 4 x 39 K 601 / 591; 4 x 25 K rows 382.9 / 382.7, 4 x 16 K 255 / 258, 1 x 25 K 117.4 / 119, by layers 409 / 411.
+    a.groups_counted = nrows > kGroupsCountedFrom || a.zero_early;
     if (a.groups_counted) hipLaunchKernelGGL(k_group_counts, dim3((groups + 15) / 16, batch), dim3(1024), 0, st, a);
+    if (a.groups_counted && !a.seg_t) {
+        // Blocks of 512 threads where the bitmap is searched, of 1024 where records are read: the search is the longer chain, and four
+        // blocks per compute unit overlap it better; records of long lists are read in few, long pieces.  us, 512 / 1024 threads:
+        // 8 x 44.5 M at 0.1 % 23.8 / 27.1; with records, 2^28 at 1 % 53.1 / 34.6.
+        if (a.row_rec) launch_gather_pieces<1024>(a, groups, batch, cus, st);
+        else launch_gather_pieces<512>(a, groups, batch, cus, st);
+        return;
+    }
     // 128 rows per block of 1024 threads; measured on the ResNet50-sized workload (4 nodes): 64 rows x 512
     // threads 18.0 us, 64 x 1024 20.2, 128 x 512 19.8, 64 x 256 21.5, this shape 18.2 (the same within noise:
     // what the kernel costs is its chain of dependent memory round trips, not the search work of its busiest block)
@@ -369,6 +519,11 @@ __device__ __forceinline__ void count_candidates(const uint32_t *cval, uint32_t 
 
 // ------------------------------------------------------------------ exact k-th key among the candidates
 
+// Zeros from the pass save a scattered zero in u and in v each, some 60 ps where the whole chip stores them; a row that holds more candidates
+// than its record is written twice.  Whole step, us, without / with zeros wherever a record is kept: 2^28, 1 %, spread evenly 1387 / 1220; in
+// clusters, where over half of the candidates lie in such rows: 260 M, 0.85 %: 1206 / 1297; 4 x 60 M, 1 %: 1194 / 1306; 8 x 44.5 M, 1 %: 1796 / 1984.
+constexpr uint32_t kZerosPerCrowdedRow = 64;
+
 // What the one thread that knows a selection's outcome on the fast path leaves behind: the node's state for the
 // kernels after it, the statistics, the word the host polls, and the record of carried thresholds (carry.h).
 __device__ __forceinline__ void report_outcome(const SelArgs &a, const int node, Sel *s, const bool ok, const uint32_t thr,
@@ -378,7 +533,10 @@ __device__ __forceinline__ void report_outcome(const SelArgs &a, const int node,
     atomicAdd(ok ? &a.stats->fast : &a.stats->fallback, 1u);
     // the host sees the outcome without synchronising; a carried threshold that failed says nothing about the data
     if (a.notify && (ok || !s->carried)) st_system32(a.notify + (ok ? 1 : 0), a.notify_value);
-    if (a.carry) carry_update(a.carry + node, a.n, a.k, false, ok, s->carried != 0, thr, t_est, total, a.carry_target, a.carry_most);
+    if (a.carry) {
+        carry_update(a.carry + node, a.n, a.k, false, ok, s->carried != 0, thr, t_est, total, a.carry_target, a.carry_most);
+        a.carry[node].zeros_pay = a.zero_early && s->recorded / kZerosPerCrowdedRow >= s->crowded;
+    }
 }
 
 
@@ -788,13 +946,33 @@ __global__ __launch_bounds__(1024) void k_count_chunks(SelArgs a) {
     }
 }
 
+// The node goes to the exact path, which reads u and v as the accumulation leaves them: what the pass has zeroed is written back
+// from the rows' records.  All blocks of the node's launch share the rows, a wavefront takes one at a time.
+__device__ __forceinline__ void unzero_rows(const SelArgs &a, const int node) {
+    const uint32_t lane = threadIdx.x & 63, nrows = (a.n + kRow - 1) / kRow, t_zero = a.sel[node].t_zero;
+    float *v = a.v + (size_t)node * a.stride, *u = a.u + (size_t)node * a.stride;
+    for (uint32_t r = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6); r < nrows; r += gridDim.x * (blockDim.x / 64)) {
+        const uint32_t held = a.row_count[(size_t)node * a.rows + r];
+        const uint32_t *rec = a.row_rec + ((size_t)node * a.rec_stride + r) * kRecordWords;
+        if (held <= (uint32_t)kZeroRecord && lane < held && (rec[lane] & 0x7fffffffu) >= t_zero) {
+            const size_t ix = (size_t)r * kRow + ((const uint16_t *)(rec + kZeroRecord))[lane];
+            v[ix] = __uint_as_float(rec[lane]);
+            u[ix] = __uint_as_float(rec[kZeroRecord + kZeroRecord / 2 + lane]);
+        }
+    }
+}
+
 __global__ __launch_bounds__(1024) void k_emit_scanned(SelArgs a) {
     __shared__ uint32_t sh_pg[16], sh_pe[16], sh_tg[16], sh_te[16];
     const int node = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const Sel *s = a.sel + node;
     const uint32_t total = s->cand_total;
     const uint32_t chunk = blockIdx.x, base = chunk * (uint32_t)kChunk, e0 = base + tid * 4;
-    if (!s->fast_ok || base >= total) return;   // uniform; fast_ok implies k <= total <= cap
+    if (!s->fast_ok) {   // uniform
+        if (a.zero_early) unzero_rows(a, node);
+        return;
+    }
+    if (base >= total) return;   // (fast_ok implies k <= total <= cap)
     const uint32_t thr = s->thr, quota = s->quota;
     const uint32_t *cidx = a.cand_idx + (size_t)node * a.cap;
     const uint32_t *cval = a.cand_val + (size_t)node * a.cap;
@@ -840,12 +1018,23 @@ __global__ __launch_bounds__(1024) void k_emit_scanned(SelArgs a) {
     float *oval = a.out_vals + (size_t)node * a.k;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
+        const uint32_t ix = ci[j] & ~kZeroed;
+        const bool zeroed = (ci[j] & kZeroed) != 0;
         if (fg[j] || (fe[j] && ce < quota)) {
             const uint32_t o = cg + (ce < quota ? ce : quota);
-            if (o < a.k) { oidx[o] = ci[j]; oval[o] = __uint_as_float(cv[j]); }
+            if (o < a.k) { oidx[o] = ix; oval[o] = __uint_as_float(cv[j]); }
             else atomicAdd(&a.stats->errors, 1u);
-            v[ci[j]] = 0.0f;
-            if (u) u[ci[j]] = 0.0f;
+            if (!zeroed) {
+                v[ix] = 0.0f;
+                if (u) u[ix] = 0.0f;
+            }
+        } else if (zeroed && e0 + j < total) {   // taken for selected by the pass, and not: its v and, from the row's record, its u again
+            const uint32_t *rec = a.row_rec + ((size_t)node * a.rec_stride + ix / kRow) * kRecordWords;
+            const uint16_t *at = (const uint16_t *)(rec + kZeroRecord);
+            const uint32_t held = a.row_count[(size_t)node * a.rows + ix / kRow];
+            for (uint32_t i = 0; i < held && i < (uint32_t)kZeroRecord; ++i)
+                if (at[i] == (ix & (kRow - 1))) { u[ix] = __uint_as_float(rec[kZeroRecord + kZeroRecord / 2 + i]); break; }
+            v[ix] = __uint_as_float(cv[j]);
         }
         cg += fg[j]; ce += fe[j];
     }
