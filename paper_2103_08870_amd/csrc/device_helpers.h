@@ -44,6 +44,26 @@ __device__ __forceinline__ uint32_t ld_agent32(const uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+__device__ __forceinline__ void st_agent32(uint32_t *p, uint32_t x) {
+    __hip_atomic_store(p, x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+__device__ __forceinline__ uint32_t mix32(uint32_t h) {
+    h *= 0x9E3779B1u; h ^= h >> 15; h *= 0x85EBCA77u; h ^= h >> 13; h *= 0xC2B2AE3Du; h ^= h >> 16;
+    return h;
+}
+
+// First element of the j-th group of 4 sampled neighbours.  Four groups make one 64-byte cluster of 16 elements; the clusters sit at
+// jittered positions, one in each of kSampleGroups / 4 strata of the vector: stratum cl = clusters [cl * C / 4096, (cl + 1) * C / 4096) of
+// the vector's C = n / 16 whole clusters (n >= kMinFastN makes none of them empty).
+__device__ __forceinline__ uint32_t sample_place(const uint32_t j, const int node, const uint32_t n) {
+    static_assert(kSampleGroups / 4 == 4096 && kMinFastN >= 16 * 4096, "4096 strata of at least one cluster");
+    const uint32_t cl = j >> 2, clusters = n >> 4;
+    const uint32_t s_lo = (uint32_t)(((unsigned long long)cl * clusters) >> 12);
+    const uint32_t s_hi = (uint32_t)(((unsigned long long)(cl + 1) * clusters) >> 12);
+    return ((s_lo + mix32(cl + 0x5bd1e995u * (uint32_t)node) % (s_hi - s_lo)) << 4) + ((j & 3u) << 2);
+}
+
 // accumulation step: three separately rounded fp32 operations, never contracted
 __device__ __forceinline__ void accum1(float g, float &u, float &v, float m) {
     u = __fadd_rn(__fmul_rn(m, u), g);

@@ -70,8 +70,10 @@ static_assert(sizeof(Sel) == 64, "Sel is one 64-byte record");
 struct Ctr {
     uint32_t ticket;      // exact path in one launch: next share to hand out (phase = ticket / shares)
     uint32_t done[5];     // completed shares of each phase
-    uint32_t sampled;     // sampling blocks of the node that have finished (the last one works out the estimate)
-    uint32_t pad[25];
+    uint32_t sampled;     // sampling blocks of the node, or shares, that have finished (the last one works out the estimate)
+    uint32_t share;       // sampling in the pass: next share to hand out
+    uint32_t ready;       // sampling in the pass: 1: the node's t_est stands
+    uint32_t pad[23];
 };
 static_assert(sizeof(Ctr) == 128, "Ctr is one 128-byte line");
 
@@ -83,7 +85,7 @@ struct Stats {
 // Per-node record that outlives the call (it is in neither state set): the exact thresholds T* of the last
 // selections of the context, as log2 of their magnitude, and, when they have moved smoothly enough, the candidate
 // threshold that the next selection may use without sampling.  Written by the one thread that reports a
-// selection's outcome, read by the sampling kernel of the next selection.  Every selection of the context ends by
+// selection's outcome, read by the sampling kernel, or the pass, of the next selection.  Every selection of the context ends by
 // writing it, on the device: the fast path its outcome, the exact path and the per-layer selection "nothing on
 // record" (len = 0, no offer); so the record is always the previous selection's, also in a replayed HIP graph.
 struct Carry {
@@ -113,6 +115,7 @@ struct SelArgs {
     uint32_t k;       // selected per node
     float momentum;
     uint32_t node0, row_begin, row_end;   // the streaming kernel's share of this launch: nodes node0.., rows [row_begin, row_end)
+    int sample_in_pass;       // 1: the pass takes the carried threshold, or samples one, itself
     uint32_t rank;    // rank of the sample's order statistic used as estimate
     uint32_t cap;     // capacity of the gathered candidate list, per node
     uint32_t rows;    // bitmap rows per node (stride of row_count; bitmap stride is rows * kRowWords)
@@ -124,6 +127,7 @@ struct SelArgs {
                               // when it falls back, to word 1 when the fast path served it
     uint32_t notify_value;
     Carry *carry;             // [batch] thresholds carried from selection to selection (null: always sample)
+    const Carry *offers;      // the same records, also where none are to be used (never null)
     float carry_target;       // log2 of (candidates aimed at by a carried threshold) / k
     float carry_most;         // log2 of (most candidates a carried threshold may be expected to flag) / k
     Carry *seg_carry;         // per-layer selection: [batch][n_seg] records, one per layer and node (null: always sample)

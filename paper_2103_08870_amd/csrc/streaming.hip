@@ -130,6 +130,102 @@ void launch_accumulate(const float *g, float *u, float *v, uint32_t n, int batch
 // has just written: the compiler puts the wait states in between that the hardware does not supply.
 __device__ uint32_t write_lane(uint32_t value, uint32_t lane, uint32_t x) __asm("llvm.amdgcn.writelane.i32");
 
+// ------------------------------------------------------------------ sampled candidate threshold
+
+// A node without a carried threshold: the pass samples kSample of the keys that it WILL produce (the fused source recomputes
+// v + (m*u + g) without storing it) and takes t_est = (roughly) the rank-th largest of them, to 2^-13 relative resolution: a
+// first level from a histogram of key >> 20, a second from the keys.  The sample is cut into shares that are handed out
+// through a ticket counter; the block that finishes the last one works out the estimate, and no block goes on to its rows, and
+// so writes u or v, before it stands.  The first kShares blocks of the node take shares at once, the others (whose tickets would only
+// queue up: atomics on one word take turns) after they have waited for some tens of microseconds.  So every share is with a running
+// block or free for any block that waits, and the waits end whatever number of the kernel's blocks the device holds and
+// whatever runs beside it; they are bounded all the same (counted as a device error).
+// As a launch of its own this took 14 us, and 4.6 us in a full queue where thresholds are carried and it had nothing to do.
+constexpr uint32_t kShares = kSample / (4 * kBlock);
+
+template <bool FUSED>
+__device__ __forceinline__ void sample_threshold(const SelArgs &a, const int node, uint32_t *hist /*[kSampleBins]*/) {
+    __shared__ uint32_t wave_tmp[kWaves], res[2], word;
+    const int tid = threadIdx.x;
+    Ctr *ctr = a.ctr + node;
+    const size_t off = (size_t)node * a.stride;
+    uint32_t *smp = a.samples + (size_t)node * kSample, *all = a.sample_hist + node * kSampleBins;
+    bool helps = blockIdx.x < kShares;
+    uint32_t spins = 0;
+    for (;;) {
+        __syncthreads();
+        if (tid == 0) {
+            // a share's number, kShares: none left (or not asked yet), kShares + 1: the estimate stands, kShares + 2: given up
+            uint32_t next = kShares;
+            if (ld_agent32(&ctr->ready)) next = kShares + 1;
+            else if (spins >= a.spin_limit) { atomicAdd(&a.stats->errors, 1u); next = kShares + 2; }
+            else if (helps || spins == 64) { next = atomicAdd(&ctr->share, 1u); next = next < kShares ? next : kShares; }
+            if (next == kShares) __builtin_amdgcn_s_sleep(16);
+            word = next;
+        }
+        __syncthreads();
+        const uint32_t share = __builtin_amdgcn_readfirstlane(word);
+        if (share > kShares) return;
+        if (share == kShares) { helps = false; ++spins; continue; }      // (block-uniform)
+        helps = true;
+        const uint32_t j = share * kBlock + tid, e = sample_place(j, node, a.n);
+        for (int i = tid; i < kSampleBins; i += kBlock) hist[i] = 0;
+        __syncthreads();
+        u4 keys;
+        f4 vv, uu = {0.f, 0.f, 0.f, 0.f}, gg = {0.f, 0.f, 0.f, 0.f};
+        vv = *(const f4u *)(a.v + off + e);
+        if (FUSED) { uu = *(const f4u *)(a.u + off + e); gg = *(const f4u *)(a.g + off + e); }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            float x = uu[i], y = vv[i];
+            if (FUSED) accum1(gg[i], x, y, a.momentum);
+            keys[i] = key_of(y);
+            atomicAdd(&hist[keys[i] >> 20], 1u);
+        }
+        *(u4 *)(smp + j * 4) = keys;
+        __syncthreads();
+        for (int i = tid; i < kSampleBins; i += kBlock) { const uint32_t h = hist[i]; if (h) atomicAdd(&all[i], h); }
+        // Every wavefront waits until its stores and atomics have been acknowledged, one thread releases them to the device and
+        // counts the share.
+        __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+        __syncthreads();
+        if (tid == 0) {
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+            word = atomicAdd(&ctr->sampled, 1u) == kShares - 1 ? 1u : 0u;
+        }
+        __syncthreads();
+        if (__builtin_amdgcn_readfirstlane(word) == 0) continue;
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // the other blocks' keys, through this XCD's caches
+        // the key of the rank-th largest: first level, second level
+        for (int i = tid; i < kSampleBins; i += kBlock) hist[i] = ld_agent32(&all[i]);
+        __syncthreads();
+        find_rank_bin<kSampleBins, kBlock>(hist, a.rank, wave_tmp, res);
+        const uint32_t bin = res[0], rank = a.rank - res[1];
+        __syncthreads();
+        for (int i = tid; i < 1024; i += kBlock) hist[i] = 0;
+        __syncthreads();
+        constexpr int kAhead = 4;   // (more would take registers that the pass has better use for)
+        static_assert(kSample / 4 % (kAhead * kBlock) == 0, "whole rounds");
+#pragma unroll 1
+        for (uint32_t i0 = tid; i0 < kSample / 4; i0 += kAhead * kBlock) {
+            u4 x[kAhead];
+#pragma unroll
+            for (int r = 0; r < kAhead; ++r) x[r] = *(const u4 *)(smp + (i0 + r * kBlock) * 4);
+#pragma unroll
+            for (int r = 0; r < kAhead; ++r)
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if ((x[r][c] >> 20) == bin) atomicAdd(&hist[(x[r][c] >> 10) & 1023u], 1u);
+        }
+        __syncthreads();
+        find_rank_bin<1024, kBlock>(hist, rank, wave_tmp, res);
+        if (tid == 0) {
+            st_agent32(&a.sel[node].t_est, (bin << 20) | ((res[0] == 0xffffffffu ? 0u : res[0]) << 10));
+            __hip_atomic_store(&ctr->ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+}
+
 // FUSED: reads g,u,v, writes u,v (the accumulation) and classifies the new v; otherwise reads v.
 // One wavefront per row of 1024 elements.  The flags "key >= t_est" of the row go out as one
 // full 128-byte line of the candidate bitmap (dense, coalesced: no partial-line writes), the
@@ -141,7 +237,8 @@ __device__ uint32_t write_lane(uint32_t value, uint32_t lane, uint32_t x) __asm(
 // element, with bit 31 set when the row runs into further segments.
 // ZERO (with REC; a.zero_early): elements with key >= t_zero, which are taken for selected, go out as zeros in u and v, and the
 // record keeps their u as well; a row with more candidates than that record holds is written as it is after all.
-template <bool FUSED, bool SEG, bool ZERO, bool REC>
+// SAMPLE: takes the carried threshold, or samples one, itself, and clears the next call's state set (otherwise the launch before did).
+template <bool FUSED, bool SEG, bool SAMPLE, bool ZERO, bool REC>
 __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
     __shared__ uint32_t record_lds[REC ? kWaves : 1][kRecordWords];
     const int node = a.node0 + blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -151,7 +248,28 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
     float *__restrict__ v = a.v + off;
     static_assert(!ZERO || (FUSED && REC && !SEG), "zeros need records");
     constexpr uint32_t kMost = ZERO ? kZeroRecord : kRecord;   // candidates that a record holds
-    const uint32_t t_est = SEG ? 0u : a.sel[node].t_est, t_zero = ZERO ? a.sel[node].t_zero : 0u;
+    static_assert(!SAMPLE || (!SEG && !ZERO), "one threshold");
+    uint32_t t_est = SEG || SAMPLE ? 0u : a.sel[node].t_est;
+    const uint32_t t_zero = ZERO ? a.sel[node].t_zero : 0u;
+    if (SAMPLE) {
+        __shared__ __align__(16) uint32_t hist[kSampleBins];
+        // scalar loads, as nothing has been stored yet: vector loads here hold up the row's (4 x 25.6 M: 386 us for 382.6)
+        const Carry *c = a.offers + node;
+        const uint32_t c_n = c->n, c_k = c->k, c_est = c->next_t_est;
+        // A node whose record of carried thresholds offers one for this very selection (same shape, the selection right after
+        // the one that wrote it) takes that one and samples nothing.
+        if (a.carry && c_n == a.n && c_k == a.k && c_est != 0) {
+            t_est = c_est;
+            if (blockIdx.x == 0 && threadIdx.x == 0) {
+                st_agent32(&a.sel[node].t_est, t_est);   // (its line holds a neighbour's record too, which its sample may be writing)
+                st_agent32(&a.sel[node].carried, 1u);
+                atomicAdd(&a.stats->carried, 1u);
+            }
+        } else {
+            sample_threshold<FUSED>(a, node, hist);
+            t_est = __builtin_amdgcn_readfirstlane(ld_agent32(&a.sel[node].t_est));
+        }
+    }
     const uint32_t *seg_t = SEG ? a.seg_t + (size_t)node * a.n_seg : nullptr;
     const float m = a.momentum;
     unsigned long long *bitmap = a.bitmap + (size_t)node * a.rows * kRowWords;
@@ -276,6 +394,10 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
             if (lane < (int)(ZERO ? 2 * kMost + kMost / 2 : kMost + kMost / 2)) a.row_rec[((size_t)node * a.rec_stride + r) * kRecordWords + lane] = rec[lane];
         }
     }
+    if (SAMPLE) {
+        const uint32_t gt = (blockIdx.y * gridDim.x + blockIdx.x) * kBlock + threadIdx.x, nt = gridDim.x * gridDim.y * kBlock;
+        for (uint32_t i = gt; i < a.next_words; i += nt) a.next_state[i] = 0;
+    }
 }
 
 void launch_candidates(const SelArgs &args, int batch, bool fused, hipStream_t st, Bracket br) {
@@ -289,11 +411,13 @@ void launch_candidates(const SelArgs &args, int batch, bool fused, hipStream_t s
         a.sparse_bitmap = (uint64_t)nrows * batch > kRowsPerLaunch;
         a.node0 = node0; a.row_begin = r0; a.row_end = r1;
         dim3 grid((r1 - r0 + kWaves - 1) / kWaves, nodes);
-#define LGC_CAND(F, S, Z, R) launch_timed(k_candidates<F, S, Z, R>, grid, dim3(kBlock), st, e, a)
-        if (seg) { if (fused) LGC_CAND(true, true, false, false); else LGC_CAND(false, true, false, false); }
-        else if (a.zero_early) LGC_CAND(true, false, true, true);
-        else if (a.row_rec) { if (fused) LGC_CAND(true, false, false, true); else LGC_CAND(false, false, false, true); }
-        else { if (fused) LGC_CAND(true, false, false, false); else LGC_CAND(false, false, false, false); }
+#define LGC_CAND(F, S, M, Z, R) launch_timed(k_candidates<F, S, M, Z, R>, grid, dim3(kBlock), st, e, a)
+#define LGC_CAND_M(F, R) do { if (a.sample_in_pass) LGC_CAND(F, false, true, false, R); else LGC_CAND(F, false, false, false, R); } while (0)
+        if (seg) { if (fused) LGC_CAND(true, true, false, false, false); else LGC_CAND(false, true, false, false, false); }
+        else if (a.zero_early) LGC_CAND(true, false, false, true, true);
+        else if (a.row_rec) { if (fused) LGC_CAND_M(true, true); else LGC_CAND_M(false, true); }
+        else { if (fused) LGC_CAND_M(true, false); else LGC_CAND_M(false, false); }
+#undef LGC_CAND_M
 #undef LGC_CAND
     });
 }
