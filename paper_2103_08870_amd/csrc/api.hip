@@ -48,11 +48,12 @@ struct lgc_ctx {
     size_t seg_carry_records = 0;
     const lgc_segments *last_seg = nullptr;   // the plan of the previous selection, if that was a per-layer one
     uint64_t last_seg_k = 0;
-    // Automatic path choice: a selection stores its call number to one of two pinned host words (fell back /
-    // served by the fast path); the host looks at them (an ordinary read, no synchronisation) when it queues the
+    // Automatic path choice: a selection stores its call number to one of the pinned host words (Outcome: fell back /
+    // served by the fast path, ..); the host looks at them (an ordinary read, no synchronisation) when it queues the
     // next selection, and after fall-backs takes the exact path outright for a while before it tries the fast path again.
     uint32_t *fell_back_host = nullptr, *fell_back_dev = nullptr;
     uint32_t call_number = 0, fell_back_seen = 0;
+    uint32_t offers_from = 0;   // the last call number before the records of carried thresholds were last emptied by the host's choice
     int exact_calls_left = 0, penalty = 0;
     // The one-launch finish holds shorter lists than a context with a large capacity: after a fall-back of it such a context
     // goes through the many-block launches for some calls.  Bit i: the call i numbers ago was one.
@@ -275,7 +276,6 @@ SelArgs make_args(lgc_ctx *c, const float *g, float *u, float *v, uint64_t n, ui
     a.notify = c->fell_back_dev;
     a.notify_value = 0;
     a.carry = c->opt_carry && !c->single_state ? c->carry : nullptr;
-    a.offers = c->carry;
     const StateLayout L = state_layout(c->max_batch, c->status_cand_stride, c->status_exact_stride);
     uint32_t *cur = c->state[c->cur];
     a.sel = (Sel *)(cur + L.sel);
@@ -292,6 +292,7 @@ SelArgs make_args(lgc_ctx *c, const float *g, float *u, float *v, uint64_t n, ui
 }
 
 constexpr int kManyBlockCalls = 64;  // selections between the tries of the one-launch finish after it fell back where longer lists are held
+constexpr int kOfferRun = 16;        // selections in a row that must have left carried thresholds before the pass is launched on the next one's
 constexpr int kMaxExactCalls = 64;   // most selections in a row that take the exact path outright after fall-backs were seen
 
 // Short vectors are selected exactly by kernels of their own, unless the exact radix path was asked for.
@@ -329,6 +330,16 @@ uint64_t record_rows(uint64_t max_n, uint64_t max_k, int max_batch) {
     const bool dense = expected_candidates((double)max_n, (double)max_k) * max_batch >= kRecordsFromList;
     const uint64_t need = dense ? all : some;
     return need * kRecordWords * 4 <= (4ull << 30) ? need : some * kRecordWords * 4 <= (4ull << 30) ? some : 0;
+}
+
+uint32_t later(uint32_t a, uint32_t b) { return (int32_t)(a - b) > 0 ? a : b; }   // of two call numbers
+
+// Whether the last kOfferRun selections and more, as far as the host has seen, all left a carried threshold for every node.
+bool offers_hold(const lgc_ctx *c) {
+    if (!c->fell_back_host) return false;
+    const volatile uint32_t *w = c->fell_back_host;
+    const uint32_t with = w[kServedOffers], without = later(later(w[kServed], w[kFellBack]), later(w[kOfferFailed], c->offers_from));
+    return (int32_t)(with - without) >= kOfferRun;
 }
 
 // accumulate (optional) + select; g == nullptr means selection only
@@ -376,7 +387,8 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         // the exact path through the failed fast path costs nearly twice what taking it outright does.  Each newly
         // seen fall-back doubles the number of selections that take the exact path outright before the fast path is
         // tried again (1, 2, 4, ... 64); a fast-path success seen after the last fall-back resets it.
-        const uint32_t served = ((volatile uint32_t *)ctx->fell_back_host)[1];
+        const volatile uint32_t *words = ctx->fell_back_host;
+        const uint32_t served = later(words[kServed], words[kServedOffers]);
         if (fell_back != ctx->fell_back_seen) {
             ctx->fell_back_seen = fell_back;
             if (!by_finish) {
@@ -403,6 +415,7 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         a.notify_value = ctx->call_number;
         ctx->spare_finishes = ctx->spare_finishes << 1 | (uint64_t)(spare_finish && finishes_in_one && fast);
     }
+    if (!fast) ctx->offers_from = ctx->call_number;
     ctx->cur ^= 1;  // this call uses the clean set and cleans the other one for the next call
     if (small) {
         if (ctx->single_state) {   // no launch has cleared the scratch before this call: the first kernel does
@@ -411,10 +424,11 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         }
         launch_small_select(a, batch, fused, ctx->cus, st, fused ? profile_bracket(ctx) : Bracket());
     } else if (fast) {
-        // A pass of one launch finds its candidate threshold itself; before a longer one a launch does (whose 5 us are then a thousandth).
-        // Whole step, us, by a launch / in the pass: 2^20 elements 31.9 / 28.8, 3 x 3.33 M 63.6 / 62.2, 4 x 25.6 M 384.3 / 382.9; 2^28, 1 %
-        // (three launches): 1233 / 1256.
-        a.sample_in_pass = !a.zero_early && (uint64_t)a.rec_stride * batch <= kRowsPerLaunch;
+        // In a run whose thresholds are carried a pass of one launch takes them itself; before a longer one a launch does (whose 5 us
+        // are then a thousandth).  Whole step, us, by a launch / in the pass: 2^20 elements 31.9 / 28.8, 3 x 3.33 M 63.6 / 62.2, 4 x 25.6 M
+        // 384.3 / 382.9; 2^28, 1 % (three launches): 1233 / 1256.  Where no threshold has been carried after all, the pass samples one, and
+        // all of its blocks wait for that: a new run's first pass 4 x 25.6 M 435 / 557, 3 x 3.33 M 119 / 176.
+        a.sample_in_pass = !a.zero_early && (uint64_t)a.rec_stride * batch <= kRowsPerLaunch && a.carry && offers_hold(ctx);
         if (!a.sample_in_pass) launch_sample(a, batch, fused, st);   // (each clears the next call's state set)
         launch_candidates(a, batch, fused, st, profile_bracket(ctx));
         if (finishes_in_one) launch_finish_from_bitmap(a, batch, true, ctx->cus, st);
@@ -1297,6 +1311,7 @@ static lgc_status run_segmented(lgc_ctx *ctx, const lgc_segments *seg, const flo
     a.carry_target = (float)log2(2.0);
     a.carry_most = (float)log2(3.2);
     ctx->last_seg = seg; ctx->last_seg_k = seg->total_k;
+    ctx->offers_from = ctx->call_number;
     ctx->cur ^= 1;  // this call uses the clean set and cleans the other one for the next call
     if (seg->n_sampled) {
         launch_seg_estimate(a, batch, fused, st);   // also clears the next call's state set
@@ -1416,6 +1431,7 @@ extern "C" lgc_status lgc_set_option(lgc_ctx *ctx, lgc_option opt, int64_t value
             return LGC_OK;
         case LGC_OPT_CARRY_THRESHOLD:
             ctx->opt_carry = value != 0;
+            ctx->offers_from = ctx->call_number;
             {   // whatever has been recorded so far serves no later selection
                 DeviceGuard guard(ctx->device);
                 if (!guard.ok) return fail(ctx, LGC_EHIP, "cannot select device %d", ctx->device);

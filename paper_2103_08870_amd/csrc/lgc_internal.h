@@ -106,6 +106,10 @@ struct Carry {
 static_assert(sizeof(Carry) == 64, "Carry is one 64-byte record");
 
 // Everything the selection kernels need; passed by value.
+// How a selection ended, as the host learns of it without synchronising: fell back from a sampled threshold; served, and no threshold
+// carried to the next selection; served, and one carried; fell back from a carried threshold.
+enum Outcome : uint32_t { kFellBack = 0, kServed = 1, kServedOffers = 2, kOfferFailed = 3 };
+
 struct SelArgs {
     const float *g;   // fresh gradient (fused source only)
     float *u;         // momentum buffer (nullable for plain selection)
@@ -115,7 +119,7 @@ struct SelArgs {
     uint32_t k;       // selected per node
     float momentum;
     uint32_t node0, row_begin, row_end;   // the streaming kernel's share of this launch: nodes node0.., rows [row_begin, row_end)
-    int sample_in_pass;       // 1: the pass takes the carried threshold, or samples one, itself
+    int sample_in_pass;       // 1: the pass takes the carried threshold (carry is not null), or samples one, itself
     uint32_t rank;    // rank of the sample's order statistic used as estimate
     uint32_t cap;     // capacity of the gathered candidate list, per node
     uint32_t rows;    // bitmap rows per node (stride of row_count; bitmap stride is rows * kRowWords)
@@ -123,11 +127,9 @@ struct SelArgs {
     uint32_t spin_limit;      // bound of a wait for the shares of the previous phase (exact path in one launch)
     int force;                // exact path chosen by the host (ignore fast_ok)
     Stats *stats;
-    uint32_t *notify;         // two pinned host words (device address; null: none): a selection stores notify_value to word 0
-                              // when it falls back, to word 1 when the fast path served it
+    uint32_t *notify;         // pinned host words (device address; null: none): a selection stores notify_value to the one of its Outcome
     uint32_t notify_value;
     Carry *carry;             // [batch] thresholds carried from selection to selection (null: always sample)
-    const Carry *offers;      // the same records, also where none are to be used (never null)
     float carry_target;       // log2 of (candidates aimed at by a carried threshold) / k
     float carry_most;         // log2 of (most candidates a carried threshold may be expected to flag) / k
     Carry *seg_carry;         // per-layer selection: [batch][n_seg] records, one per layer and node (null: always sample)

@@ -140,7 +140,8 @@ __device__ uint32_t write_lane(uint32_t value, uint32_t lane, uint32_t x) __asm(
 // queue up: atomics on one word take turns) after they have waited for some tens of microseconds.  So every share is with a running
 // block or free for any block that waits, and the waits end whatever number of the kernel's blocks the device holds and
 // whatever runs beside it; they are bounded all the same (counted as a device error).
-// As a launch of its own this took 14 us, and 4.6 us in a full queue where thresholds are carried and it had nothing to do.
+// A launch of its own costs 4.6 us in a full queue where thresholds are carried and it has nothing to do; sampling takes 14 us there and 60 to
+// 130 us here, as all blocks wait.  So this is for the odd selection in a run of carried ones (offers_hold, api.hip).
 constexpr uint32_t kShares = kSample / (4 * kBlock);
 
 template <bool FUSED>
@@ -254,11 +255,11 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
     if (SAMPLE) {
         __shared__ __align__(16) uint32_t hist[kSampleBins];
         // scalar loads, as nothing has been stored yet: vector loads here hold up the row's (4 x 25.6 M: 386 us for 382.6)
-        const Carry *c = a.offers + node;
+        const Carry *c = a.carry + node;
         const uint32_t c_n = c->n, c_k = c->k, c_est = c->next_t_est;
         // A node whose record of carried thresholds offers one for this very selection (same shape, the selection right after
         // the one that wrote it) takes that one and samples nothing.
-        if (a.carry && c_n == a.n && c_k == a.k && c_est != 0) {
+        if (c_n == a.n && c_k == a.k && c_est != 0) {
             t_est = c_est;
             if (blockIdx.x == 0 && threadIdx.x == 0) {
                 st_agent32(&a.sel[node].t_est, t_est);   // (its line holds a neighbour's record too, which its sample may be writing)

@@ -516,12 +516,14 @@ __device__ __forceinline__ void report_outcome(const SelArgs &a, const int node,
     s->fast_ok = ok;
     if (ok) { s->thr = thr; s->quota = quota; }
     atomicAdd(ok ? &a.stats->fast : &a.stats->fallback, 1u);
-    // the host sees the outcome without synchronising; a carried threshold that failed says nothing about the data
-    if (a.notify && (ok || !s->carried)) st_system32(a.notify + (ok ? 1 : 0), a.notify_value);
+    bool offers = false;
     if (a.carry) {
         carry_update(a.carry + node, a.n, a.k, false, ok, s->carried != 0, thr, t_est, total, a.carry_target, a.carry_most);
         a.carry[node].zeros_pay = a.zero_early && s->recorded / kZerosPerCrowdedRow >= s->crowded;
+        offers = a.carry[node].next_t_est != 0;
     }
+    // the host sees the outcome without synchronising; a carried threshold that failed says nothing about the data
+    if (a.notify) st_system32(a.notify + (ok ? (offers ? kServedOffers : kServed) : s->carried ? kOfferFailed : kFellBack), a.notify_value);
 }
 
 
@@ -1342,7 +1344,7 @@ __device__ __forceinline__ void finish_node(const SelArgs &a, const int node, co
         if (report) report_outcome(a, node, s, true, thr, quota, total, s->t_est);
         else {   // short vectors: one node speaks for those served (256 stores to host memory would take 25 us)
             carry_lapse(a, node);
-            if (a.notify && node == 0) st_system32(a.notify + 1, a.notify_value);
+            if (a.notify && node == 0) st_system32(a.notify + kServed, a.notify_value);
         }
     }
     // ordered output: kLen consecutive entries per thread
@@ -1404,7 +1406,7 @@ __global__ __launch_bounds__(1024) void k_finish_or_exact(SelArgs a, int report)
     if (ok) finish_node(a, node, total, report, offs, hist, wave_tmp, res);
     else if (tid == 0) {
         if (report) report_outcome(a, node, a.sel + node, false, 0, 0, total, a.sel[node].t_est);
-        else if (a.notify) st_system32(a.notify, a.notify_value);
+        else if (a.notify) st_system32(a.notify + kFellBack, a.notify_value);
     }
 }
 

@@ -131,6 +131,37 @@ def fall_backs_of_the_one_launch_finish(h):
     return out
 
 
+def who_samples(h):
+    """One letter per selection of 2^20 elements: l, a launch samples before the pass; p, the pass takes the carried threshold or samples."""
+    ctx = h.ctx(1 << 28, 1 << 18, 1)
+    words = C.cast(p.in_dll(h.fake, "pinned"), C.POINTER(C.c_uint32))
+    numbered = 0
+
+    def run(outcomes, n=1 << 20):
+        nonlocal numbered
+        seen = ""
+        for word in outcomes:
+            h.topk(ctx, n, 1000, 1)
+            numbered += 1
+            if word is not None:
+                words[word] = numbered
+            seen += "l" if "k_sample" in h.raw else "p"
+        return seen
+
+    out = {"served, nothing carried": run([1] * 20), "carried": run([2] * 20), "carried, long vector": run([2], 1 << 28)}
+    out["once not, by one node of two"] = run([1]) + run([2] * 18)
+    out["once not seen yet"] = run([None, 2])
+    out["a carried one fell back"] = run([3]) + run([2] * 17)
+    assert h.lib.lgc_set_option(ctx, 0, C.c_int64(1)) == 0      # LGC_OPT_SELECT_PATH: exact, which carries nothing
+    h.topk(ctx, 1 << 20, 1000, 1)
+    assert h.lib.lgc_set_option(ctx, 0, C.c_int64(0)) == 0
+    out["after an exact selection"] = run([2] * 17)
+    assert h.lib.lgc_set_option(ctx, 2, C.c_int64(0)) == 0      # LGC_OPT_CARRY_THRESHOLD
+    out["option off"] = run([1] * 2)
+    h.lib.lgc_destroy(ctx)
+    return out
+
+
 @pytest.fixture(scope="module")
 def answers(tmp_path_factory):
     """Every scenario (a function above, by name), run in one process of its own."""
@@ -172,6 +203,13 @@ def test_fall_backs_of_the_one_launch_finish(answers):
     assert got["larger, each"] == (["finish"] + ["many"] * 64) * 2 + ["finish"] + ["many"] * 9
 
 
+def test_the_pass_samples_only_in_a_run_of_carried_thresholds(answers):
+    assert answers["who_samples"] == {
+        "served, nothing carried": "l" * 20, "carried": "l" * 16 + "p" * 4, "carried, long vector": "l",
+        "once not, by one node of two": "p" + "l" * 16 + "p" * 2, "once not seen yet": "pp", "a carried one fell back": "p" + "l" * 16 + "p",
+        "after an exact selection": "l" * 16 + "p", "option off": "ll"}
+
+
 if __name__ == "__main__":
     host = Host(sys.argv[1], sys.argv[2])
-    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place, records, fall_backs_of_the_one_launch_finish)}))
+    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place, records, fall_backs_of_the_one_launch_finish, who_samples)}))
