@@ -339,7 +339,7 @@ lgc_status lgc_reserve(lgc_ctx *ctx, const lgc_ae *ae /* nullable */, uint64_t k
  *       a context with room for more first takes the launches that use it, for
  *       64 selections, when that one falls back.)
  *       It sees the outcomes without any synchronisation: each selection
- *       stores its number to one of two pinned host words, which the host
+ *       stores its number to one of the pinned host words, which the host
  *       reads when it queues the next selection, so the switch comes some
  *       calls late when the host runs ahead of the device, and a recorded
  *       HIP graph keeps the choice made when it was recorded.
