@@ -16,6 +16,10 @@
 
 using namespace lgc;
 
+#ifndef LGC_SAMPLE_SPINS   // build.py makes a second library with a short bound, for the test of what happens when it is reached
+#define LGC_SAMPLE_SPINS (1u << 22)
+#endif
+
 struct lgc_ctx {
     int device = 0;
     uint64_t max_n = 0, max_k = 0;
@@ -271,6 +275,7 @@ SelArgs make_args(lgc_ctx *c, const float *g, float *u, float *v, uint64_t n, ui
     a.rank = 0; a.cap = c->cap; a.rows = c->rows;
     a.status_cand_stride = c->status_cand_stride; a.status_exact_stride = c->status_exact_stride;
     a.spin_limit = 1u << 22;
+    a.sample_spins = LGC_SAMPLE_SPINS;
     a.force = 0;
     a.stats = c->stats;
     a.notify = c->fell_back_dev;

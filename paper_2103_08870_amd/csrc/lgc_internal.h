@@ -72,7 +72,7 @@ struct Ctr {
     uint32_t done[5];     // completed shares of each phase
     uint32_t sampled;     // sampling blocks of the node, or shares, that have finished (the last one works out the estimate)
     uint32_t share;       // sampling in the pass: next share to hand out
-    uint32_t ready;       // sampling in the pass: 1: the node's t_est stands
+    uint32_t ready;       // sampling in the pass: 1 + the threshold that all blocks of the node go by (0: none yet); set once
     uint32_t pad[23];
 };
 static_assert(sizeof(Ctr) == 128, "Ctr is one 128-byte line");
@@ -125,6 +125,7 @@ struct SelArgs {
     uint32_t rows;    // bitmap rows per node (stride of row_count; bitmap stride is rows * kRowWords)
     uint32_t status_cand_stride, status_exact_stride;  // 64-bit words per node: chunk counts of the candidate list, block counts of the exact path
     uint32_t spin_limit;      // bound of a wait for the shares of the previous phase (exact path in one launch)
+    uint32_t sample_spins;    // bound of a block's wait for the threshold (sampling in the pass)
     int force;                // exact path chosen by the host (ignore fast_ok)
     Stats *stats;
     uint32_t *notify;         // pinned host words (device address; null: none): a selection stores notify_value to the one of its Outcome

@@ -139,14 +139,17 @@ __device__ uint32_t write_lane(uint32_t value, uint32_t lane, uint32_t x) __asm(
 // so writes u or v, before it stands.  The first kShares blocks of the node take shares at once, the others (whose tickets would only
 // queue up: atomics on one word take turns) after they have waited for some tens of microseconds.  So every share is with a running
 // block or free for any block that waits, and the waits end whatever number of the kernel's blocks the device holds and
-// whatever runs beside it; they are bounded all the same (counted as a device error).
+// whatever runs beside it.  They are bounded all the same.  A block that has waited too long settles on "no candidates", for the whole node:
+// ctr->ready holds the one threshold that all of its blocks go by, whoever sets it first.  Rows cut at different thresholds would
+// make a list that lacks elements above T*; a node without candidates takes the exact path.
 // A launch of its own costs 4.6 us in a full queue where thresholds are carried and it has nothing to do; sampling takes 14 us there and 60 to
 // 130 us here, as all blocks wait.  So this is for the odd selection in a run of carried ones (offers_hold, api.hip).
 constexpr uint32_t kShares = kSample / (4 * kBlock);
+constexpr uint32_t kNoCandidates = 0x80000000u;   // a threshold above every key
 
 template <bool FUSED>
-__device__ __forceinline__ void sample_threshold(const SelArgs &a, const int node, uint32_t *hist /*[kSampleBins]*/) {
-    __shared__ uint32_t wave_tmp[kWaves], res[2], word;
+__device__ __forceinline__ uint32_t sample_threshold(const SelArgs &a, const int node, uint32_t *hist /*[kSampleBins]*/) {
+    __shared__ uint32_t wave_tmp[kWaves], res[2], word, stands;
     const int tid = threadIdx.x;
     Ctr *ctr = a.ctr + node;
     const size_t off = (size_t)node * a.stride;
@@ -156,17 +159,18 @@ __device__ __forceinline__ void sample_threshold(const SelArgs &a, const int nod
     for (;;) {
         __syncthreads();
         if (tid == 0) {
-            // a share's number, kShares: none left (or not asked yet), kShares + 1: the estimate stands, kShares + 2: given up
-            uint32_t next = kShares;
-            if (ld_agent32(&ctr->ready)) next = kShares + 1;
-            else if (spins >= a.spin_limit) { atomicAdd(&a.stats->errors, 1u); next = kShares + 2; }
-            else if (helps || spins == 64) { next = atomicAdd(&ctr->share, 1u); next = next < kShares ? next : kShares; }
-            if (next == kShares) __builtin_amdgcn_s_sleep(16);
-            word = next;
+            uint32_t next = kShares, set = ld_agent32(&ctr->ready);   // a share's number (kShares: none left, or not asked yet); 1 + the threshold
+            if (set == 0 && spins >= a.sample_spins) {
+                set = atomicCAS(&ctr->ready, 0u, kNoCandidates + 1);
+                if (set == 0) set = kNoCandidates + 1;
+            }
+            if (set == 0 && (helps || spins == 64)) { next = atomicAdd(&ctr->share, 1u); next = next < kShares ? next : kShares; }
+            if (set == 0 && next == kShares) __builtin_amdgcn_s_sleep(16);
+            word = next; stands = set;
         }
         __syncthreads();
-        const uint32_t share = __builtin_amdgcn_readfirstlane(word);
-        if (share > kShares) return;
+        const uint32_t share = __builtin_amdgcn_readfirstlane(word), set = __builtin_amdgcn_readfirstlane(stands);
+        if (set != 0) return set - 1;
         if (share == kShares) { helps = false; ++spins; continue; }      // (block-uniform)
         helps = true;
         const uint32_t j = share * kBlock + tid, e = sample_place(j, node, a.n);
@@ -220,10 +224,7 @@ __device__ __forceinline__ void sample_threshold(const SelArgs &a, const int nod
         }
         __syncthreads();
         find_rank_bin<1024, kBlock>(hist, rank, wave_tmp, res);
-        if (tid == 0) {
-            st_agent32(&a.sel[node].t_est, (bin << 20) | ((res[0] == 0xffffffffu ? 0u : res[0]) << 10));
-            __hip_atomic_store(&ctr->ready, 1u, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        if (tid == 0) atomicCAS(&ctr->ready, 0u, 1u + ((bin << 20) | ((res[0] == 0xffffffffu ? 0u : res[0]) << 10)));
     }
 }
 
@@ -259,16 +260,11 @@ __global__ __launch_bounds__(kBlock) void k_candidates(SelArgs a) {
         const uint32_t c_n = c->n, c_k = c->k, c_est = c->next_t_est;
         // A node whose record of carried thresholds offers one for this very selection (same shape, the selection right after
         // the one that wrote it) takes that one and samples nothing.
-        if (c_n == a.n && c_k == a.k && c_est != 0) {
-            t_est = c_est;
-            if (blockIdx.x == 0 && threadIdx.x == 0) {
-                st_agent32(&a.sel[node].t_est, t_est);   // (its line holds a neighbour's record too, which its sample may be writing)
-                st_agent32(&a.sel[node].carried, 1u);
-                atomicAdd(&a.stats->carried, 1u);
-            }
-        } else {
-            sample_threshold<FUSED>(a, node, hist);
-            t_est = __builtin_amdgcn_readfirstlane(ld_agent32(&a.sel[node].t_est));
+        const bool offered = c_n == a.n && c_k == a.k && c_est != 0;
+        t_est = offered ? c_est : sample_threshold<FUSED>(a, node, hist);
+        if (blockIdx.x == 0 && threadIdx.x == 0) {
+            a.sel[node].t_est = t_est;
+            if (offered) { a.sel[node].carried = 1; atomicAdd(&a.stats->carried, 1u); }
         }
     }
     const uint32_t *seg_t = SEG ? a.seg_t + (size_t)node * a.n_seg : nullptr;
