@@ -52,15 +52,13 @@ constexpr uint32_t kRowsPerLaunch = 104 * 1024;
 // call clears the set of the next one.
 struct Sel {
     uint32_t t_est;       // fast path: candidates are the elements with key >= t_est
-    uint32_t cand_total;  // number of candidates found (atomic adds in the gather kernel only)
+    uint32_t cand_total;  // number of candidates found (summed by atomic adds in k_gather, stored by one thread in k_gather_pieces and k_finish_or_exact)
     uint32_t thr;         // exact k-th largest key T*
     uint32_t quota;       // how many elements with key == T* are taken (lowest indices first)
     uint32_t fast_ok;     // 1: the fast path produced this node's output
     uint32_t carried;     // 1: t_est was carried over from earlier selections, not sampled
     uint32_t t_zero;      // zero_early: the pass zeroes the elements with key >= t_zero (>= t_est; ~0: none) of the rows that keep a record
-    uint32_t recorded;    // zeros: candidates of the rows with up to kZeroRecord, and rows with more (atomic adds in the gather kernel only)
-    uint32_t crowded;
-    uint32_t pad[7];
+    uint32_t pad[9];
 };
 static_assert(sizeof(Sel) == 64, "Sel is one 64-byte record");
 
@@ -73,7 +71,9 @@ struct Ctr {
     uint32_t sampled;     // sampling blocks of the node, or shares, that have finished (the last one works out the estimate)
     uint32_t share;       // sampling in the pass: next share to hand out
     uint32_t ready;       // sampling in the pass: 1 + the threshold that all blocks of the node go by (0: none yet); set once
-    uint32_t pad[23];
+    uint32_t recorded;    // zeros from the pass: candidates of the rows with up to kZeroRecord, and rows with more
+    uint32_t crowded;
+    uint32_t pad[21];
 };
 static_assert(sizeof(Ctr) == 128, "Ctr is one 128-byte line");
 

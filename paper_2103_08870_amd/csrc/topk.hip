@@ -323,11 +323,11 @@ __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
 }
 
 // For the next selection's zeros from the pass (a.zero_early), what they would save and cost: a lane's row holds c candidates
-__device__ __forceinline__ void count_crowded(Sel *s, const uint32_t c) {
+__device__ __forceinline__ void count_crowded(Ctr *ctr, const uint32_t c) {
     const uint32_t held = wave_sum(c <= (uint32_t)kZeroRecord ? c : 0u), crowded = (uint32_t)__popcll(__ballot(c > (uint32_t)kZeroRecord));
     if ((threadIdx.x & 63) == 0) {
-        if (held) atomicAdd(&s->recorded, held);
-        if (crowded) atomicAdd(&s->crowded, crowded);
+        if (held) atomicAdd(&ctr->recorded, held);
+        if (crowded) atomicAdd(&ctr->crowded, crowded);
     }
 }
 
@@ -401,7 +401,7 @@ __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
             const uint32_t incl = wave_prefix(rc);
             offs[tid] = incl - rc;
             if (lane == 63) tmp[wave] = incl;
-            if (a.zero_early && piece[1] == 0) count_crowded(s, rc);
+            if (a.zero_early && piece[1] == 0) count_crowded(a.ctr + node, rc);
         }
         __syncthreads();
         if (q < all) {
@@ -521,7 +521,7 @@ __device__ __forceinline__ void report_outcome(const SelArgs &a, const int node,
     bool offers = false;
     if (a.carry) {
         carry_update(a.carry + node, a.n, a.k, false, ok, s->carried != 0, thr, t_est, total, a.carry_target, a.carry_most);
-        a.carry[node].zeros_pay = a.zero_early && s->recorded / kZerosPerCrowdedRow >= s->crowded;
+        a.carry[node].zeros_pay = a.zero_early && a.ctr[node].recorded / kZerosPerCrowdedRow >= a.ctr[node].crowded;
         offers = a.carry[node].next_t_est != 0;
     }
     // the host sees the outcome without synchronising; a carried threshold that failed says nothing about the data

@@ -1,4 +1,5 @@
-"""The gfx950 assembly of every kernel, as the library's build flags make it: wait states the hardware does not supply."""
+"""The gfx950 assembly of every kernel, as the library's build flags make it: wait states the hardware does not supply.  And in the
+sources: no record of a node's selection that gets both atomics and plain stores from one kernel."""
 import os
 import re
 import subprocess
@@ -66,3 +67,44 @@ def test_scalar_registers_written_by_vector_instructions_are_waited_for():
     for source, text in listings.items():
         assert source == "api.hip" or text.count("v_cmp") > 0   # (the host side has no kernels)
         assert short_waits(text) == [], source
+
+
+def functions(text):
+    """{name: [body, ..]} of the functions defined at namespace level."""
+    text, found, at = re.sub(r"//[^\n]*|__launch_bounds__\([^()]*\)", "", text), {}, 0
+    for m in re.finditer(r"^(?!namespace)[\w].*?\b(\w+)\([^;{}]*\)\s*\{", text, re.M):
+        if m.start() < at:
+            continue
+        depth, at = 1, m.end()
+        while depth:
+            depth += {"{": 1, "}": -1}.get(text[at], 0)
+            at += 1
+        found.setdefault(m[1], []).append((m[0], text[m.end():at]))
+    return found
+
+
+def test_a_node_s_record_gets_atomics_or_plain_stores_from_a_kernel():
+    # Each XCD has an L2 of its own: a line that several of them update by atomics can lose what one of them stores.  `s`, `sel`: a Sel record
+    every = {}
+    for name in ("device_helpers.h", "carry.h", *build.SOURCES):
+        with open(os.path.join(build.CSRC, name)) as f:
+            for k, v in functions(f.read()).items():
+                every.setdefault(k, []).extend(v)
+
+    def reached(name, seen):
+        for _, body in every.get(name, []):
+            for other in set(re.findall(r"\b(\w+)(?:<[^;()]*>)?\(", body)) & every.keys() - seen:
+                reached(other, seen | {name})
+                seen.add(other)
+        return seen
+
+    kernels = [k for k, v in every.items() if any("__global__" in head for head, _ in v)]
+    assert {"k_gather", "k_gather_pieces", "k_candidates", "k_sample", "k_count_chunks", "k_finish_or_exact"} <= set(kernels)
+    record = r"(?:\bs->|\bsel\[[^\]]*\]\.)"
+    stored = set()
+    for kernel in kernels:
+        text = "".join(body for f in {kernel} | reached(kernel, set()) for _, body in every[f])
+        atomics, stores = re.findall(r"atomic\w+\(&(?:a\.)?" + record + r"(\w+)", text), re.findall(record + r"(\w+) = ", text)
+        assert not (atomics and stores), (kernel, atomics, stores)
+        stored |= set(stores) | set(atomics)
+    assert {"t_est", "cand_total", "thr", "fast_ok"} <= stored
