@@ -62,7 +62,10 @@ void launch_clear(uint32_t *words, uint32_t count, hipStream_t st) {
 // A node whose record of carried thresholds offers a candidate threshold for this very selection (same shape, the
 // selection right after the one that wrote it) takes that one and samples nothing.
 // The kernel also clears the state set that the next call will use.
-template <bool FUSED>
+// ZEROS (a.zero_early): and t_zero, from a second order statistic, whose second level is counted in the same sweep over the keys.  (A sweep
+// for each, in one form for all, took 128 registers and spilled two, against 75 and 79 here: a call without a context, 262 144 elements 28.0 us
+// against 26.9, 2 x 302 826 44.0 / 42.8, 3.3 M 57.2 / 56.4.)
+template <bool FUSED, bool ZEROS>
 __global__ __launch_bounds__(1024) void k_sample(SelArgs a) {
     __shared__ __align__(16) uint32_t hist[kSampleBins];
     __shared__ uint32_t wave_tmp[16], res[2];
@@ -78,7 +81,7 @@ __global__ __launch_bounds__(1024) void k_sample(SelArgs a) {
         if (t != 0 && c->n == a.n && c->k == a.k) {
             if (blockIdx.x == 0 && tid == 0) {
                 a.sel[node].t_est = t; a.sel[node].carried = 1; atomicAdd(&a.stats->carried, 1u);
-                a.sel[node].t_zero = !c->zeros_pay ? ~0u : c->next_t > t ? c->next_t : t;
+                if (ZEROS) a.sel[node].t_zero = !c->zeros_pay ? ~0u : c->next_t > t ? c->next_t : t;
             }
             return;
         }
@@ -124,43 +127,46 @@ __global__ __launch_bounds__(1024) void k_sample(SelArgs a) {
     find_rank_bin<kSampleBins, 1024>(hist, a.rank, wave_tmp, res);
     const uint32_t b1 = res[0], need = a.rank - res[1];
     __syncthreads();
-    if (b1 == 0xffffffffu) { if (tid == 0) a.sel[node].t_zero = ~0u; return; }  // cannot happen (rank <= kSample); t_est stays 0: everything is a candidate
-    uint32_t b2 = 0, need2 = 0;
+    if (b1 == 0xffffffffu) { if (ZEROS && tid == 0) a.sel[node].t_zero = ~0u; return; }  // cannot happen (rank <= kSample); t_est stays 0: everything is a candidate
+    uint32_t b2 = 0xffffffffu, need2 = 0;   // ZEROS: the same of the order statistic that t_zero is taken from
     // (the record is the previous selection's, of this shape)
-    const bool zeros = a.zero_early && a.carry && a.carry[node].len > 0 && a.carry[node].n == a.n && a.carry[node].k == a.k && a.carry[node].zeros_pay;
+    const bool zeros = ZEROS && a.carry && a.carry[node].len > 0 && a.carry[node].n == a.n && a.carry[node].k == a.k && a.carry[node].zeros_pay;
     if (zeros) {
         find_rank_bin<kSampleBins, 1024>(hist, a.rank_zero, wave_tmp, res);
         b2 = res[0]; need2 = a.rank_zero - res[1];
         __syncthreads();
     }
-    // the key, 2^-13 resolution, of the need-th largest of the sampled keys of first-level bin `bin`
-    auto refine = [&](const uint32_t bin, const uint32_t rank) -> uint32_t {
-        hist[tid] = 0;
-        __syncthreads();
+    // second level, 2^-13 resolution: the sampled keys of first-level bin b1 (words 0 .. 1023) and of b2 (those after them)
+    hist[tid] = 0;
+    if (ZEROS) hist[1024 + tid] = 0;
+    __syncthreads();
 #pragma unroll
-        for (int r = 0; r < (int)(kSample / 4 / 1024); ++r) {
+    for (int r = 0; r < (int)(kSample / 4 / 1024); ++r) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if ((x[r][i] >> 20) == bin) atomicAdd(&hist[(x[r][i] >> 10) & 1023u], 1u);
+        for (int i = 0; i < 4; ++i) {
+            if ((x[r][i] >> 20) == b1) atomicAdd(&hist[(x[r][i] >> 10) & 1023u], 1u);
+            if (ZEROS && (x[r][i] >> 20) == b2) atomicAdd(&hist[1024 + ((x[r][i] >> 10) & 1023u)], 1u);
         }
-        __syncthreads();
-        find_rank_bin<1024, 1024>(hist, rank, wave_tmp, res);
-        return (bin << 20) | ((res[0] == 0xffffffffu ? 0u : res[0]) << 10);
-    };
-    const uint32_t t = refine(b1, need);
-    if (tid == 0) a.sel[node].t_est = t;
-    uint32_t t2 = ~0u;
-    if (zeros) {   // (rank_zero <= rank: t_zero >= t_est)
-        __syncthreads();
-        t2 = refine(b2, need2);
     }
-    if (tid == 0) a.sel[node].t_zero = t2;
+    __syncthreads();
+    find_rank_bin<1024, 1024>(hist, need, wave_tmp, res);
+    if (tid == 0) a.sel[node].t_est = (b1 << 20) | ((res[0] == 0xffffffffu ? 0u : res[0]) << 10);
+    if (ZEROS) {   // (rank_zero <= rank: t_zero >= t_est)
+        uint32_t t2 = ~0u;
+        if (zeros) {
+            __syncthreads();
+            find_rank_bin<1024, 1024>(hist + 1024, need2, wave_tmp, res);
+            t2 = (b2 << 20) | ((res[0] == 0xffffffffu ? 0u : res[0]) << 10);
+        }
+        if (tid == 0) a.sel[node].t_zero = t2;
+    }
 }
 
 void launch_sample(const SelArgs &a, int batch, bool fused, hipStream_t st) {
     dim3 grid(kSampleGroups / 1024, batch);
-    if (fused) hipLaunchKernelGGL(k_sample<true>, grid, dim3(1024), 0, st, a);
-    else hipLaunchKernelGGL(k_sample<false>, grid, dim3(1024), 0, st, a);
+    if (a.zero_early) hipLaunchKernelGGL((k_sample<true, true>), grid, dim3(1024), 0, st, a);   // (fused, always)
+    else if (fused) hipLaunchKernelGGL((k_sample<true, false>), grid, dim3(1024), 0, st, a);
+    else hipLaunchKernelGGL((k_sample<false, false>), grid, dim3(1024), 0, st, a);
 }
 
 // ------------------------------------------------------------------ gather of the candidates

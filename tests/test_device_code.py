@@ -1,9 +1,11 @@
-"""The gfx950 assembly of every kernel, as the library's build flags make it: wait states the hardware does not supply.  And in the
-sources: no record of a node's selection that gets both atomics and plain stores from one kernel."""
+"""The gfx950 assembly of every kernel, as the library's build flags make it: wait states the hardware does not supply,
+registers and scratch memory.  And in the sources: no record of a node's selection that gets both atomics and plain stores from one kernel."""
 import os
 import re
 import subprocess
 from concurrent.futures import ThreadPoolExecutor
+
+import pytest
 
 from paper_2103_08870_amd import build
 
@@ -61,9 +63,28 @@ def test_the_check_sees_a_short_wait():
     assert not short_waits("v_cmp_ne_u32_e64 s[0:1], 0, v0\ns_mov_b32 s0, s5\nv_mov_b32_e32 v20, s0\n")
 
 
-def test_scalar_registers_written_by_vector_instructions_are_waited_for():
+@pytest.fixture(scope="module")
+def listings():
     with ThreadPoolExecutor(max_workers=8) as ex:
-        listings = dict(zip(build.SOURCES, ex.map(assembly, build.SOURCES)))
+        return dict(zip(build.SOURCES, ex.map(assembly, build.SOURCES)))
+
+
+def resources(text):
+    """{kernel: {"vgpr_count": .., ..}} as the listing's metadata has it."""
+    found = {}
+    for part in text.split("- .agpr_count:")[1:]:
+        found[re.search(r"\.name:\s+(\S+)", part)[1]] = {k: int(v) for k, v in re.findall(r"\.(\w+_(?:count|size)):\s+(\d+)", part)}
+    return found
+
+
+def test_no_kernel_keeps_registers_in_memory(listings):
+    every = {kernel: r for text in listings.values() for kernel, r in resources(text).items()}
+    assert len(every) > 50 and all("vgpr_count" in r for r in every.values())
+    # (scalar registers are spilled into the lanes of vector registers, which costs no memory)
+    assert {k: r for k, r in every.items() if r["private_segment_fixed_size"] or r["vgpr_spill_count"]} == {}
+
+
+def test_scalar_registers_written_by_vector_instructions_are_waited_for(listings):
     for source, text in listings.items():
         assert source == "api.hip" or text.count("v_cmp") > 0   # (the host side has no kernels)
         assert short_waits(text) == [], source
