@@ -84,6 +84,12 @@ def test_no_kernel_keeps_registers_in_memory(listings):
     assert {k: r for k, r in every.items() if r["private_segment_fixed_size"] or r["vgpr_spill_count"]} == {}
 
 
+def test_the_pass_leaves_room_for_seven_wavefronts(listings):
+    # 512 vector registers per SIMD, handed out in eights: the flat selection's forms, with and without records or their own sample
+    forms = {k: r["vgpr_count"] for k, r in resources(listings["streaming.hip"]).items() if re.search(r"k_candidatesILb[01]ELb0ELb[01]ELb0E", k)}
+    assert len(forms) == 8 and max(forms.values()) <= 72, forms
+
+
 def test_scalar_registers_written_by_vector_instructions_are_waited_for(listings):
     for source, text in listings.items():
         assert source == "api.hip" or text.count("v_cmp") > 0   # (the host side has no kernels)
