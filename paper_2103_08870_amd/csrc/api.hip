@@ -57,7 +57,9 @@ struct lgc_ctx {
     // next selection, and after fall-backs takes the exact path outright for a while before it tries the fast path again.
     uint32_t *fell_back_host = nullptr, *fell_back_dev = nullptr;
     uint32_t call_number = 0, fell_back_seen = 0;
-    uint32_t offers_from = 0;   // the last call number before the records of carried thresholds were last emptied by the host's choice
+    uint32_t offers_from = 0;   // the last call number before the records of carried thresholds were last emptied by the host's choice, or the shape changed
+    uint64_t last_n = 0, last_k = 0;   // shape of the previous selection
+    int last_batch = 0;
     int exact_calls_left = 0, penalty = 0;
     // The one-launch finish holds shorter lists than a context with a large capacity: after a fall-back of it such a context
     // goes through the many-block launches for some calls.  Bit i: the call i numbers ago was one.
@@ -297,7 +299,10 @@ SelArgs make_args(lgc_ctx *c, const float *g, float *u, float *v, uint64_t n, ui
 }
 
 constexpr int kManyBlockCalls = 64;  // selections between the tries of the one-launch finish after it fell back where longer lists are held
-constexpr int kOfferRun = 16;        // selections in a row that must have left carried thresholds before the pass is launched on the next one's
+// Selections in a row, per node, that must have left carried thresholds before the pass is launched on the next one's: about what the pass has to
+// gain to make up for one that samples itself.  us, gained per call / lost by that one: 2^18 elements 1.9 / 12, 2^20 1.8 / 14, 16 M 1.7 / 27; 2 x 12 M
+// 2 / 65; 3 x 3.33 M 2.4 / 36; 4 x 25.6 M 2 / 130; 8 x 2^20 2.2 / 76, 8 x 3 M 2.6 / 141, 8 x 13 M 1.5 / 290: 6 to 24 calls per node.
+constexpr int kOfferRun = 24;
 constexpr int kMaxExactCalls = 64;   // most selections in a row that take the exact path outright after fall-backs were seen
 
 // Short vectors are selected exactly by kernels of their own, unless the exact radix path was asked for.
@@ -339,12 +344,16 @@ uint64_t record_rows(uint64_t max_n, uint64_t max_k, int max_batch) {
 
 uint32_t later(uint32_t a, uint32_t b) { return (int32_t)(a - b) > 0 ? a : b; }   // of two call numbers
 
-// Whether the last kOfferRun selections and more, as far as the host has seen, all left a carried threshold for every node.
-bool offers_hold(const lgc_ctx *c) {
+// Whether the last kOfferRun * batch selections and more, as far as the host has seen, were of this call's shape and all left a carried threshold
+// for every node; and the call is not being recorded: what a recorded one will find when it is replayed nobody knows.
+bool offers_hold(const lgc_ctx *c, int batch, hipStream_t st) {
     if (!c->fell_back_host) return false;
     const volatile uint32_t *w = c->fell_back_host;
     const uint32_t with = w[kServedOffers], without = later(later(w[kServed], w[kFellBack]), later(w[kOfferFailed], c->offers_from));
-    return (int32_t)(with - without) >= kOfferRun;
+    if ((int32_t)(with - without) < kOfferRun * batch) return false;
+    hipStreamCaptureStatus recorded = hipStreamCaptureStatusActive;
+    if (hipStreamIsCapturing(st, &recorded) != hipSuccess) { (void)hipGetLastError(); return false; }
+    return recorded == hipStreamCaptureStatusNone;
 }
 
 // accumulate (optional) + select; g == nullptr means selection only
@@ -421,6 +430,8 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         ctx->spare_finishes = ctx->spare_finishes << 1 | (uint64_t)(spare_finish && finishes_in_one && fast);
     }
     if (!fast) ctx->offers_from = ctx->call_number;
+    else if (n != ctx->last_n || k != ctx->last_k || batch != ctx->last_batch) ctx->offers_from = ctx->call_number - 1;   // no record is of this shape
+    ctx->last_n = n; ctx->last_k = k; ctx->last_batch = batch;
     ctx->cur ^= 1;  // this call uses the clean set and cleans the other one for the next call
     if (small) {
         if (ctx->single_state) {   // no launch has cleared the scratch before this call: the first kernel does
@@ -432,8 +443,8 @@ lgc_status run_select(lgc_ctx *ctx, const float *g, float *u, float *v, uint64_t
         // In a run whose thresholds are carried a pass of one launch takes them itself; before a longer one a launch does (whose 5 us
         // are then a thousandth).  Whole step, us, by a launch / in the pass: 2^20 elements 31.9 / 28.8, 3 x 3.33 M 63.6 / 62.2, 4 x 25.6 M
         // 384.3 / 382.9; 2^28, 1 % (three launches): 1233 / 1256.  Where no threshold has been carried after all, the pass samples one, and
-        // all of its blocks wait for that: a new run's first pass 4 x 25.6 M 435 / 557, 3 x 3.33 M 119 / 176.
-        a.sample_in_pass = !a.zero_early && (uint64_t)a.rec_stride * batch <= kRowsPerLaunch && a.carry && offers_hold(ctx);
+        // all of its blocks wait for that (kOfferRun).
+        a.sample_in_pass = !a.zero_early && (uint64_t)a.rec_stride * batch <= kRowsPerLaunch && a.carry && offers_hold(ctx, batch, st);
         if (!a.sample_in_pass) launch_sample(a, batch, fused, st);   // (each clears the next call's state set)
         launch_candidates(a, batch, fused, st, profile_bracket(ctx));
         if (finishes_in_one) launch_finish_from_bitmap(a, batch, true, ctx->cus, st);

@@ -209,7 +209,7 @@ __device__ __forceinline__ uint32_t sample_threshold(const SelArgs &a, const int
         __syncthreads();
         for (int i = tid; i < 1024; i += kBlock) hist[i] = 0;
         __syncthreads();
-        constexpr int kAhead = 2;   // (four take 76 registers, which leaves room for six wavefronts per SIMD, not seven)
+        constexpr int kAhead = 2;   // (four: 76 registers, room for six wavefronts per SIMD instead of seven; 3 x 3.33 M, whole step: 62.1 us for 61.7)
         static_assert(kSample / 4 % (kAhead * kBlock) == 0, "whole rounds");
 #pragma unroll 1
         for (uint32_t i0 = tid; i0 < kSample / 4; i0 += kAhead * kBlock) {

@@ -46,6 +46,12 @@ hipError_t hipGetDeviceProperties(hipDeviceProp_t *p, int) { memset(p, 0, sizeof
 hipError_t hipDeviceGetAttribute(int *x, hipDeviceAttribute_t, int) { *x = 256; return hipSuccess; }
 hipError_t hipDeviceSynchronize() { return hipSuccess; }
 hipError_t hipGetLastError() { return hipSuccess; }
+int capturing;   // whether the stream is being recorded; negative: the runtime refuses to say
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) {
+    if (capturing < 0) return hipErrorStreamCaptureImplicit;
+    *s = capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
 hipError_t hipMalloc(void **p, size_t bytes) {
     *p = (void *)next_address;
     next_address += (bytes + 8191) / 4096 * 4096;

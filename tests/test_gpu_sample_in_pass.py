@@ -15,7 +15,7 @@ import torch
 
 pytestmark = pytest.mark.gpu
 ONE_LAUNCH = 104 * 1024 * 1024      # elements of all nodes, in rows of 1024
-RUN = 16                            # selections in a row that must have left carried thresholds
+RUN = 24                            # selections in a row, per node, that must have left carried thresholds
 
 
 def library(name):
@@ -64,16 +64,17 @@ class Run:
         return vals, idx
 
     def carry(self, gen):
-        """Selections from fixed residuals, one after the other: T* falls smoothly, thresholds are carried, and more than RUN in a row."""
+        """Selections from fixed residuals, one after the other: T* falls smoothly, thresholds are carried, and for more than a run."""
         self.v.normal_(generator=gen).mul_(1e-3)
         row = 0
-        for _ in range(16 * RUN):
+        run = RUN * self.nodes
+        for _ in range(run + 64):
             before = self.B.lgc_stats_carried(self.ctx)
             self.step(self.still)
             row = row + 1 if self.B.lgc_stats_carried(self.ctx) - before == self.nodes else 0
-            if row == RUN + 1:
+            if row == run + 1:
                 break
-        assert row == RUN + 1, row
+        assert row == run + 1, row
         self.B.lgc_stats(self.ctx)                # (counts anew)
         self.ru.copy_(self.u)
         self.rv = self.v.clone()

@@ -133,29 +133,43 @@ def fall_backs_of_the_one_launch_finish(h):
 
 def who_samples(h):
     """One letter per selection of 2^20 elements: l, a launch samples before the pass; p, the pass takes the carried threshold or samples."""
-    ctx = h.ctx(1 << 28, 1 << 18, 1)
+    ctx = h.ctx(1 << 28, 1 << 18, 4)
     words = C.cast(p.in_dll(h.fake, "pinned"), C.POINTER(C.c_uint32))
+    capturing = C.c_int.in_dll(h.fake, "capturing")
     numbered = 0
 
-    def run(outcomes, n=1 << 20):
+    def run(outcomes, n=1 << 20, k=1000, batch=1):
         nonlocal numbered
         seen = ""
         for word in outcomes:
-            h.topk(ctx, n, 1000, 1)
+            h.topk(ctx, n, k, batch)
             numbered += 1
             if word is not None:
                 words[word] = numbered
             seen += "l" if "k_sample" in h.raw else "p"
         return seen
 
-    out = {"served, nothing carried": run([1] * 20), "carried": run([2] * 20), "carried, long vector": run([2], 1 << 28)}
-    out["once not, by one node of two"] = run([1]) + run([2] * 18)
+    out = {"served, nothing carried": run([1] * 30), "carried": run([2] * 28), "carried, long vector": run([2], 1 << 28)}
+    run([2] * 24)
+    out["once not, by one node of two"] = run([1]) + run([2] * 26)
     out["once not seen yet"] = run([None, 2])
-    out["a carried one fell back"] = run([3]) + run([2] * 17)
+    out["a carried one fell back"] = run([3]) + run([2] * 25)
+    out["another length"] = run([2] * 26, (1 << 20) + 1)
+    out["another count"] = run([2] * 26, (1 << 20) + 1, 1001)
+    out["four nodes"] = run([2] * 98, batch=4)
+    out["one of them, unseen"] = run([None] * 3)
+    out["and four again"] = run([None] * 2 + [2], batch=4)
+    run([2] * 24)
+    capturing.value = 1
+    out["recorded"] = run([2])
+    capturing.value = -1
+    out["no answer to that"] = run([2])
+    capturing.value = 0
+    out["not recorded"] = run([2])
     assert h.lib.lgc_set_option(ctx, 0, C.c_int64(1)) == 0      # LGC_OPT_SELECT_PATH: exact, which carries nothing
     h.topk(ctx, 1 << 20, 1000, 1)
     assert h.lib.lgc_set_option(ctx, 0, C.c_int64(0)) == 0
-    out["after an exact selection"] = run([2] * 17)
+    out["after an exact selection"] = run([2] * 25)
     assert h.lib.lgc_set_option(ctx, 2, C.c_int64(0)) == 0      # LGC_OPT_CARRY_THRESHOLD
     out["option off"] = run([1] * 2)
     h.lib.lgc_destroy(ctx)
@@ -204,10 +218,12 @@ def test_fall_backs_of_the_one_launch_finish(answers):
 
 
 def test_the_pass_samples_only_in_a_run_of_carried_thresholds(answers):
+    # a run is 24 selections of one shape per node
     assert answers["who_samples"] == {
-        "served, nothing carried": "l" * 20, "carried": "l" * 16 + "p" * 4, "carried, long vector": "l",
-        "once not, by one node of two": "p" + "l" * 16 + "p" * 2, "once not seen yet": "pp", "a carried one fell back": "p" + "l" * 16 + "p",
-        "after an exact selection": "l" * 16 + "p", "option off": "ll"}
+        "served, nothing carried": "l" * 30, "carried": "l" * 24 + "p" * 4, "carried, long vector": "l",
+        "once not, by one node of two": "p" + "l" * 24 + "p" * 2, "once not seen yet": "pp", "a carried one fell back": "p" + "l" * 24 + "p",
+        "another length": "l" * 24 + "pp", "another count": "l" * 24 + "pp", "four nodes": "l" * 96 + "pp", "one of them, unseen": "lll",
+        "and four again": "lll", "recorded": "l", "no answer to that": "l", "not recorded": "p", "after an exact selection": "l" * 24 + "p", "option off": "ll"}
 
 
 if __name__ == "__main__":
