@@ -339,6 +339,8 @@ __device__ __forceinline__ void count_crowded(Ctr *ctr, const uint32_t c) {
 
 // The same for the flat selection of long vectors (a.groups_counted), with the work cut where the candidates are, not where the
 // rows are: a piece is up to T candidates of one group of kGroupRows rows, one per thread, and the node's blocks take the pieces in turn.
+// Where the bitmap is searched and no group of the node holds more than 4 T, a piece is a whole group, as each piece stages its group's 16 KB
+// (one node, spread evenly, pieces of T / whole groups: 60 M, 1 % 28.9 / 27.8 us, 40 M, 0.5 % 18.0 / 16.1).
 // Groups without candidates cost nothing, and where the candidates cluster no block is left with a multiple of the others' work.
 // us, a block per group (with the row counts summed per 8192 rows, its launch included) / pieces: 8 x 44.5 M at 0.1 % 44.8 / 28.6;
 // 2^28, 1 %, spread evenly 58.6 / 39.5; 260 M, 0.85 %, in clusters 80.2 / 75.9; 4 x 60 M, 1 %, in clusters 72.8 / 64.4.
@@ -360,11 +362,14 @@ __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
 
     // this thread's run of groups: its candidates and pieces, and those before it
     const uint32_t per = (groups + T - 1) / T, g0 = tid * per;
-    uint32_t c = 0, w = 0;
+    uint32_t c = 0, w = 0, filled = 0;
+    bool crowds = a.row_rec != nullptr;
     for (uint32_t i = 0; i < per; ++i) {
         const uint32_t x = g0 + i < groups ? sums[g0 + i] : 0u;
-        c += x; w += (x + T - 1) / T;
+        c += x; w += (x + T - 1) / T; filled += x != 0; crowds |= x > 4 * T;
     }
+    const bool whole = !__syncthreads_or(crowds);   // (the same in all the node's blocks)
+    if (whole) w = filled;
     for (int i = tid; i < kFineBins; i += T) hist[i] = 0;
     const uint32_t c_incl = wave_prefix(c), w_incl = wave_prefix(w);
     if (lane == 63) { tmp[wave] = c_incl; tmp[W + wave] = w_incl; }
@@ -381,7 +386,7 @@ __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
             if (per > 1) {
                 for (;; ++g) {   // (ends within the run: it holds the piece)
                     x = sums[g];
-                    const uint32_t here = (x + T - 1) / T;
+                    const uint32_t here = whole ? (uint32_t)(x != 0) : (x + T - 1) / T;
                     if (j < here) break;
                     j -= here; at += x;
                 }
@@ -389,7 +394,8 @@ __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
             piece[0] = g; piece[1] = j * T; piece[2] = x; piece[3] = at;
         }
         __syncthreads();
-        const uint32_t first = piece[0] * kGroupRows, q = piece[1] + tid, all = piece[2], before = piece[3];
+        const uint32_t first = piece[0] * kGroupRows, q0 = piece[1], all = piece[2], before = piece[3];
+        const uint32_t end = whole || all - q0 < (uint32_t)T ? all : q0 + T;
         const uint32_t mine = nrows - first < (uint32_t)kGroupRows ? nrows - first : (uint32_t)kGroupRows;
         const uint32_t rc = (uint32_t)tid < mine ? cnt[first + tid] : 0u;
         const unsigned long long *bitmap = a.bitmap + ((size_t)node * a.rows + first) * kRowWords;
@@ -407,10 +413,10 @@ __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
             const uint32_t incl = wave_prefix(rc);
             offs[tid] = incl - rc;
             if (lane == 63) tmp[wave] = incl;
-            if (a.zero_early && piece[1] == 0) count_crowded(a.ctr + node, rc);
+            if (a.zero_early && q0 == 0) count_crowded(a.ctr + node, rc);
         }
         __syncthreads();
-        if (q < all) {
+        for (uint32_t q = q0 + tid; q < end; q += T) {
             // last row r with start(r) <= q: it is the one that holds candidate q of the group
             const uint32_t half = tmp[0];
             auto start = [&](uint32_t r) { return offs[r] + (r < 64 ? 0u : half); };
@@ -469,8 +475,10 @@ void launch_gather(const SelArgs &args, int batch, int cus, hipStream_t st) {
     if (a.groups_counted && !a.seg_t) {
         // Blocks of 512 threads where the bitmap is searched, of 1024 where records are read: the search is the longer chain, and four
         // blocks per compute unit overlap it better; records of long lists are read in few, long pieces.  us, 512 / 1024 threads:
-        // 8 x 44.5 M at 0.1 % 23.8 / 27.1; with records, 2^28 at 1 % 53.1 / 34.6.
-        if (a.row_rec) launch_gather_pieces<1024>(a, groups, batch, cus, st);
+        // 8 x 44.5 M at 0.1 % 23.8 / 27.1; with records, 2^28 at 1 % 53.1 / 34.6.  And of 1024 where one node's groups hold 1024 candidates and more
+        // each, as its groups alone leave compute units without threads: 60 M, 1 %, spread evenly 27.8 / 24.8, in clusters 25.5 / 24.1; but 40 M, 0.5 % 16.1 / 17.1.
+        const bool dense = batch == 1 && (uint64_t)a.k * (kGroupRows * kRow) >= 1024ull * a.n;
+        if (a.row_rec || dense) launch_gather_pieces<1024>(a, groups, batch, cus, st);
         else launch_gather_pieces<512>(a, groups, batch, cus, st);
         return;
     }

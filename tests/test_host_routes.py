@@ -131,6 +131,22 @@ def fall_backs_of_the_one_launch_finish(h):
     return out
 
 
+GATHERS = [  # elements, kept, nodes; which kernel lists the candidates: measured sizes on either side of each line of the rule
+    (25_600_000, 25_600, 4, "k_gatherILb1E"), (33_000_000, 33_000, 1, "k_gatherILb1E"), (44_500_000, 44_500, 8, "k_gather_piecesILi512E"),
+    (60_000_000, 600_000, 1, "k_gather_piecesILi1024E"), (60_000_000, 600_000, 2, "k_gather_piecesILi512E"), (40_000_000, 200_000, 1, "k_gather_piecesILi512E"),
+    (1 << 28, 2_684_354, 1, "k_gather_piecesILi1024E"), (30_000_000, 300_000, 8, "k_gather_piecesILi1024E")]
+
+
+def gathers(h):
+    out = []
+    for n, k, batch, _ in GATHERS:
+        ctx = h.ctx(n, k, batch)
+        h.topk(ctx, n, k, batch)
+        out.append([line.split()[1] for line in h.raw.splitlines() if "k_gather" in line])
+        h.lib.lgc_destroy(ctx)
+    return out
+
+
 def who_samples(h):
     """One letter per selection of 2^20 elements: l, a launch samples before the pass; p, the pass takes the carried threshold or samples."""
     ctx = h.ctx(1 << 28, 1 << 18, 4)
@@ -217,6 +233,11 @@ def test_fall_backs_of_the_one_launch_finish(answers):
     assert got["larger, each"] == (["finish"] + ["many"] * 64) * 2 + ["finish"] + ["many"] * 9
 
 
+def test_how_the_candidates_are_listed(answers):
+    for (n, k, batch, wanted), got in zip(GATHERS, answers["gathers"]):
+        assert len(got) == 1 and wanted in got[0], (n, k, batch, got)
+
+
 def test_the_pass_samples_only_in_a_run_of_carried_thresholds(answers):
     # a run is 24 selections of one shape per node
     assert answers["who_samples"] == {
@@ -228,4 +249,4 @@ def test_the_pass_samples_only_in_a_run_of_carried_thresholds(answers):
 
 if __name__ == "__main__":
     host = Host(sys.argv[1], sys.argv[2])
-    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place, records, fall_backs_of_the_one_launch_finish, who_samples)}))
+    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place, records, fall_backs_of_the_one_launch_finish, gathers, who_samples)}))
