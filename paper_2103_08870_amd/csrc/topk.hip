@@ -339,18 +339,18 @@ __device__ __forceinline__ void count_crowded(Ctr *ctr, const uint32_t c) {
 
 // The same for the flat selection of long vectors (a.groups_counted), with the work cut where the candidates are, not where the
 // rows are: a piece is up to T candidates of one group of kGroupRows rows, one per thread, and the node's blocks take the pieces in turn.
-// Where the bitmap is searched and no group of the node holds more than 4 T, a piece is a whole group, as each piece stages its group's 16 KB
-// (one node, spread evenly, pieces of T / whole groups: 60 M, 1 % 28.9 / 27.8 us, 40 M, 0.5 % 18.0 / 16.1).
 // Groups without candidates cost nothing, and where the candidates cluster no block is left with a multiple of the others' work.
 // us, a block per group (with the row counts summed per 8192 rows, its launch included) / pieces: 8 x 44.5 M at 0.1 % 44.8 / 28.6;
 // 2^28, 1 %, spread evenly 58.6 / 39.5; 260 M, 0.85 %, in clusters 80.2 / 75.9; 4 x 60 M, 1 %, in clusters 72.8 / 64.4.
-template <int T>
+// EVEN (the bitmap is searched): where the node's groups hold T candidates on average and none holds more than 4 T, a piece is a whole group,
+// as each piece stages its group's 16 KB (one node, spread evenly, pieces of T / whole groups: 60 M, 1 % 28.9 / 27.8 us, 40 M, 0.5 % 18.0 / 16.0).
+template <int T, bool EVEN>
 __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
     constexpr int W = T / 64, kPairs = kGroupRows * kRowWords / 2 / T;   // wavefronts; pairs of bitmap words per thread
     __shared__ __align__(16) uint32_t hist[kFineBins];
     __shared__ unsigned long long rows_lds[kGroupRows * kRowWords];
     __shared__ uint32_t offs[kGroupRows];
-    __shared__ uint32_t tmp[2 * W], piece[4];
+    __shared__ uint32_t tmp[(EVEN ? 3 : 2) * W], piece[4];
     static_assert(kGroupRows == 128 && kPairs * 2 * T == kGroupRows * kRowWords && W >= 2, "two wavefronts' rows");
     const int node = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     Sel *s = a.sel + node;
@@ -362,21 +362,28 @@ __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
 
     // this thread's run of groups: its candidates and pieces, and those before it
     const uint32_t per = (groups + T - 1) / T, g0 = tid * per;
-    uint32_t c = 0, w = 0, filled = 0;
-    bool crowds = a.row_rec != nullptr;
+    static_assert((1u << 31) / (kGroupRows * kRow) < 1u << 16, "both counts in one word");
+    uint32_t c = 0, w = 0, f = 0;   // candidates, pieces of T; EVEN: groups that hold any | groups that hold more than 4 T << 16
     for (uint32_t i = 0; i < per; ++i) {
         const uint32_t x = g0 + i < groups ? sums[g0 + i] : 0u;
-        c += x; w += (x + T - 1) / T; filled += x != 0; crowds |= x > 4 * T;
+        c += x; w += (x + T - 1) / T;
+        if (EVEN) f += (uint32_t)(x != 0) + ((uint32_t)(x > 4 * T) << 16);
     }
-    const bool whole = !__syncthreads_or(crowds);   // (the same in all the node's blocks)
-    if (whole) w = filled;
     for (int i = tid; i < kFineBins; i += T) hist[i] = 0;
-    const uint32_t c_incl = wave_prefix(c), w_incl = wave_prefix(w);
-    if (lane == 63) { tmp[wave] = c_incl; tmp[W + wave] = w_incl; }
+    const uint32_t c_incl = wave_prefix(c), w_incl = wave_prefix(w), f_incl = EVEN ? wave_prefix(f) : 0u;
+    if (lane == 63) { tmp[wave] = c_incl; tmp[W + wave] = w_incl; if (EVEN) tmp[2 * W + wave] = f_incl; }
     __syncthreads();
     const uint32_t cw = lane < W ? tmp[lane] : 0u, ww = lane < W ? tmp[W + lane] : 0u;
-    const uint32_t c_before = c_incl - c + wave_sum(lane < wave ? cw : 0u), w_before = w_incl - w + wave_sum(lane < wave ? ww : 0u);
-    const uint32_t pieces = wave_sum(ww), total = wave_sum(cw);
+    const uint32_t c_before = c_incl - c + wave_sum(lane < wave ? cw : 0u);
+    uint32_t w_before = w_incl - w + wave_sum(lane < wave ? ww : 0u);
+    uint32_t pieces = wave_sum(ww);
+    const uint32_t total = wave_sum(cw);
+    bool whole = false;
+    if (EVEN) {
+        const uint32_t fw = lane < W ? tmp[2 * W + lane] : 0u, filled = wave_sum(fw);
+        whole = filled >> 16 == 0 && total >= (unsigned long long)filled * T;   // (the same in all the node's blocks)
+        if (whole) { pieces = filled; w_before = f_incl - f + wave_sum(lane < wave ? fw : 0u); w = f; }
+    }
     if (blockIdx.x == 0 && tid == 0) s->cand_total = total;
 
     for (uint32_t p = blockIdx.x; p < pieces; p += gridDim.x) {   // block-uniform, from scalar registers
@@ -416,7 +423,7 @@ __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
             if (a.zero_early && q0 == 0) count_crowded(a.ctr + node, rc);
         }
         __syncthreads();
-        for (uint32_t q = q0 + tid; q < end; q += T) {
+        for (uint32_t q = q0 + tid; q < (EVEN ? end : all); q += T) {   // (without EVEN a thread has one, and the loop costs a tenth of the kernel's time)
             // last row r with start(r) <= q: it is the one that holds candidate q of the group
             const uint32_t half = tmp[0];
             auto start = [&](uint32_t r) { return offs[r] + (r < 64 ? 0u : half); };
@@ -438,6 +445,7 @@ __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
             if (before + q < a.cap) { cidx[before + q] = ix; cval[before + q] = vb; }
             const uint32_t d = ((vb & 0x7fffffffu) - t_est) >> kFineShift;
             atomicAdd(&hist[d < (uint32_t)kFineBins - 1 ? d : (uint32_t)kFineBins - 1], 1u);
+            if (!EVEN) break;
         }
     }
     __syncthreads();
@@ -445,13 +453,13 @@ __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
     for (int i = tid; i < kFineBins; i += T) { const uint32_t h = hist[i]; if (h) atomicAdd(&fine[i], h); }
 }
 
-template <int T>
+template <int T, bool EVEN>
 static void launch_gather_pieces(const SelArgs &a, uint32_t groups, int batch, int cus, hipStream_t st) {
     // 2048 threads per compute unit, shared by the nodes; no more blocks than there can be pieces, and no more than 512 per node: each adds its
     // histogram to the node's, on the same words (one node, whole step, us, 1024 / 512 blocks: 60 M, 1 %, spread evenly 334.1 / 329.6;
     // 100 M, 1 %, in clusters 499.5 / 496.1; 240 M, 0.1 % 881 / 875)
     const uint32_t pieces = groups + a.cap / T, most = pieces < 512u ? pieces : 512u, fill = (uint32_t)((2048 / T * cus + batch - 1) / batch);
-    hipLaunchKernelGGL(k_gather_pieces<T>, dim3(fill < most ? fill : most, batch), dim3(T), 0, st, a);
+    hipLaunchKernelGGL((k_gather_pieces<T, EVEN>), dim3(fill < most ? fill : most, batch), dim3(T), 0, st, a);
 }
 
 constexpr uint32_t kGroupsCountedFrom = 32 * 1024;
@@ -475,11 +483,15 @@ void launch_gather(const SelArgs &args, int batch, int cus, hipStream_t st) {
     if (a.groups_counted && !a.seg_t) {
         // Blocks of 512 threads where the bitmap is searched, of 1024 where records are read: the search is the longer chain, and four
         // blocks per compute unit overlap it better; records of long lists are read in few, long pieces.  us, 512 / 1024 threads:
-        // 8 x 44.5 M at 0.1 % 23.8 / 27.1; with records, 2^28 at 1 % 53.1 / 34.6.  And of 1024 where one node's groups hold 1024 candidates and more
-        // each, as its groups alone leave compute units without threads: 60 M, 1 %, spread evenly 27.8 / 24.8, in clusters 25.5 / 24.1; but 40 M, 0.5 % 16.1 / 17.1.
-        const bool dense = batch == 1 && (uint64_t)a.k * (kGroupRows * kRow) >= 1024ull * a.n;
-        if (a.row_rec || dense) launch_gather_pieces<1024>(a, groups, batch, cus, st);
-        else launch_gather_pieces<512>(a, groups, batch, cus, st);
+        // 8 x 44.5 M at 0.1 % 23.8 / 27.1; with records, 2^28 at 1 % 53.1 / 34.6.
+        // One node's groups alone leave compute units without threads: whole groups where they would hold 512 candidates each if spread evenly, blocks
+        // of 1024 threads from 1024 on.  Pieces of 512 / EVEN, 512 threads / 1024: 60 M, 1 %, spread evenly 28.9 / 27.8 / 24.5, in clusters 24.8 / 25.5 / 24.1; 40 M,
+        // 0.5 % 18.0 / 16.0 / 17.1.  With more nodes not: 2 x 60 M, 1 %, spread evenly 51.4 / 53.2, in clusters 38.1 / 42.5; 8 x 44.5 M, 0.1 % 23.5 / 25.9.
+        const uint64_t each = (uint64_t)a.k * (kGroupRows * kRow) / a.n;
+        if (a.row_rec) launch_gather_pieces<1024, false>(a, groups, batch, cus, st);
+        else if (batch > 1 || each < 512) launch_gather_pieces<512, false>(a, groups, batch, cus, st);
+        else if (each < 1024) launch_gather_pieces<512, true>(a, groups, batch, cus, st);
+        else launch_gather_pieces<1024, true>(a, groups, batch, cus, st);
         return;
     }
     // 128 rows per block of 1024 threads; measured on the ResNet50-sized workload (4 nodes): 64 rows x 512
