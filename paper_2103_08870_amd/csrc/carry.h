@@ -19,10 +19,10 @@ namespace lgc {
 
 // ok: the selection was served from the candidates above t_est (`total` of them, >= k); carried: t_est had been
 // offered by the record.  target, most: log2 of the candidate counts over k (aimed at / at most).  fresh: the
-// record is not the previous selection's (another kind of selection came between).
-__device__ __forceinline__ void carry_update(Carry *c, const uint32_t n, const uint32_t k, const bool fresh, const bool ok,
-                                             const bool carried, const uint32_t thr, const uint32_t t_est,
-                                             const uint32_t total, const float target, const float most) {
+// record is not the previous selection's (another kind of selection came between).  Returns the offer (0: none).
+__device__ __forceinline__ uint32_t carry_update(Carry *c, const uint32_t n, const uint32_t k, const bool fresh, const bool ok,
+                                                 const bool carried, const uint32_t thr, const uint32_t t_est,
+                                                 const uint32_t total, const float target, const float most) {
     const bool same = !fresh && c->n == n && c->k == k;     // the record is the previous selection's, of this shape
     const bool follows = same && c->len > 0;
     const float l1 = c->log2_t[0], l2 = c->log2_t[1];
@@ -51,6 +51,7 @@ __device__ __forceinline__ void carry_update(Carry *c, const uint32_t n, const u
     c->n = n; c->k = k; c->len = len;
     c->log2_t[0] = l0; c->log2_t[1] = l1; c->log2_t[2] = l2;
     c->next_t_est = next; c->next_t = next_t; c->fails = fails; c->held = held; c->miss = miss;
+    return next;
 }
 
 }  // namespace lgc

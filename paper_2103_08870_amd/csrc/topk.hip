@@ -546,9 +546,8 @@ __device__ __forceinline__ void report_outcome(const SelArgs &a, const int node,
     atomicAdd(ok ? &a.stats->fast : &a.stats->fallback, 1u);
     bool offers = false;
     if (a.carry) {
-        carry_update(a.carry + node, a.n, a.k, false, ok, s->carried != 0, thr, t_est, total, a.carry_target, a.carry_most);
+        offers = carry_update(a.carry + node, a.n, a.k, false, ok, s->carried != 0, thr, t_est, total, a.carry_target, a.carry_most) != 0;
         a.carry[node].zeros_pay = a.zero_early && a.ctr[node].recorded / kZerosPerCrowdedRow >= a.ctr[node].crowded;
-        offers = a.carry[node].next_t_est != 0;
     }
     // the host sees the outcome without synchronising; a carried threshold that failed says nothing about the data
     if (a.notify) st_system32(a.notify + (ok ? (offers ? kServedOffers : kServed) : s->carried ? kOfferFailed : kFellBack), a.notify_value);
@@ -977,6 +976,8 @@ __device__ __forceinline__ void unzero_rows(const SelArgs &a, const int node) {
     }
 }
 
+// ZERO (a.zero_early): zeros are written where the pass has not, and what it has zeroed and is not selected is written back.
+template <bool ZERO>
 __global__ __launch_bounds__(1024) void k_emit_scanned(SelArgs a) {
     __shared__ uint32_t sh_pg[16], sh_pe[16], sh_tg[16], sh_te[16];
     const int node = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -984,7 +985,7 @@ __global__ __launch_bounds__(1024) void k_emit_scanned(SelArgs a) {
     const uint32_t total = s->cand_total;
     const uint32_t chunk = blockIdx.x, base = chunk * (uint32_t)kChunk, e0 = base + tid * 4;
     if (!s->fast_ok) {   // uniform
-        if (a.zero_early) unzero_rows(a, node);
+        if (ZERO) unzero_rows(a, node);
         return;
     }
     if (base >= total) return;   // (fast_ok implies k <= total <= cap)
@@ -1033,8 +1034,8 @@ __global__ __launch_bounds__(1024) void k_emit_scanned(SelArgs a) {
     float *oval = a.out_vals + (size_t)node * a.k;
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-        const uint32_t ix = ci[j] & ~kZeroed;
-        const bool zeroed = (ci[j] & kZeroed) != 0;
+        const uint32_t ix = ZERO ? ci[j] & ~kZeroed : ci[j];
+        const bool zeroed = ZERO && (ci[j] & kZeroed) != 0;
         if (fg[j] || (fe[j] && ce < quota)) {
             const uint32_t o = cg + (ce < quota ? ce : quota);
             if (o < a.k) { oidx[o] = ix; oval[o] = __uint_as_float(cv[j]); }
@@ -1531,7 +1532,8 @@ bool launch_output_from_candidates(const SelArgs &a, int batch, bool direct, int
     hipLaunchKernelGGL(k_select_level2, dim3(blocks, batch), dim3(1024), 0, st, a);
     const uint32_t chunks = (a.cap + kChunk - 1) / kChunk;
     hipLaunchKernelGGL(k_count_chunks, dim3((chunks + kCountChunks - 1) / kCountChunks, batch), dim3(1024), 0, st, a);
-    hipLaunchKernelGGL(k_emit_scanned, dim3(chunks, batch), dim3(1024), 0, st, a);
+    if (a.zero_early) hipLaunchKernelGGL(k_emit_scanned<true>, dim3(chunks, batch), dim3(1024), 0, st, a);
+    else hipLaunchKernelGGL(k_emit_scanned<false>, dim3(chunks, batch), dim3(1024), 0, st, a);
     return false;
 }
 

@@ -148,6 +148,18 @@ def gathers(h):
     return out
 
 
+def zeros(h):
+    """The kernels with a form for zeros from the pass, of selections with long lists: records, none, records and no carried thresholds."""
+    out = []
+    for n, k, carry in ((1 << 28, 2_684_354, 1), (67_000_000, 536_000, 1), (1 << 28, 2_684_354, 0)):
+        ctx = h.ctx(n, k, 1)
+        assert h.lib.lgc_set_option(ctx, 2, C.c_int64(carry)) == 0
+        h.topk(ctx, n, k, 1)
+        out.append(sorted({line.split()[1] for line in h.raw.splitlines() if any(x in line for x in ("k_sample", "k_emit_scanned", "k_candidates"))}))
+        h.lib.lgc_destroy(ctx)
+    return out
+
+
 def who_samples(h):
     """One letter per selection of 2^20 elements: l, a launch samples before the pass; p, the pass takes the carried threshold or samples."""
     ctx = h.ctx(1 << 28, 1 << 18, 4)
@@ -239,6 +251,12 @@ def test_how_the_candidates_are_listed(answers):
         assert len(got) == 1 and wanted in got[0], (n, k, batch, got)
 
 
+def test_only_selections_with_zeros_from_the_pass_take_the_kernels_that_know_of_them(answers):
+    for got, yes in zip(answers["zeros"], (True, False, False)):
+        emit, (sample, passes) = [x for x in got if "k_emit" in x], sorted((x for x in got if "k_emit" not in x), key=lambda x: "k_cand" in x)
+        assert ["k_emit_scannedILb1E" in x for x in emit] == [yes] and ("k_sampleILb1ELb1E" in sample) == yes and ("ELb1ELb1EEEv" in passes) == yes, got
+
+
 def test_the_pass_samples_only_in_a_run_of_carried_thresholds(answers):
     # a run is 24 selections of one shape per node
     assert answers["who_samples"] == {
@@ -250,4 +268,4 @@ def test_the_pass_samples_only_in_a_run_of_carried_thresholds(answers):
 
 if __name__ == "__main__":
     host = Host(sys.argv[1], sys.argv[2])
-    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place, records, fall_backs_of_the_one_launch_finish, gathers, who_samples)}))
+    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place, records, fall_backs_of_the_one_launch_finish, gathers, zeros, who_samples)}))
