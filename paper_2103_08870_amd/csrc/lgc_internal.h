@@ -150,7 +150,6 @@ struct SelArgs {
     // bulk scratch
     uint32_t *samples;        // [batch][kSample]
     uint32_t *row_count;      // [batch][rows]  candidates per row
-    int groups_counted;       // 1: the candidates of every kGroupRows rows are summed by a launch of its own (group_counts, device_helpers.h)
     int sparse_bitmap;        // 1: the lines of rows without candidates are not written
     unsigned long long *bitmap;  // [batch][rows][kRowWords]
     uint32_t *row_rec;           // [batch][rec_stride][kRecordWords]  records of the rows with few candidates (null: none are kept)

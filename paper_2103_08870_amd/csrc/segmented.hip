@@ -337,7 +337,7 @@ __global__ __launch_bounds__(kSelThreads) void k_seg_select(SelArgs a) {
                         const uint32_t cnt = below <= 0 ? 0u : (((uint32_t)below + 3u) >> 2 > 64u ? 64u : ((uint32_t)below + 3u) >> 2);
                         const unsigned long long w = a.bitmap[((size_t)node * a.rows + row) * kRowWords + lane];
                         const unsigned long long m = cnt >= 64u ? ~0ull : ((1ull << cnt) - 1ull);
-                        c = a.row_count[(size_t)node * a.rows + row] != 0 ? (uint32_t)__popcll(w & m) : 0u;   // (no flags are kept for a row without)
+                        c = (uint32_t)__popcll(w & m);
                     }
                     if (lane == 16) c = a.row_prefix[(size_t)node * a.rows + row];
                 } else if (lane == 16) {

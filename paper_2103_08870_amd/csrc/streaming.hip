@@ -404,8 +404,9 @@ void launch_candidates(const SelArgs &args, int batch, bool fused, hipStream_t s
         SelArgs a = args;
         // Passes of several launches leave out the bitmap lines of rows without candidates (whole step without / with: 8 x 44.5 M 1316 / 1306 us,
         // 4 x 40 M 595 / 593); a pass of one launch writes them all, which then lie in the caches (4 x 25.6 M 382.6 when left out, 378.5 when not;
-        // 60 M 240.7 / 242.3).
-        a.sparse_bitmap = (uint64_t)nrows * batch > kRowsPerLaunch;
+        // 60 M 240.7 / 242.3).  By layers it gains nothing (7 x 33.6 M 932 / 932), and the selection, which looks for a layer's ends in them, would have
+        // to read the row's count first (4 x 3.1 M, 14 layers: 0.3 us).
+        a.sparse_bitmap = !seg && (uint64_t)nrows * batch > kRowsPerLaunch;
         a.node0 = node0; a.row_begin = r0; a.row_end = r1;
         dim3 grid((r1 - r0 + kWaves - 1) / kWaves, nodes);
 #define LGC_CAND(F, S, M, Z, R) launch_timed(k_candidates<F, S, M, Z, R>, grid, dim3(kBlock), st, e, a)

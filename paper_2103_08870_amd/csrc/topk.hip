@@ -192,7 +192,7 @@ __device__ __forceinline__ uint32_t block_sum(uint32_t x, uint32_t *tmp /*[16]*/
 // adds the block's count to the node's total.  The block's part of the bitmap is staged in LDS;
 // the work is balanced over the threads by output position (binary search of the owning row,
 // then of the bit inside the row), whatever the spread of the candidates.
-// Long vectors (a.groups_counted): the candidates of every block's rows are summed by a kernel of their own, one wavefront each, so that a
+// COUNTED (long vectors): the candidates of every block's rows are summed by a kernel of their own, one wavefront each, so that a
 // block adds up the sums before its own instead of all the row counts.
 __global__ __launch_bounds__(1024) void k_group_counts(SelArgs a) {
     const int node = blockIdx.y, lane = threadIdx.x & 63;
@@ -235,11 +235,12 @@ __device__ __forceinline__ uint32_t row_element(const unsigned long long *w, uin
     return sub * 256 + l * 4 + j;
 }
 
-template <bool HIST, int ROWS, int THREADS>
+template <bool HIST, bool COUNTED, int ROWS, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
     constexpr int kGatherRows = ROWS;
     constexpr int kPairs = (ROWS * kRowWords / 2 + THREADS - 1) / THREADS;   // pairs of bitmap words per thread
     static_assert(ROWS % 64 == 0 && ROWS <= THREADS && (ROWS & (ROWS - 1)) == 0, "rows per block");
+    static_assert(!COUNTED || ROWS == kGroupRows, "a block per group");
     __shared__ __align__(16) uint32_t hist[HIST ? kFineBins : 1];
     __shared__ unsigned long long rows_lds[kGatherRows * kRowWords];
     __shared__ uint32_t offs[kGatherRows];
@@ -265,7 +266,7 @@ __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
     const uint32_t t_est = HIST ? s->t_est : 0u;
     // candidates before the block
     uint32_t part = 0;
-    if (a.groups_counted) {
+    if constexpr (COUNTED) {
         const uint32_t *sums = group_counts(a, node);
         for (uint32_t i = tid; i < blockIdx.x; i += THREADS) part += sums[i];
     } else for (uint32_t i0 = tid * 4; i0 < first; i0 += 4 * THREADS * 4) {   // first and the row stride are multiples of 4
@@ -337,7 +338,7 @@ __device__ __forceinline__ void count_crowded(Ctr *ctr, const uint32_t c) {
     }
 }
 
-// The same for the flat selection of long vectors (a.groups_counted), with the work cut where the candidates are, not where the
+// The same for the flat selection of long vectors, with the work cut where the candidates are, not where the
 // rows are: a piece is up to T candidates of one group of kGroupRows rows, one per thread, and the node's blocks take the pieces in turn.
 // Groups without candidates cost nothing, and where the candidates cluster no block is left with a multiple of the others' work.
 // us, a block per group (with the row counts summed per 8192 rows, its launch included) / pieces: 8 x 44.5 M at 0.1 % 44.8 / 28.6;
@@ -464,23 +465,14 @@ static void launch_gather_pieces(const SelArgs &a, uint32_t groups, int batch, i
 
 constexpr uint32_t kGroupsCountedFrom = 32 * 1024;
 
-template <int ROWS, int THREADS>
-static void launch_gather_shape(const SelArgs &g, uint32_t nrows, int batch, hipStream_t st) {
-    const dim3 grid((nrows + ROWS - 1) / ROWS, batch);
-    // the per-layer selection has one threshold per segment, so no histogram above "the" estimate
-    if (g.seg_t) hipLaunchKernelGGL((k_gather<false, ROWS, THREADS>), grid, dim3(THREADS), 0, st, g);
-    else hipLaunchKernelGGL((k_gather<true, ROWS, THREADS>), grid, dim3(THREADS), 0, st, g);
-}
-
-void launch_gather(const SelArgs &args, int batch, int cus, hipStream_t st) {
-    SelArgs a = args;
+void launch_gather(const SelArgs &a, int batch, int cus, hipStream_t st) {
     const uint32_t nrows = (a.n + kRow - 1) / kRow, groups = (nrows + kGroupRows - 1) / kGroupRows;
     // Records with zeros from the pass are read by pieces at any length (8 x 30 M, 1 %, block per group / pieces: 1231 / 1222 us).
     // The sums pay for their launch from about 32 K rows on: 8 x 43.5 K rows, whole step without / with them and the
     // pieces: 1318 / 1303 us, 4 x 39 K 601 / 591; 4 x 25 K rows 382.9 / 382.7, 4 x 16 K 255 / 258, 1 x 25 K 117.4 / 119, by layers 409 / 411.
-    a.groups_counted = nrows > kGroupsCountedFrom || a.zero_early;
-    if (a.groups_counted) hipLaunchKernelGGL(k_group_counts, dim3((groups + 15) / 16, batch), dim3(1024), 0, st, a);
-    if (a.groups_counted && !a.seg_t) {
+    const bool counted = nrows > kGroupsCountedFrom || a.zero_early;
+    if (counted) hipLaunchKernelGGL(k_group_counts, dim3((groups + 15) / 16, batch), dim3(1024), 0, st, a);
+    if (counted && !a.seg_t) {
         // Blocks of 512 threads where the bitmap is searched, of 1024 where records are read: the search is the longer chain, and four
         // blocks per compute unit overlap it better; records of long lists are read in few, long pieces.  us, 512 / 1024 threads:
         // 8 x 44.5 M at 0.1 % 23.8 / 27.1; with records, 2^28 at 1 % 53.1 / 34.6.
@@ -497,7 +489,11 @@ void launch_gather(const SelArgs &args, int batch, int cus, hipStream_t st) {
     // 128 rows per block of 1024 threads; measured on the ResNet50-sized workload (4 nodes): 64 rows x 512
     // threads 18.0 us, 64 x 1024 20.2, 128 x 512 19.8, 64 x 256 21.5, this shape 18.2 (the same within noise:
     // what the kernel costs is its chain of dependent memory round trips, not the search work of its busiest block)
-    launch_gather_shape<kGroupRows, 1024>(a, nrows, batch, st);
+    // The per-layer selection has one threshold per segment, so no histogram above "the" estimate.
+    const dim3 grid(groups, batch), block(1024);
+    if (!a.seg_t) hipLaunchKernelGGL((k_gather<true, false, kGroupRows, 1024>), grid, block, 0, st, a);
+    else if (counted) hipLaunchKernelGGL((k_gather<false, true, kGroupRows, 1024>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((k_gather<false, false, kGroupRows, 1024>), grid, block, 0, st, a);
 }
 
 // Adds, for every candidate i < total that passes `member`, one count to hist[digit(d)], where

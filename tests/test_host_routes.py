@@ -132,7 +132,7 @@ def fall_backs_of_the_one_launch_finish(h):
 
 
 GATHERS = [  # elements, kept, nodes; which kernel lists the candidates: measured sizes on either side of each line of the rule
-    (25_600_000, 25_600, 4, "k_gatherILb1E"), (33_000_000, 33_000, 1, "k_gatherILb1E"), (44_500_000, 44_500, 8, "k_gather_piecesILi512ELb0E"),
+    (25_600_000, 25_600, 4, "k_gatherILb1ELb0E"), (33_000_000, 33_000, 1, "k_gatherILb1ELb0E"), (44_500_000, 44_500, 8, "k_gather_piecesILi512ELb0E"),
     (60_000_000, 600_000, 1, "k_gather_piecesILi1024ELb1E"), (60_000_000, 600_000, 2, "k_gather_piecesILi512ELb0E"),
     (40_000_000, 200_000, 1, "k_gather_piecesILi512ELb1E"), (100_000_000, 100_000, 1, "k_gather_piecesILi512ELb0E"),
     (1 << 28, 2_684_354, 1, "k_gather_piecesILi1024ELb0E"), (30_000_000, 300_000, 8, "k_gather_piecesILi1024ELb0E")]
@@ -145,6 +145,14 @@ def gathers(h):
         h.topk(ctx, n, k, batch)
         out.append([line.split()[1] for line in h.raw.splitlines() if "k_gather" in line])
         h.lib.lgc_destroy(ctx)
+    for n in (25_600_000, 44_500_000):       # by layers: two halves
+        ctx, seg = h.ctx(n, n // 1000, 4), p()
+        assert h.lib.lgc_segments_create(C.byref(seg), 0, u64(n), u64(2), (u64 * 3)(0, n // 2, n), (u64 * 2)(n // 2000, n // 2000)) == 0
+        assert h.lib.lgc_reserve(ctx, None, u64(0), 0, seg) == 0
+        h.log()
+        assert h.lib.lgc_topk_segmented(ctx, seg, p(1 << 42), None, 4, u64(n), p(1 << 43), p(1 << 43), None) == 0
+        h.log()
+        out.append([line.split()[1] for line in h.raw.splitlines() if "k_gather" in line or "k_group" in line])
     return out
 
 
@@ -249,6 +257,9 @@ def test_fall_backs_of_the_one_launch_finish(answers):
 def test_how_the_candidates_are_listed(answers):
     for (n, k, batch, wanted), got in zip(GATHERS, answers["gathers"]):
         assert len(got) == 1 and wanted in got[0], (n, k, batch, got)
+    short, long = answers["gathers"][len(GATHERS):]
+    assert len(short) == 1 and "k_gatherILb0ELb0E" in short[0], short
+    assert len(long) == 2 and "k_group_counts" in long[0] and "k_gatherILb0ELb1E" in long[1], long
 
 
 def test_only_selections_with_zeros_from_the_pass_take_the_kernels_that_know_of_them(answers):
