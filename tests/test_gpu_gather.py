@@ -1,8 +1,10 @@
 """The list of candidates (flags of the pass -> positions and values in index order) where its parts have edges: groups of 128
 rows, groups without candidates, sums per group (from 32 K rows on, and more of them than a block has threads), bitmap lines left out
-(passes of several launches); flat and by layers.  Against the selection's definition in torch, bit for bit."""
+(flat passes of several launches); flat and by layers.  Against the selection's definition in torch, bit for bit."""
 import pytest
 import torch
+
+from selection import top
 
 pytestmark = pytest.mark.gpu
 GROUP = 128 * 1024       # elements per group of rows
@@ -14,14 +16,6 @@ def B():
     binding.lib()
     assert torch.cuda.is_available()
     return binding
-
-
-def top(v, k):
-    """Positions of the k largest magnitudes, lowest positions first among equals, ascending."""
-    key = v.view(torch.int32) & 0x7FFFFFFF
-    bar = key.topk(k).values[-1]
-    above, equal = (key > bar).nonzero()[:, 0], (key == bar).nonzero()[:, 0]
-    return torch.cat([above, equal[:k - above.numel()]]).sort().values
 
 
 def vector(layout, n, k, gen):

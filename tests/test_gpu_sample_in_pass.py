@@ -13,6 +13,8 @@ import os
 import pytest
 import torch
 
+from selection import top
+
 pytestmark = pytest.mark.gpu
 ONE_LAUNCH = 104 * 1024 * 1024      # elements of all nodes, in rows of 1024
 RUN = 24                            # selections in a row, per node, that must have left carried thresholds
@@ -36,14 +38,6 @@ def B(request):
     b.expires = request.param != "liblgc.so"
     assert torch.cuda.is_available()
     return b
-
-
-def top(v, k):
-    """Positions of the k largest magnitudes, lowest positions first among equals, ascending."""
-    key = v.view(torch.int32) & 0x7FFFFFFF
-    bar = key.topk(k).values[-1]
-    above, equal = (key > bar).nonzero()[:, 0], (key == bar).nonzero()[:, 0]
-    return torch.cat([above, equal[:k - above.numel()]]).sort().values
 
 
 class Run:
