@@ -388,8 +388,8 @@ lgc_status lgc_set_option(lgc_ctx *ctx, lgc_option opt, int64_t value);
  * lgc_stats: selections served by the fast path, selections that fell back
  * to the exact path on the device (one selection = one node in lgc_topk /
  * lgc_accumulate_topk, one sampled layer of one node in the per-layer calls),
- * and the device-side error count (bounded waits that expired; positions out
- * of range or out of order in lgc_scatter / lgc_gather).  Selections of fewer
+ * and the device-side error count (bounded waits of the exact path that expired;
+ * positions out of range or out of order in lgc_scatter / lgc_gather).  Selections of fewer
  * than 2^18 elements, and those that take the exact path outright, are counted
  * by neither of the first two.  Returns LGC_EDEVICE if errors != 0. */
 lgc_status lgc_stats(lgc_ctx *ctx, uint64_t *fast, uint64_t *fallback, uint64_t *errors);

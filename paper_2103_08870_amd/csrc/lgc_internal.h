@@ -105,11 +105,11 @@ struct Carry {
 };
 static_assert(sizeof(Carry) == 64, "Carry is one 64-byte record");
 
-// Everything the selection kernels need; passed by value.
 // How a selection ended, as the host learns of it without synchronising: fell back from a sampled threshold; served, and no threshold
 // carried to the next selection; served, and one carried; fell back from a carried threshold.
 enum Outcome : uint32_t { kFellBack = 0, kServed = 1, kServedOffers = 2, kOfferFailed = 3 };
 
+// Everything the selection kernels need; passed by value.
 struct SelArgs {
     const float *g;   // fresh gradient (fused source only)
     float *u;         // momentum buffer (nullable for plain selection)

@@ -142,8 +142,8 @@ __device__ uint32_t write_lane(uint32_t value, uint32_t lane, uint32_t x) __asm(
 // whatever runs beside it.  They are bounded all the same.  A block that has waited too long settles on "no candidates", for the whole node:
 // ctr->ready holds the one threshold that all of its blocks go by, whoever sets it first.  Rows cut at different thresholds would
 // make a list that lacks elements above T*; a node without candidates takes the exact path.
-// A launch of its own costs 4.6 us in a full queue where thresholds are carried and it has nothing to do; sampling takes 14 us there and 60 to
-// 130 us here, as all blocks wait.  So this is for the odd selection in a run of carried ones (offers_hold, api.hip).
+// A launch of its own costs 4.6 us in a full queue where thresholds are carried and it has nothing to do, and 14 us where it samples; here sampling takes
+// 25 to 300 us, as all blocks wait.  So this is for the odd selection in a run of carried ones (offers_hold, kOfferRun in api.hip).
 constexpr uint32_t kShares = kSample / (4 * kBlock);
 constexpr uint32_t kNoCandidates = 0x80000000u;   // a threshold above every key
 

@@ -1291,7 +1291,8 @@ __global__ __launch_bounds__(1024) void k_output_or_exact(SelArgs a, uint32_t ou
 // memory for the other to read.  What it costs is one block's chain: 2 us for the row counts, 1 us per 1024 entries
 // for rows and records, 1.3 us per digit, 2.5 us for the ordered output.  All loops are kept rolled: code that runs once per
 // launch is fetched as it runs, and four entries per thread side by side took 1.5 times as long.
-// Measured against the two launches: one node of 2^20 elements, k = 1 024: 10.4 us against 17; 3 x 3.33 M, k = 3 333: 20 against 22.6.
+// Measured against the two launches: one node of 2^20 elements, k = 1 024: 10.4 us against 17; beyond takes_finish's line (api.hip),
+// 3 x 3.33 M, k = 3 333, 5 000 listed: 22.4 against 18.7, whole step 66.8 / 61.7.
 constexpr int kFinishBins = 8192;
 static_assert(kFinishBins >= kRadixBins, "the exact path counts in the same words");
 
