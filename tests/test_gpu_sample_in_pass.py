@@ -17,7 +17,7 @@ from selection import top
 
 pytestmark = pytest.mark.gpu
 ONE_LAUNCH = 104 * 1024 * 1024      # elements of all nodes, in rows of 1024
-RUN = 24                            # selections in a row, per node, that must have left carried thresholds
+RUN = 16                            # selections in a row, per node, that must have left carried thresholds
 
 
 def library(name):

@@ -186,17 +186,17 @@ def who_samples(h):
             seen += "l" if "k_sample" in h.raw else "p"
         return seen
 
-    out = {"served, nothing carried": run([1] * 30), "carried": run([2] * 28), "carried, long vector": run([2], 1 << 28)}
-    run([2] * 24)
-    out["once not, by one node of two"] = run([1]) + run([2] * 26)
+    out = {"served, nothing carried": run([1] * 30), "carried": run([2] * 20), "carried, long vector": run([2], 1 << 28)}
+    run([2] * 16)
+    out["once not, by one node of two"] = run([1]) + run([2] * 18)
     out["once not seen yet"] = run([None, 2])
-    out["a carried one fell back"] = run([3]) + run([2] * 25)
-    out["another length"] = run([2] * 26, (1 << 20) + 1)
-    out["another count"] = run([2] * 26, (1 << 20) + 1, 1001)
-    out["four nodes"] = run([2] * 98, batch=4)
+    out["a carried one fell back"] = run([3]) + run([2] * 17)
+    out["another length"] = run([2] * 18, (1 << 20) + 1)
+    out["another count"] = run([2] * 18, (1 << 20) + 1, 1001)
+    out["four nodes"] = run([2] * 66, batch=4)
     out["one of them, unseen"] = run([None] * 3)
     out["and four again"] = run([None] * 2 + [2], batch=4)
-    run([2] * 24)
+    run([2] * 16)
     capturing.value = 1
     out["recorded"] = run([2])
     capturing.value = -1
@@ -206,7 +206,7 @@ def who_samples(h):
     assert h.lib.lgc_set_option(ctx, 0, C.c_int64(1)) == 0      # LGC_OPT_SELECT_PATH: exact, which carries nothing
     h.topk(ctx, 1 << 20, 1000, 1)
     assert h.lib.lgc_set_option(ctx, 0, C.c_int64(0)) == 0
-    out["after an exact selection"] = run([2] * 25)
+    out["after an exact selection"] = run([2] * 17)
     assert h.lib.lgc_set_option(ctx, 2, C.c_int64(0)) == 0      # LGC_OPT_CARRY_THRESHOLD
     out["option off"] = run([1] * 2)
     h.lib.lgc_destroy(ctx)
@@ -269,12 +269,12 @@ def test_only_selections_with_zeros_from_the_pass_take_the_kernels_that_know_of_
 
 
 def test_the_pass_samples_only_in_a_run_of_carried_thresholds(answers):
-    # a run is 24 selections of one shape per node
+    # a run is 16 selections of one shape per node
     assert answers["who_samples"] == {
-        "served, nothing carried": "l" * 30, "carried": "l" * 24 + "p" * 4, "carried, long vector": "l",
-        "once not, by one node of two": "p" + "l" * 24 + "p" * 2, "once not seen yet": "pp", "a carried one fell back": "p" + "l" * 24 + "p",
-        "another length": "l" * 24 + "pp", "another count": "l" * 24 + "pp", "four nodes": "l" * 96 + "pp", "one of them, unseen": "lll",
-        "and four again": "lll", "recorded": "l", "no answer to that": "l", "not recorded": "p", "after an exact selection": "l" * 24 + "p", "option off": "ll"}
+        "served, nothing carried": "l" * 30, "carried": "l" * 16 + "p" * 4, "carried, long vector": "l",
+        "once not, by one node of two": "p" + "l" * 16 + "p" * 2, "once not seen yet": "pp", "a carried one fell back": "p" + "l" * 16 + "p",
+        "another length": "l" * 16 + "pp", "another count": "l" * 16 + "pp", "four nodes": "l" * 64 + "pp", "one of them, unseen": "lll",
+        "and four again": "lll", "recorded": "l", "no answer to that": "l", "not recorded": "p", "after an exact selection": "l" * 16 + "p", "option off": "ll"}
 
 
 if __name__ == "__main__":
