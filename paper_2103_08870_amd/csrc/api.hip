@@ -301,7 +301,10 @@ SelArgs make_args(lgc_ctx *c, const float *g, float *u, float *v, uint64_t n, ui
 constexpr int kManyBlockCalls = 64;  // selections between the tries of the one-launch finish after it fell back where longer lists are held
 // Selections in a row, per node, that must have left carried thresholds before the pass is launched on the next one's: about what the pass has to
 // gain to make up for one that samples itself.  us, gained per call / lost by that one: 2^18 elements 1.9 / 12, 2^20 1.8 / 14, 16 M 1.7 / 27; 2 x 12 M
-// 2 / 65; 3 x 3.33 M 2.4 / 36; 4 x 25.6 M 2 / 130; 8 x 2^20 2.2 / 76, 8 x 3 M 2.6 / 141, 8 x 13 M 1.5 / 290: 4 to 32 calls per node, and 5 to 16 for most.
+// 2 / 65; 3 x 3.33 M 2.4 / 36; 4 x 25.6 M 2 / 140; 8 x 2^20 2.2 / 76, 8 x 3 M 2.6 / 145, 8 x 13 M 1.5 / 310 (some 35 per node of a long vector: the
+// blocks of one after the other's wait): 4 to 32 calls per node, and 5 to 16 for most.  A run that ends may cost four of them, as the next offer comes after four
+// selections, where the host has queued that far ahead; runs in progress rarely end (4 x 25.6 M, whole step, 64 calls / 64 per
+// node: 381.5 / 382.0).
 constexpr int kOfferRun = 16;
 constexpr int kMaxExactCalls = 64;   // most selections in a row that take the exact path outright after fall-backs were seen
 
