@@ -342,7 +342,7 @@ __device__ __forceinline__ void count_crowded(Ctr *ctr, const uint32_t c) {
 // rows are: a piece is up to T candidates of one group of kGroupRows rows, one per thread, and the node's blocks take the pieces in turn.
 // Groups without candidates cost nothing, and where the candidates cluster no block is left with a multiple of the others' work.
 // us, a block per group (with the row counts summed per 8192 rows, its launch included) / pieces: 8 x 44.5 M at 0.1 % 44.8 / 28.6;
-// 2^28, 1 %, spread evenly 58.6 / 39.5; 260 M, 0.85 %, in clusters 80.2 / 75.9; 4 x 60 M, 1 %, in clusters 72.8 / 64.4.
+// 2^28, 1 %, spread evenly, records of 32 58.6 / 36.8; 260 M, 0.85 %, in clusters 80.2 / 75.9; 4 x 60 M, 1 %, in clusters 72.8 / 64.4.
 // EVEN (the bitmap is searched): where the node's groups hold T candidates on average and none holds more than 4 T, a piece is a whole group,
 // as each piece stages its group's 16 KB (one node, spread evenly, pieces of T / whole groups: 60 M, 1 % 28.9 / 27.8 us, 40 M, 0.5 % 18.0 / 16.0).
 template <int T, bool EVEN>
@@ -475,7 +475,8 @@ void launch_gather(const SelArgs &a, int batch, int cus, hipStream_t st) {
     if (counted && !a.seg_t) {
         // Blocks of 512 threads where the bitmap is searched, of 1024 where records are read: the search is the longer chain, and four
         // blocks per compute unit overlap it better; records of long lists are read in few, long pieces.  us, 512 / 1024 threads:
-        // 8 x 44.5 M at 0.1 % 23.8 / 27.1; with records, 2^28 at 1 % 53.1 / 34.6.
+        // 8 x 44.5 M at 0.1 % 23.8 / 27.1; 2^28 at 1 %, records of 32 45.0 / 32.0, of 24 beside zeros from the pass 73.4 / 70.0 (rows that hold more are searched
+        // in memory), 8 x 44.5 M at 1 %, in clusters, the same 93.0 / 97.8.
         // One node's groups alone leave compute units without threads: whole groups where they would hold 512 candidates each if spread evenly, blocks
         // of 1024 threads from 1024 on.  Pieces of 512 / EVEN, 512 threads / 1024: 60 M, 1 %, spread evenly 28.9 / 27.8 / 24.5, in clusters 24.8 / 25.5 / 24.1; 40 M,
         // 0.5 % 18.0 / 16.0 / 17.1.  With more nodes not: 2 x 60 M, 1 %, spread evenly 51.4 / 53.2, in clusters 38.1 / 42.5; 8 x 44.5 M, 0.1 % 23.5 / 25.9.
