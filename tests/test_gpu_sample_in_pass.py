@@ -7,6 +7,7 @@ the host asks for, hold the stream up, and queue a selection whose residuals jum
 goes through the pass all the same, as the host knows nothing of the jump.  Every case also runs on the library with a bound on the pass's waits that
 expires at once (liblgc_short_wait.so), where the exact path serves the nodes that would sample: that it does shows that the
 pass was to sample."""
+import copy
 import importlib.util
 import os
 
@@ -45,7 +46,7 @@ class Run:
 
     def __init__(self, B, n, k, nodes):
         self.B, self.n, self.k, self.nodes = B, n, k, nodes
-        self.ctx = B.Context(n, k, nodes)
+        self.ctx = B.Context(n, k + 1, nodes)
         B.lgc_set_option(self.ctx, B.LGC_OPT_SELECT_PATH, 2)
         self.u, self.v = torch.zeros((nodes, n), device="cuda"), torch.zeros((nodes, n), device="cuda")
         self.ru = self.u.clone()
@@ -74,6 +75,13 @@ class Run:
         self.B.lgc_stats(self.ctx)                # (counts anew)
         self.ru.copy_(self.u)
         self.rv = self.v.clone()
+
+    def first(self, nodes):
+        """The first nodes of this run, as a run on the same context."""
+        part = copy.copy(self)
+        part.nodes = nodes
+        part.u, part.v, part.ru, part.still = (x[:nodes] for x in (self.u, self.v, self.ru, self.still))
+        return part
 
     def jump(self, nodes):
         """Gradients that put these nodes' residuals a tenth lower: nothing lies above the carried threshold, the exact path serves them and leaves none."""
@@ -133,6 +141,21 @@ def test_nodes_that_sample_beside_nodes_that_carry(B, jumps):
     expired = len(jumps) if B.expires else 0
     assert B.lgc_stats_carried(run.ctx) == 2 * nodes - len(jumps)
     assert B.lgc_stats(run.ctx) == (2 * nodes - len(jumps) - expired, len(jumps) + expired, 0)
+
+
+@pytest.mark.parametrize("n,k,nodes", [((1 << 18) + 1, 3000, 3), (2_000_001, 2000, 3), (ONE_LAUNCH // 4, 20_000, 4), (ONE_LAUNCH // 4 + 1, 20_000, 4)])
+def test_another_number_of_nodes_or_another_count(B, n, k, nodes):
+    # right after a run of carried thresholds of the first node; the host knows that no offer is for these, and a launch samples
+    run, gen = Run(B, n, k, nodes), generator(n)
+    run.first(1).carry(gen)
+    run.rv, run.ru = run.v.clone(), run.u.clone()
+    for run.k, carried in ((k, 1), (k + 1, 0), (k + 1, 0)):
+        g = torch.zeros_like(run.v)
+        g[1:].normal_(generator=gen)
+        run.queued = [(g, *run.step(g))]
+        run.check()
+        assert B.lgc_stats_carried(run.ctx) == carried
+        assert B.lgc_stats(run.ctx) == (nodes, 0, 0)
 
 
 def test_a_node_that_samples_beside_nodes_that_carry(B):
