@@ -143,6 +143,25 @@ def test_nodes_that_sample_beside_nodes_that_carry(B, jumps):
     assert B.lgc_stats(run.ctx) == (2 * nodes - len(jumps) - expired, len(jumps) + expired, 0)
 
 
+def test_a_graph_recorded_in_a_run_of_carried_thresholds(B):
+    # a launch samples in what was recorded, whatever it finds when it is replayed: no wait that could expire
+    run = Run(B, 2_000_001, 2000, 2)
+    run.carry(generator(8))
+    g = torch.zeros_like(run.v)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run.queued = [(g, *run.step(g)) for _ in range(2)]      # two: the scratch's two halves take turns
+    for kind, stats in (("still", (4, 0, 0)), ("jump", (2, 2, 0)), ("still", None), ("jump", None), ("still", None)):
+        torch.mul(run.v, -0.1 if kind == "jump" else 0.0, out=g)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        run.check()
+        got = B.lgc_stats(run.ctx)
+        assert got[2] == 0 and stats in (None, got), (kind, got)
+
+
 @pytest.mark.parametrize("n,k,nodes", [((1 << 18) + 1, 3000, 3), (2_000_001, 2000, 3), (ONE_LAUNCH // 4, 20_000, 4), (ONE_LAUNCH // 4 + 1, 20_000, 4)])
 def test_another_number_of_nodes_or_another_count(B, n, k, nodes):
     # right after a run of carried thresholds of the first node; the host knows that no offer is for these, and a launch samples
