@@ -478,13 +478,15 @@ void launch_gather(const SelArgs &a, int batch, int cus, hipStream_t st) {
         // 8 x 44.5 M at 0.1 % 23.8 / 27.1; 2^28 at 1 %, records of 32 45.0 / 32.0, of 24 beside zeros from the pass 73.4 / 70.0 (rows that hold more are searched
         // in memory), 8 x 44.5 M at 1 %, in clusters, the same 93.0 / 97.8.
         // One node's groups alone leave compute units without threads: whole groups where they would hold 512 candidates each if spread evenly, blocks
-        // of 1024 threads from 1024 on.  Pieces of 512 / EVEN, 512 threads / 1024: 60 M, 1 %, spread evenly 28.9 / 27.8 / 24.5, in clusters 24.8 / 25.5 / 24.1; 40 M,
-        // 0.5 % 18.0 / 16.0 / 17.1.  With more nodes not: 2 x 60 M, 1 %, spread evenly 51.4 / 53.2, in clusters 38.1 / 42.5; 8 x 44.5 M, 0.1 % 23.5 / 25.9.
+        // of 1024 threads from 1024 on, there for two nodes as well.  Pieces of 512 / EVEN, 512 threads / 1024: 60 M, 1 %, spread evenly 28.9 / 27.8 / 24.5, in clusters
+        // 24.8 / 25.5 / 24.1; 40 M, 0.5 % 18.0 / 16.0 / 17.1; 2 x 60 M, 1 %, evenly 51.2 / 53.2 / 46.9, in clusters 37.8 / 42.5 / 37.2; 2 x 100 M, 1 %, in clusters
+        // 65.8 / - / 66.8.  With more nodes the clusters lose what an even spread gains: 3 x 60 M, 1 %, in clusters 57.5 / - / 62.6, 4 x 45 M, 1 % 54.9 / - / 57.5, evenly
+        // 81.4 / - / 76.4; 8 x 44.5 M, 0.1 % 23.5 / 25.9.
         const uint64_t each = (uint64_t)a.k * (kGroupRows * kRow) / a.n;
         if (a.row_rec) launch_gather_pieces<1024, false>(a, groups, batch, cus, st);
-        else if (batch > 1 || each < 512) launch_gather_pieces<512, false>(a, groups, batch, cus, st);
-        else if (each < 1024) launch_gather_pieces<512, true>(a, groups, batch, cus, st);
-        else launch_gather_pieces<1024, true>(a, groups, batch, cus, st);
+        else if (batch <= 2 && each >= 1024) launch_gather_pieces<1024, true>(a, groups, batch, cus, st);
+        else if (batch == 1 && each >= 512) launch_gather_pieces<512, true>(a, groups, batch, cus, st);
+        else launch_gather_pieces<512, false>(a, groups, batch, cus, st);
         return;
     }
     // 128 rows per block of 1024 threads; measured on the ResNet50-sized workload (4 nodes): 64 rows x 512

@@ -40,7 +40,7 @@ def check(B, v, got_v, vals, idx, want):
 @pytest.mark.parametrize("layout", ["spread", "stretch", "edges"])
 @pytest.mark.parametrize("n,k,batch", [(2 * GROUP + 1, 6000, 1), (8 * GROUP, 9000, 2), (8 * GROUP - 1, 9001, 3),   # with records
                                        (33_600_001, 33_600, 1), (12_000_001, 40_000, 3),                           # without
-                                       (33_600_001, 400_000, 1), (33_600_001, 150_000, 1),                         # one node's dense groups as pieces
+                                       (33_600_001, 400_000, 1), (33_600_001, 150_000, 1), (33_600_001, 400_000, 2),   # dense groups as pieces
                                        (257 * GROUP, 30_000, 1), (813 * GROUP + 1, 100_000, 1), (1025 * GROUP - 5, 2_400_000, 1)])
 def test_flat_selection(B, layout, n, k, batch):
     gen = torch.Generator(device="cuda")

@@ -133,8 +133,8 @@ def fall_backs_of_the_one_launch_finish(h):
 
 GATHERS = [  # elements, kept, nodes; which kernel lists the candidates: measured sizes on either side of each line of the rule
     (25_600_000, 25_600, 4, "k_gatherILb1ELb0E"), (33_000_000, 33_000, 1, "k_gatherILb1ELb0E"), (44_500_000, 44_500, 8, "k_gather_piecesILi512ELb0E"),
-    (60_000_000, 600_000, 1, "k_gather_piecesILi1024ELb1E"), (60_000_000, 600_000, 2, "k_gather_piecesILi512ELb0E"),
-    (40_000_000, 200_000, 1, "k_gather_piecesILi512ELb1E"), (100_000_000, 100_000, 1, "k_gather_piecesILi512ELb0E"),
+    (60_000_000, 600_000, 1, "k_gather_piecesILi1024ELb1E"), (60_000_000, 600_000, 2, "k_gather_piecesILi1024ELb1E"),
+    (60_000_000, 600_000, 3, "k_gather_piecesILi512ELb0E"), (40_000_000, 200_000, 1, "k_gather_piecesILi512ELb1E"), (40_000_000, 200_000, 2, "k_gather_piecesILi512ELb0E"), (100_000_000, 100_000, 1, "k_gather_piecesILi512ELb0E"),
     (1 << 28, 2_684_354, 1, "k_gather_piecesILi1024ELb0E"), (30_000_000, 300_000, 8, "k_gather_piecesILi1024ELb0E")]
 
 
