@@ -15,12 +15,13 @@
 // 64 bits: the cost cannot be told from none (4 x 25 600: 26.0 us either way), and in 32 bits those sums were over half
 // of the latent's error.
 // Measured against one fp32-MFMA launch per deep layer (ae_mfma.hip, which other stacks still use): 4 nodes x 25 600
-// values, encoder 79.4 -> 26.8 us (165 TFLOP/s of fp32 products), decoder 58.0 -> 21.3 us (126); 8 x 67 000, both
-// together 468 -> 230 us (162); 1 x 1 023 (latency) 79 -> 29 us.  Relative error against 64 bits, six sizes from 1 x 500 to
+// values, encoder 79.4 -> 26.8 us (165 TFLOP/s of fp32 products), decoder 58.0 -> 20.6 us (130); 8 x 67 000, both
+// together 468 -> 215 us (173); 1 x 1 023 (latency) 79 -> 24.8 us.  Relative error against 64 bits, six sizes from 1 x 500 to
 // 8 x 67 000 x six seeds, mean (least to largest): latent 1.15e-7 (0.87 to 1.46) -> 0.41e-7 (0.34 to 0.51; 0.99e-7 with the
-// last sums in 32 bits), decoder 3.86e-8 (2.96 to 5.54) -> 3.46e-8 (2.81 to 4.93; 3.73e-8): lower at every size with every
+// last sums in 32 bits), decoder 3.86e-8 (2.96 to 5.54) -> 2.95e-8 (2.20 to 3.86): lower at every size with every
 // seed.  What bounds it: while a compute unit has blocks its matrix cores are busy 54-57 % of the cycles (encoder) and
-// 39-44 % (decoder).
+// 45 % (decoder).  A wavefront's products, once begun, hold them until it waits; what else its block has to do goes on beside another
+// wavefront's products only where no barrier stands between.
 //
 // The split is exact only for finite values; an Inf would meet products of both signs.  Such a value (or one that rounds
 // to Inf) leaves a NaN among its parts, which makes every output it reaches a NaN.  And it is exact only while the parts
@@ -85,17 +86,34 @@ __device__ __forceinline__ void mma6(acc16 (&acc)[MT][NT], acc16 (&cross)[MT][NT
             }
 }
 
-// The even and the odd outputs of a transposed layer for one step: x0, x1 = inputs m, m + 1; a[t] = tap t
-__device__ __forceinline__ void mma6_up(acc16 &even, acc16 &odd, const u4v (&a)[3][3], const u4v (&x)[2][3]) {
+// sum[i] + cross[i] += a[i] x for one step, as in mma6 (the five products that hold an m or an l have sums of their own)
+template <int N>
+__device__ __forceinline__ void mma6_by(acc16 (&sum)[2], acc16 (&cross)[2], const u4v (&a)[N][3], const u4v (&x)[3]) {
+    constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+    for (int q = 0; q < 6; ++q)
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            acc16 &c = q < 5 ? cross[i] : sum[i];
+            c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, a[i][kA[q]]), __builtin_bit_cast(bf8, x[kB[q]]), c, 0, 0, 0);
+        }
+}
+
+// The four outputs of two transposed layers in a row: e, o = the first one's outputs 2i and 2i + 1, n = its 2i + 2;
+// a = taps 2, 1, 0
+__device__ __forceinline__ void mma6_up4(acc16 (&y)[4], const u4v (&a)[3][3], const u4v (&e)[3], const u4v (&o)[3], const u4v (&n)[3]) {
     constexpr int kA[6] = {2, 0, 1, 1, 0, 0}, kB[6] = {0, 2, 1, 0, 1, 0};
     auto mul = [](const u4v &p, const u4v &q, const acc16 &c) {
         return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf8, p), __builtin_bit_cast(bf8, q), c, 0, 0, 0);
     };
 #pragma unroll
     for (int q = 0; q < 6; ++q) {
-        odd = mul(a[2][kA[q]], x[0][kB[q]], odd);
-        even = mul(a[1][kA[q]], x[0][kB[q]], even);
-        odd = mul(a[0][kA[q]], x[1][kB[q]], odd);
+        y[1] = mul(a[0][kA[q]], e[kB[q]], y[1]);
+        y[3] = mul(a[0][kA[q]], o[kB[q]], y[3]);
+        y[0] = mul(a[1][kA[q]], e[kB[q]], y[0]);
+        y[2] = mul(a[1][kA[q]], o[kB[q]], y[2]);
+        y[1] = mul(a[2][kA[q]], o[kB[q]], y[1]);
+        y[3] = mul(a[2][kA[q]], n[kB[q]], y[3]);
     }
 }
 
@@ -148,23 +166,49 @@ __device__ __forceinline__ void store_tile(unsigned char *row, const int co0, co
     }
 }
 
+// One result tile with the non-linearity as operands of the next layer, 16 channels a step: r[step][part] (weights `as_results`)
+__device__ __forceinline__ void as_operands(const acc16 &acc, const float slope, const bool valid, u4v (&r)[2][3]) {
+#pragma unroll
+    for (int i = 0; i < 16; i += 2) {
+        float y[2];
+#pragma unroll
+        for (int c = 0; c < 2; ++c) { y[c] = leaky_f(acc[i + c], slope); y[c] = valid ? y[c] : 0.f; }
+        uint32_t h, m, l;
+        split2(y[0], y[1], h, m, l);
+        r[i >> 3][0][(i & 7) >> 1] = h; r[i >> 3][1][(i & 7) >> 1] = m; r[i >> 3][2][(i & 7) >> 1] = l;
+    }
+}
+
+// The same of the next lane's position (of the last lane of each half: whatever)
+__device__ __forceinline__ void next_position(const u4v (&r)[2][3], u4v (&n)[2][3]) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) n[q][p][i] = __builtin_amdgcn_update_dpp(0u, r[q][p][i], 0x130 /* wave_shl:1 */, 0xf, 0xf, true);
+}
+
 // ---- weights as bf16 fragments --------------------------------------------------------------------
 // out[((mt * steps + s) * 3 + part) * 512 + lane * 8 + e], s = tap * (c_in / 16) + ci / 16: part `part` of
 // w[co = 32 mt + lane % 32][ci = 16 (s % (c_in / 16)) + 8 (lane / 32) + e][tap].  One thread per (mt, s, lane).
+// as_results: element e of half h is input channel 4 h + e (e < 4) or 8 + 4 h + e - 4 of the 16 instead, which is where a lane of
+// the layer before holds them among its results: those then are operands without leaving their registers.
 // *bad counts the weights that are not finite (the handle then keeps to the fp32 kernels).
 __global__ __launch_bounds__(256) void k_weights_split(const float *__restrict__ w, uint16_t *__restrict__ out, int c_in, int c_out,
-                                                       int transposed, uint32_t *bad) {
+                                                       int transposed, int as_results, uint32_t *bad) {
     const int steps = 3 * (c_in / 16), total = (c_out / 32) * steps * 64;
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= total) return;
     const int lane = i & 63, s = (i >> 6) % steps, mt = (i >> 6) / steps;
-    const int tap = s / (c_in / 16), co = 32 * mt + (lane & 31), ci0 = 16 * (s % (c_in / 16)) + 8 * (lane >> 5);
+    const int tap = s / (c_in / 16), co = 32 * mt + (lane & 31), ci0 = 16 * (s % (c_in / 16));
+    const int half = lane >> 5;
     uint16_t *o = out + (size_t)((i >> 6) * 3) * 512 + lane * 8;
     float chk = 0.f;
     for (int e = 0; e < 8; e += 2) {
         float x[2];
         for (int c = 0; c < 2; ++c) {
-            const int ci = ci0 + e + c;
+            const int i = e + c, ci = ci0 + (as_results ? 8 * (i >> 2) + 4 * half + (i & 3) : 8 * half + i);
             x[c] = transposed ? w[((size_t)ci * c_out + co) * 3 + tap] : w[((size_t)co * c_in + ci) * 3 + tap];
         }
         uint32_t h, m, l;
@@ -186,9 +230,9 @@ __global__ __launch_bounds__(256) void k_most(const float *__restrict__ w, int c
 
 }  // namespace
 
-void launch_weights_split(const float *w, uint16_t *out, int c_in, int c_out, bool transposed, uint32_t *bad, hipStream_t st) {
+void launch_weights_split(const float *w, uint16_t *out, int c_in, int c_out, bool transposed, bool as_results, uint32_t *bad, hipStream_t st) {
     const int total = (c_out / 32) * 3 * (c_in / 16) * 64;
-    hipLaunchKernelGGL(k_weights_split, dim3((total + 255) / 256), dim3(256), 0, st, w, out, c_in, c_out, (int)transposed, bad);
+    hipLaunchKernelGGL(k_weights_split, dim3((total + 255) / 256), dim3(256), 0, st, w, out, c_in, c_out, (int)transposed, (int)as_results, bad);
 }
 
 void launch_most(const float *w, int count, uint32_t *most, hipStream_t st) {
@@ -602,60 +646,117 @@ __device__ __forceinline__ void store_fp32(float *row, const int co0, const int 
 }  // namespace
 
 // T latent positions per block of four wavefronts.  Local numbering from 1, 2, 4, 8 and 16 p0 on: T + 1 outputs of
-// deconv1, 2T + 1 of deconv2, 4T + 1 of deconv3, 8T + 1 of deconv4 and 16T of deconv5.  deconv4's outputs are made
-// and consumed in two runs of D4 / 2 channels, so that two blocks fit a compute unit's LDS, and its registers: the bound
-// of two wavefronts per SIMD keeps the redo from taking more.
-template <int D0, int D1, int D2, int D3, int D4, int D5, int T>
+// deconv1, 2T + 1 of deconv2, 4T + 1 of deconv3, 8T + 1 of deconv4 and 16T of deconv5.  A wavefront takes 32 of deconv3's
+// positions through deconv4 and deconv5, 32 channels of deconv4 at a time: lane i holds its outputs 2i and 2i + 1, splits them in
+// registers and multiplies on, so that no barrier and no exchange through the LDS stands between the two layers that make up the
+// work, and one wavefront converts while another one multiplies.  deconv5's output 4i + 3 needs deconv4's 2i + 2, which is the next
+// lane's: 31 of the 32 positions come out.  4 / NP wavefronts share a position tile's channels of deconv4 and add their sums up at the end.
+// The bound of two wavefronts per SIMD leaves room for the weights' fragments that are under way (one step ahead).
+// Through the LDS, in two runs of 64 channels with four barriers each, 4 x 25 600 values took 22.2 us (20.6 now), 8 x 67 000 87.8 (82.8), 1 x 1 023
+// 12.5 (8.8, with 7 positions per block).  What bounds it: two blocks on a compute unit have 18.4 K cycles of products in 39 K; the rest is each block's way
+// to the first product (9 K: a read from memory, three small layers, three barriers) and its end (5 K).
+template <int D0, int D1, int D2, int D3, int D4, int D5, int T, bool RING>
 __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restrict__ z, float *__restrict__ out, DecoderDev w,
                                                        uint32_t lz, uint32_t l2, uint32_t l3, uint32_t l4, uint32_t l5,
                                                        float slope) {
-    constexpr int M3 = 2 * (T + 1), M4 = 4 * (T + 1), M5 = 8 * (T + 1);   // tile widths: input positions of deconv3, 4, 5
-    constexpr int CH = D4 / 2;                                             // channels of deconv4 per run
-    constexpr int R2 = row_bytes(D2), R3 = row_bytes(D3), R4 = row_bytes(CH);
-    constexpr int kBytesA = (M5 + 1) * R4, kBytesB = (M4 + 1) * R3;
-    static_assert(M3 == 32 && M4 == 64 && M5 == 128 && D2 % 16 == 0 && D3 == 64 && CH == 64 && D5 == 32, "tiles");
-    static_assert((M3 + 1) * R2 <= kBytesA && 4 * 2 * 1024 * 4 <= kBytesA, "region A");
-    static_assert(row_floats(D2) * 4 <= R2 && row_floats(D3) * 4 <= R3 && row_floats(CH) * 4 <= R4, "rows of fp32 take no more room");
-    __shared__ __align__(16) unsigned char bufA[kBytesA];   // deconv2's outputs, then deconv4's run by run
-    __shared__ __align__(16) unsigned char bufB[kBytesB];   // deconv3's outputs
+    constexpr int NP = (4 * T + 30) / 31, KG = 4 / NP, CT = D4 / 32 / KG;   // position tiles; wavefronts per tile; their tiles of 32 channels
+    constexpr int M3 = 2 * (T + 1), M4 = 4 * (T + 1), M5 = 8 * (T + 1);     // outputs of deconv2, 3, 4 that are kept (of which one or three too many)
+    constexpr int R2 = row_bytes(D2), R3 = row_bytes(D3), CH = 32;          // CH: channels of deconv4 per run of the redo
+    constexpr int kStep = KG * 9 * 1024;                                    // a step's fragments: three parts of three taps per group of channels
+    constexpr int kHandOver = 2 * (KG == 4 ? 3 : 2) * 4096;                 // sums that change wavefronts: half of them
+    constexpr int kRedo = (M5 + 1) * row_floats(CH) * 4, kMost = kRedo > kHandOver ? kRedo : kHandOver;
+    constexpr int kBytesA = RING && kStep > kMost ? kStep : kMost;
+    static_assert(!RING || KG == 2, "two wavefronts read a step");
+    static_assert(NP * KG == 4 && CT * KG * 32 == D4 && M3 <= 32 && D2 % 16 == 0 && D3 == 64 && D4 == 128 && D5 == 32, "tiles");
+    static_assert(row_floats(D2) * 4 <= R2 && row_floats(D3) * 4 <= R3 && M4 <= 64 && 31 * NP + 2 <= 65, "rows");
+    // steps of weights on their way to the wavefronts; sums handed over; the first one in the redo: deconv4's outputs run by run
+    __shared__ __align__(16) unsigned char ring0[kBytesA], ring1[kBytesA];
+    __shared__ __align__(16) unsigned char bufA[33 * R2], bufB[65 * R3];   // deconv2's outputs, deconv3's
     __shared__ float zs[D0 * (T + 3)], h1[D1 * (T + 1)];
+    // the small layers' weights and all biases
+    constexpr int kW2 = 0, kB3 = kW2 + D1 * D2 * 3, kB5 = kB3 + D3, kW6 = kB5 + D5, kB4 = kW6 + D5, kW1 = kB4 + D4, kB1 = kW1 + 3 * D0 * D1, kB2 = 736;
+    __shared__ __align__(16) float small[768];
+    static_assert(kB3 == 384 && kB4 == 512 && kW1 == 640 && kB1 == 688 && kB1 + D1 <= kB2 && kB2 + D2 <= 768, "three words per thread");
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
     const long long p0 = (long long)blockIdx.x * T;
     z += (size_t)blockIdx.y * D0 * lz;
     out += (size_t)blockIdx.y * l5;
 
-    for (int i = tid; i < D0 * (T + 3); i += 256) {
-        const int c = i / (T + 3);
-        const long long e = p0 - 1 + i % (T + 3);
-        zs[i] = e >= 0 && e < (long long)lz ? z[(size_t)c * lz + e] : 0.f;
+    // everything that the first three layers read from memory, at once: one wait instead of four in a row
+    constexpr int kCh = D2 / 8, kPer3 = D2 / 16;
+    static_assert(D0 == 4 && D1 == 4 && kCh == 4 && D0 * (T + 3) <= 256 && D1 * (T + 1) <= 256, "one value per thread");
+    const int zc = tid / (T + 3);
+    const long long ze = p0 - 1 + tid % (T + 3);
+    const float zv = zc < D0 && ze >= 0 && ze < (long long)lz ? z[(size_t)zc * lz + ze] : 0.f;
+    float sv[3];
+    sv[0] = w.w2[tid];
+    sv[1] = *(tid < 128 ? w.w2 + 256 + tid : tid < 192 ? w.b3 + tid - 128 : tid < 224 ? w.b5 + tid - 192 : w.w6 + tid - 224);
+    sv[2] = *(tid < 128 ? w.b4 + tid : tid < 176 ? w.w1 + tid - 128 : tid < 180 ? w.b1 + tid - 176 : w.b2 + (tid < 224 ? 0 : tid - 224));
+    const int mt3 = wave & 1, par3 = wave >> 1;   // deconv3: wavefront = channel tile x (even or odd outputs)
+    u4v a3[2 * kPer3][1][3];
+    {
+        const u4v *a = (const u4v *)w.s3 + (size_t)mt3 * 3 * kPer3 * 192 + lane;
+#pragma unroll
+        for (int s = 0; s < kPer3; ++s) {
+            load_a(a3[s][0], a, (par3 ? 2 : 1) * kPer3 + s);
+            load_a(a3[kPer3 + s][0], a, s);   // of the odd outputs only
+        }
     }
+    __builtin_amdgcn_sched_barrier(0);
+    // deconv4 and deconv5: this wavefront's position tile and channels, the latter's weights step by step (four steps of deconv4, two of
+    // deconv5 for each 32 channels)
+    const int pt = wave % NP, kg = wave / NP;
+    constexpr int kPer = D3 / 16, kPer5 = D4 / 16, kSteps = kPer + 2;
+    const u4v *a4 = (const u4v *)w.s4 + (size_t)(kg * CT) * 3 * kPer * 192, *a5 = (const u4v *)w.s5 + kg * CT * 2 * 192;
+    const uint32_t lane16 = 16u * (uint32_t)lane;
+    auto fragments = [&](const int ct, const int s, const int t) {   // of tap 2 - t
+        return s < kPer ? a4 + (ct * 3 * kPer + (2 - t) * kPer + s) * 192 : a5 + (ct * 2 + (2 - t) * kPer5 + s - kPer) * 192;
+    };
+    auto scalar = [](const u4v *p) {   // left alone the compiler keeps a pair of vector registers for each of these addresses
+        uint64_t at = (uint64_t)p;
+        asm("" : "+s"(at));
+        return at;
+    };
+    // RING: the two wavefronts of a group of channels fetch a step's fragments for both, into the LDS without registers on the way
+    auto fetch = [&](unsigned char *ring, const int ct, const int s) {
+#pragma unroll
+        for (int i = 0; i < 5; ++i) {   // nine between two: both fetch the middle one, so that each knows how many it waits for
+            const int f = pt * 4 + i;
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(scalar(fragments(ct, s, f / 3) + (f % 3) * 64) + lane16),
+                                             (__attribute__((address_space(3))) void *)(ring + (kg * 9 + f) * 1024), 16, 0, 0);
+        }
+    };
+    if (zc < D0) zs[tid] = zv;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) small[256 * i + tid] = sv[i];
+    __builtin_amdgcn_sched_barrier(0);
+    if (RING) { fetch(ring0, 0, 0); fetch(ring1, 0, 1); }   // (ahead of those stores the compiler waits for it before them)
     __syncthreads();
-    for (int i = tid; i < D1 * (T + 1); i += 256) {   // deconv1
-        const int c = i / (T + 1), j = i % (T + 1);
-        float a = w.b1[c];
+    if (tid < D1 * (T + 1)) {   // deconv1: thread = channel x position
+        const int c = tid / (T + 1), j = tid % (T + 1);
+        float a = small[kB1 + c];
 #pragma unroll
         for (int ci = 0; ci < D0; ++ci) {
-            const float *wc = w.w1 + (ci * D1 + c) * 3, *zc = zs + ci * (T + 3) + j;
-            a = fmaf(wc[0], zc[2], a);
-            a = fmaf(wc[1], zc[1], a);
-            a = fmaf(wc[2], zc[0], a);
+            const float *zi = zs + ci * (T + 3) + j, *wc = small + kW1 + (ci * D1 + c) * 3;
+            a = fmaf(wc[0], zi[2], a);
+            a = fmaf(wc[1], zi[1], a);
+            a = fmaf(wc[2], zi[0], a);
         }
-        h1[i] = p0 + j < (long long)lz ? leaky_f(a, slope) : 0.f;
+        h1[tid] = p0 + j < (long long)lz ? leaky_f(a, slope) : 0.f;
     }
     __syncthreads();
-    constexpr int kCh = D2 / 8;
-    auto deconv2 = [&](float (&y)[kCh]) {   // thread = position x group of D2 / 8 channels
-        const int j = tid & 31, cg = tid >> 5, m = j >> 1;
+    auto deconv2 = [&](float (&y)[kCh], const int thread) {   // thread = position x group of D2 / 8 channels
+        const int j = thread & 31, m = j >> 1;
         const bool odd = j & 1, valid = 2 * p0 + j < (long long)l2 && j < 2 * T + 1;
 #pragma unroll
-        for (int c = 0; c < kCh; ++c) y[c] = w.b2[cg * kCh + c];
+        for (int c = 0; c < kCh; ++c) y[c] = small[kB2 + (thread >> 5) * kCh + c];
 #pragma unroll
         for (int ci = 0; ci < D1; ++ci) {
-            const float x0 = h1[ci * (T + 1) + m], x1 = m < T ? h1[ci * (T + 1) + m + 1] : 0.f;
+            const float x0 = m <= T ? h1[ci * (T + 1) + m] : 0.f, x1 = m < T ? h1[ci * (T + 1) + m + 1] : 0.f;
 #pragma unroll
             for (int c = 0; c < kCh; ++c) {
-                const float *wc = w.w2 + (ci * D2 + cg * kCh + c) * 3;
+                const float *wc = small + kW2 + (ci * D2 + (thread >> 5) * kCh + c) * 3;
                 const float e = fmaf(wc[1], x0, y[c]), o = fmaf(wc[2], x0, fmaf(wc[0], x1, y[c]));
                 y[c] = odd ? o : e;
             }
@@ -665,7 +766,7 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
     };
     {
         float y[kCh];
-        deconv2(y);
+        deconv2(y, tid);
         unsigned char *row = bufA + (tid & 31) * R2 + (tid >> 5) * kCh * 2;
 #pragma unroll
         for (int c = 0; c < kCh; c += 2) {
@@ -676,183 +777,191 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
             *(uint32_t *)(row + 4 * D2 + 2 * c) = l;
         }
     }
-    {   // deconv3: wavefront = channel tile x (even or odd outputs)
-        constexpr int kPer = D2 / 16;
-        const int mt = wave & 1, par = wave >> 1;
-        const u4v *a = (const u4v *)w.s3 + (size_t)mt * 3 * kPer * 192 + lane;
+    __syncthreads();
+    {   // deconv3
         const unsigned char *b = bufA + col * R2 + half * 16;
-        acc16 acc[1][1];
-        acc[0][0] = bias16(w.b3, mt * 32, half);
-        acc16 cross[1][1];
+        acc16 acc[1][1], cross[1][1];
+        acc[0][0] = bias16(small + kB3, mt3 * 32, half);
         cross[0][0] = zero16();
-        u4v ra[2 * kPer][1][3];
-#pragma unroll
-        for (int s = 0; s < kPer; ++s) {
-            load_a(ra[s][0], a, (par ? 2 : 1) * kPer + s);
-            load_a(ra[kPer + s][0], a, s);   // of the odd outputs only
-        }
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
         u4v rb[1][3];
 #pragma unroll
-        for (int s = 0; s < kPer; ++s) {
+        for (int s = 0; s < kPer3; ++s) {
             load_b<D2>(rb[0], b, 32 * s);
-            mma6<1, 1>(acc, cross, ra[s], rb);
-            if (par) {
+            mma6<1, 1>(acc, cross, a3[s], rb);
+            if (par3) {
                 load_b<D2>(rb[0], b + R2, 32 * s);
-                mma6<1, 1>(acc, cross, ra[kPer + s], rb);
+                mma6<1, 1>(acc, cross, a3[kPer3 + s], rb);
             }
         }
         acc[0][0] += cross[0][0];
-        const int i = 2 * col + par;
-        store_tile<D3>(bufB + i * R3, mt * 32, half, acc[0][0], slope, 4 * p0 + i < (long long)l3 && i < 4 * T + 1);
+        const int i = 2 * col + par3;
+        store_tile<D3>(bufB + i * R3, mt3 * 32, half, acc[0][0], slope, 4 * p0 + i < (long long)l3 && i < 4 * T + 1);
     }
 
-    const int np = wave & 1, kh = wave >> 1;   // deconv5: wavefront = pair of position tiles x half of each run's channels
-    acc16 e5[2], o5[2];
+    const int i0 = 31 * pt + col;   // this lane's position of deconv3
+    acc16 y[4];   // deconv5's outputs 4 i0 .. 4 i0 + 3
 #pragma unroll
-    for (int j = 0; j < 2; ++j) { e5[j] = zero16(); o5[j] = zero16(); }
-#pragma unroll 1
-    for (int run = 0; run < 2; ++run) {
-        {   // deconv4: wavefront = channel tile of the run x position tile, even and odd outputs
-            constexpr int kPer = D3 / 16;
-            const int mt = wave & 1, n0 = wave >> 1;
-            const u4v *a = (const u4v *)w.s4 + (size_t)(2 * run + mt) * 3 * kPer * 192 + lane;
-            const unsigned char *b = bufB + (n0 * 32 + col) * R3 + half * 16;
-            u4v ra[2][3][3], rb[2][2][3];
-            auto fetch = [&](const int s) {
+    for (int j = 0; j < 4; ++j) y[j] = zero16();
+    {
+        const unsigned char *b = bufB + i0 * R3 + half * 16;
+        u4v ra[2][3][3], x0[3], x1[3];   // taps 2, 1, 0; inputs i0 and i0 + 1
+        auto take = [&](const int ct, const int s) {   // step s into registers
 #pragma unroll
-                for (int t = 0; t < 3; ++t) load_a(ra[s & 1][t], a, t * kPer + s);
-            };
-            auto read = [&](const int s) {
-                load_b<D3>(rb[s & 1][0], b, 32 * s);
-                load_b<D3>(rb[s & 1][1], b + R3, 32 * s);
-            };
-            fetch(0);
-            __builtin_amdgcn_sched_barrier(0);
-            acc16 even = bias16(w.b4 + run * CH, mt * 32, half), odd = even;
-            __syncthreads();   // deconv3's outputs are there; the previous run's of deconv4 have been read
-            read(0);
+            for (int t = 0; t < 3; ++t)
 #pragma unroll
-            for (int s = 0; s < kPer; ++s) {
-                if (s + 1 < kPer) { fetch(s + 1); read(s + 1); }
-                __builtin_amdgcn_sched_barrier(0);
-                mma6_up(even, odd, ra[s & 1], rb[s & 1]);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-            const int i = 2 * (n0 * 32 + col);
-            store_tile<CH>(bufA + i * R4, mt * 32, half, even, slope, 8 * p0 + i < (long long)l4 && i < 8 * T + 1);
-            store_tile<CH>(bufA + (i + 1) * R4, mt * 32, half, odd, slope, 8 * p0 + i + 1 < (long long)l4 && i + 1 < 8 * T + 1);
-        }
-        {   // deconv5, this run's channels
-            constexpr int kPer = D4 / 16, kSteps = CH / 32;
-            const u4v *a = (const u4v *)w.s5 + lane;
-            u4v ra[2][3][3], rb[2][2][3];
-            const unsigned char *b = bufA + (np * 64 + col) * R4 + half * 16 + 32 * kh * kSteps;
-            auto fetch = [&](const int q) {
-#pragma unroll
-                for (int t = 0; t < 3; ++t) load_a(ra[q & 1][t], a, t * kPer + run * (CH / 16) + kh * kSteps + q);
-            };
-            auto read = [&](const int q, const int j) {
-                load_b<CH>(rb[j][0], b + j * 32 * R4, 32 * q);
-                load_b<CH>(rb[j][1], b + j * 32 * R4 + R4, 32 * q);
-            };
-            fetch(0);
-            __builtin_amdgcn_sched_barrier(0);
-            __syncthreads();
-            read(0, 0);
-#pragma unroll
-            for (int q = 0; q < kSteps; ++q) {
-                if (q + 1 < kSteps) fetch(q + 1);
-#pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    if (j == 0) read(q, 1);
-                    else if (q + 1 < kSteps) read(q + 1, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    mma6_up(e5[j], o5[j], ra[q & 1], rb[j]);
+                for (int p = 0; p < 3; ++p)
+                    if (RING) ra[s & 1][t][p] = *(const u4v *)(((s & 1) ? ring1 : ring0) + (kg * 9 + t * 3 + p) * 1024 + lane16);
+                    else ra[s & 1][t][p] = *(const __attribute__((address_space(1))) u4v *)(scalar(fragments(ct, s, t) + p * 64) + lane16);
+        };
+        // Before step s: the next one into registers, and the one after it under way.  What is in the ring is there for all once each wavefront has waited
+        // for its own share; what was in its other half has been read.
+        auto advance = [&](const int ct, const int s) {
+            if (RING) {
+                if (s + 1 < kSteps || ct + 1 < CT) {
+                    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0), lgkmcnt(0)
+                    __builtin_amdgcn_s_barrier();
                     __builtin_amdgcn_sched_barrier(0);
                 }
+                if (s + 2 < kSteps) fetch((s & 1) ? ring1 : ring0, ct, s + 2);
+                else if (ct + 1 < CT) fetch((s & 1) ? ring1 : ring0, ct + 1, s + 2 - kSteps);
+            }
+            if (s + 1 < kSteps) take(ct, s + 1);
+            else if (ct + 1 < CT) take(ct + 1, 0);
+        };
+        if (!RING) take(0, 0);
+        if (RING) __builtin_amdgcn_s_waitcnt(0x0070);
+        __syncthreads();   // deconv3's outputs are there, and the first two steps
+        if (RING) take(0, 0);
+#pragma unroll 1
+        for (int ct = 0; ct < CT; ++ct) {
+            acc16 up[2], cross[2];   // the odd and the even outputs
+            up[0] = bias16(small + kB4 + (kg * CT + ct) * 32, 0, half);
+            up[1] = up[0];
+            cross[0] = zero16(); cross[1] = zero16();
+            load_b<D3>(x0, b, 0);
+#pragma unroll
+            for (int s = 0; s < kPer; ++s) {
+                load_b<D3>(x1, b + R3, 32 * s);
+                advance(ct, s);
+                __builtin_amdgcn_sched_barrier(0);
+                mma6_by<2>(up, cross, (const u4v (&)[2][3])ra[s & 1], x0);
+                __builtin_amdgcn_sched_barrier(0);
+                if (s + 1 < kPer) load_b<D3>(x0, b, 32 * (s + 1));
+                __builtin_amdgcn_sched_barrier(0);
+                mma6_by<1>(up, cross, (const u4v (&)[1][3])ra[s & 1][2], x1);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            up[0] += cross[0]; up[1] += cross[1];
+            u4v e[2][3], o[2][3], n[2][3];
+            as_operands(up[1], slope, 8 * p0 + 2 * i0 < (long long)l4 && 2 * i0 < 8 * T + 1, e);
+            as_operands(up[0], slope, 8 * p0 + 2 * i0 + 1 < (long long)l4 && 2 * i0 + 1 < 8 * T + 1, o);
+            next_position(e, n);
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                advance(ct, kPer + q);
+                __builtin_amdgcn_sched_barrier(0);
+                mma6_up4(y, ra[q & 1], e[q], o[q], n[q]);
+                __builtin_amdgcn_sched_barrier(0);
             }
         }
     }
-    __syncthreads();
-    // the two halves of the contraction meet: wavefront (np, kh) finishes tile 2 np + kh and hands the other one over
-    float *swap = (float *)bufA;
-    {
-        float *to = swap + (size_t)wave * 2048 + lane;
+    if (RING) __syncthreads();   // the last step has been read
+    // The numbers of this thread anew, from its lane: kept over the loop they would be the registers too many.  (Unknown to the compiler as
+    // well, so that the values loaded above are not kept for the redo.)
+    uint32_t every = ~0u;
+    asm volatile("" : "+s"(every));
+    const int ln = (int)__builtin_amdgcn_mbcnt_hi(every, __builtin_amdgcn_mbcnt_lo(every, 0u)), id = wave * 64 + ln, hf = ln >> 5, cl = ln & 31, at = 31 * pt + cl;
+    // the sums of a tile's wavefronts meet: wavefront kg finishes outputs kOwn kg .. of every four and hands the others over
+    constexpr int kOwn = 4 / KG;   // 2 or 1
+    // [tile][output][from: the other wavefronts in order][16][64], the first two outputs of a tile in one half of the ring
+    auto swap = [&](const int j) { return (float *)(j < 2 ? ring0 : ring1) + (pt * 2 + (j & 1)) * (KG - 1) * 1024 + ln; };
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            to[r * 64] = kh ? e5[0][r] : e5[1][r];
-            to[1024 + r * 64] = kh ? o5[0][r] : o5[1][r];
+    for (int j = 0; j < 4; ++j) {
+        if (j / kOwn != kg) {      // wave-uniform
+            const int from = kg < j / kOwn ? kg : kg - 1;
+            float *to = swap(j) + from * 1024;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) to[r * 64] = y[j][r];
         }
     }
     __syncthreads();
-    double se = 0., so = 0.;
-    {
-        const float *from = swap + (size_t)(np + 2 * (kh ^ 1)) * 2048 + lane;
+    double sum[kOwn];
+    acc16 own[kOwn];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int co = (r >> 2) * 8 + half * 4 + (r & 3);
-            const float bv = w.b5[co], wv = w.w6[co];
-            const float ye = (kh ? e5[1][r] : e5[0][r]) + from[r * 64] + bv;
-            const float yo = (kh ? o5[1][r] : o5[0][r]) + from[1024 + r * 64] + bv;
-            se = fma((double)wv, (double)leaky_f(ye, slope), se);
-            so = fma((double)wv, (double)leaky_f(yo, slope), so);
+    for (int k = 0; k < KG; ++k)
+        if (kg == k) {             // wave-uniform
+#pragma unroll
+            for (int j = 0; j < kOwn; ++j) own[j] = y[k * kOwn + j];
         }
+#pragma unroll
+    for (int j = 0; j < kOwn; ++j) {
+        const float *from = swap(kg * kOwn + j);
+        sum[j] = 0.;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const f4v bv = *(const f4v *)(small + kB5 + 8 * g + 4 * hf), wv = *(const f4v *)(small + kW6 + 8 * g + 4 * hf);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int r = 4 * g + c;
+                float x = own[j][r];
+#pragma unroll
+                for (int k = 0; k < KG - 1; ++k) x += from[k * 1024 + r * 64];
+                sum[j] = fma((double)wv[c], (double)leaky_f(x + bv[c], slope), sum[j]);
+            }
+        }
+        sum[j] += __shfl_xor(sum[j], 32, 64);
     }
-    se += __shfl_xor(se, 32, 64);
-    so += __shfl_xor(so, 32, 64);
-    const int m = (np * 2 + kh) * 32 + col, i = 2 * m + half;   // lanes 0..31 store the even, lanes 32..63 the odd outputs
-    const bool mine = m < 8 * T && 16 * p0 + i < (long long)l5;
-    const float y = (float)(w.b6[0] + (half ? so : se));
-    bool redo = __syncthreads_or(mine && !(fabsf(y) >= w.limits.least && fabsf(y) < INFINITY));
+    // the halves of a wavefront have the same sums: two outputs are stored by a half each, one by the first half
+    const int o = kg * kOwn + (kOwn == 2 ? hf : 0), i = 4 * at + o;
+    const bool mine = cl < 31 && (kOwn == 2 || hf == 0) && i < 16 * T && 16 * p0 + i < (long long)l5;
+    const float result = (float)(w.b6[0] + (kOwn == 2 && hf ? sum[kOwn - 1] : sum[0]));
+    bool redo = __syncthreads_or(mine && !(fabsf(result) >= w.limits.least && fabsf(result) < INFINITY));
     if (redo && w.limits.no_bias) {   // nothing but zeros gives zeros
-        redo = __syncthreads_or(tid < D0 * (T + 3) && zs[tid] != 0.f);
-        static_assert(D0 * (T + 3) <= 256, "one value per thread");
+        redo = __syncthreads_or(id < D0 * (T + 3) && zs[id] != 0.f);
     }
     if (!redo) {
-        if (mine) out[16 * p0 + i] = y;
+        if (mine) out[16 * p0 + i] = result;
         return;
     }
-    float *fa = (float *)bufA, *fb = (float *)bufB;
-    int hf = half;
-    asm("" : "+v"(hf));   // the same number, unknown to the compiler: the values loaded above are not kept in registers for the redo
+    float *fd = (float *)bufA, *fa = (float *)ring0, *fb = (float *)bufB;
     {
-        float y[kCh];
-        deconv2(y);
+        float y2[kCh];
+        deconv2(y2, id);
 #pragma unroll
-        for (int c = 0; c < kCh; ++c) fa[(tid & 31) * row_floats(D2) + (tid >> 5) * kCh + c] = y[c];
+        for (int c = 0; c < kCh; ++c) fd[(id & 31) * row_floats(D2) + (id >> 5) * kCh + c] = y2[c];
     }
     __syncthreads();
     if (wave < D3 / 32) {   // deconv3: wavefront = channel tile
         acc16 even = bias16(w.b3, wave * 32, hf), odd = even;
-        up_fp32<D2, D3, row_floats(D2)>(even, odd, w.w3 + (4 * hf * D3 + wave * 32 + col) * 3, fa + col * row_floats(D2) + 4 * hf);
-        const int j = 2 * col;
+        up_fp32<D2, D3, row_floats(D2)>(even, odd, w.w3 + (4 * hf * D3 + wave * 32 + cl) * 3, fd + cl * row_floats(D2) + 4 * hf);
+        const int j = 2 * cl;
         store_fp32(fb + j * row_floats(D3), wave * 32, hf, even, slope, 4 * p0 + j < (long long)l3 && j < 4 * T + 1);
         store_fp32(fb + (j + 1) * row_floats(D3), wave * 32, hf, odd, slope, 4 * p0 + j + 1 < (long long)l3 && j + 1 < 4 * T + 1);
     }
-    acc16 e = bias16(w.b5, 0, hf), o = e;   // deconv5: wavefront = position tile
+    acc16 e = bias16(w.b5, 0, hf), od = e;   // deconv5: wavefront = position tile
 #pragma unroll 1
-    for (int run = 0; run < 2; ++run) {
-        const int co0 = run * CH + (wave & 1) * 32, m0 = (wave >> 1) * 32 + col, j = 2 * m0;   // deconv4: channel tile x position tile
+    for (int run = 0; run < D4 / CH; ++run) {
+        const int co0 = run * CH, m0 = wave * 32 + cl, j = 2 * m0;   // deconv4: the first M4 / 32 wavefronts, a position tile each
         acc16 even = bias16(w.b4, co0, hf), odd = even;
         __syncthreads();
-        up_fp32<D3, D4, row_floats(D3)>(even, odd, w.w4 + (4 * hf * D4 + co0 + col) * 3, fb + m0 * row_floats(D3) + 4 * hf);
-        store_fp32(fa + j * row_floats(CH), (wave & 1) * 32, hf, even, slope, 8 * p0 + j < (long long)l4 && j < 8 * T + 1);
-        store_fp32(fa + (j + 1) * row_floats(CH), (wave & 1) * 32, hf, odd, slope, 8 * p0 + j + 1 < (long long)l4 && j + 1 < 8 * T + 1);
+        if (wave < M4 / 32) {
+            up_fp32<D3, D4, row_floats(D3)>(even, odd, w.w4 + (4 * hf * D4 + co0 + cl) * 3, fb + m0 * row_floats(D3) + 4 * hf);
+            store_fp32(fa + j * row_floats(CH), 0, hf, even, slope, 8 * p0 + j < (long long)l4 && j < 8 * T + 1);
+            store_fp32(fa + (j + 1) * row_floats(CH), 0, hf, odd, slope, 8 * p0 + j + 1 < (long long)l4 && j + 1 < 8 * T + 1);
+        }
         __syncthreads();
-        up_fp32<CH, D5, row_floats(CH)>(e, o, w.w5 + ((run * CH + 4 * hf) * D5 + col) * 3, fa + (wave * 32 + col) * row_floats(CH) + 4 * hf);
+        if (wave < M5 / 32) up_fp32<CH, D5, row_floats(CH)>(e, od, w.w5 + ((run * CH + 4 * hf) * D5 + cl) * 3, fa + (wave * 32 + cl) * row_floats(CH) + 4 * hf);
     }
-    se = 0.; so = 0.;
+    double se = 0., so = 0.;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
         const float wv = w.w6[(r >> 2) * 8 + hf * 4 + (r & 3)];
         se = fma((double)wv, (double)leaky_f(e[r], slope), se);
-        so = fma((double)wv, (double)leaky_f(o[r], slope), so);
+        so = fma((double)wv, (double)leaky_f(od[r], slope), so);
     }
     se += __shfl_xor(se, 32, 64);
     so += __shfl_xor(so, 32, 64);
-    const int m1 = wave * 32 + col, i1 = 2 * m1 + hf;
+    const int m1 = wave * 32 + cl, i1 = 2 * m1 + hf;
     if (m1 < 8 * T && 16 * p0 + i1 < (long long)l5) out[16 * p0 + i1] = (float)(w.b6[0] + (hf ? so : se));
 }
 
@@ -895,7 +1004,7 @@ bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int cou
 }
 
 bool launch_decoder_fused(const float *z, float *out, const LayerDev *l, int count, uint64_t l_z, const uint64_t *len, int batch,
-                          float slope, const FusedLimits &limits, hipStream_t st) {
+                          float slope, const FusedLimits &limits, int cus, hipStream_t st) {
     if (!decoder_fused_covers(l, count) || !l[2].ws || !l[3].ws || !l[4].ws) return false;
     if (len[4] == 0) return true;
     DecoderDev w;
@@ -906,9 +1015,16 @@ bool launch_decoder_fused(const float *z, float *out, const LayerDev *l, int cou
     w.w5 = l[4].w; w.b5 = l[4].b; w.s5 = l[4].ws;
     w.w6 = l[5].w; w.b6 = l[5].b;
     w.limits = limits;
-    constexpr int T = 15;
-    hipLaunchKernelGGL((k_decoder_fused<4, 4, 32, 64, 128, 32, T>), dim3(((uint32_t)l_z + T - 1) / T, batch), dim3(256), 0, st, z, out, w,
-                       (uint32_t)l_z, (uint32_t)len[1], (uint32_t)len[2], (uint32_t)len[3], (uint32_t)len[4], slope);
+#define LGC_DEC(T, RING) hipLaunchKernelGGL((k_decoder_fused<4, 4, 32, 64, 128, 32, T, RING>), dim3(((uint32_t)l_z + T - 1) / T, batch), dim3(256), 0, st, z, out, w, \
+                                            (uint32_t)l_z, (uint32_t)len[1], (uint32_t)len[2], (uint32_t)len[3], (uint32_t)len[4], slope)
+    // 7 positions per block while that gives every compute unit at most one: the shorter chain counts (1 x 1 023 values: 8.8 us against 12.4 with 15, 4 x 5 000: 9.4
+    // against 12.6); from two such blocks per compute unit on 15 are better (2 x 15 000: 14.3 against 12.4).  Where those come to two per compute unit as
+    // well, their wavefronts fetch the weights once for two, through the LDS (4 x 25 600: 21.9 against 20.4 us, 8 x 67 000: 85.1 against 82.6); a block that has its
+    // compute unit to itself loses more by the barriers than it gains (4 x 15 000: 12.5 against 13.4).
+    if ((uint64_t)((l_z + 6) / 7) * batch <= (uint64_t)cus) LGC_DEC(7, false);
+    else if ((uint64_t)((l_z + 14) / 15) * batch <= (uint64_t)cus) LGC_DEC(15, false);
+    else LGC_DEC(15, true);
+#undef LGC_DEC
     return true;
 }
 

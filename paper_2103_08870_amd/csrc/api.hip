@@ -810,7 +810,7 @@ extern "C" lgc_status lgc_ae_create(lgc_ae **out, int device, int n_enc, const l
                     LayerDev &l = ls[first + i];
                     launch_most(l.w, l.c_in * l.c_out * l.ksize, w + 1 + i, nullptr);
                     if (i == 3) break;
-                    launch_weights_split(l.w, ae->weights_s + s_off, l.c_in, l.c_out, transposed, w, nullptr);
+                    launch_weights_split(l.w, ae->weights_s + s_off, l.c_in, l.c_out, transposed, transposed && i == 2, w, nullptr);
                     l.ws = ae->weights_s + s_off;
                     s_off += size(l);
                 }
@@ -1064,7 +1064,7 @@ static lgc_status run_decode(lgc_ctx *ctx, const lgc_ae *ae, const float *latent
         return fail(ctx, LGC_EINVAL, "lgc_decode: activation scratch for k = %llu, batch = %d not reserved: call "
                                      "lgc_reserve(ctx, ae, k, batch, NULL) once beforehand", (unsigned long long)k, batch);
     if (!innov && !overlap(latent, (uint64_t)batch * ae->dec[0].c_in * in_len, rec, k * batch) &&
-        launch_decoder_fused(latent, rec, ae->dec_dev.data(), (int)nl, in_len, out_len.data(), batch, ae->slope, ae->dec_limits, st)) {
+        launch_decoder_fused(latent, rec, ae->dec_dev.data(), (int)nl, in_len, out_len.data(), batch, ae->slope, ae->dec_limits, ctx->cus, st)) {
         hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e1));
         return LGC_OK;

@@ -252,7 +252,7 @@ bool launch_convt3s2_mfma_head(const float *z, float *out, const LayerDev &h1, c
 bool encoder_fused_covers(const LayerDev *l, int count);
 bool decoder_fused_covers(const LayerDev *l, int count);
 // *bad (device): incremented if a weight is not finite; *most (device): raised to the largest magnitude's bits
-void launch_weights_split(const float *w, uint16_t *out, int c_in, int c_out, bool transposed, uint32_t *bad, hipStream_t st);
+void launch_weights_split(const float *w, uint16_t *out, int c_in, int c_out, bool transposed, bool as_results, uint32_t *bad, hipStream_t st);
 void launch_most(const float *w, int count, uint32_t *most, hipStream_t st);
 struct FusedLimits {
     float least = 0.f;   // outputs of smaller magnitude may feel what the split's products lose: their blocks are redone in fp32
@@ -264,7 +264,7 @@ bool fused_limits(const LayerDev *l, int split, const float *most, bool transpos
 bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int count, const uint64_t *len, int batch, float slope,
                           const FusedLimits &limits, int cus, hipStream_t st);
 bool launch_decoder_fused(const float *z, float *out, const LayerDev *l, int count, uint64_t l_z, const uint64_t *len, int batch,
-                          float slope, const FusedLimits &limits, hipStream_t st);
+                          float slope, const FusedLimits &limits, int cus, hipStream_t st);
 void launch_gather_at(float *v, float *u, uint64_t stride, uint32_t n, int batch, const uint32_t *idx, uint32_t k,
                       float *out, Stats *stats, hipStream_t st);
 void launch_average(const float *x, uint32_t len, int batch, float scale, float *out, hipStream_t st);

@@ -69,6 +69,16 @@ def test_lengths_at_the_edges_of_a_block(B, oracle, k, batch):
     ae.close()
 
 
+# The decoder's blocks take 7 latent positions (112 values), 15 (240), or 15 with the weights through the LDS: a last block of all, of one and of two.
+@pytest.mark.parametrize("k,batch", [(112, 1), (113, 1), (224, 2), (112 * 3 + 17, 3), (3840, 8), (3841, 8), (3857, 8), (7920, 8), (7921, 8), (7937, 8)])
+def test_lengths_at_the_edges_of_a_decoder_block(B, oracle, k, batch):
+    ae, enc, dec, host = stacks(B)
+    x = np.random.default_rng(k).laplace(0, 0.3, (batch, k)).astype(np.float32)
+    _, _, rec, orec = both_ways(B, oracle, ae, enc, dec, host, x)
+    assert_near(rec, orec, ("reconstruction", k))
+    ae.close()
+
+
 # The one-launch stacks may not be further from the 64-bit result than one fp32 launch per layer was.  The bounds are what those
 # kernels measured for the same weights and values (error of the latent, of the reconstruction, in 1e-8, seeds 0 to 3).
 FP32 = {1_023: ((14.31, 3.74), (9.44, 2.28), (11.37, 7.27), (10.05, 3.30)),
@@ -112,10 +122,10 @@ def test_error_against_64_bits(B, k, batch):
 
 # Positive weights: an Inf stays one Inf all the way (weights of both signs would turn it into NaN at once), so the
 # values that bf16 parts cannot carry have one right answer.  The largest finite values round to Inf in bf16.  Blocks of
-# 15 latent positions (600 values), and of 31 where there are enough of them (7 nodes x 10 000); the values sit inside a
+# 15 latent positions (600 values; the decoder's of 7, and of 15 for 5 nodes x 6 000), and of 31 where there are enough of them (7 nodes x 10 000); the values sit inside a
 # block, where two blocks' windows overlap, and in the last, partly filled block.  At 1e-33 the split's low parts, and their products,
 # are below the least normal number (the reconstruction, about 3e-38, is just above it); no biases, which would hide it.
-@pytest.mark.parametrize("k,batch", [(600, 2), (10_000, 7)])
+@pytest.mark.parametrize("k,batch", [(600, 2), (6_000, 5), (10_000, 7)])
 @pytest.mark.parametrize("special", [np.inf, np.nan, 3.4e38, 1e-30, 1e-33, 0.0])
 def test_values_that_the_split_cannot_carry(B, oracle, special, k, batch):
     def change(a, which):
