@@ -16,7 +16,7 @@
 // of the latent's error.
 // Measured against one fp32-MFMA launch per deep layer (ae_mfma.hip, which other stacks still use): 4 nodes x 25 600
 // values, encoder 79.4 -> 26.8 us (165 TFLOP/s of fp32 products), decoder 58.0 -> 20.6 us (130); 8 x 67 000, both
-// together 468 -> 215 us (173); 1 x 1 023 (latency) 79 -> 24.8 us.  Relative error against 64 bits, six sizes from 1 x 500 to
+// together 468 -> 211 us (176); 1 x 1 023 (latency) 79 -> 24.8 us.  Relative error against 64 bits, six sizes from 1 x 500 to
 // 8 x 67 000 x six seeds, mean (least to largest): latent 1.15e-7 (0.87 to 1.46) -> 0.41e-7 (0.34 to 0.51; 0.99e-7 with the
 // last sums in 32 bits), decoder 3.86e-8 (2.96 to 5.54) -> 2.95e-8 (2.20 to 3.86): lower at every size with every
 // seed.  What bounds it: while a compute unit has blocks its matrix cores are busy 54-57 % of the cycles (encoder) and
@@ -59,13 +59,29 @@ namespace {
 
 __device__ __forceinline__ float leaky_f(float x, float slope) { return x > 0.f ? x : slope * x; }
 
-// Two values split into three bf16 pairs.  A value that is not finite leaves a NaN in m, one that rounds to Inf an Inf in m and a NaN in l.
+// The non-linearity at a position: the factors of positive and other values, both 0 where the position does not exist (an Inf
+// there leaves a NaN, as the redo's trigger).
+struct Act {
+    float pos, neg;
+    __device__ __forceinline__ Act(const float slope, const bool valid) : pos(valid ? 1.f : 0.f), neg(valid ? slope : 0.f) {}
+    __device__ __forceinline__ float operator()(const float x) const { return x * (x > 0.f ? pos : neg); }
+};
+
+// Two values split into three bf16 pairs.  What a part leaves is taken by one instruction a value, a - h.lo * 1 + h.hi * 0 and the like, exact as there
+// is nothing to round (by shift or mask and subtraction two; with the choice of factors above, 8 x 67 000 values, encoder 132.9 -> 130.7 us, decoder 82.8 ->
+// 80.4).  A value that is not finite, or rounds to Inf, leaves NaNs among the parts of both.
+// The factors come in scalar registers: as constants within the instruction they would go to the wrong halves.
 __device__ __forceinline__ void split2(const float a, const float b, uint32_t &h, uint32_t &m, uint32_t &l) {
-    h = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){a, b}, bf2));
-    const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xffff0000u);
-    m = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){ra, rb}, bf2));
-    const float ma = __uint_as_float(m << 16), mb = __uint_as_float(m & 0xffff0000u);
-    l = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){ra - ma, rb - mb}, bf2));
+    uint32_t minus_lo = 0x0000bf80u, minus_hi = 0xbf800000u;
+    asm("" : "+s"(minus_lo), "+s"(minus_hi));
+    const bf2 lo = __builtin_bit_cast(bf2, minus_lo), hi = __builtin_bit_cast(bf2, minus_hi);
+    const bf2 x = __builtin_convertvector((f2v){a, b}, bf2);
+    const float ra = __builtin_amdgcn_fdot2_f32_bf16(x, lo, a, false), rb = __builtin_amdgcn_fdot2_f32_bf16(x, hi, b, false);
+    const bf2 y = __builtin_convertvector((f2v){ra, rb}, bf2);
+    const float sa = __builtin_amdgcn_fdot2_f32_bf16(y, lo, ra, false), sb = __builtin_amdgcn_fdot2_f32_bf16(y, hi, rb, false);
+    h = __builtin_bit_cast(uint32_t, x);
+    m = __builtin_bit_cast(uint32_t, y);
+    l = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){sa, sb}, bf2));
 }
 
 // acc[i][j] + cross[i][j] += A[i] B[j] for one step of 16 input channels, both operands in three parts.  The five
@@ -144,20 +160,15 @@ constexpr int row_bytes(int c) { return 6 * c + 16; }
 template <int C>
 __device__ __forceinline__ void store_tile(unsigned char *row, const int co0, const int half, const acc16 &acc,
                                            const float slope, const bool valid) {
+    const Act act(slope, valid);
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
         const int co = co0 + 8 * g + 4 * half;
-        float y[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) {
-            y[c] = leaky_f(acc[4 * g + c], slope);
-            y[c] = valid ? y[c] : 0.f;
-        }
         u2v h, m, l;
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             uint32_t x, z, w;
-            split2(y[2 * c], y[2 * c + 1], x, z, w);
+            split2(act(acc[4 * g + 2 * c]), act(acc[4 * g + 2 * c + 1]), x, z, w);
             h[c] = x; m[c] = z; l[c] = w;
         }
         *(u2v *)(row + 2 * co) = h;
@@ -168,13 +179,11 @@ __device__ __forceinline__ void store_tile(unsigned char *row, const int co0, co
 
 // One result tile with the non-linearity as operands of the next layer, 16 channels a step: r[step][part] (weights `as_results`)
 __device__ __forceinline__ void as_operands(const acc16 &acc, const float slope, const bool valid, u4v (&r)[2][3]) {
+    const Act act(slope, valid);
 #pragma unroll
     for (int i = 0; i < 16; i += 2) {
-        float y[2];
-#pragma unroll
-        for (int c = 0; c < 2; ++c) { y[c] = leaky_f(acc[i + c], slope); y[c] = valid ? y[c] : 0.f; }
         uint32_t h, m, l;
-        split2(y[0], y[1], h, m, l);
+        split2(act(acc[i]), act(acc[i + 1]), h, m, l);
         r[i >> 3][0][(i & 7) >> 1] = h; r[i >> 3][1][(i & 7) >> 1] = m; r[i >> 3][2][(i & 7) >> 1] = l;
     }
 }
@@ -427,7 +436,7 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
         for (int unit = wave; unit < (C1 / 8) * (2 * N2 / 64); unit += W) {
             const int o8 = unit % (C1 / 8), i = (unit / (C1 / 8)) * 64 + lane;
             const long long q = 8 * p0 - 7 + i;
-            const uint32_t valid = q >= 0 && q < (long long)l1 ? ~0u : 0u;   // (a mask: a choice becomes a branch around the loads of every channel)
+            const Act act(slope, q >= 0 && q < (long long)l1);
             const float x0 = xs[2 * i], x1 = xs[2 * i + 1], x2 = xs[2 * i + 2];
             float y[8];
 #pragma unroll
@@ -437,7 +446,7 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
                 a = fmaf(wc[0], x0, a);
                 a = fmaf(wc[1], x1, a);
                 a = fmaf(wc[2], x2, a);
-                y[c] = __uint_as_float(__float_as_uint(leaky_f(a, slope)) & valid);
+                y[c] = act(a);
             }
             put(i, o8, y);
         }
@@ -652,7 +661,7 @@ __device__ __forceinline__ void store_fp32(float *row, const int co0, const int 
 // work, and one wavefront converts while another one multiplies.  deconv5's output 4i + 3 needs deconv4's 2i + 2, which is the next
 // lane's: 31 of the 32 positions come out.  4 / NP wavefronts share a position tile's channels of deconv4 and add their sums up at the end.
 // The bound of two wavefronts per SIMD leaves room for the weights' fragments that are under way (one step ahead).
-// Through the LDS, in two runs of 64 channels with four barriers each, 4 x 25 600 values took 22.2 us (20.6 now), 8 x 67 000 87.8 (82.8), 1 x 1 023
+// Through the LDS, in two runs of 64 channels with four barriers each, 4 x 25 600 values took 22.2 us (20.6 now), 8 x 67 000 87.8 (80.4), 1 x 1 023
 // 12.5 (8.8, with 7 positions per block).  What bounds it: two blocks on a compute unit have 18.4 K cycles of products in 39 K; the rest is each block's way
 // to the first product (9 K: a read from memory, three small layers, three barriers) and its end (5 K).
 template <int D0, int D1, int D2, int D3, int D4, int D5, int T, bool RING>
