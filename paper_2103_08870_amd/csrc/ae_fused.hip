@@ -16,7 +16,7 @@
 // of the latent's error.
 // Measured against one fp32-MFMA launch per deep layer (ae_mfma.hip, which other stacks still use): 4 nodes x 25 600
 // values, encoder 79.4 -> 26.8 us (165 TFLOP/s of fp32 products), decoder 58.0 -> 20.6 us (130); 8 x 67 000, both
-// together 468 -> 211 us (176); 1 x 1 023 (latency) 79 -> 24.8 us.  Relative error against 64 bits, six sizes from 1 x 500 to
+// together 468 -> 206 us (180); 1 x 1 023 (latency) 79 -> 20.8 us.  Relative error against 64 bits, six sizes from 1 x 500 to
 // 8 x 67 000 x six seeds, mean (least to largest): latent 1.15e-7 (0.87 to 1.46) -> 0.41e-7 (0.34 to 0.51; 0.99e-7 with the
 // last sums in 32 bits), decoder 3.86e-8 (2.96 to 5.54) -> 2.95e-8 (2.20 to 3.86): lower at every size with every
 // seed.  What bounds it: while a compute unit has blocks its matrix cores are busy 54-57 % of the cycles (encoder) and
@@ -155,26 +155,31 @@ __device__ __forceinline__ acc16 zero16() {
 // Bytes of one position with C channels in the LDS: three parts, 16 bytes of padding.
 constexpr int row_bytes(int c) { return 6 * c + 16; }
 
+// Four consecutive channels of one position, co on, split and stored.  AS_RESULTS: to where weights laid out `as_results` meet them.
+template <int C, bool AS_RESULTS>
+__device__ __forceinline__ void store_split(unsigned char *row, const int co, const float (&y)[4]) {
+    const int at = AS_RESULTS ? (co & ~15) + 2 * (co & 4) + ((co & 8) >> 1) : co;
+    u2v h, m, l;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+        uint32_t x, z, w;
+        split2(y[2 * c], y[2 * c + 1], x, z, w);
+        h[c] = x; m[c] = z; l[c] = w;
+    }
+    *(u2v *)(row + 2 * at) = h;
+    *(u2v *)(row + 2 * C + 2 * at) = m;
+    *(u2v *)(row + 4 * C + 2 * at) = l;
+}
+
 // One 32 x 32 result tile with the non-linearity into the LDS: `row` is the lane's position, channels
 // co0 + 8 (r / 4) + 4 half + r % 4.  Positions that do not exist (valid false) hold zeros.
-template <int C>
+template <int C, bool AS_RESULTS = false>
 __device__ __forceinline__ void store_tile(unsigned char *row, const int co0, const int half, const acc16 &acc,
                                            const float slope, const bool valid) {
     const Act act(slope, valid);
 #pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const int co = co0 + 8 * g + 4 * half;
-        u2v h, m, l;
-#pragma unroll
-        for (int c = 0; c < 2; ++c) {
-            uint32_t x, z, w;
-            split2(act(acc[4 * g + 2 * c]), act(acc[4 * g + 2 * c + 1]), x, z, w);
-            h[c] = x; m[c] = z; l[c] = w;
-        }
-        *(u2v *)(row + 2 * co) = h;
-        *(u2v *)(row + 2 * C + 2 * co) = m;
-        *(u2v *)(row + 4 * C + 2 * co) = l;
-    }
+    for (int g = 0; g < 4; ++g)
+        store_split<C, AS_RESULTS>(row, co0 + 8 * g + 4 * half, {act(acc[4 * g]), act(acc[4 * g + 1]), act(acc[4 * g + 2]), act(acc[4 * g + 3])});
 }
 
 // One result tile with the non-linearity as operands of the next layer, 16 channels a step: r[step][part] (weights `as_results`)
@@ -280,56 +285,72 @@ struct EncoderDev {
 
 namespace {
 
-// The K loop of one convolution for MT x NT tiles: STEPS steps of 16 input channels from step s0 on, tap-major.  `b`:
-// the LDS rows of this lane's positions for tap 0; the odd positions lie `odd` bytes behind the even ones, so
-// that a stride-2 window (2i, 2i + 1, 2i + 2) is a read of row i of either half, and of row i + 1.  `a`: fragments
-// of the first tile's first step, this lane's 16 bytes; the tiles are a_tile (in 16-byte units) apart.  The
-// fragments come from the L2: AHEAD steps of them are kept in flight, the first ones from before the barrier that
-// the loop waits at, and the LDS reads run one step ahead.  The scheduling barriers keep it that way (left to
+// Fragments of one step of 16 input channels: the three parts of one tap
+__device__ __forceinline__ void load_a(u4v (&r)[3], const u4v *__restrict__ a, const int step) {
+#pragma unroll
+    for (int p = 0; p < 3; ++p) r[p] = a[(step * 3 + p) * 64];
+}
+
+// The order of one step's instructions: a read from the LDS, then a load, behind each product in turn, which they then cost no time beside (ahead of the
+// products they are issued while the matrix cores wait; a block of 31 positions 57.4 -> 54.5 K cycles, 8 x 67 000 values 129.4 -> 127.9 us, as the clock falls with
+// the denser products).
+template <int MMAS, int READS, int LOADS>
+__device__ __forceinline__ void interleave() {
+#pragma unroll
+    for (int i = 0; i < MMAS; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        if (i < READS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        else if (i < READS + LOADS) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
+}
+
+// The K loop of one convolution for MT x NT tiles: STEPS steps of 16 input channels.  where(j, s): the LDS address of this lane's position of tile j
+// for step s.  frag(i, s): this lane's fragments of tile i.  They come from the L2: AHEAD steps of them are kept in flight, the first ones from before
+// the barrier that the loop waits at, and the LDS reads run one step ahead.  interleave() keeps it that way (left to
 // itself the compiler moves the loads down to their uses: conv4 then waits out the L2's latency in every step).
 template <int MT, int AHEAD>
 struct Fragments { u4v r[AHEAD + 1][MT][3]; };
 
-template <int MT, int AHEAD>
-__device__ __forceinline__ void fragments_start(Fragments<MT, AHEAD> &f, const u4v *__restrict__ a, const int a_tile) {
+template <int MT, int AHEAD, typename Frag>
+__device__ __forceinline__ void fragments_start(Fragments<MT, AHEAD> &f, Frag frag) {
 #pragma unroll
     for (int d = 0; d < AHEAD; ++d)
 #pragma unroll
         for (int i = 0; i < MT; ++i)
 #pragma unroll
-            for (int p = 0; p < 3; ++p) f.r[d][i][p] = a[i * a_tile + (d * 3 + p) * 64];
+            for (int p = 0; p < 3; ++p) f.r[d][i][p] = frag(i, d)[p * 64];
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int C, int MT, int NT, int S0, int STEPS, int AHEAD>
-__device__ __forceinline__ void conv_mma(acc16 (&acc)[MT][NT], Fragments<MT, AHEAD> &f, const u4v *__restrict__ a, const int a_tile,
-                                         const unsigned char *const (&b)[NT], const int odd) {
-    constexpr int kPer = C / 16;   // steps per tap
+template <int C, int MT, int NT, int STEPS, int AHEAD, typename Frag, typename Where>
+__device__ __forceinline__ void conv_mma(acc16 (&acc)[MT][NT], Fragments<MT, AHEAD> &f, Frag frag, Where where) {
     u4v rb[2][NT][3];
     auto read_b = [&](u4v (&r)[NT][3], const int s) {
-        const int tap = s / kPer, at = (tap == 1 ? odd : (tap >> 1) * row_bytes(C)) + 32 * (s % kPer);
 #pragma unroll
-        for (int j = 0; j < NT; ++j)
+        for (int j = 0; j < NT; ++j) {
+            const unsigned char *b = where(j, s);
 #pragma unroll
-            for (int p = 0; p < 3; ++p) r[j][p] = *(const u4v *)(b[j] + p * 2 * C + at);
+            for (int p = 0; p < 3; ++p) r[j][p] = *(const u4v *)(b + p * 2 * C);
+        }
     };
     acc16 cross[MT][NT];
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) cross[i][j] = zero16();
-    read_b(rb[0], S0);
+    read_b(rb[0], 0);
 #pragma unroll
     for (int s = 0; s < STEPS; ++s) {
         if (s + AHEAD < STEPS) {
 #pragma unroll
             for (int i = 0; i < MT; ++i)
 #pragma unroll
-                for (int p = 0; p < 3; ++p) f.r[(s + AHEAD) % (AHEAD + 1)][i][p] = a[i * a_tile + ((s + AHEAD) * 3 + p) * 64];
+                for (int p = 0; p < 3; ++p) f.r[(s + AHEAD) % (AHEAD + 1)][i][p] = frag(i, s + AHEAD)[p * 64];
         }
-        if (s + 1 < STEPS) read_b(rb[(s + 1) & 1], S0 + s + 1);
-        __builtin_amdgcn_sched_barrier(0);
+        if (s + 1 < STEPS) read_b(rb[(s + 1) & 1], s + 1);
+        if (NT == 1) __builtin_amdgcn_sched_barrier(0);   // (too few products to put them behind: 4 x 15 000 values 20.7 us so, 19.8 ahead of them)
         mma6<MT, NT>(acc, cross, f.r[s % (AHEAD + 1)], rb[s & 1]);
+        if (NT > 1) interleave<6 * MT * NT, 3 * NT, 3 * MT>();
         __builtin_amdgcn_sched_barrier(0);
     }
 #pragma unroll
@@ -401,57 +422,74 @@ __device__ __forceinline__ void layer_fp32(float *buf, const float *__restrict__
 
 }  // namespace
 
+namespace {
+
 // P latent positions per block of W wavefronts.  Local numbering: conv3's position i is 2 p0 - 1 + i, conv2's 4 p0 - 3 + i,
 // conv1's 8 p0 - 7 + i, the input's 16 p0 - 15 + i, so that position i of one layer takes 2i, 2i + 1, 2i + 2 of
 // the layer before; 2P + 1, 4P + 3, 8P + 7 and 16P + 15 of them are needed, and the tiles hold one more.
-template <int C1, int C2, int C3, int C4, int C5, int P, int W>
-__global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restrict__ x, float *__restrict__ out, EncoderDev w,
-                                                          uint32_t l0, uint32_t l1, uint32_t l2, uint32_t l3, uint32_t l4,
-                                                          float slope) {
-    constexpr int N4 = P + 1, N3 = 2 * N4, N2 = 4 * N4;   // tile widths (positions) of conv4, conv3, conv2
-    constexpr int R1 = row_bytes(C1), R2 = row_bytes(C2), R3 = row_bytes(C3);
-    constexpr int kBytes1 = (2 * N2 + 1) * R1, kBytes2 = (2 * N3 + 1) * R2, kBytes3 = (2 * N4 + 1) * R3;
-    constexpr int kBytes = kBytes1 > kBytes2 ? (kBytes1 > kBytes3 ? kBytes1 : kBytes3) : (kBytes2 > kBytes3 ? kBytes2 : kBytes3);
-    constexpr int kSplit = W / (C4 / 32);                 // conv4: wavefronts that share a tile, each a run of its steps
-    static_assert(C1 % 16 == 0 && C2 % 32 == 0 && C3 % 32 == 0 && C4 % 32 == 0 && N3 % 32 == 0 && N4 <= 32 && C5 <= 4, "tiles");
-    static_assert(row_floats(C1) * 4 <= R1 && row_floats(C2) * 4 <= R2 && row_floats(C3) * 4 <= R3 && 2 * (N4 / 2 + 1) * row_floats(C4) * 4 <= kBytes,
-                  "rows of fp32 take no more room");
-    __shared__ __align__(16) unsigned char buf[kBytes];
-    __shared__ float xs[4 * N2 + 4];
+//
+// S blocks share a run of 15 positions: each makes conv1 and conv2 for itself, 1 / S of conv3's channels (whose steps several wavefronts share) and what
+// those give of conv4's sums; the last one to come adds them up, in order whichever it is, and goes on.  Short vectors would leave most compute units idle,
+// and draw 1 MB of weights through each one that works: 1 x 1 023 values (5 runs) 15.7 us with a block each, 11.9 with four; 2 x 5 000 (42 runs) 16.1 / 13.5, 4 x 5 000 (84
+// runs, two blocks) 16.7 / 15.4.
+template <int P, int S, int C1, int C2, int C3, int C4, int C5, int W>
+struct EncoderRun {
+    static constexpr int N4 = P + 1, N3 = 2 * N4, N2 = 4 * N4;   // tile widths (positions) of conv4, conv3, conv2
+    static constexpr int CS = C3 / S, R1 = row_bytes(C1), R2 = row_bytes(C2), R3 = row_bytes(CS);
+    static constexpr int kSplit = W / (C4 / 32);                 // conv4: wavefronts that share a tile, each a run of its steps
+    static constexpr int kPart3 = S > 1 ? W * 32 * 33 * 4 : 0;   // conv3's partial sums, ahead of its rows
+    static constexpr int max(int a, int b) { return a > b ? a : b; }
+    static constexpr int kRedo = max(max((2 * N2 + 1) * row_floats(C1), (2 * N3 + 1) * row_floats(C2)), max((2 * N4 + 1) * row_floats(C3), 2 * (N4 / 2 + 1) * row_floats(C4))) * 4;
+    static constexpr int kBytes = max(max(max((2 * N2 + 1) * R1, (2 * N3 + 1) * R2), kPart3 + (2 * N4 + 1) * R3), max(kRedo, kSplit * C4 * 33 * 4 + W * 2 * C5 * 32 * 8));
+    static constexpr int kXs = 4 * N2 + 4, kSmall = 4 * C1 + C5 * C4 + C4 + C5;
+    static_assert(C1 == 8 * W && C2 % 32 == 0 && CS % 32 == 0 && C4 == 64 && C3 == 32 * W && N3 % 32 == 0 && N4 <= 32 && C5 <= 4, "tiles");
+    static_assert(S == 1 || P == 15 && (S == 2 || S == 4), "shares");
+};
+
+// sums: [S][C4][16] per run of positions, taken: the counts of the blocks that have come (zero between calls)
+template <int P, int S, int C1, int C2, int C3, int C4, int C5, int W>
+__device__ __forceinline__ void encode_run(const float *__restrict__ x, float *__restrict__ out, const EncoderDev &w, const uint32_t l0, const uint32_t l1,
+                                           const uint32_t l2, const uint32_t l3, const uint32_t l4, const float slope, const long long p0, const int share,
+                                           float *sums, uint32_t *taken, unsigned char *buf, float *xs, float *small) {
+    using K = EncoderRun<P, S, C1, C2, C3, C4, C5, W>;
+    constexpr int N4 = K::N4, N3 = K::N3, N2 = K::N2, CS = K::CS, R1 = K::R1, R2 = K::R2, R3 = K::R3, kSplit = K::kSplit;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
-    const long long p0 = (long long)blockIdx.x * P;
-    x += (size_t)blockIdx.y * l0;
-    out += (size_t)blockIdx.y * C5 * l4;
+    // the small layers' weights and biases
+    constexpr int kB1 = 3 * C1, kW5 = kB1 + C1, kB4 = kW5 + C5 * C4, kB5 = kB4 + C4;
+    static_assert(kB4 == W * 64 && K::kSmall == kB5 + C5 && C4 + C5 <= W * 64, "a word per thread, and one more for some");
 
-    for (int i = tid; i < 4 * N2 + 3; i += W * 64) {
-        const long long e = 16 * p0 - 15 + i;
-        xs[i] = e >= 0 && e < (long long)l0 ? x[e] : 0.f;
-    }
-    __syncthreads();
-
-    // conv1: a wavefront takes 64 positions x 8 channels at a time (weights wave-uniform); put(position, group of 8 channels, values)
+    // conv1: a wavefront takes 8 channels at 64 positions at a time; put(position, values)
     auto conv1 = [&](auto put) {
+        f4v wt[6], bias[2];
+#pragma unroll
+        for (int i = 0; i < 6; ++i) wt[i] = *(const f4v *)(small + wave * 24 + 4 * i);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) bias[i] = *(const f4v *)(small + kB1 + wave * 8 + 4 * i);
 #pragma unroll 1
-        for (int unit = wave; unit < (C1 / 8) * (2 * N2 / 64); unit += W) {
-            const int o8 = unit % (C1 / 8), i = (unit / (C1 / 8)) * 64 + lane;
+        for (int i = lane; i < 2 * N2; i += 64) {
             const long long q = 8 * p0 - 7 + i;
             const Act act(slope, q >= 0 && q < (long long)l1);
             const float x0 = xs[2 * i], x1 = xs[2 * i + 1], x2 = xs[2 * i + 2];
             float y[8];
 #pragma unroll
             for (int c = 0; c < 8; ++c) {
-                const float *wc = w.w1 + (o8 * 8 + c) * 3;
-                float a = w.b1[o8 * 8 + c];
-                a = fmaf(wc[0], x0, a);
-                a = fmaf(wc[1], x1, a);
-                a = fmaf(wc[2], x2, a);
-                y[c] = act(a);
+                auto tap = [&](const int t) { return wt[(3 * c + t) / 4][(3 * c + t) % 4]; };
+                y[c] = act(fmaf(tap(2), x2, fmaf(tap(1), x1, fmaf(tap(0), x0, bias[c / 4][c % 4]))));
             }
-            put(i, o8, y);
+            put(i, y);
         }
     };
-    conv1([&](const int i, const int o8, const float (&y)[8]) {
+    const float s0 = *(tid < kB1 ? w.w1 + tid : tid < kW5 ? w.b1 + tid - kB1 : w.w5 + tid - kW5);
+    const float s1 = *(tid < C4 ? w.b4 + tid : w.b5 + (tid < C4 + C5 ? tid - C4 : 0));
+    for (int i = tid; i < 4 * N2 + 3; i += W * 64) {
+        const long long e = 16 * p0 - 15 + i;
+        xs[i] = e >= 0 && e < (long long)l0 ? x[e] : 0.f;
+    }
+    small[tid] = s0;
+    if (tid < C4 + C5) small[kB4 + tid] = s1;
+    __syncthreads();
+    conv1([&](const int i, const float (&y)[8]) {
         u4v h, m, l;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
@@ -459,108 +497,170 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
             split2(y[2 * c], y[2 * c + 1], a, b, d);
             h[c] = a; m[c] = b; l[c] = d;
         }
-        unsigned char *row = buf + ((i & 1) ? (N2 + 1) * R1 : 0) + (i >> 1) * R1 + o8 * 16;
+        unsigned char *row = buf + ((i & 1) ? (N2 + 1) * R1 : 0) + (i >> 1) * R1 + wave * 16;
         *(u4v *)row = h;
         *(u4v *)(row + 2 * C1) = m;
         *(u4v *)(row + 4 * C1) = l;
     });
 
     {   // conv2: C2 / 32 channel tiles x N2 / 32 position tiles
-        constexpr int kM = C2 / 32, kNW = W / kM, NT = N2 / 32 / kNW, kSteps = 3 * C1 / 16, kAhead = 2;
+        constexpr int kM = C2 / 32, kNW = W / kM, NT = N2 / 32 / kNW, kPer = C1 / 16, kSteps = 3 * kPer, kAhead = 2;
         static_assert(W % kM == 0 && (N2 / 32) % kNW == 0, "conv2 tiles");
         const int mt = wave / kNW, n0 = (wave % kNW) * NT;
         const u4v *a = (const u4v *)w.s2 + (size_t)mt * kSteps * 192 + lane;
+        auto frag = [&](int, const int s) { return a + s * 192; };
         Fragments<1, kAhead> f;
-        fragments_start(f, a, 0);
+        fragments_start(f, frag);
         acc16 acc[1][NT];
+#pragma unroll
+        for (int j = 0; j < NT; ++j) acc[0][j] = bias16(w.b2, mt * 32, half);
         const unsigned char *b[NT];
 #pragma unroll
-        for (int j = 0; j < NT; ++j) { acc[0][j] = bias16(w.b2, mt * 32, half); b[j] = buf + ((n0 + j) * 32 + col) * R1 + half * 16; }
+        for (int j = 0; j < NT; ++j) b[j] = buf + ((n0 + j) * 32 + col) * R1 + half * 16;
         __syncthreads();
-        conv_mma<C1, 1, NT, 0, kSteps, kAhead>(acc, f, a, 0, b, (N2 + 1) * R1);
+        conv_mma<C1, 1, NT, kSteps, kAhead>(acc, f, frag, [&](const int j, const int s) {
+            const int tap = s / kPer;
+            return b[j] + (tap == 1 ? (N2 + 1) * R1 : (tap >> 1) * R1) + 32 * (s % kPer);
+        });
         __syncthreads();   // conv1's outputs have been read
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
             const int i = (n0 + j) * 32 + col;
             const long long q = 4 * p0 - 3 + i;
-            store_tile<C2>(buf + ((i & 1) ? (N3 + 1) * R2 : 0) + (i >> 1) * R2, mt * 32, half, acc[0][j], slope,
-                           q >= 0 && q < (long long)l2 && i < N2 - 1);
-        }
-    }
-
-    {   // conv3
-        constexpr int kM = C3 / 32, kMW = kM < W ? kM : W, MT = kM / kMW, kNW = W / kMW, NT = N3 / 32 / kNW, kSteps = 3 * C2 / 16, kAhead = 1;
-        static_assert(kM % kMW == 0 && W % kMW == 0 && (N3 / 32) % kNW == 0, "conv3 tiles");
-        const int m0 = (wave / kNW) * MT, n0 = (wave % kNW) * NT;
-        const u4v *a = (const u4v *)w.s3 + (size_t)m0 * kSteps * 192 + lane;
-        Fragments<MT, kAhead> f;
-        fragments_start(f, a, kSteps * 192);
-        acc16 acc[MT][NT];
-        const unsigned char *b[NT];
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            b[j] = buf + ((n0 + j) * 32 + col) * R2 + half * 16;
-#pragma unroll
-            for (int i = 0; i < MT; ++i) acc[i][j] = bias16(w.b3, (m0 + i) * 32, half);
-        }
-        __syncthreads();
-        conv_mma<C2, MT, NT, 0, kSteps, kAhead>(acc, f, a, kSteps * 192, b, (N3 + 1) * R2);
-        __syncthreads();
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            const int i = (n0 + j) * 32 + col;
-            const long long q = 2 * p0 - 1 + i;
-            unsigned char *row = buf + ((i & 1) ? (N4 + 1) * R3 : 0) + (i >> 1) * R3;
-#pragma unroll
-            for (int k = 0; k < MT; ++k)
-                store_tile<C3>(row, (m0 + k) * 32, half, acc[k][j], slope, q >= 0 && q < (long long)l3 && i < N3 - 1);
+            unsigned char *row = buf + ((i & 1) ? (N3 + 1) * R2 : 0) + (i >> 1) * R2;
+            store_tile<C2>(row, mt * 32, half, acc[0][j], slope, q >= 0 && q < (long long)l2 && i < N2 - 1);
         }
     }
 
     float *part = (float *)buf;                               // conv4's partial sums [kSplit][C4][33]
     double *red = (double *)(part + kSplit * C4 * 33);         // conv5's [W * 2][C5][32]
-    static_assert(kSplit * C4 * 33 % 2 == 0 && kBytes >= kSplit * C4 * 33 * 4 + W * 2 * C5 * 32 * 8, "partial sums");
-    {   // conv4: one position tile (of which N4 columns are used); the steps are shared out over kSplit wavefronts
-        constexpr int kSteps = 3 * C3 / 16 / kSplit, kAhead = 4;
-        static_assert((3 * C3 / 16) % kSplit == 0, "conv4 steps");
-        const int mt = wave / kSplit, ks = wave % kSplit;
-        const u4v *a = (const u4v *)w.s4 + (size_t)(mt * kSplit + ks) * kSteps * 192 + lane;
-        Fragments<1, kAhead> f;
-        fragments_start(f, a, 0);
-        acc16 acc[1][1];
-        acc[0][0] = zero16();
-        const int c4 = col < N4 ? col : N4 - 1;
-        const unsigned char *b[1] = {buf + c4 * R3 + half * 16};
-        auto run = [&](auto k) {
-            constexpr int S = decltype(k)::value % kSplit;
-            conv_mma<C3, 1, 1, S * kSteps, kSteps, kAhead>(acc, f, a, 0, b, (N4 + 1) * R3);
-        };
-        __syncthreads();
-        if (ks == 0) run(std::integral_constant<int, 0>());    // wave-uniform
-        else if (ks == 1) run(std::integral_constant<int, 1>());
-        else if (ks == 2) run(std::integral_constant<int, 2>());
-        else run(std::integral_constant<int, 3>());
-        __syncthreads();
+    static_assert(kSplit * C4 * 33 % 2 == 0, "partial sums");
+    constexpr int kPer2 = C2 / 16, kPer3 = C3 / 16;
+    {
+        unsigned char *rows3 = buf + K::kPart3;
+        {   // conv3: a channel tile is shared by S wavefronts, each a run of its steps
+            constexpr int NT = N3 / 32, kSteps = 3 * kPer2 / S, kAhead = 1;
+            static_assert(S == 1 || NT == 1, "one tile to share");
+            const int mt = wave / S, s0 = (wave % S) * kSteps;
+            const u4v *a = (const u4v *)w.s3 + (size_t)((share * (CS / 32) + mt) * 3 * kPer2 + s0) * 192 + lane;
+            auto frag = [&](int, const int s) { return a + s * 192; };
+            Fragments<1, kAhead> f;
+            fragments_start(f, frag);
+            acc16 acc[1][NT];
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
-            part[(ks * C4 + mt * 32 + (r >> 2) * 8 + half * 4 + (r & 3)) * 33 + col] = acc[0][0][r];
+            for (int j = 0; j < NT; ++j) {
+                if (S == 1) acc[0][j] = bias16(w.b3, mt * 32, half);
+                else acc[0][j] = zero16();
+            }
+            const unsigned char *b[NT];
+#pragma unroll
+            for (int j = 0; j < NT; ++j) b[j] = buf + (j * 32 + col) * R2 + half * 16;
+            __syncthreads();
+            conv_mma<C2, 1, NT, kSteps, kAhead>(acc, f, frag, [&](const int j, const int s) {
+                const int tap = (s0 + s) / kPer2;
+                return b[j] + (tap == 1 ? (N3 + 1) * R2 : (tap >> 1) * R2) + 32 * ((s0 + s) % kPer2);
+            });
+            __syncthreads();
+            const long long q = 2 * p0 - 1;
+            auto row = [&](const int i) { return rows3 + ((i & 1) ? (N4 + 1) * R3 : 0) + (i >> 1) * R3; };
+            if constexpr (S == 1) {
+#pragma unroll
+                for (int j = 0; j < NT; ++j) {
+                    const int i = 32 * j + col;
+                    store_tile<CS, true>(row(i), mt * 32, half, acc[0][j], slope, q + i >= 0 && q + i < (long long)l3 && i < N3 - 1);
+                }
+            } else {   // [S][CS][33], then a position and four channels a thread
+                float *part3 = (float *)buf;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) part3[((wave % S) * CS + mt * 32 + (r >> 2) * 8 + half * 4 + (r & 3)) * 33 + col] = acc[0][0][r];
+                __syncthreads();
+                const int i = tid & 31;
+                const Act act(slope, q + i >= 0 && q + i < (long long)l3 && i < N3 - 1);
+#pragma unroll
+                for (int g = tid >> 5; g < CS / 4; g += W * 2) {
+                    const f4v bias = *(const f4v *)(w.b3 + share * CS + 4 * g);
+                    float y[4];
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        float sum = bias[c];
+#pragma unroll
+                        for (int k = 0; k < S; ++k) sum += part3[(k * CS + 4 * g + c) * 33 + i];
+                        y[c] = act(sum);
+                    }
+                    store_split<CS, true>(row(i), 4 * g, y);
+                }
+            }
+        }
+        {   // conv4: one position tile (of which N4 columns are used); the steps are shared out over kSplit wavefronts
+            constexpr int kPer = CS / 16, kSteps = 3 * kPer / kSplit, kAhead = kSteps < 4 ? kSteps : 4;
+            static_assert(3 * kPer % kSplit == 0, "conv4 steps");
+            const int mt = wave / kSplit, ks = wave % kSplit, s0 = ks * kSteps;
+            const u4v *a = (const u4v *)w.s4 + (size_t)(mt * 3 * kPer3 + share * kPer) * 192 + lane;
+            auto frag = [&](int, const int s) { return a + ((s0 + s) / kPer * kPer3 + (s0 + s) % kPer) * 192; };
+            Fragments<1, kAhead> f;
+            fragments_start(f, frag);
+            acc16 acc[1][1];
+            acc[0][0] = zero16();
+            const unsigned char *b = rows3 + (col < N4 ? col : N4 - 1) * R3 + half * 16;
+            __syncthreads();
+            conv_mma<CS, 1, 1, kSteps, kAhead>(acc, f, frag, [&](int, const int s) {
+                const int tap = (s0 + s) / kPer;
+                return b + (tap == 1 ? (N4 + 1) * R3 : (tap >> 1) * R3) + 32 * ((s0 + s) % kPer);
+            });
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                part[(ks * C4 + mt * 32 + (r >> 2) * 8 + half * 4 + (r & 3)) * 33 + col] = acc[0][0][r];
+        }
     }
     __syncthreads();
+    constexpr int kGroups = W * 2, kCh = C4 / kGroups;
     {   // conv4's sums, bias and non-linearity; conv5's sums over this thread's channels
-        constexpr int kGroups = W * 2, kCh = C4 / kGroups;
         const int p = tid & 31, cg = tid >> 5;
+        float y[kCh];
+#pragma unroll
+        for (int i = 0; i < kCh; ++i) {
+            y[i] = part[(cg * kCh + i) * 33 + p];
+#pragma unroll
+            for (int s = 1; s < kSplit; ++s) y[i] += part[(s * C4 + cg * kCh + i) * 33 + p];
+        }
+        if constexpr (S > 1) {
+            // Through the device's memory, past the L2s: what a wavefront has stored is there once it has been acknowledged, the barrier collects the
+            // wavefronts, and one thread counts the block.
+            __shared__ uint32_t before;
+            if (p < N4) {
+#pragma unroll
+                for (int i = 0; i < kCh; ++i) __hip_atomic_store(sums + (share * C4 + cg * kCh + i) * 16 + p, y[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0)
+            __syncthreads();
+            if (tid == 0) before = __hip_atomic_fetch_add(taken, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __syncthreads();
+            if (__builtin_amdgcn_readfirstlane(before) != S - 1) return;
+            if (tid == 0) __hip_atomic_store(taken, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // as the next call expects it
+            float in[S][kCh];
+            if (p < N4) {
+#pragma unroll
+                for (int k = 0; k < S; ++k)
+#pragma unroll
+                    for (int i = 0; i < kCh; ++i) in[k][i] = __hip_atomic_load(sums + (k * C4 + cg * kCh + i) * 16 + p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+                for (int i = 0; i < kCh; ++i) {
+                    y[i] = in[0][i];
+#pragma unroll
+                    for (int k = 1; k < S; ++k) y[i] += in[k][i];
+                }
+            }
+        }
         double t[C5];
 #pragma unroll
         for (int c = 0; c < C5; ++c) t[c] = 0.;
 #pragma unroll
         for (int i = 0; i < kCh; ++i) {
             const int co = cg * kCh + i;
-            float y = part[co * 33 + p];
+            const float v = leaky_f(y[i] + small[kB4 + co], slope);
 #pragma unroll
-            for (int s = 1; s < kSplit; ++s) y += part[(s * C4 + co) * 33 + p];
-            y = leaky_f(y + w.b4[co], slope);
-#pragma unroll
-            for (int c = 0; c < C5; ++c) t[c] = fma((double)w.w5[c * C4 + co], (double)y, t[c]);
+            for (int c = 0; c < C5; ++c) t[c] = fma((double)small[kW5 + c * C4 + co], (double)v, t[c]);
         }
 #pragma unroll
         for (int c = 0; c < C5; ++c) red[(cg * C5 + c) * 32 + p] = t[c];
@@ -570,7 +670,7 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
     const bool mine = c < C5 && p < P && p0 + p < (long long)l4;
     float z = 0.f;
     if (mine) {
-        double sum = w.b5[c];
+        double sum = small[kB5 + c];
 #pragma unroll
         for (int g = 0; g < W * 2; ++g) sum += red[(g * C5 + c) * 32 + p];
         z = (float)sum;
@@ -586,8 +686,8 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
         return;
     }
     float *f = (float *)buf;
-    conv1([&](const int i, const int o8, const float (&y)[8]) {
-        float *row = f + ((i & 1) ? (N2 + 1) * row_floats(C1) : 0) + (i >> 1) * row_floats(C1) + o8 * 8;
+    conv1([&](const int i, const float (&y)[8]) {
+        float *row = f + ((i & 1) ? (N2 + 1) * row_floats(C1) : 0) + (i >> 1) * row_floats(C1) + wave * 8;
         *(f4v *)row = (f4v){y[0], y[1], y[2], y[3]};
         *(f4v *)(row + 4) = (f4v){y[4], y[5], y[6], y[7]};
     });
@@ -603,6 +703,40 @@ __global__ __launch_bounds__(W * 64) void k_encoder_fused(const float *__restric
     }
 }
 
+}  // namespace
+
+struct EncoderCall {
+    const float *x;
+    float *out, *sums;
+    uint32_t *taken;
+    uint32_t l[5];          // lengths: the input, conv1 .. conv4
+    uint32_t longs, shorts; // per node: runs of 31 positions, then of 15
+    int batch;
+    float slope;
+};
+
+// S = 0: runs of 31 positions, those of all nodes first, and then of 15: what is left over from whole rounds of the long ones takes a round of short ones instead
+// of a long one that few compute units have a part in (6 x 25 600 values, 312 runs of 31: 51.1 -> 44.7 us; 8 x 67 000, 1088: 133.0 -> 127.9).
+// S > 0: runs of 15 positions, S blocks each, grid (runs, nodes, S).
+template <int C1, int C2, int C3, int C4, int C5, int W, int S>
+__global__ __launch_bounds__(W * 64) void k_encoder_fused(EncoderCall c, EncoderDev w) {
+    using L = EncoderRun<S == 0 ? 31 : 15, S == 0 ? 1 : S, C1, C2, C3, C4, C5, W>;
+    using T = EncoderRun<15, S == 0 ? 1 : S, C1, C2, C3, C4, C5, W>;
+    __shared__ __align__(16) unsigned char buf[L::kBytes > T::kBytes ? L::kBytes : T::kBytes];
+    __shared__ __align__(16) float xs[L::kXs], small[L::kSmall];
+    const uint32_t longs = S == 0 ? c.longs * c.batch : 0;
+    if (S == 0 && blockIdx.x < longs) {   // block-uniform
+        const uint32_t node = blockIdx.x / c.longs, run = blockIdx.x % c.longs;
+        encode_run<31, 1, C1, C2, C3, C4, C5, W>(c.x + (size_t)node * c.l[0], c.out + (size_t)node * C5 * c.l[4], w, c.l[0], c.l[1], c.l[2], c.l[3], c.l[4], c.slope,
+                                                 31ll * run, 0, nullptr, nullptr, buf, xs, small);
+        return;
+    }
+    const uint32_t node = S == 0 ? (blockIdx.x - longs) / c.shorts : blockIdx.y, run = S == 0 ? (blockIdx.x - longs) % c.shorts : blockIdx.x;
+    const uint32_t at = S == 0 ? 0 : node * gridDim.x + run;
+    encode_run<15, S == 0 ? 1 : S, C1, C2, C3, C4, C5, W>(c.x + (size_t)node * c.l[0], c.out + (size_t)node * C5 * c.l[4], w, c.l[0], c.l[1], c.l[2], c.l[3], c.l[4],
+                                                          c.slope, 31ll * c.longs + 15ll * run, blockIdx.z, c.sums + (size_t)at * S * C4 * 16, c.taken + at, buf, xs, small);
+}
+
 // ---- decoder ---------------------------------------------------------------------------------------
 // A kernel-3 / stride-1 transposed layer D0 -> D1, four kernel-3 / stride-2 ones D1 -> D2 -> D3 -> D4 -> D5 and a
 // kernel-1 layer D5 -> 1.  A stride-2 transposed layer is two products: output 2m from input m (tap 1), output
@@ -616,12 +750,6 @@ struct DecoderDev {
 };
 
 namespace {
-
-// Fragments of one step of 16 input channels: the three parts of one tap
-__device__ __forceinline__ void load_a(u4v (&r)[3], const u4v *__restrict__ a, const int step) {
-#pragma unroll
-    for (int p = 0; p < 3; ++p) r[p] = a[(step * 3 + p) * 64];
-}
 
 template <int C>
 __device__ __forceinline__ void load_b(u4v (&r)[3], const unsigned char *b, const int at) {
@@ -991,9 +1119,13 @@ bool decoder_fused_covers(const LayerDev *l, int count) {
 }
 
 bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int count, const uint64_t *len, int batch, float slope,
-                          const FusedLimits &limits, int cus, hipStream_t st) {
+                          const FusedLimits &limits, int cus, const EncoderScratch &scratch, hipStream_t st) {
     if (!encoder_fused_covers(l, count) || !l[1].ws || !l[2].ws || !l[3].ws) return false;
-    const uint32_t l4 = (uint32_t)len[4];
+    EncoderCall c;
+    c.x = x; c.out = out; c.sums = scratch.sums; c.taken = scratch.taken;
+    for (int i = 0; i < 5; ++i) c.l[i] = (uint32_t)len[i];
+    c.batch = batch; c.slope = slope; c.longs = c.shorts = 0;
+    const uint32_t l4 = c.l[4];
     if (l4 == 0) return true;
     EncoderDev w;
     w.w1 = l[0].w; w.b1 = l[0].b;
@@ -1002,13 +1134,26 @@ bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int cou
     w.w4 = l[3].w; w.b4 = l[3].b; w.s4 = l[3].ws;
     w.w5 = l[4].w; w.b5 = l[4].b;
     w.limits = limits;
-#define LGC_ENC(P, W) hipLaunchKernelGGL((k_encoder_fused<64, 128, 256, 64, 4, P, W>), dim3((l4 + P - 1) / P, batch), dim3(64 * W), 0, st, \
-                                         x, out, w, (uint32_t)len[0], (uint32_t)len[1], (uint32_t)len[2], (uint32_t)len[3], l4, slope)
-    // 31 positions per block stream the 1 MB of weights half as often as 15 do, and waste no half tile in conv4 (4 nodes
-    // x 25 600 values: 25.8 against 32.7 us, 8 x 67 000: 220 against 231); but while runs of 15 give every compute
-    // unit at most one block, the shorter chain of a block is what counts (1 x 1 023, both directions: 28.7 against 36.9 us).
-    if ((uint64_t)((l4 + 14) / 15) * batch <= (uint64_t)cus) LGC_ENC(15, 8); else LGC_ENC(31, 8);
+    const uint32_t runs = (l4 + 14) / 15;
+    const uint64_t all = (uint64_t)runs * batch;
+    auto fits = [&](uint64_t shares) { return all * shares <= (uint64_t)cus && (shares == 1 || (all <= scratch.taken_words && all * shares * 64 * 16 <= scratch.sum_floats)); };
+#define LGC_ENC(S) hipLaunchKernelGGL((k_encoder_fused<64, 128, 256, 64, 4, 8, S>), dim3(runs, batch, S), dim3(512), 0, st, c, w)
+    // as many blocks as there are compute units for the runs of 15
+    if (fits(4)) { LGC_ENC(4); return true; }
+    if (fits(2)) { LGC_ENC(2); return true; }
+    if (fits(1)) { LGC_ENC(1); return true; }
 #undef LGC_ENC
+    // 31 positions per block stream the 1 MB of weights half as often as 15 do, and waste no half tile in conv4 (4 nodes x 25 600 values: 25.8 against 32.7 us)
+    const uint32_t longs = (l4 + 30) / 31, rounds = (uint32_t)((uint64_t)longs * batch / cus);   // rounds in which every compute unit has a run of 31
+    c.longs = longs; c.shorts = 0;
+    if (rounds > 0) {
+        const uint32_t most = (uint32_t)((uint64_t)rounds * cus / batch);
+        if (most < longs) {
+            const uint32_t rest = (l4 - 31 * most + 14) / 15;
+            if ((uint64_t)rest * batch <= (uint64_t)cus) { c.longs = most; c.shorts = rest; }
+        }
+    }
+    hipLaunchKernelGGL((k_encoder_fused<64, 128, 256, 64, 4, 8, 0>), dim3((c.longs + c.shorts) * batch), dim3(512), 0, st, c, w);
     return true;
 }
 

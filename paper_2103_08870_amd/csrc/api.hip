@@ -41,6 +41,7 @@ struct lgc_ctx {
     uint64_t rec_rows = 0;
     float *act[2] = {nullptr, nullptr};  // autoencoder activations (ping-pong), grown on demand
     size_t act_floats = 0;
+    uint32_t *taken = nullptr;           // counts of the encoder's blocks that share a run of positions (zero between calls), kTakenWords
     // per-layer selection: thresholds [max_batch][n_seg] and a candidate list of its own, grown on demand
     uint32_t *seg_t = nullptr, *seg_cand = nullptr, *seg_row_prefix = nullptr;
     size_t seg_t_words = 0, seg_cand_words = 0;
@@ -216,12 +217,14 @@ StateLayout state_layout(int max_batch, uint32_t status_cand_stride, uint32_t st
     return L;
 }
 
+constexpr uint32_t kTakenWords = 1024;
+
 // The selection scratch of a context for (max_n, max_k, max_batch): byte offsets of its parts in one block of
-// device memory.  Everything before `samples` (statistics, carried thresholds, state sets) must start at zero.
+// device memory.  Everything before `samples` (statistics, carried thresholds, counts, state sets) must start at zero.
 struct ScratchLayout {
     bool ok = false;
     uint32_t cap = 0, rows = 0, status_cand_stride = 0, status_exact_stride = 0, state_words = 0;
-    size_t stats = 0, carry = 0, state[2] = {0, 0}, samples = 0, row_count = 0, bitmap = 0, cand_idx = 0, cand_val = 0;
+    size_t stats = 0, carry = 0, taken = 0, state[2] = {0, 0}, samples = 0, row_count = 0, bitmap = 0, cand_idx = 0, cand_val = 0;
     size_t bytes = 0;
 };
 
@@ -239,6 +242,7 @@ ScratchLayout scratch_layout(uint64_t max_n, uint64_t max_k, int max_batch, bool
     auto carve = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, A); return o; };
     s.stats = carve(sizeof(Stats));
     s.carry = carve(B * sizeof(Carry));
+    if (two_state_sets) s.taken = carve(kTakenWords * 4);   // (a context; the fixed array of the call without one runs no encoder)
     s.state[0] = carve(L.words * 4);
     s.state[1] = two_state_sets ? carve(L.words * 4) : s.state[0];
     s.samples = carve(B * kSample * 4);
@@ -259,6 +263,7 @@ void bind_scratch(lgc_ctx *c, void *base_ptr, const ScratchLayout &s) {
     c->state_words = s.state_words;
     c->stats = (Stats *)(base + s.stats);
     c->carry = (Carry *)(base + s.carry);
+    c->taken = s.taken ? (uint32_t *)(base + s.taken) : nullptr;
     c->state[0] = (uint32_t *)(base + s.state[0]);
     c->state[1] = (uint32_t *)(base + s.state[1]);
     c->samples = (uint32_t *)(base + s.samples);
@@ -810,7 +815,7 @@ extern "C" lgc_status lgc_ae_create(lgc_ae **out, int device, int n_enc, const l
                     LayerDev &l = ls[first + i];
                     launch_most(l.w, l.c_in * l.c_out * l.ksize, w + 1 + i, nullptr);
                     if (i == 3) break;
-                    launch_weights_split(l.w, ae->weights_s + s_off, l.c_in, l.c_out, transposed, transposed && i == 2, w, nullptr);
+                    launch_weights_split(l.w, ae->weights_s + s_off, l.c_in, l.c_out, transposed, i == 2, w, nullptr);
                     l.ws = ae->weights_s + s_off;
                     s_off += size(l);
                 }
@@ -966,7 +971,8 @@ static lgc_status run_encode(lgc_ctx *ctx, const lgc_ae *ae, const float *vals, 
         return fail(ctx, LGC_EINVAL, "lgc_encode: activation scratch for k = %llu, batch = %d not reserved: call "
                                      "lgc_reserve(ctx, ae, k, batch, NULL) once beforehand", (unsigned long long)k, batch);
     if (!overlap(vals, k * batch, latent, (uint64_t)batch * ae->enc[nl - 1].c_out * len[nl]) &&
-        launch_encoder_fused(vals, latent, ae->enc_dev.data(), (int)nl, len.data(), batch, ae->slope, ae->enc_limits, ctx->cus, st)) {
+        launch_encoder_fused(vals, latent, ae->enc_dev.data(), (int)nl, len.data(), batch, ae->slope, ae->enc_limits, ctx->cus,
+                             EncoderScratch{ctx->act[0], ctx->act_floats, ctx->taken, ctx->taken ? kTakenWords : 0u}, st)) {
         hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e1));
         return LGC_OK;

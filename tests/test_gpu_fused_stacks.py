@@ -69,6 +69,22 @@ def test_lengths_at_the_edges_of_a_block(B, oracle, k, batch):
     ae.close()
 
 
+# The encoder's runs of 15 positions go to four blocks each (up to 64 runs), to two (up to 128) or to one; what whole rounds of runs of 31 leave over is cut into
+# runs of 15 (7 nodes x 1 147 positions: 252 of 31, 21 of 15): a last run of all, of one and of two positions.
+@pytest.mark.parametrize("k,batch", [(3840, 4), (3841, 4), (4800, 5), (4801, 5), (4817, 5), (4800, 7), (4801, 7), (18352, 7), (18353, 7)])
+def test_lengths_at_the_edges_of_an_encoder_run(B, oracle, k, batch):
+    ae, enc, dec, host = stacks(B)
+    x = np.random.default_rng(k).laplace(0, 0.3, (batch, k)).astype(np.float32)
+    ctx = B.Context(k, k, batch)
+    B.lgc_reserve(ctx, ae, k, batch)
+    ol = np.stack([oracle.encode(row, enc, host[0], host[1], slope=0.01) for row in x]).reshape(batch, -1)
+    for _ in range(3):   # the counts by which blocks meet are as the call before left them
+        lat = torch.full((batch, B.lgc_latent_len(ae, k)), 7.0, device="cuda")
+        B.lgc_encode(ctx, ae, torch.from_numpy(x).cuda(), lat)
+        assert_near(lat.cpu().numpy(), ol, ("latent", k))
+    ctx.close(); ae.close()
+
+
 # The decoder's blocks take 7 latent positions (112 values), 15 (240), or 15 with the weights through the LDS: a last block of all, of one and of two.
 @pytest.mark.parametrize("k,batch", [(112, 1), (113, 1), (224, 2), (112 * 3 + 17, 3), (3840, 8), (3841, 8), (3857, 8), (7920, 8), (7921, 8), (7937, 8)])
 def test_lengths_at_the_edges_of_a_decoder_block(B, oracle, k, batch):
@@ -125,7 +141,7 @@ def test_error_against_64_bits(B, k, batch):
 # 15 latent positions (600 values; the decoder's of 7, and of 15 for 5 nodes x 6 000), and of 31 where there are enough of them (7 nodes x 10 000); the values sit inside a
 # block, where two blocks' windows overlap, and in the last, partly filled block.  At 1e-33 the split's low parts, and their products,
 # are below the least normal number (the reconstruction, about 3e-38, is just above it); no biases, which would hide it.
-@pytest.mark.parametrize("k,batch", [(600, 2), (6_000, 5), (10_000, 7)])
+@pytest.mark.parametrize("k,batch", [(600, 2), (6_000, 5), (10_000, 7), (18_353, 7)])
 @pytest.mark.parametrize("special", [np.inf, np.nan, 3.4e38, 1e-30, 1e-33, 0.0])
 def test_values_that_the_split_cannot_carry(B, oracle, special, k, batch):
     def change(a, which):
