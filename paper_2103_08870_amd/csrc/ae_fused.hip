@@ -15,8 +15,8 @@
 // 64 bits: the cost cannot be told from none (4 x 25 600: 26.0 us either way), and in 32 bits those sums were over half
 // of the latent's error.
 // Measured against one fp32-MFMA launch per deep layer (ae_mfma.hip, which other stacks still use): 4 nodes x 25 600
-// values, encoder 79.4 -> 26.8 us (165 TFLOP/s of fp32 products), decoder 58.0 -> 20.6 us (130); 8 x 67 000, both
-// together 468 -> 206 us (180); 1 x 1 023 (latency) 79 -> 20.8 us.  Relative error against 64 bits, six sizes from 1 x 500 to
+// values, encoder 79.4 -> 26.8 us (165 TFLOP/s of fp32 products), decoder 58.0 -> 19.9 us (134); 8 x 67 000, both
+// together 468 -> 205 us (181); 1 x 1 023 (latency) 79 -> 20.3 us.  Relative error against 64 bits, six sizes from 1 x 500 to
 // 8 x 67 000 x six seeds, mean (least to largest): latent 1.15e-7 (0.87 to 1.46) -> 0.41e-7 (0.34 to 0.51; 0.99e-7 with the
 // last sums in 32 bits), decoder 3.86e-8 (2.96 to 5.54) -> 2.95e-8 (2.20 to 3.86): lower at every size with every
 // seed.  What bounds it: while a compute unit has blocks its matrix cores are busy 54-57 % of the cycles (encoder) and
@@ -293,7 +293,7 @@ __device__ __forceinline__ void load_a(u4v (&r)[3], const u4v *__restrict__ a, c
 
 // The order of one step's instructions: a read from the LDS, then a load, behind each product in turn, which they then cost no time beside (ahead of the
 // products they are issued while the matrix cores wait; a block of 31 positions 57.4 -> 54.5 K cycles, 8 x 67 000 values 129.4 -> 127.9 us, as the clock falls with
-// the denser products).
+// the denser products; the decoder's steps, 8 x 67 000 82.4 -> 80.8, 1 x 1 023 8.5 -> 8.2).
 template <int MMAS, int READS, int LOADS>
 __device__ __forceinline__ void interleave() {
 #pragma unroll
@@ -789,8 +789,8 @@ __device__ __forceinline__ void store_fp32(float *row, const int co0, const int 
 // work, and one wavefront converts while another one multiplies.  deconv5's output 4i + 3 needs deconv4's 2i + 2, which is the next
 // lane's: 31 of the 32 positions come out.  4 / NP wavefronts share a position tile's channels of deconv4 and add their sums up at the end.
 // The bound of two wavefronts per SIMD leaves room for the weights' fragments that are under way (one step ahead).
-// Through the LDS, in two runs of 64 channels with four barriers each, 4 x 25 600 values took 22.2 us (20.6 now), 8 x 67 000 87.8 (80.4), 1 x 1 023
-// 12.5 (8.8, with 7 positions per block).  What bounds it: two blocks on a compute unit have 18.4 K cycles of products in 39 K; the rest is each block's way
+// Through the LDS, in two runs of 64 channels with four barriers each, 4 x 25 600 values took 22.2 us (19.9 now), 8 x 67 000 87.8 (79), 1 x 1 023
+// 12.5 (8.3, with 7 positions per block).  What bounds it: two blocks on a compute unit have 18.4 K cycles of products in 39 K; the rest is each block's way
 // to the first product (9 K: a read from memory, three small layers, three barriers) and its end (5 K).
 template <int D0, int D1, int D2, int D3, int D4, int D5, int T, bool RING>
 __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restrict__ z, float *__restrict__ out, DecoderDev w,
@@ -979,13 +979,14 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
 #pragma unroll
             for (int s = 0; s < kPer; ++s) {
                 load_b<D3>(x1, b + R3, 32 * s);
-                advance(ct, s);
                 __builtin_amdgcn_sched_barrier(0);
+                advance(ct, s);
                 mma6_by<2>(up, cross, (const u4v (&)[2][3])ra[s & 1], x0);
+                interleave<12, RING ? 9 : 0, RING ? 5 : 9>();
                 __builtin_amdgcn_sched_barrier(0);
                 if (s + 1 < kPer) load_b<D3>(x0, b, 32 * (s + 1));
-                __builtin_amdgcn_sched_barrier(0);
                 mma6_by<1>(up, cross, (const u4v (&)[1][3])ra[s & 1][2], x1);
+                interleave<6, 3, 0>();
                 __builtin_amdgcn_sched_barrier(0);
             }
             up[0] += cross[0]; up[1] += cross[1];
@@ -996,8 +997,8 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
 #pragma unroll
             for (int q = 0; q < 2; ++q) {
                 advance(ct, kPer + q);
-                __builtin_amdgcn_sched_barrier(0);
                 mma6_up4(y, ra[q & 1], e[q], o[q], n[q]);
+                interleave<36, RING ? 9 : 0, RING ? 5 : 9>();
                 __builtin_amdgcn_sched_barrier(0);
             }
         }
@@ -1171,10 +1172,10 @@ bool launch_decoder_fused(const float *z, float *out, const LayerDev *l, int cou
     w.limits = limits;
 #define LGC_DEC(T, RING) hipLaunchKernelGGL((k_decoder_fused<4, 4, 32, 64, 128, 32, T, RING>), dim3(((uint32_t)l_z + T - 1) / T, batch), dim3(256), 0, st, z, out, w, \
                                             (uint32_t)l_z, (uint32_t)len[1], (uint32_t)len[2], (uint32_t)len[3], (uint32_t)len[4], slope)
-    // 7 positions per block while that gives every compute unit at most one: the shorter chain counts (1 x 1 023 values: 8.8 us against 12.4 with 15, 4 x 5 000: 9.4
-    // against 12.6); from two such blocks per compute unit on 15 are better (2 x 15 000: 14.3 against 12.4).  Where those come to two per compute unit as
+    // 7 positions per block while that gives every compute unit at most one: the shorter chain counts (1 x 1 023 values: 8.3 us against 11.6 with 15, 4 x 5 000: 8.9
+    // against 11.6); from two such blocks per compute unit on 15 are better (2 x 15 000: 14.3 against 12.4).  Where those come to two per compute unit as
     // well, their wavefronts fetch the weights once for two, through the LDS (4 x 25 600: 21.9 against 20.4 us, 8 x 67 000: 85.1 against 82.6); a block that has its
-    // compute unit to itself loses more by the barriers than it gains (4 x 15 000: 12.5 against 13.4).
+    // compute unit to itself loses more by the barriers than it gains (4 x 15 000: 12.5 against 13.4; both before their loads went behind the products).
     if ((uint64_t)((l_z + 6) / 7) * batch <= (uint64_t)cus) LGC_DEC(7, false);
     else if ((uint64_t)((l_z + 14) / 15) * batch <= (uint64_t)cus) LGC_DEC(15, false);
     else LGC_DEC(15, true);
