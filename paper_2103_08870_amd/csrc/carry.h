@@ -19,14 +19,15 @@ namespace lgc {
 
 // ok: the selection was served from the candidates above t_est (`total` of them, >= k); carried: t_est had been
 // offered by the record.  target, most: log2 of the candidate counts over k (aimed at / at most).  fresh: the
-// record is not the previous selection's (another kind of selection came between).  Returns the offer (0: none).
-__device__ __forceinline__ uint32_t carry_update(Carry *c, const uint32_t n, const uint32_t k, const bool fresh, const bool ok,
+// record is not the previous selection's (another kind of selection came between).  old: the record as it was, at c or a copy.  Returns the
+// offer (0: none).
+__device__ __forceinline__ uint32_t carry_update(Carry *c, const Carry *old, const uint32_t n, const uint32_t k, const bool fresh, const bool ok,
                                                  const bool carried, const uint32_t thr, const uint32_t t_est,
                                                  const uint32_t total, const float target, const float most) {
-    const bool same = !fresh && c->n == n && c->k == k;     // the record is the previous selection's, of this shape
-    const bool follows = same && c->len > 0;
-    const float l1 = c->log2_t[0], l2 = c->log2_t[1];
-    uint32_t len = 0, next = 0, next_t = 0, fails = same ? c->fails : 0u, held = same ? c->held : 0u;
+    const bool same = !fresh && old->n == n && old->k == k;     // the record is the previous selection's, of this shape
+    const bool follows = same && old->len > 0;
+    const float l1 = old->log2_t[0], l2 = old->log2_t[1];
+    uint32_t len = 0, next = 0, next_t = 0, fails = same ? old->fails : 0u, held = same ? old->held : 0u;
     if (carried) {
         if (!ok) { fails = fails < 5 ? fails + 1 : 5u; held = 0; }
         else if (++held >= 64) { fails = fails ? fails - 1 : 0u; held = 0; }
@@ -35,8 +36,8 @@ __device__ __forceinline__ uint32_t carry_update(Carry *c, const uint32_t n, con
     constexpr uint32_t kMinNormal = 0x00800000u, kInf = 0x7f800000u;
     if (ok && thr >= kMinNormal && thr < kInf && t_est >= kMinNormal && t_est < thr) {
         l0 = log2f(__uint_as_float(thr));
-        len = follows ? (c->len < 255 ? c->len + 1 : 255u) : 1u;
-        if (len >= 3) miss = fmaxf(fabsf(l0 - (2.f * l1 - l2)), len > 3 ? 0.85f * c->miss : 0.f);
+        len = follows ? (old->len < 255 ? old->len + 1 : 255u) : 1u;
+        if (len >= 3) miss = fmaxf(fabsf(l0 - (2.f * l1 - l2)), len > 3 ? 0.85f * old->miss : 0.f);
         const float ratio = total > k ? log2f((float)total / (float)k) : 0.f;
         const float used = l0 - log2f(__uint_as_float(t_est));
         if (len >= (4u << fails) && ratio >= 0.05f && used > 0.f) {

@@ -372,7 +372,7 @@ __global__ __launch_bounds__(kSelThreads) void k_seg_select(SelArgs a) {
         Carry *c = a.seg_carry + (size_t)node * a.n_seg + l;
         // a layer that keeps few values may flag k + 256: what its k-th magnitude does is noisy, and the candidates cost nothing
         const float most = fmaxf(a.carry_most, log2f((float)(k + 256u) / (float)k));
-        carry_update(c, hi - lo, k, a.carry_fresh != 0, from_list, c->carried_now != 0, thr,
+        carry_update(c, c, hi - lo, k, a.carry_fresh != 0, from_list, c->carried_now != 0, thr,
                      a.seg_t[(size_t)node * a.n_seg + l], p1 - p0, a.carry_target, most);
     }
 }

@@ -122,7 +122,13 @@ __global__ __launch_bounds__(1024) void k_sample(SelArgs a) {
     u4 x[kSample / 4 / 1024];
 #pragma unroll
     for (int r = 0; r < (int)(kSample / 4 / 1024); ++r) x[r] = *(const u4 *)(smp + (r * 1024 + tid) * 4);
-    for (int i = tid; i < kSampleBins; i += 1024) hist[i] = ld_agent32(&sh[i]);
+    {
+        uint32_t h[kSampleBins / 1024];   // (a loop over them is a wait for memory per round)
+#pragma unroll
+        for (int r = 0; r < kSampleBins / 1024; ++r) h[r] = ld_agent32(&sh[r * 1024 + tid]);
+#pragma unroll
+        for (int r = 0; r < kSampleBins / 1024; ++r) hist[r * 1024 + tid] = h[r];
+    }
     __syncthreads();
     find_rank_bin<kSampleBins, 1024>(hist, a.rank, wave_tmp, res);
     const uint32_t b1 = res[0], need = a.rank - res[1];
@@ -538,50 +544,47 @@ constexpr uint32_t kZerosPerCrowdedRow = 64;
 
 // What the one thread that knows a selection's outcome on the fast path leaves behind: the node's state for the
 // kernels after it, the statistics, the word the host polls, and the record of carried thresholds (carry.h).
-__device__ __forceinline__ void report_outcome(const SelArgs &a, const int node, Sel *s, const bool ok, const uint32_t thr,
-                                               const uint32_t quota, const uint32_t total, const uint32_t t_est) {
+// old: the node's record as it was, in the LDS (read ahead) or where it is.
+__device__ __forceinline__ void report_outcome(const SelArgs &a, const int node, Sel *s, const Carry *old, const bool ok, const uint32_t thr,
+                                               const uint32_t quota, const uint32_t total, const uint32_t t_est, const uint32_t carried) {
     s->fast_ok = ok;
     if (ok) { s->thr = thr; s->quota = quota; }
     atomicAdd(ok ? &a.stats->fast : &a.stats->fallback, 1u);
     bool offers = false;
     if (a.carry) {
-        offers = carry_update(a.carry + node, a.n, a.k, false, ok, s->carried != 0, thr, t_est, total, a.carry_target, a.carry_most) != 0;
+        offers = carry_update(a.carry + node, old, a.n, a.k, false, ok, carried != 0, thr, t_est, total, a.carry_target, a.carry_most) != 0;
         a.carry[node].zeros_pay = a.zero_early && a.ctr[node].recorded / kZerosPerCrowdedRow >= a.ctr[node].crowded;
     }
     // the host sees the outcome without synchronising; a carried threshold that failed says nothing about the data
-    if (a.notify) st_system32(a.notify + (ok ? (offers ? kServedOffers : kServed) : s->carried ? kOfferFailed : kFellBack), a.notify_value);
+    if (a.notify) st_system32(a.notify + (ok ? (offers ? kServedOffers : kServed) : carried ? kOfferFailed : kFellBack), a.notify_value);
 }
 
 
 
+// A thread's four bins (of 1024 threads) of a node's histogram: one load, where a loop over single words is a wait for memory per round.
+__device__ __forceinline__ u4 fine_bins(const uint32_t *hist, const int node) {
+    static_assert(kFineBins == 4 * 1024, "four bins per thread");
+    return ((const u4 *)(hist + node * kFineBins))[threadIdx.x];
+}
+
 // Block-wide: the exact k-th largest key T* and the number of ties to take, from the fine
 // histogram (first level, bins of 2^12 above t_est) and a second-level histogram of the low 12
-// bits inside the bin that holds the k-th key.  LOCAL = true: the second level is counted here
-// from all gathered candidates; false: it was counted by k_select_level2 into a.level2_hist.
+// bits inside the bin that holds the k-th key, counted by k_select_level2.
 // Returns false (for all threads alike) if count(candidates) < k, candidates were lost, or T*
 // lies in the open-ended last bin: then the node is left to the exact path.
-template <bool LOCAL>
 __device__ bool find_threshold(const SelArgs &a, int node, uint32_t total, uint32_t *hist /*[kFineBins]*/,
                                uint32_t *wave_tmp, uint32_t *res, uint32_t &thr, uint32_t &quota) {
-    const Sel *s = a.sel + node;
-    const int tid = threadIdx.x, nt = blockDim.x;
+    const int tid = threadIdx.x;
+    const u4 first = fine_bins(a.fine_hist, node), second = fine_bins(a.level2_hist, node);
+    const uint32_t t_est = a.sel[node].t_est;
     if (total < a.k || total > a.cap) return false;
-    const uint32_t t_est = s->t_est;
-    for (int i = tid; i < kFineBins; i += nt) hist[i] = a.fine_hist[node * kFineBins + i];
+    ((u4 *)hist)[tid] = first;
     __syncthreads();
     find_rank_bin<kFineBins, 1024>(hist, a.k, wave_tmp, res);
     const uint32_t bin = res[0], need = a.k - res[1];
     __syncthreads();
     if (bin >= (uint32_t)kFineBins - 1) return false;
-    if (LOCAL) {
-        for (int i = tid; i < kFineBins; i += nt) hist[i] = 0;
-        __syncthreads();
-        count_candidates(a.cand_val + (size_t)node * a.cap, total, t_est, hist,
-                         [=](uint32_t d) { return (d >> kFineShift) == bin; },
-                         [=](uint32_t d) { return d & ((1u << kFineShift) - 1); });
-    } else {
-        for (int i = tid; i < kFineBins; i += nt) hist[i] = a.level2_hist[node * kFineBins + i];
-    }
+    ((u4 *)hist)[tid] = second;
     __syncthreads();
     find_rank_bin<kFineBins, 1024>(hist, need, wave_tmp, res);
     thr = t_est + (bin << kFineShift) + res[0];
@@ -599,7 +602,7 @@ __global__ __launch_bounds__(1024) void k_select_level2(SelArgs a) {
     const uint32_t total = s->cand_total;
     if (total < a.k || total > a.cap) return;
     const uint32_t t_est = s->t_est;
-    for (int i = tid; i < kFineBins; i += 1024) hist[i] = a.fine_hist[node * kFineBins + i];
+    ((u4 *)hist)[tid] = fine_bins(a.fine_hist, node);
     __syncthreads();
     find_rank_bin<kFineBins, 1024>(hist, a.k, wave_tmp, res);
     const uint32_t bin = res[0];
@@ -629,35 +632,38 @@ constexpr int kKeep = 16;   // 16-byte key groups per thread held in registers
 __device__ __forceinline__ void output_direct(const SelArgs &a, const int node, const uint32_t block, uint32_t *hist /*[kFineBins]*/,
                                               uint32_t *wave_tmp /*[16]*/, uint32_t *res /*[2]*/) {
     __shared__ uint32_t sh_pg[16], sh_pe[16], sh_tg[16], sh_te[16];
+    __shared__ Carry old;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     Sel *s = a.sel + node;
-    const uint32_t total = s->cand_total;
     const uint32_t *cidx = a.cand_idx + (size_t)node * a.cap;
     const uint32_t *cval = a.cand_val + (size_t)node * a.cap;
     const uint32_t base = block * 4096u, e0 = base + tid * 4;
-    bool ok = total >= a.k && total <= a.cap;
-    const uint32_t n4 = ok ? (total + 3) / 4 : 0u;   // 16-byte groups (the list's capacity is a multiple of 4)
 
-    // independent loads first: the keys, my four positions and values, the fine histogram.
-    // The registers hold keys (sign cleared); entries past the end of the list hold 0xffffffff,
-    // which no key equals and which lies in no histogram bin.
+    // independent loads first: the fine histogram, the keys, my four positions and values.  The keys are what long lists wait for: a compute unit draws
+    // them at some 15 bytes a cycle (4 x 38 K keys: 10 K of 22 K cycles).  Short ones waited for the histogram, word by word, and for instructions on keys that
+    // were not there: 3 x 3.33 M elements, 5 000 listed: 13.3 -> 11.0 us; whole step 61.5 -> 59.5, 25.6 M, k = 25 600 (one node) 377.4 -> 376.5 with its three others.
+    // A block beyond the list's end leaves before it draws any of it (the list has room for 1.5 times what is expected).
+    const uint32_t total = s->cand_total, t_est = s->t_est, carried = s->carried;
+    bool ok = total >= a.k && total <= a.cap;
+    const uint32_t held = ok ? total : 0u, n4 = (held + 3) / 4;   // 16-byte groups (the list's capacity is a multiple of 4096)
+    const bool reports = block == 0;
+    if (base >= held && !reports) return;
+    const u4 fine = fine_bins(a.fine_hist, node);
+    if (reports && a.carry && tid < (int)(sizeof(Carry) / 4)) ((uint32_t *)&old)[tid] = ((const uint32_t *)(a.carry + node))[tid];
+    u4 keys[kKeep];
+#pragma unroll
+    for (int r = 0; r < kKeep; ++r)
+        keys[r] = r * 1024u + tid < n4 ? *(const u4 *)(cval + r * 4096u + tid * 4) : (u4){0u, 0u, 0u, 0u};
+    u4 ci = {0, 0, 0, 0}, cv = {0u, 0u, 0u, 0u};
+    if (e0 < held) { ci = *(const u4 *)(cidx + e0); cv = *(const u4 *)(cval + e0); }
+    ((u4 *)hist)[tid] = fine;
+    // The registers hold the list, from the tally on as keys (sign cleared).  In the list's last round entries past its end count as 0xffffffff, which
+    // no key equals and which lies in no histogram bin.
     auto as_keys = [&](u4 x, uint32_t g4) -> u4 {
 #pragma unroll
         for (int c = 0; c < 4; ++c) x[c] = g4 * 4 + c < total ? (x[c] & 0x7fffffffu) : 0xffffffffu;
         return x;
     };
-    u4 keys[kKeep];
-#pragma unroll
-    for (int r = 0; r < kKeep; ++r) {
-        const uint32_t g4 = r * 1024 + tid;
-        keys[r] = g4 < n4 ? *(const u4 *)(cval + (size_t)g4 * 4) : (u4){0u, 0u, 0u, 0u};
-    }
-    u4 ci = {0, 0, 0, 0}, cv = {0u, 0u, 0u, 0u};
-    if (ok && e0 < total) { ci = *(const u4 *)(cidx + e0); cv = *(const u4 *)(cval + e0); }
-#pragma unroll
-    for (int r = 0; r < kKeep; ++r) keys[r] = as_keys(keys[r], r * 1024 + tid);
-    for (int i = tid; i < kFineBins; i += 1024) hist[i] = a.fine_hist[node * kFineBins + i];
-    const uint32_t t_est = s->t_est;
     __syncthreads();
 
     uint32_t thr = 0, quota = 0;
@@ -674,10 +680,22 @@ __device__ __forceinline__ void output_direct(const SelArgs &a, const int node, 
                 const uint32_t d = key - bin_base;
                 if (d < (1u << kFineShift)) atomicAdd(&hist[d], 1u);
             };
+            // (four keys at a time: few are in the bin)
 #pragma unroll
             for (int r = 0; r < kKeep; ++r) {
+                if ((r + 1) * 4096u <= held) {   // uniform
+                    uint32_t d[4], least = ~0u;
 #pragma unroll
-                for (int c = 0; c < 4; ++c) tally(keys[r][c]);
+                    for (int c = 0; c < 4; ++c) { keys[r][c] &= 0x7fffffffu; d[c] = keys[r][c] - bin_base; least = d[c] < least ? d[c] : least; }
+                    if (least < (1u << kFineShift)) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) if (d[c] < (1u << kFineShift)) atomicAdd(&hist[d[c]], 1u);
+                    }
+                } else if (r * 4096u < held) {
+                    const u4 x = as_keys(keys[r], r * 1024 + tid);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) tally(x[c]);
+                }
             }
             for (uint32_t g4 = kKeep * 1024 + tid; g4 < n4; g4 += 1024) {
                 const u4 x = as_keys(*(const u4 *)(cval + (size_t)g4 * 4), g4);
@@ -690,8 +708,8 @@ __device__ __forceinline__ void output_direct(const SelArgs &a, const int node, 
             quota = need - res[1];
         }
     }
-    if (block == 0 && tid == 0) report_outcome(a, node, s, ok, thr, quota, total, t_est);
-    if (!ok || base >= total) return;
+    if (reports && tid == 0) report_outcome(a, node, s, &old, ok, thr, quota, total, t_est, carried);
+    if (!ok) return;
 
     // selected-or-tied counts among the candidates before mine: groups r*1024 + tid, r < block
     // (all of those lie before the end of the list, so none is the 0xffffffff filler)
@@ -932,8 +950,8 @@ __global__ __launch_bounds__(1024) void k_count_chunks(SelArgs a) {
         x[c] = (in_range && e0 < total) ? *(const u4 *)(cval + e0) : (u4){0u, 0u, 0u, 0u};
     }
     uint32_t thr = 0, quota = 0;
-    const bool ok = find_threshold<false>(a, node, total, hist, wave_tmp, res, thr, quota);
-    if (blockIdx.x == 0 && tid == 0) report_outcome(a, node, s, ok, thr, quota, total, s->t_est);
+    const bool ok = find_threshold(a, node, total, hist, wave_tmp, res, thr, quota);
+    if (blockIdx.x == 0 && tid == 0) report_outcome(a, node, s, a.carry + node, ok, thr, quota, total, s->t_est, s->carried);
     if (!ok || base >= total) return;
 #pragma unroll
     for (int c = 0; c < kCountChunks; ++c) {
@@ -1277,7 +1295,7 @@ __global__ __launch_bounds__(1024) void k_output_or_exact(SelArgs a, uint32_t ou
     const uint32_t total = a.sel[node].cand_total;
     bool ok = total >= a.k && total <= a.cap;
     if (ok) {   // the same for the whole block
-        for (int i = tid; i < kFineBins; i += 1024) hist[i] = a.fine_hist[node * kFineBins + i];
+        ((u4 *)hist)[tid] = fine_bins(a.fine_hist, node);
         __syncthreads();
         find_rank_bin<kFineBins, 1024>(hist, a.k, wave_tmp, res);
         ok = res[0] < (uint32_t)kFineBins - 1;
@@ -1370,7 +1388,7 @@ __device__ __forceinline__ void finish_node(const SelArgs &a, const int node, co
     }
     const uint32_t thr = least + prefix, quota = need;
     if (tid == 0) {
-        if (report) report_outcome(a, node, s, true, thr, quota, total, s->t_est);
+        if (report) report_outcome(a, node, s, a.carry + node, true, thr, quota, total, s->t_est, s->carried);
         else {   // short vectors: one node speaks for those served (256 stores to host memory would take 25 us)
             carry_lapse(a, node);
             if (a.notify && node == 0) st_system32(a.notify + kServed, a.notify_value);
@@ -1434,7 +1452,7 @@ __global__ __launch_bounds__(1024) void k_finish_or_exact(SelArgs a, int report)
     if (tid == 0) a.sel[node].cand_total = total;
     if (ok) finish_node(a, node, total, report, offs, hist, wave_tmp, res);
     else if (tid == 0) {
-        if (report) report_outcome(a, node, a.sel + node, false, 0, 0, total, a.sel[node].t_est);
+        if (report) report_outcome(a, node, a.sel + node, a.carry + node, false, 0, 0, total, a.sel[node].t_est, a.sel[node].carried);
         else if (a.notify) st_system32(a.notify + kFellBack, a.notify_value);
     }
 }
