@@ -335,15 +335,6 @@ __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
     }
 }
 
-// For the next selection's zeros from the pass (a.zero_early), what they would save and cost: a lane's row holds c candidates
-__device__ __forceinline__ void count_crowded(Ctr *ctr, const uint32_t c) {
-    const uint32_t held = wave_sum(c <= (uint32_t)kZeroRecord ? c : 0u), crowded = (uint32_t)__popcll(__ballot(c > (uint32_t)kZeroRecord));
-    if ((threadIdx.x & 63) == 0) {
-        if (held) atomicAdd(&ctr->recorded, held);
-        if (crowded) atomicAdd(&ctr->crowded, crowded);
-    }
-}
-
 // The same for the flat selection of long vectors, with the work cut where the candidates are, not where the
 // rows are: a piece is up to T candidates of one group of kGroupRows rows, one per thread, and the node's blocks take the pieces in turn.
 // Groups without candidates cost nothing, and where the candidates cluster no block is left with a multiple of the others' work.
@@ -367,6 +358,7 @@ __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
     uint32_t *cidx = a.cand_idx + (size_t)node * a.cap, *cval = a.cand_val + (size_t)node * a.cap;
     const uint32_t t_est = s->t_est, t_zero = a.zero_early ? s->t_zero : ~0u;
 
+    uint32_t recorded = 0, over_full = 0;   // this thread's rows' candidates in rows that a zero record holds; its rows that hold more
     // this thread's run of groups: its candidates and pieces, and those before it
     const uint32_t per = (groups + T - 1) / T, g0 = tid * per;
     static_assert((1u << 31) / (kGroupRows * kRow) < 1u << 16, "both counts in one word");
@@ -427,7 +419,10 @@ __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
             const uint32_t incl = wave_prefix(rc);
             offs[tid] = incl - rc;
             if (lane == 63) tmp[wave] = incl;
-            if (a.zero_early && q0 == 0) count_crowded(a.ctr + node, rc);
+            if (a.zero_early && q0 == 0) {
+                recorded += rc <= (uint32_t)kZeroRecord ? rc : 0u;
+                over_full += rc > (uint32_t)kZeroRecord;
+            }
         }
         __syncthreads();
         for (uint32_t q = q0 + tid; q < (EVEN ? end : all); q += T) {   // (without EVEN a thread has one, and the loop costs a tenth of the kernel's time)
@@ -456,6 +451,15 @@ __global__ __launch_bounds__(T) void k_gather_pieces(SelArgs a) {
         }
     }
     __syncthreads();
+    // For the next selection's zeros from the pass (a.zero_early), what they would save and cost.  One add per wavefront and block: adds to the
+    // same word are served one after the other (2^28, 1 %, adds per group / per block: kernel 72.4 / 39.8 us, whole step 1243 / 1214).
+    if (a.zero_early && wave < kGroupRows / 64) {
+        recorded = wave_sum(recorded); over_full = wave_sum(over_full);
+        if (lane == 0) {
+            if (recorded) atomicAdd(&a.ctr[node].recorded, recorded);
+            if (over_full) atomicAdd(&a.ctr[node].crowded, over_full);
+        }
+    }
     uint32_t *fine = a.fine_hist + node * kFineBins;
     for (int i = tid; i < kFineBins; i += T) { const uint32_t h = hist[i]; if (h) atomicAdd(&fine[i], h); }
 }
@@ -481,8 +485,8 @@ void launch_gather(const SelArgs &a, int batch, int cus, hipStream_t st) {
     if (counted && !a.seg_t) {
         // Blocks of 512 threads where the bitmap is searched, of 1024 where records are read: the search is the longer chain, and four
         // blocks per compute unit overlap it better; records of long lists are read in few, long pieces.  us, 512 / 1024 threads:
-        // 8 x 44.5 M at 0.1 % 23.8 / 27.1; 2^28 at 1 %, records of 32 45.0 / 32.0, of 24 beside zeros from the pass 73.4 / 70.0 (rows that hold more are searched
-        // in memory), 8 x 44.5 M at 1 %, in clusters, the same 93.0 / 97.8.
+        // 8 x 44.5 M at 0.1 % 23.8 / 27.1; 2^28 at 1 %, records of 32 45.0 / 32.0, of 24 beside zeros from the pass (rows that hold more are searched in memory; both
+        // with 32 us of adds that have since gone) 73.4 / 70.0, 8 x 44.5 M at 1 %, in clusters, the same 93.0 / 97.8.
         // One node's groups alone leave compute units without threads: whole groups where they would hold 512 candidates each if spread evenly, blocks
         // of 1024 threads from 1024 on, there for two nodes as well.  Pieces of 512 / EVEN, 512 threads / 1024: 60 M, 1 %, spread evenly 28.9 / 27.8 / 24.5, in clusters
         // 24.8 / 25.5 / 24.1; 40 M, 0.5 % 18.0 / 16.0 / 17.1; 2 x 60 M, 1 %, evenly 51.2 / 53.2 / 46.9, in clusters 37.8 / 42.5 / 37.2; 2 x 100 M, 1 %, in clusters
