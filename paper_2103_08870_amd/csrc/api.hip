@@ -1138,7 +1138,7 @@ extern "C" lgc_status lgc_innovation(lgc_ctx *ctx, const lgc_segments *seg, cons
     DeviceGuard guard(ctx->device);
     if (!guard.ok) return fail(ctx, LGC_EHIP, "cannot select device %d", ctx->device);
     launch_innovation(vals, out, (uint32_t)seg->n, batch, seg->n_seg, seg->off, seg->k, ctx->stats,
-                      (hipStream_t)stream);
+                      ctx->cus, (hipStream_t)stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e));
     return LGC_OK;
@@ -1348,7 +1348,7 @@ static lgc_status run_segmented(lgc_ctx *ctx, const lgc_segments *seg, const flo
             launch_accumulate(g, u, v, (uint32_t)seg->n, batch, stride, m, st, profile_bracket(ctx));
         }
     }
-    launch_seg_select(a, batch, st);
+    launch_seg_select(a, batch, ctx->cus, st);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e));
     return LGC_OK;

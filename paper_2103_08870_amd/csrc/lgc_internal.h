@@ -198,9 +198,9 @@ bool small_select_covers(uint64_t n, uint64_t k);
 void launch_small_select(const SelArgs &a, int batch, bool fused, int cus, hipStream_t st, Bracket br = Bracket());
 // per-layer selection (segmented.hip)
 void launch_seg_estimate(const SelArgs &a, int batch, bool fused, hipStream_t st);
-void launch_seg_select(const SelArgs &a, int batch, hipStream_t st);
+void launch_seg_select(const SelArgs &a, int batch, int cus, hipStream_t st);
 void launch_innovation(const float *vals, float *out, uint32_t n, int batch, uint32_t n_seg, const uint32_t *seg_off,
-                       const uint32_t *seg_k, Stats *stats, hipStream_t st);
+                       const uint32_t *seg_k, Stats *stats, int cus, hipStream_t st);
 
 // autoencoder.hip
 struct LayerDev {

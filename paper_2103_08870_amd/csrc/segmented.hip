@@ -181,14 +181,19 @@ void launch_seg_estimate(const SelArgs &a, int batch, bool fused, hipStream_t st
 // A long source is read four times (three digit passes and the output pass; it stays in the L2
 // after the first) in rolled loops: unrolling those for 64 K entries was an order of magnitude
 // slower (instruction fetch).
-constexpr int kSelKeep = 8;                // 16-byte groups per thread that the register-cached path holds
+
+// 16-byte groups per thread that a block holds in registers, by the blocks of the launch: eight while two blocks per compute unit are all of them
+// (16 K entries are read once), three beyond.  With three k_seg_select needs 72 vector registers and three of its blocks share a compute unit, with
+// eight 95 and two.  us, eight / three groups: 161 layers of 4 nodes, k_seg_select 22.1 / 17.3, whole step 403.4 / 397.8; 300 layers of 8 nodes, k_seg_select
+// 45.8 / 38.2, k_innovation 21.2 / 17.8; 40 layers of one node, 1 % of 2 M elements, k_seg_select 20.4 / 24.2.
+constexpr int kKeepFew = 8, kKeepMany = 3;
 constexpr int kSelThreads = 512;          // most segments and candidate runs are a few thousand entries
 
 // DENSE: instead of the compact (position, value) output and the clearing of v and u, every entry p
 // of the source gets dense[p] = its value if kept, +0 otherwise (the innovation component).
-// SMALL: the source spans at most kSelKeep rounds (16 K entries from begin & ~3 on): it is read once
+// SMALL: the source spans at most KEEP rounds (of 2 K entries, from begin & ~3 on): it is read once
 // and kept in registers for all four sweeps (the layers' candidate runs and the small layers).
-template <bool DENSE, bool SMALL>
+template <bool DENSE, bool SMALL, int KEEP>
 __device__ __forceinline__ uint32_t select_in_block(const uint32_t *__restrict__ bits, const uint32_t *__restrict__ pos,
                                                 const uint32_t begin, const uint32_t end, const uint32_t k,
                                                 float *__restrict__ v, float *__restrict__ u,
@@ -218,15 +223,15 @@ __device__ __forceinline__ uint32_t select_in_block(const uint32_t *__restrict__
     };
     auto inside = [&](uint32_t g, int c) { const uint32_t p = a0 + (g << 2) + c; return p >= begin && p < end; };
 
-    u4 keep[SMALL ? kSelKeep : 1];
+    u4 keep[SMALL ? KEEP : 1];
     if (SMALL) {
 #pragma unroll
-        for (int r = 0; r < kSelKeep; ++r) keep[r] = load_group(r * T + tid);
+        for (int r = 0; r < KEEP; ++r) keep[r] = load_group(r * T + tid);
     }
     auto each_key = [&](auto f) {
         if (SMALL) {
 #pragma unroll
-            for (int r = 0; r < kSelKeep; ++r) {
+            for (int r = 0; r < KEEP; ++r) {
                 if ((uint32_t)r < rounds) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c)
@@ -254,6 +259,8 @@ __device__ __forceinline__ uint32_t select_in_block(const uint32_t *__restrict__
     // ordered output: entries are enumerated round by round, thread by thread, c = 0..3
     uint32_t run_g = 0, run_e = 0;                           // kept-or-tied entries of the earlier rounds
     auto emit_round = [&](const u4 x, const uint32_t g) {
+        u4 at = {0u, 0u, 0u, 0u};                            // on their way while the round is counted
+        if (!DENSE && pos && g < groups) at = *(const u4 *)(pos + a0 + (g << 2));   // (the list's room is whole groups of four)
         bool fg[4], fe[4];
         uint32_t lg = 0, le = 0, tg = 0, te = 0;
 #pragma unroll
@@ -285,7 +292,7 @@ __device__ __forceinline__ uint32_t select_in_block(const uint32_t *__restrict__
                 if (inside(g, c)) dense[p] = kept ? __uint_as_float(x[c]) : 0.0f;
             } else if (kept) {
                 const uint32_t o = cg + (ce < quota ? ce : quota);
-                const uint32_t ix = pos ? pos[p] : p;
+                const uint32_t ix = pos ? at[c] : p;
                 if (o < k) { oidx[o] = ix; oval[o] = __uint_as_float(x[c]); }
                 else atomicAdd(&stats->errors, 1u);
                 v[ix] = 0.0f;
@@ -296,7 +303,7 @@ __device__ __forceinline__ uint32_t select_in_block(const uint32_t *__restrict__
     };
     if (SMALL) {
 #pragma unroll
-        for (int r = 0; r < kSelKeep; ++r)
+        for (int r = 0; r < KEEP; ++r)
             if ((uint32_t)r < rounds) emit_round(keep[r], r * T + tid);   // block-uniform condition
     } else {
         u4 x = load_group(tid);
@@ -312,76 +319,69 @@ __device__ __forceinline__ uint32_t select_in_block(const uint32_t *__restrict__
 }
 
 // One block per (segment, node).
+template <int KEEP>
 __global__ __launch_bounds__(kSelThreads) void k_seg_select(SelArgs a) {
     __shared__ __align__(16) uint32_t hist[4096];
     __shared__ uint32_t wave_tmp[16], res[2], sh_g[16], sh_e[16];
     const uint32_t l = blockIdx.x;
     const int node = blockIdx.y;
+    if (KEEP == kKeepFew) touch_arguments<SelArgs>();
+    // one wait for all of these: scalar loads, as nothing has been stored yet
+    const uint32_t k = a.seg_k[l], lo = a.seg_off[l], hi = a.seg_off[l + 1], o0 = a.seg_out[l], rank = a.seg_rank[l];
+    asm volatile("" ::"s"(k), "s"(lo), "s"(hi), "s"(o0), "s"(rank));
     // a selection of another kind on this context: the flat selection's carried thresholds lapse
     if (a.carry && l == 0 && threadIdx.x == 0) { a.carry[node].len = 0; a.carry[node].next_t_est = 0; }
-    const uint32_t k = a.seg_k[l];
     if (k == 0) return;
-    const uint32_t lo = a.seg_off[l], hi = a.seg_off[l + 1];
     float *v = a.v + (size_t)node * a.stride;
     float *u = a.u ? a.u + (size_t)node * a.stride : nullptr;
-    uint32_t *oidx = a.out_idx + (size_t)node * a.k + a.seg_out[l];
-    float *oval = a.out_vals + (size_t)node * a.k + a.seg_out[l];
+    uint32_t *oidx = a.out_idx + (size_t)node * a.k + o0;
+    float *oval = a.out_vals + (size_t)node * a.k + o0;
 
     bool from_list = false;
     uint32_t p0 = 0, p1 = 0;
     const uint32_t *cidx = a.cand_idx + (size_t)node * a.cap;
     const uint32_t *cval = a.cand_val + (size_t)node * a.cap;
-    if (a.seg_rank[l] != 0) {                                // sampled segment: its run of the candidate list
-        const uint32_t total = a.sel[node].cand_total;
-        if (total <= a.cap) {                                // nothing was lost
-            // candidates listed before position x: those of the rows before x's row (written by the
-            // gather kernel) plus the flags of x's row below x; wavefront 0 finds both ends
-            if (threadIdx.x < 64) {
-                const uint32_t lane = threadIdx.x & 31u, x = threadIdx.x < 32 ? lo : hi;
-                uint32_t c = 0;
-                const uint32_t row = x >> 10, e = x & 1023u;
-                if (x < a.n) {
-                    if (lane < (uint32_t)kRowWords) {
-                        // word 4s+j, bit i  <->  element 256 s + 4 i + j of the row: those with 256 s + 4 i + j < e
-                        const uint32_t sidx = lane >> 2, j = lane & 3u;
-                        const int below = (int)e - (int)(256u * sidx + j);          // 4 i < below
-                        const uint32_t cnt = below <= 0 ? 0u : (((uint32_t)below + 3u) >> 2 > 64u ? 64u : ((uint32_t)below + 3u) >> 2);
-                        const unsigned long long w = a.bitmap[((size_t)node * a.rows + row) * kRowWords + lane];
-                        const unsigned long long m = cnt >= 64u ? ~0ull : ((1ull << cnt) - 1ull);
-                        c = (uint32_t)__popcll(w & m);
-                    }
-                    if (lane == 16) c = a.row_prefix[(size_t)node * a.rows + row];
-                } else if (lane == 16) {
-                    c = total;                               // the vector's end: everything is before it
-                }
-#pragma unroll
-                for (int d = 16; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);   // sums inside each half of the wavefront
-                if (lane == 0) res[threadIdx.x >> 5] = c;
+    if (rank != 0) {                                         // sampled segment: its run of the candidate list
+        // candidates listed before position x: those of the rows before x's row (written by the
+        // gather kernel) plus the flags of x's row below x; wavefront 0 finds both ends
+        const uint32_t total = a.sel[node].cand_total;       // (on its way with what the ends are found from)
+        if (threadIdx.x < 64) {
+            const uint32_t lane = threadIdx.x & 31u, x = threadIdx.x < 32 ? lo : hi;
+            uint32_t c = 0;
+            const uint32_t row = x >> 10, e = x & 1023u;
+            if (x < a.n) {
+                const unsigned long long w = a.bitmap[((size_t)node * a.rows + row) * kRowWords + (lane & (kRowWords - 1u))];
+                const uint32_t rows_before = a.row_prefix[(size_t)node * a.rows + row];
+                // word 4s+j, bit i  <->  element 256 s + 4 i + j of the row: those with 256 s + 4 i + j < e
+                const uint32_t sidx = lane >> 2 & 3u, j = lane & 3u;
+                const int below = (int)e - (int)(256u * sidx + j);          // 4 i < below
+                const uint32_t cnt = below <= 0 ? 0u : (((uint32_t)below + 3u) >> 2 > 64u ? 64u : ((uint32_t)below + 3u) >> 2);
+                const unsigned long long m = cnt >= 64u ? ~0ull : ((1ull << cnt) - 1ull);
+                c = lane < (uint32_t)kRowWords ? (uint32_t)__popcll(w & m) : lane == 16 ? rows_before : 0u;
+            } else if (lane == 16) {
+                c = total;                                   // the vector's end: everything is before it
             }
-            __syncthreads();
-            p0 = res[0]; p1 = res[1];
-            __syncthreads();
-            from_list = p1 - p0 >= k;
+#pragma unroll
+            for (int d = 16; d >= 1; d >>= 1) c += __shfl_xor(c, d, 64);   // sums inside each half of the wavefront
+            if (lane == 0) res[threadIdx.x >> 5] = c;
         }
+        __syncthreads();
+        if (total <= a.cap) { p0 = res[0]; p1 = res[1]; }    // nothing was lost
+        __syncthreads();
+        from_list = total <= a.cap && p1 - p0 >= k;
     }
-    constexpr uint32_t kSmall = (uint32_t)kSelKeep * kSelThreads * 4u;
-    uint32_t thr;
-    if (from_list) {
-        if (p1 - (p0 & ~3u) <= kSmall)
-            thr = select_in_block<false, true>(cval, cidx, p0, p1, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
-        else
-            thr = select_in_block<false, false>(cval, cidx, p0, p1, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
-    } else {
-        if (hi - (lo & ~3u) <= kSmall)
-            thr = select_in_block<false, true>((const uint32_t *)v, nullptr, lo, hi, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
-        else
-            thr = select_in_block<false, false>((const uint32_t *)v, nullptr, lo, hi, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
-    }
+    constexpr uint32_t kSmall = (uint32_t)KEEP * kSelThreads * 4u;
+    auto select = [&](const uint32_t *bits, const uint32_t *pos, const uint32_t begin, const uint32_t end) {
+        if (end - (begin & ~3u) <= kSmall)
+            return select_in_block<false, true, KEEP>(bits, pos, begin, end, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
+        return select_in_block<false, false, KEEP>(bits, pos, begin, end, k, v, u, oidx, oval, nullptr, a.stats, hist, wave_tmp, res, sh_g, sh_e);
+    };
+    const uint32_t thr = from_list ? select(cval, cidx, p0, p1) : select((const uint32_t *)v, nullptr, lo, hi);
     // (last: the layers' adds to one word are served one after the other, and later loads would wait
     // for this block's; 161 layers of 4 nodes, before / after the selection: 23.1 / 22.1 us)
-    if (a.seg_rank[l] != 0 && threadIdx.x == 0) atomicAdd(from_list ? &a.stats->fast : &a.stats->fallback, 1u);
+    if (rank != 0 && threadIdx.x == 0) atomicAdd(from_list ? &a.stats->fast : &a.stats->fallback, 1u);
     // sampled layers: the record of this layer's exact thresholds, and its offer to the next selection
-    if (a.seg_carry && a.seg_rank[l] != 0 && threadIdx.x == 0) {
+    if (a.seg_carry && rank != 0 && threadIdx.x == 0) {
         Carry *c = a.seg_carry + (size_t)node * a.n_seg + l;
         // a layer that keeps few values may flag k + 256: what its k-th magnitude does is noisy, and the candidates cost nothing
         const float most = fmaxf(a.carry_most, log2f((float)(k + 256u) / (float)k));
@@ -393,6 +393,7 @@ __global__ __launch_bounds__(kSelThreads) void k_seg_select(SelArgs a) {
 // Innovation component (Alg. 1: threshold_inv, mask_inv; Sec. IV-C): per segment of the vector of
 // selected values the k_l largest magnitudes stay, everything else becomes +0.  The input is not
 // modified.  One block per (segment, node).
+template <int KEEP>
 __global__ __launch_bounds__(kSelThreads) void k_innovation(const float *__restrict__ vals, float *__restrict__ out,
                                                             uint32_t n, const uint32_t *__restrict__ seg_off,
                                                             const uint32_t *__restrict__ seg_k, Stats *stats) {
@@ -406,23 +407,27 @@ __global__ __launch_bounds__(kSelThreads) void k_innovation(const float *__restr
         for (uint32_t p = lo + threadIdx.x; p < hi; p += kSelThreads) dst[p] = 0.0f;
         return;
     }
-    if (hi - (lo & ~3u) <= (uint32_t)kSelKeep * kSelThreads * 4u)
-        select_in_block<true, true>((const uint32_t *)src, nullptr, lo, hi, k, nullptr, nullptr, nullptr, nullptr, dst, stats,
+    if (hi - (lo & ~3u) <= (uint32_t)KEEP * kSelThreads * 4u)
+        select_in_block<true, true, KEEP>((const uint32_t *)src, nullptr, lo, hi, k, nullptr, nullptr, nullptr, nullptr, dst, stats,
                                          hist, wave_tmp, res, sh_g, sh_e);
     else
-        select_in_block<true, false>((const uint32_t *)src, nullptr, lo, hi, k, nullptr, nullptr, nullptr, nullptr, dst, stats,
+        select_in_block<true, false, KEEP>((const uint32_t *)src, nullptr, lo, hi, k, nullptr, nullptr, nullptr, nullptr, dst, stats,
                                           hist, wave_tmp, res, sh_g, sh_e);
 }
 
+static bool few_blocks(uint32_t n_seg, int batch, int cus) { return (uint64_t)n_seg * batch <= 2ull * cus; }
+
 void launch_innovation(const float *vals, float *out, uint32_t n, int batch, uint32_t n_seg, const uint32_t *seg_off,
-                       const uint32_t *seg_k, Stats *stats, hipStream_t st) {
+                       const uint32_t *seg_k, Stats *stats, int cus, hipStream_t st) {
     dim3 grid(n_seg, batch);
-    hipLaunchKernelGGL(k_innovation, grid, dim3(kSelThreads), 0, st, vals, out, n, seg_off, seg_k, stats);
+    if (few_blocks(n_seg, batch, cus)) hipLaunchKernelGGL(k_innovation<kKeepFew>, grid, dim3(kSelThreads), 0, st, vals, out, n, seg_off, seg_k, stats);
+    else hipLaunchKernelGGL(k_innovation<kKeepMany>, grid, dim3(kSelThreads), 0, st, vals, out, n, seg_off, seg_k, stats);
 }
 
-void launch_seg_select(const SelArgs &a, int batch, hipStream_t st) {
+void launch_seg_select(const SelArgs &a, int batch, int cus, hipStream_t st) {
     dim3 grid(a.n_seg, batch);
-    hipLaunchKernelGGL(k_seg_select, grid, dim3(kSelThreads), 0, st, a);
+    if (few_blocks(a.n_seg, batch, cus)) hipLaunchKernelGGL(k_seg_select<kKeepFew>, grid, dim3(kSelThreads), 0, st, a);
+    else hipLaunchKernelGGL(k_seg_select<kKeepMany>, grid, dim3(kSelThreads), 0, st, a);
 }
 
 }  // namespace lgc

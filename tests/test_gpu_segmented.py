@@ -79,6 +79,35 @@ def test_small_segments_selected_from_v(B, oracle, n, n_seg, batch, pad):
     seg.close(); ctx.close()
 
 
+@pytest.mark.parametrize("held,more,first", [(6_144, 300, 1), (6_144, 300, 4), (16_384, 0, 1), (16_384, 0, 6)])
+def test_sources_at_the_edges_of_the_register_path(B, oracle, held, more, first):
+    # A block keeps up to `held` entries from its source's start (rounded down to 4) on in registers, 6144 in launches of more than two blocks per
+    # compute unit (here by 300 layers of 3 elements) and 16384 in others: layers of about that many elements, too dense to be sampled, that start
+    # at different places in a group of four, and runs of the list on both sides of it.
+    sizes = [first, held - 1, held, held + 1, held - 5, held + 3, held - 2, 4_096, 2_049, 900_000, 400_001, held - 3] + [3] * more
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    n, lens = int(off[-1]), np.diff(off)
+    ks = np.array([1, held - 1, held // 3, held // 2, held // 4, held + 3, held // 3, 40, 2_049, 9_000, 3_000, held // 2] + [1] * more)
+    rng = np.random.default_rng(first + held)
+    ctx = B.Context(n, int(ks.sum()), 2)
+    seg = B.Segments(off.tolist(), ks.tolist())
+    B.lgc_reserve(ctx, seg=seg)
+    v0 = rng.laplace(0, 1e-2, (2, n)).astype(np.float32)
+    v0[1] = np.round(v0[1] * 512) / 512                      # few magnitudes among the small ones: ties at the cuts
+    u0, g = rng.standard_normal((2, 2, n)).astype(np.float32) * 1e-2
+    fast, fallback = run_segmented(B, oracle, ctx, seg, off, ks, v0, u0)
+    assert fast + fallback == 4 and fast >= 2                # the two long layers of two nodes are sampled
+    run_segmented(B, oracle, ctx, seg, off, ks, v0, u0, g)
+    kept = B.Segments(off.tolist(), np.maximum(1, lens // 10).tolist())
+    inno = B.Context(n, n, 2)
+    out = torch.full((2, n), 7.0, device="cuda")
+    B.lgc_innovation(inno, kept, dev(v0), out)
+    assert B.lgc_stats(inno)[2] == 0
+    for b in range(2):
+        assert same_bits(out[b], oracle.innovation(v0[b], off, np.maximum(1, lens // 10))), b
+    inno.close(); kept.close(); seg.close(); ctx.close()
+
+
 def mixed_layout():
     """Sampled and direct segments side by side, boundaries at odd places (rows of 1024 elements
     that hold several segments, segments that start and end inside a row)."""
