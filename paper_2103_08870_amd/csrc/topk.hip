@@ -243,6 +243,7 @@ __device__ __forceinline__ uint32_t row_element(const unsigned long long *w, uin
 
 template <bool HIST, bool COUNTED, int ROWS, int THREADS>
 __global__ __launch_bounds__(THREADS) void k_gather(SelArgs a) {
+    if (!HIST) touch_arguments<SelArgs>();
     constexpr int kGatherRows = ROWS;
     constexpr int kPairs = (ROWS * kRowWords / 2 + THREADS - 1) / THREADS;   // pairs of bitmap words per thread
     static_assert(ROWS % 64 == 0 && ROWS <= THREADS && (ROWS & (ROWS - 1)) == 0, "rows per block");
@@ -1436,6 +1437,7 @@ __device__ __forceinline__ void finish_node(const SelArgs &a, const int node, co
 }
 
 __global__ __launch_bounds__(1024) void k_finish_or_exact(SelArgs a, int report) {
+    touch_arguments<SelArgs>();
     __shared__ __align__(16) uint32_t hist[kFinishBins];
     __shared__ uint32_t wave_tmp[16], res[2];
     __shared__ uint32_t offs[kFinishRows + 1];
