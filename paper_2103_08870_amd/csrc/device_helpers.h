@@ -20,21 +20,6 @@ __device__ __forceinline__ uint32_t lanes_below(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// Brings the lines of a kernel's arguments, of which Args is the first, to the scalar cache at once: they are read where they are used, and each
-// line is a wait of its own there.  For kernels that are one chain of waits in few blocks; with more blocks than are resident at once, or where what
-// is held from here on costs registers, it loses (us, without / with: k_finish_or_exact, 1 M, 12.6 / 12.2; k_seg_select, 40 layers of 2 M, 12.1 / 11.1, 161 of 4 x
-// 25.6 M 17.5 / 17.9; k_gather, 4 x 25.6 M, by layers 13.6 / 13.3, flat 16.9 / 20.1).
-template <typename Args>
-__device__ __forceinline__ void touch_arguments() {
-    typedef const __attribute__((address_space(4))) uint32_t *Scalar;
-    Scalar at = (Scalar)__builtin_amdgcn_kernarg_segment_ptr();
-    asm("" : "+s"(at));
-    uint32_t any = at[sizeof(Args) / 4 - 1];
-#pragma unroll
-    for (uint32_t i = 0; i < sizeof(Args) / 4; i += 16) any ^= at[i];
-    asm volatile("" ::"s"(any));
-}
-
 // Inclusive prefix sum over the lanes of a wavefront, register to register (DPP: four shifts inside rows of 16 lanes,
 // two row broadcasts).  All 64 lanes must be active.  A shuffle through the LDS unit costs some 60 cycles a step.
 __device__ __forceinline__ uint32_t wave_prefix(uint32_t x) {

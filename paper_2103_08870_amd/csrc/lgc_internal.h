@@ -174,6 +174,21 @@ struct SelArgs {
     uint32_t *row_prefix;     // [batch][rows]  candidates listed before each row (written by the gather kernel)
 };
 
+// Brings the lines of a kernel's arguments, of which Args is the first, to the scalar cache at once: they are read where they are used, and each
+// line is a wait of its own there.  For kernels that are one chain of waits in few blocks; with more blocks than are resident at once, or where what
+// is held from here on costs registers, it loses (us, without / with: k_finish_or_exact, 1 M, 12.6 / 12.2; k_seg_select, 40 layers of 2 M, 12.1 / 11.1, 161 of 4 x
+// 25.6 M 17.5 / 17.9; k_gather, 4 x 25.6 M, by layers 13.6 / 13.3, flat 16.9 / 20.1).
+template <typename Args>
+__device__ __forceinline__ void touch_arguments() {
+    typedef const __attribute__((address_space(4))) uint32_t *Scalar;
+    Scalar at = (Scalar)__builtin_amdgcn_kernarg_segment_ptr();
+    asm("" : "+s"(at));
+    uint32_t any = at[sizeof(Args) / 4 - 1];
+#pragma unroll
+    for (uint32_t i = 0; i < sizeof(Args) / 4; i += 16) any ^= at[i];
+    asm volatile("" ::"s"(any));
+}
+
 // launchers (topk.hip) — all asynchronous on `st`
 // Timing of a streaming call's launches (null events: none): `start` is given the start time of the first
 // launch, `stop` the end time of the last one, by the launches themselves, with no packet of their own in the queue.
