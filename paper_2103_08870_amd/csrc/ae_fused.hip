@@ -59,8 +59,8 @@ namespace {
 
 __device__ __forceinline__ float leaky_f(float x, float slope) { return x > 0.f ? x : slope * x; }
 
-// The non-linearity at a position: the factors of positive and other values, both 0 where the position does not exist (an Inf
-// there leaves a NaN, as the redo's trigger).
+// The non-linearity at a position: the factors of positive and other values, both 0 where the position does not exist.  A sum that is
+// not finite leaves a NaN there, where a 0 belongs: right for the split's pass alone, whose NaNs make the block redo its outputs.
 struct Act {
     float pos, neg;
     __device__ __forceinline__ Act(const float slope, const bool valid) : pos(valid ? 1.f : 0.f), neg(valid ? slope : 0.f) {}
@@ -688,8 +688,10 @@ __device__ __forceinline__ void encode_run(const float *__restrict__ x, float *_
     float *f = (float *)buf;
     conv1([&](const int i, const float (&y)[8]) {
         float *row = f + ((i & 1) ? (N2 + 1) * row_floats(C1) : 0) + (i >> 1) * row_floats(C1) + wave * 8;
-        *(f4v *)row = (f4v){y[0], y[1], y[2], y[3]};
-        *(f4v *)(row + 4) = (f4v){y[4], y[5], y[6], y[7]};
+        const long long q = 8 * p0 - 7 + i;
+        const bool valid = q >= 0 && q < (long long)l1;   // (chosen, not multiplied: see Act)
+        *(f4v *)row = valid ? (f4v){y[0], y[1], y[2], y[3]} : (f4v){0.f, 0.f, 0.f, 0.f};
+        *(f4v *)(row + 4) = valid ? (f4v){y[4], y[5], y[6], y[7]} : (f4v){0.f, 0.f, 0.f, 0.f};
     });
     __syncthreads();
     layer_fp32<C1, C2, N2, W>(f, w.w2, w.b2, wave, 4 * p0 - 3, l2, slope);

@@ -137,11 +137,13 @@ def test_error_against_64_bits(B, k, batch):
 
 
 # Positive weights: an Inf stays one Inf all the way (weights of both signs would turn it into NaN at once), so the
-# values that bf16 parts cannot carry have one right answer.  The largest finite values round to Inf in bf16.  Blocks of
-# 15 latent positions (600 values; the decoder's of 7, and of 15 for 5 nodes x 6 000), and of 31 where there are enough of them (7 nodes x 10 000); the values sit inside a
-# block, where two blocks' windows overlap, and in the last, partly filled block.  At 1e-33 the split's low parts, and their products,
+# values that bf16 parts cannot carry have one right answer.  The largest finite values round to Inf in bf16.  The encoder's runs of
+# 15 latent positions with four blocks each (600 values), two (5 nodes x 6 000) and one (7 x 4 802), of 31 (7 x 10 000), and of both (7 x 18 353); the decoder's of 7 and
+# of 15.  The values sit inside a block, where two blocks' windows overlap, and at the very end: where a layer's length is even and the next
+# one's odd (lengths that leave 2 of 4 values over: conv1; 604: conv2; 600: conv3), that is also the input of a position that
+# does not exist, and which the next layer's last output reads as 0.  At 1e-33 the split's low parts, and their products,
 # are below the least normal number (the reconstruction, about 3e-38, is just above it); no biases, which would hide it.
-@pytest.mark.parametrize("k,batch", [(600, 2), (6_000, 5), (10_000, 7), (18_353, 7)])
+@pytest.mark.parametrize("k,batch", [(600, 2), (602, 2), (604, 2), (608, 2), (4_802, 7), (6_000, 5), (10_000, 7), (10_002, 7), (18_353, 7)])
 @pytest.mark.parametrize("special", [np.inf, np.nan, 3.4e38, 1e-30, 1e-33, 0.0])
 def test_values_that_the_split_cannot_carry(B, oracle, special, k, batch):
     def change(a, which):
@@ -166,6 +168,25 @@ def test_values_that_the_split_cannot_carry(B, oracle, special, k, batch):
     assert_near(rec, orec, ("reconstruction", special))
     if not np.isfinite(special):
         assert (~np.isfinite(ol)).any() and np.isfinite(ol[0]).all()   # the case is what it says
+    ae.close()
+
+
+# The sum at the position behind conv1's last one overflows (the last input times the first tap), no sum at a position that exists does.
+@pytest.mark.parametrize("k,batch", [(602, 2), (4_802, 7), (6_002, 5), (10_002, 7)])
+def test_a_sum_that_overflows_where_there_is_no_position(B, oracle, k, batch):
+    def change(a, which):
+        if which % 2:
+            return np.abs(a)
+        a = np.abs(a) * np.float32(0.05)
+        if which == 0 and a.shape[1] == 1:
+            a[:, 0, 0], a[:, 0, 2] = 3.0, 1e-5
+        return a
+    ae, enc, dec, host = stacks(B, change)
+    x = np.abs(np.random.default_rng(k).normal(0, 1, (batch, k))).astype(np.float32)
+    x[batch - 1, k - 1] = 3e38
+    lat, ol, _, _ = both_ways(B, oracle, ae, enc, dec, host, x, np.ones((batch, 4 * -(-k // 16)), np.float32))
+    assert np.isfinite(ol).all() and ol[-1].max() > 1e30    # the case is what it says
+    assert_near(lat, ol, "latent")
     ae.close()
 
 
