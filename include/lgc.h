@@ -184,8 +184,11 @@ uint64_t lgc_latent_len(const lgc_ae *ae, uint64_t k);
  * their intermediate tensors in the context's activation scratch, which must
  * have been reserved (lgc_reserve); the call itself never allocates.  The
  * stacks of Table I / Table II run as one launch that keeps them on chip, and
- * use the reserved scratch only in place (latent overlapping vals, in
- * lgc_decode rec overlapping latent) or if a weight is not finite. */
+ * use the activation scratch only in place (latent overlapping vals, in
+ * lgc_decode rec overlapping latent) or if a weight is not finite.  Table I's
+ * exchanges partial sums between blocks through another part of the context
+ * where the vectors are short (up to 128 runs of 240 values, all nodes
+ * together): as everywhere, calls on one context must not overlap. */
 lgc_status lgc_encode(lgc_ctx *ctx, const lgc_ae *ae, const float *vals, uint64_t k, int batch,
                       float *latent, void *stream);
 
@@ -314,7 +317,8 @@ lgc_status lgc_average(lgc_ctx *ctx, const float *x, uint64_t len, int batch, fl
  *   ae  (nullable): the activation buffers lgc_encode / lgc_decode /
  *        lgc_decode_innovation need with this autoencoder for inputs of up to
  *        k values per node and up to `batch` nodes (the largest intermediate
- *        tensor of either stack, twice);
+ *        tensor of either stack, twice; with the stack of Table I once 1 MB
+ *        that later reservations leave where it is);
  *   seg (nullable): the per-layer thresholds and the candidate list of
  *        lgc_topk_segmented / lgc_accumulate_topk_segmented with this plan.
  * A later reservation only ever grows the buffers, so one call per

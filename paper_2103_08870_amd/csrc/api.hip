@@ -41,7 +41,8 @@ struct lgc_ctx {
     uint64_t rec_rows = 0;
     float *act[2] = {nullptr, nullptr};  // autoencoder activations (ping-pong), grown on demand
     size_t act_floats = 0;
-    uint32_t *taken = nullptr;           // counts of the encoder's blocks that share a run of positions (zero between calls), kTakenWords
+    // where the encoder's blocks that share a run of positions meet: never replaced, as a recorded graph holds its address
+    EncoderScratch shares;
     // per-layer selection: thresholds [max_batch][n_seg] and a candidate list of its own, grown on demand
     uint32_t *seg_t = nullptr, *seg_cand = nullptr, *seg_row_prefix = nullptr;
     size_t seg_t_words = 0, seg_cand_words = 0;
@@ -217,14 +218,12 @@ StateLayout state_layout(int max_batch, uint32_t status_cand_stride, uint32_t st
     return L;
 }
 
-constexpr uint32_t kTakenWords = 1024;
-
 // The selection scratch of a context for (max_n, max_k, max_batch): byte offsets of its parts in one block of
-// device memory.  Everything before `samples` (statistics, carried thresholds, counts, state sets) must start at zero.
+// device memory.  Everything before `samples` (statistics, carried thresholds, state sets) must start at zero.
 struct ScratchLayout {
     bool ok = false;
     uint32_t cap = 0, rows = 0, status_cand_stride = 0, status_exact_stride = 0, state_words = 0;
-    size_t stats = 0, carry = 0, taken = 0, state[2] = {0, 0}, samples = 0, row_count = 0, bitmap = 0, cand_idx = 0, cand_val = 0;
+    size_t stats = 0, carry = 0, state[2] = {0, 0}, samples = 0, row_count = 0, bitmap = 0, cand_idx = 0, cand_val = 0;
     size_t bytes = 0;
 };
 
@@ -242,7 +241,6 @@ ScratchLayout scratch_layout(uint64_t max_n, uint64_t max_k, int max_batch, bool
     auto carve = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, A); return o; };
     s.stats = carve(sizeof(Stats));
     s.carry = carve(B * sizeof(Carry));
-    if (two_state_sets) s.taken = carve(kTakenWords * 4);   // (a context; the fixed array of the call without one runs no encoder)
     s.state[0] = carve(L.words * 4);
     s.state[1] = two_state_sets ? carve(L.words * 4) : s.state[0];
     s.samples = carve(B * kSample * 4);
@@ -263,7 +261,6 @@ void bind_scratch(lgc_ctx *c, void *base_ptr, const ScratchLayout &s) {
     c->state_words = s.state_words;
     c->stats = (Stats *)(base + s.stats);
     c->carry = (Carry *)(base + s.carry);
-    c->taken = s.taken ? (uint32_t *)(base + s.taken) : nullptr;
     c->state[0] = (uint32_t *)(base + s.state[0]);
     c->state[1] = (uint32_t *)(base + s.state[1]);
     c->samples = (uint32_t *)(base + s.samples);
@@ -542,6 +539,7 @@ extern "C" void lgc_destroy(lgc_ctx *ctx) {
     (void)hipDeviceSynchronize();
     for (hipEvent_t e : ctx->ev) (void)hipEventDestroy(e);
     if (ctx->act[0]) (void)hipFree(ctx->act[0]);
+    if (ctx->shares.sums) (void)hipFree(ctx->shares.sums);
     if (ctx->seg_t) (void)hipFree(ctx->seg_t);
     if (ctx->seg_carry) (void)hipFree(ctx->seg_carry);
     if (ctx->seg_cand) (void)hipFree(ctx->seg_cand);
@@ -927,6 +925,25 @@ static lgc_status ensure_act(lgc_ctx *ctx, size_t floats) {
     return LGC_OK;
 }
 
+// The same for the blocks that share a run: the counts start at zero.  Of one size whatever the calls, so that later reservations leave it alone.
+static lgc_status ensure_shares(lgc_ctx *ctx, const lgc_ae *ae) {
+    if (ctx->shares.sums || !encoder_fused_covers(ae->enc_dev.data(), (int)ae->enc_dev.size())) return LGC_OK;
+    EncoderScratch made = encoder_scratch(ctx->cus);
+    const size_t sums = made.sum_floats * 4, bytes = sums + made.taken_words * 4;
+    void *block = nullptr;
+    HIP_TRY(ctx, hipMalloc(&block, bytes));
+    hipError_t e = hipMemset((char *)block + sums, 0, bytes - sums);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e != hipSuccess) {
+        (void)hipFree(block);
+        return fail(ctx, LGC_EHIP, "hipMemset: %s", hipGetErrorString(e));
+    }
+    made.sums = (float *)block;
+    made.taken = (uint32_t *)((char *)block + sums);
+    ctx->shares = made;
+    return LGC_OK;
+}
+
 static lgc_status check_ae_call(lgc_ctx *ctx, const lgc_ae *ae, const void *a, const void *b, uint64_t k, int batch) {
     if (!ctx) return fail(nullptr, LGC_EINVAL, "ctx is NULL");
     if (!ae) return fail(ctx, LGC_EINVAL, "ae is NULL");
@@ -972,7 +989,7 @@ static lgc_status run_encode(lgc_ctx *ctx, const lgc_ae *ae, const float *vals, 
                                      "lgc_reserve(ctx, ae, k, batch, NULL) once beforehand", (unsigned long long)k, batch);
     if (!overlap(vals, k * batch, latent, (uint64_t)batch * ae->enc[nl - 1].c_out * len[nl]) &&
         launch_encoder_fused(vals, latent, ae->enc_dev.data(), (int)nl, len.data(), batch, ae->slope, ae->enc_limits, ctx->cus,
-                             EncoderScratch{ctx->act[0], ctx->act_floats, ctx->taken, ctx->taken ? kTakenWords : 0u}, st)) {
+                             ctx->shares, st)) {
         hipError_t e1 = hipGetLastError();
         if (e1 != hipSuccess) return fail(ctx, LGC_EHIP, "kernel launch: %s", hipGetErrorString(e1));
         return LGC_OK;
@@ -1434,7 +1451,7 @@ extern "C" lgc_status lgc_reserve(lgc_ctx *ctx, const lgc_ae *ae, uint64_t k, in
     if (!guard.ok) return fail(ctx, LGC_EHIP, "cannot select device %d", ctx->device);
     return no_throw(ctx, [&]() -> lgc_status {
         lgc_status s = LGC_OK;
-        if (ae && k > 0 && (s = ensure_act(ctx, act_need(ae, k, batch))) != LGC_OK) return s;
+        if (ae && k > 0 && ((s = ensure_act(ctx, act_need(ae, k, batch))) != LGC_OK || (s = ensure_shares(ctx, ae)) != LGC_OK)) return s;
         if (seg && (s = ensure_seg_scratch(ctx, seg)) != LGC_OK) return s;
         return LGC_OK;
     });

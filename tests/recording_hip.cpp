@@ -15,6 +15,8 @@ std::map<const void *, std::string> &kernels() { static std::map<const void *, s
 std::string log_text, taken;
 uintptr_t next_address = 1ull << 44;
 unsigned char static_array[64];
+std::map<uintptr_t, size_t> &held() { static std::map<uintptr_t, size_t> h; return h; }   // device memory: address, bytes
+const void *shares[4];   // the first pointers of the last encoder launch's first argument: input, output, sums, counts
 
 hipError_t record_launch(const void *f, dim3 grid) {
     char dims[64];
@@ -37,7 +39,18 @@ static size_t call_lds;
 static hipStream_t call_stream;
 hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t l, hipStream_t s) { call_grid = g; call_block = b; call_lds = l; call_stream = s; return hipSuccess; }
 hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *l, hipStream_t *s) { *g = call_grid; *b = call_block; *l = call_lds; *s = call_stream; return hipSuccess; }
-hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **, size_t, hipStream_t) { return record_launch(f, grid); }
+hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3, void **args, size_t, hipStream_t) {
+    if (kernels()[f].find("k_encoder_fused") != std::string::npos) memcpy(shares, args[0], sizeof shares);
+    return record_launch(f, grid);
+}
+// where the last encoder launch's blocks meet, and the device memory from `at` on that is still allocated
+const void *encoder_shares(int counts) { return shares[2 + counts]; }
+size_t allocated_from(uintptr_t at) {
+    auto next = held().upper_bound(at);
+    if (next == held().begin()) return 0;
+    --next;
+    return at < next->first + next->second ? next->first + next->second - at : 0;
+}
 hipError_t hipExtLaunchKernel(const void *f, dim3 grid, dim3, void **, size_t, hipStream_t, hipEvent_t, hipEvent_t, int) { return record_launch(f, grid); }
 hipError_t hipGetDeviceCount(int *n) { *n = 1; return hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
@@ -54,11 +67,12 @@ hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) {
 }
 hipError_t hipMalloc(void **p, size_t bytes) {
     *p = (void *)next_address;
+    held()[next_address] = bytes;
     next_address += (bytes + 8191) / 4096 * 4096;
     log_text += "malloc " + std::to_string(bytes) + "\n";
     return hipSuccess;
 }
-hipError_t hipFree(void *) { return hipSuccess; }
+hipError_t hipFree(void *p) { held().erase((uintptr_t)p); return hipSuccess; }
 void *pinned;   // the last pinned allocation
 hipError_t hipHostMalloc(void **p, size_t bytes, unsigned) { *p = pinned = calloc(1, bytes); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipHostFree(void *p) { free(p); return hipSuccess; }

@@ -85,6 +85,35 @@ def test_lengths_at_the_edges_of_an_encoder_run(B, oracle, k, batch):
     ctx.close(); ae.close()
 
 
+def test_a_recorded_encode_replays_after_a_larger_reservation(B):
+    # 4 and 2 blocks share a run; the activation scratch moves in between, as eager calls of the context need more of it
+    ae, _, _, _ = stacks(B)
+    small, large = [(1, 1_023), (4, 5_000)], (8, 30_000)
+    ctx = B.Context(large[1], large[1], large[0])
+    xs = [torch.randn(shape, device="cuda") * 0.3 for shape in small + [large]]
+    lats = [torch.empty((x.shape[0], B.lgc_latent_len(ae, x.shape[1])), device="cuda") for x in xs]
+    graphs, want = [], []
+    for x, lat in zip(xs[:2], lats):
+        B.lgc_reserve(ctx, ae, x.shape[1], x.shape[0])
+        B.lgc_encode(ctx, ae, x, lat)
+        want.append(lat.clone())
+        torch.cuda.synchronize()
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            B.lgc_encode(ctx, ae, x, lat)
+    B.lgc_reserve(ctx, ae, large[1], large[0])
+    other = torch.full((1 << 22,), 5.0, device="cuda")     # what may have taken the old scratch's place
+    for _ in range(4):
+        for graph, lat, first in zip(graphs, lats, want):
+            lat.fill_(7.0)
+            graph.replay()
+            B.lgc_encode(ctx, ae, xs[2], lats[2])
+            torch.cuda.synchronize()
+            assert torch.equal(lat, first)
+    assert (other == 5.0).all()
+    ctx.close(); ae.close()
+
+
 # The decoder's blocks take 7 latent positions (112 values), 15 (240), or 15 with the weights through the LDS: a last block of all, of one and of two.
 @pytest.mark.parametrize("k,batch", [(112, 1), (113, 1), (224, 2), (112 * 3 + 17, 3), (3840, 8), (3841, 8), (3857, 8), (7920, 8), (7921, 8), (7937, 8)])
 def test_lengths_at_the_edges_of_a_decoder_block(B, oracle, k, batch):

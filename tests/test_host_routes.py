@@ -213,6 +213,29 @@ def who_samples(h):
     return out
 
 
+SHARED = [  # values, nodes; blocks per run of 15 positions: on either side of what 256 compute units have room for
+    (1_023, 1, 4), (240, 64, 4), (241, 32, 4), (240, 65, 2), (240, 128, 2), (15_360, 2, 2), (15_361, 2, 1)]
+
+
+def shared_runs(h):
+    """Per (values, nodes) of an encode, as one that is recorded in a graph would hold it: blocks per run, and the bytes still allocated where its
+    blocks meet (sums, counts) after larger reservations."""
+    max_k = 1_000_000
+    ctx, ae = h.ctx(max_k, max_k, 128), h.autoencoder(*PAPER)
+    shares, allocated = h.fake.encoder_shares, h.fake.allocated_from
+    shares.restype, allocated.restype = p, C.c_size_t
+    out, held = [], []
+    for k, batch, _ in SHARED:
+        assert h.lib.lgc_reserve(ctx, ae, u64(k), batch, None) == 0
+        h.log()
+        assert h.encode(ctx, ae, 1 << 40, k, batch, 1 << 41) == 0
+        (_, kernel, grid), = h.log()
+        out.append([kernel, grid])
+        held.append([shares(0), shares(1)])
+    assert h.lib.lgc_reserve(ctx, ae, u64(max_k), 8, None) == 0
+    return [x + [allocated(u64(a or 0)) for a in addresses] for x, addresses in zip(out, held)]
+
+
 @pytest.fixture(scope="module")
 def answers(tmp_path_factory):
     """Every scenario (a function above, by name), run in one process of its own."""
@@ -277,6 +300,14 @@ def test_the_pass_samples_only_in_a_run_of_carried_thresholds(answers):
         "and four again": "lll", "recorded": "l", "no answer to that": "l", "not recorded": "p", "after an exact selection": "l" * 16 + "p", "option off": "ll"}
 
 
+def test_where_an_encoder_s_blocks_meet_outlives_later_reservations(answers):
+    for (k, batch, blocks), (kernel, grid, sums, counts) in zip(SHARED, answers["shared_runs"]):
+        runs = -(-(-(-k // 16)) // 15)
+        assert kernel == "k_encoder_fused" and grid == [runs, batch, blocks], (k, batch, grid)
+        # as much room as the blocks write: 64 channels x 16 positions each, a count per run
+        assert blocks == 1 or (sums >= 4096 * runs * batch * blocks and counts >= 4 * runs * batch), (k, batch, sums, counts)
+
+
 if __name__ == "__main__":
     host = Host(sys.argv[1], sys.argv[2])
-    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place, records, fall_backs_of_the_one_launch_finish, gathers, zeros, who_samples)}))
+    print(json.dumps({f.__name__: f(host) for f in (paper_stacks_in_place, records, fall_backs_of_the_one_launch_finish, gathers, zeros, who_samples, shared_runs)}))
