@@ -29,9 +29,9 @@
 // do to an output has a bound that the weights give (fused_limits).  A block with an output that is not finite, or is
 // small enough for the bound to matter, redoes its outputs in plain fp32 on the fp32 matrix cores, which keep small numbers
 // (inputs of about 1e-33, no biases: the reconstruction is 5.7e-7 off; 9.4e-4 without the redo, 7.3e-7 with fp32
-// launches).  Every block doing so: 4 nodes x 25 600 values, encoder 32 -> 95 us, decoder 26 -> 53 us; 8 x 67 000: 141 -> 466
-// and 89 -> 232 us (one fp32-MFMA launch per layer: 83, 59, 270 and 194 us; one position after the other on the vector
-// units: 3.3, 1.6, 16 and 8 ms).
+// launches).  Every block doing so: 4 nodes x 25 600 values, encoder 25 -> 92 us, decoder 18 -> 50 us; 8 x 67 000: 114 -> 424
+// and 74 -> 213 us; 1 x 1 023: 12 -> 55 and 8 -> 23 us (one fp32-MFMA launch per layer: 83, 59, 270 and 194 us for the
+// first four; one position after the other on the vector units: 3.3, 1.6, 16 and 8 ms).
 //
 // Operand layout of v_mfma_f32_32x32x16_bf16: lane l supplies A[i = l % 32][k = 8 (l / 32) + 0..7] and
 // B[k = 8 (l / 32) + 0..7][j = l % 32]; result r of 16 is C[i = 8 (r / 4) + 4 (l / 32) + r % 4][j = l % 32].  Here
@@ -800,15 +800,17 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
                                                        float slope) {
     constexpr int NP = (4 * T + 30) / 31, KG = 4 / NP, CT = D4 / 32 / KG;   // position tiles; wavefronts per tile; their tiles of 32 channels
     constexpr int M3 = 2 * (T + 1), M4 = 4 * (T + 1), M5 = 8 * (T + 1);     // outputs of deconv2, 3, 4 that are kept (of which one or three too many)
-    constexpr int R2 = row_bytes(D2), R3 = row_bytes(D3), CH = 32;          // CH: channels of deconv4 per run of the redo
+    constexpr int R2 = row_bytes(D2), R3 = row_bytes(D3);
+    constexpr int CH = 64, RH = row_floats(CH);                             // the redo: 64 of deconv4's outputs x CH channels in each half of the ring
     constexpr int kStep = KG * 9 * 1024;                                    // a step's fragments: three parts of three taps per group of channels
     constexpr int kHandOver = 2 * (KG == 4 ? 3 : 2) * 4096;                 // sums that change wavefronts: half of them
-    constexpr int kRedo = (M5 + 1) * row_floats(CH) * 4, kMost = kRedo > kHandOver ? kRedo : kHandOver;
+    constexpr int kRedo = 65 * RH * 4, kMost = kRedo > kHandOver ? kRedo : kHandOver;
     constexpr int kBytesA = RING && kStep > kMost ? kStep : kMost;
     static_assert(!RING || KG == 2, "two wavefronts read a step");
+    static_assert((M5 == 128 || M5 == 64) && D4 == 2 * CH, "two wavefronts per half of the ring");
     static_assert(NP * KG == 4 && CT * KG * 32 == D4 && M3 <= 32 && D2 % 16 == 0 && D3 == 64 && D4 == 128 && D5 == 32, "tiles");
     static_assert(row_floats(D2) * 4 <= R2 && row_floats(D3) * 4 <= R3 && M4 <= 64 && 31 * NP + 2 <= 65, "rows");
-    // steps of weights on their way to the wavefronts; sums handed over; the first one in the redo: deconv4's outputs run by run
+    // steps of weights on their way to the wavefronts; sums handed over; in the redo: deconv4's outputs
     __shared__ __align__(16) unsigned char ring0[kBytesA], ring1[kBytesA];
     __shared__ __align__(16) unsigned char bufA[33 * R2], bufB[65 * R3];   // deconv2's outputs, deconv3's
     __shared__ float zs[D0 * (T + 3)], h1[D1 * (T + 1)];
@@ -1063,7 +1065,7 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
         if (mine) out[16 * p0 + i] = result;
         return;
     }
-    float *fd = (float *)bufA, *fa = (float *)ring0, *fb = (float *)bufB;
+    float *fd = (float *)bufA, *fb = (float *)bufB;
     {
         float y2[kCh];
         deconv2(y2, id);
@@ -1078,19 +1080,28 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
         store_fp32(fb + j * row_floats(D3), wave * 32, hf, even, slope, 4 * p0 + j < (long long)l3 && j < 4 * T + 1);
         store_fp32(fb + (j + 1) * row_floats(D3), wave * 32, hf, odd, slope, 4 * p0 + j + 1 < (long long)l3 && j + 1 < 4 * T + 1);
     }
+    // deconv4, every wavefront a tile of 32 channels x 32 of deconv3's positions: two of each, run by run, for 128 outputs, and the halves of the ring hold 64
+    // outputs each, the first one also the next after them; all four channel tiles at once for 64, and they hold 64 channels each.
+    // (Every block redoing: 22.8 us for 1 x 1 023 values, 213 for 8 x 67 000; runs of 32 channels in one half, which half of the wavefronts or a quarter
+    // of them made, took 35.5 and 268.)
+    __syncthreads();
+    constexpr bool kRuns = M5 == 128;
+    float *const mine4 = (float *)(wave >= 2 ? ring1 : ring0);
     acc16 e = bias16(w.b5, 0, hf), od = e;   // deconv5: wavefront = position tile
 #pragma unroll 1
-    for (int run = 0; run < D4 / CH; ++run) {
-        const int co0 = run * CH, m0 = wave * 32 + cl, j = 2 * m0;   // deconv4: the first M4 / 32 wavefronts, a position tile each
+    for (int run = 0; run < (kRuns ? 2 : 1); ++run) {
+        const int co0 = (kRuns ? run * CH : (wave >> 1) * CH) + (wave & 1) * 32, m0 = (kRuns ? (wave >> 1) * 32 : 0) + cl, j = 2 * m0;
         acc16 even = bias16(w.b4, co0, hf), odd = even;
+        up_fp32<D3, D4, row_floats(D3)>(even, odd, w.w4 + (4 * hf * D4 + co0 + cl) * 3, fb + m0 * row_floats(D3) + 4 * hf);
+        __syncthreads();   // the run before has been read
+        const bool valid = 8 * p0 + j < (long long)l4 && j < 8 * T + 1;
+        store_fp32(mine4 + 2 * cl * RH, (wave & 1) * 32, hf, even, slope, valid);
+        store_fp32(mine4 + (2 * cl + 1) * RH, (wave & 1) * 32, hf, odd, slope, 8 * p0 + j + 1 < (long long)l4 && j + 1 < 8 * T + 1);
+        if (kRuns && wave >= 2 && cl == 0) store_fp32((float *)ring0 + 64 * RH, (wave & 1) * 32, hf, even, slope, valid);
         __syncthreads();
-        if (wave < M4 / 32) {
-            up_fp32<D3, D4, row_floats(D3)>(even, odd, w.w4 + (4 * hf * D4 + co0 + cl) * 3, fb + m0 * row_floats(D3) + 4 * hf);
-            store_fp32(fa + j * row_floats(CH), 0, hf, even, slope, 8 * p0 + j < (long long)l4 && j < 8 * T + 1);
-            store_fp32(fa + (j + 1) * row_floats(CH), 0, hf, odd, slope, 8 * p0 + j + 1 < (long long)l4 && j + 1 < 8 * T + 1);
-        }
-        __syncthreads();
-        if (wave < M5 / 32) up_fp32<CH, D5, row_floats(CH)>(e, od, w.w5 + ((run * CH + 4 * hf) * D5 + cl) * 3, fa + (wave * 32 + cl) * row_floats(CH) + 4 * hf);
+        auto multiply = [&](const float *x, const int ci0) { up_fp32<CH, D5, RH>(e, od, w.w5 + ((ci0 + 4 * hf) * D5 + cl) * 3, x + ((wave & 1) * 32 + cl) * RH + 4 * hf); };
+        if (kRuns) multiply(mine4, run * CH);
+        else if (wave < 2) { multiply((const float *)ring0, 0); multiply((const float *)ring1, CH); }
     }
     double se = 0., so = 0.;
 #pragma unroll
