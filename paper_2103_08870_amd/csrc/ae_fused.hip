@@ -41,8 +41,6 @@
 // padded by 16 bytes: eight neighbouring positions then start in eight different groups of banks.
 #include <math.h>
 
-#include <type_traits>
-
 #include "lgc_internal.h"
 
 namespace lgc {
@@ -955,12 +953,14 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
                     else ra[s & 1][t][p] = *(const __attribute__((address_space(1))) u4v *)(scalar(fragments(ct, s, t) + p * 64) + lane16);
         };
         // Before step s: the next one into registers, and the one after it under way.  What is in the ring is there for all once each wavefront has waited
-        // for its own share; what was in its other half has been read.
+        // for its own share; what was in its other half has been read.  The fences keep the LDS reads of either step on their side of the barrier.
         auto advance = [&](const int ct, const int s) {
             if (RING) {
                 if (s + 1 < kSteps || ct + 1 < CT) {
+                    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
                     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0), lgkmcnt(0)
                     __builtin_amdgcn_s_barrier();
+                    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 if (s + 2 < kSteps) fetch((s & 1) ? ring1 : ring0, ct, s + 2);
