@@ -41,6 +41,8 @@
 // padded by 16 bytes: eight neighbouring positions then start in eight different groups of banks.
 #include <math.h>
 
+#include <type_traits>
+
 #include "lgc_internal.h"
 
 namespace lgc {
@@ -592,19 +594,28 @@ __device__ __forceinline__ void encode_run(const float *__restrict__ x, float *_
         {   // conv4: one position tile (of which N4 columns are used); the steps are shared out over kSplit wavefronts
             constexpr int kPer = CS / 16, kSteps = 3 * kPer / kSplit, kAhead = kSteps < 4 ? kSteps : 4;
             static_assert(3 * kPer % kSplit == 0, "conv4 steps");
-            const int mt = wave / kSplit, ks = wave % kSplit, s0 = ks * kSteps;
+            static_assert(kSplit == 4, "runs of steps");
+            const int mt = wave / kSplit, ks = wave % kSplit;
             const u4v *a = (const u4v *)w.s4 + (size_t)(mt * 3 * kPer3 + share * kPer) * 192 + lane;
-            auto frag = [&](int, const int s) { return a + ((s0 + s) / kPer * kPer3 + (s0 + s) % kPer) * 192; };
+            auto frag = [&](int, const int s) { return a + ((ks * kSteps + s) / kPer * kPer3 + (ks * kSteps + s) % kPer) * 192; };
             Fragments<1, kAhead> f;
             fragments_start(f, frag);
             acc16 acc[1][1];
             acc[0][0] = zero16();
             const unsigned char *b = rows3 + (col < N4 ? col : N4 - 1) * R3 + half * 16;
+            // a constant for each wavefront: the addresses of its steps are then parts of the instructions (4 x 10 000 values 16.5 us without, 16.1 with)
+            auto run = [&](auto k) {
+                constexpr int s0 = decltype(k)::value * kSteps;
+                conv_mma<CS, 1, 1, kSteps, kAhead>(acc, f, [&](int, const int s) { return a + ((s0 + s) / kPer * kPer3 + (s0 + s) % kPer) * 192; }, [&](int, const int s) {
+                    const int tap = (s0 + s) / kPer;
+                    return b + (tap == 1 ? (N4 + 1) * R3 : (tap >> 1) * R3) + 32 * ((s0 + s) % kPer);
+                });
+            };
             __syncthreads();
-            conv_mma<CS, 1, 1, kSteps, kAhead>(acc, f, frag, [&](int, const int s) {
-                const int tap = (s0 + s) / kPer;
-                return b + (tap == 1 ? (N4 + 1) * R3 : (tap >> 1) * R3) + 32 * ((s0 + s) % kPer);
-            });
+            if (ks == 0) run(std::integral_constant<int, 0>());    // wave-uniform
+            else if (ks == 1) run(std::integral_constant<int, 1>());
+            else if (ks == 2) run(std::integral_constant<int, 2>());
+            else run(std::integral_constant<int, 3>());
             __syncthreads();
 #pragma unroll
             for (int r = 0; r < 16; ++r)
