@@ -74,8 +74,8 @@ typedef enum {
  * per node, max_k selected values per node and max_batch nodes per call.
  * Allocates all selection scratch here (device memory, 0.2 to 0.9 bytes per
  * element: 26 MB for 4 nodes x 25.6 M elements with k = 25 600, 143 MB for
- * one node of 2^28 elements with k = 2 684 354); nothing else allocates on
- * the selection path. */
+ * one node of 2^28 elements with k = 2 684 354; and up to 1 MB for lgc_encode);
+ * nothing else allocates on the selection path. */
 lgc_status lgc_create(lgc_ctx **out, int device, uint64_t max_n, uint64_t max_k, int max_batch);
 void lgc_destroy(lgc_ctx *ctx);
 const char *lgc_last_error(const lgc_ctx *ctx);
@@ -317,8 +317,7 @@ lgc_status lgc_average(lgc_ctx *ctx, const float *x, uint64_t len, int batch, fl
  *   ae  (nullable): the activation buffers lgc_encode / lgc_decode /
  *        lgc_decode_innovation need with this autoencoder for inputs of up to
  *        k values per node and up to `batch` nodes (the largest intermediate
- *        tensor of either stack, twice; with the stack of Table I once 1 MB
- *        that later reservations leave where it is);
+ *        tensor of either stack, twice);
  *   seg (nullable): the per-layer thresholds and the candidate list of
  *        lgc_topk_segmented / lgc_accumulate_topk_segmented with this plan.
  * A later reservation only ever grows the buffers, so one call per

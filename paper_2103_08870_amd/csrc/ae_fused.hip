@@ -41,6 +41,7 @@
 // padded by 16 bytes: eight neighbouring positions then start in eight different groups of banks.
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "lgc_internal.h"
@@ -1143,11 +1144,13 @@ bool decoder_fused_covers(const LayerDev *l, int count) {
            is_layer(l[3], 64, 128, 3, 2) && is_layer(l[4], 128, 32, 3, 2) && is_layer(l[5], 32, 1, 1, 1);
 }
 
-// Runs are shared while there are no more blocks than compute units: at least two of them a run, 64 channels x 16 positions each
-EncoderScratch encoder_scratch(int cus) {
+// Runs of 15 positions, each of which 16 values make, are shared while there are no more blocks than compute units: two or four of them a
+// run, with 64 channels x 16 positions each
+EncoderScratch encoder_scratch(uint64_t max_k, int max_batch, int cus) {
+    const uint64_t runs = (max_k + 239) / 240 * max_batch;
     EncoderScratch s;
-    s.sum_floats = (size_t)cus * 64 * 16;
-    s.taken_words = (uint32_t)cus / 2;
+    s.sum_floats = (size_t)std::min<uint64_t>(4 * runs, cus) * 64 * 16;
+    s.taken_words = (uint32_t)std::min<uint64_t>(runs, cus / 2);
     return s;
 }
 
@@ -1169,7 +1172,7 @@ bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int cou
     w.limits = limits;
     const uint32_t runs = (l4 + 14) / 15;
     const uint64_t all = (uint64_t)runs * batch;
-    auto fits = [&](uint64_t shares) { return all * shares <= (uint64_t)cus && (shares == 1 || (scratch.sums && all <= scratch.taken_words && all * shares * 64 * 16 <= scratch.sum_floats)); };
+    auto fits = [&](uint64_t shares) { return all * shares <= (uint64_t)cus && (shares == 1 || (all <= scratch.taken_words && all * shares * 64 * 16 <= scratch.sum_floats)); };
 #define LGC_ENC(S) hipLaunchKernelGGL((k_encoder_fused<64, 128, 256, 64, 4, 8, S>), dim3(runs, batch, S), dim3(512), 0, st, c, w)
     // as many blocks as there are compute units for the runs of 15
     if (fits(4)) { LGC_ENC(4); return true; }

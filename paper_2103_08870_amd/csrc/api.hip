@@ -41,8 +41,7 @@ struct lgc_ctx {
     uint64_t rec_rows = 0;
     float *act[2] = {nullptr, nullptr};  // autoencoder activations (ping-pong), grown on demand
     size_t act_floats = 0;
-    // where the encoder's blocks that share a run of positions meet: never replaced, as a recorded graph holds its address
-    EncoderScratch shares;
+    EncoderScratch shares;               // in `scratch`, which no reservation replaces: a recorded graph holds these addresses
     // per-layer selection: thresholds [max_batch][n_seg] and a candidate list of its own, grown on demand
     uint32_t *seg_t = nullptr, *seg_cand = nullptr, *seg_row_prefix = nullptr;
     size_t seg_t_words = 0, seg_cand_words = 0;
@@ -219,15 +218,17 @@ StateLayout state_layout(int max_batch, uint32_t status_cand_stride, uint32_t st
 }
 
 // The selection scratch of a context for (max_n, max_k, max_batch): byte offsets of its parts in one block of
-// device memory.  Everything before `samples` (statistics, carried thresholds, state sets) must start at zero.
+// device memory.  Everything before `samples` (statistics, carried thresholds, counts, state sets) must start at zero.
 struct ScratchLayout {
     bool ok = false;
     uint32_t cap = 0, rows = 0, status_cand_stride = 0, status_exact_stride = 0, state_words = 0;
-    size_t stats = 0, carry = 0, state[2] = {0, 0}, samples = 0, row_count = 0, bitmap = 0, cand_idx = 0, cand_val = 0;
+    size_t stats = 0, carry = 0, taken = 0, state[2] = {0, 0}, samples = 0, row_count = 0, bitmap = 0, cand_idx = 0, cand_val = 0, sums = 0;
+    EncoderScratch shares;   // sizes
     size_t bytes = 0;
 };
 
-ScratchLayout scratch_layout(uint64_t max_n, uint64_t max_k, int max_batch, bool two_state_sets) {
+// cus: compute units, for a context; 0: the fixed array of the call without one, which has one state set and runs no encoder
+ScratchLayout scratch_layout(uint64_t max_n, uint64_t max_k, int max_batch, int cus) {
     ScratchLayout s;
     s.cap = candidate_capacity(max_n, max_k);
     s.rows = (uint32_t)align_up((max_n + kRow - 1) / kRow, 4);
@@ -241,13 +242,16 @@ ScratchLayout scratch_layout(uint64_t max_n, uint64_t max_k, int max_batch, bool
     auto carve = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, A); return o; };
     s.stats = carve(sizeof(Stats));
     s.carry = carve(B * sizeof(Carry));
+    s.shares = encoder_scratch(max_k, max_batch, cus);
+    s.taken = carve(s.shares.taken_words * 4);
     s.state[0] = carve(L.words * 4);
-    s.state[1] = two_state_sets ? carve(L.words * 4) : s.state[0];
+    s.state[1] = cus ? carve(L.words * 4) : s.state[0];
     s.samples = carve(B * kSample * 4);
     s.row_count = carve(B * s.rows * 4);
     s.bitmap = carve(B * (size_t)s.rows * kRowWords * 8);
     s.cand_idx = carve(B * (size_t)s.cap * 4);
     s.cand_val = carve(B * (size_t)s.cap * 4);
+    s.sums = carve(s.shares.sum_floats * 4);
     s.bytes = off;
     s.ok = true;
     return s;
@@ -268,6 +272,9 @@ void bind_scratch(lgc_ctx *c, void *base_ptr, const ScratchLayout &s) {
     c->bitmap = (unsigned long long *)(base + s.bitmap);
     c->cand_idx = (uint32_t *)(base + s.cand_idx);
     c->cand_val = (uint32_t *)(base + s.cand_val);
+    c->shares = s.shares;
+    c->shares.sums = (float *)(base + s.sums);
+    c->shares.taken = (uint32_t *)(base + s.taken);
 }
 
 SelArgs make_args(lgc_ctx *c, const float *g, float *u, float *v, uint64_t n, uint64_t stride, float m,
@@ -496,7 +503,7 @@ extern "C" lgc_status lgc_create(lgc_ctx **out, int device, uint64_t max_n, uint
         if (pe != hipSuccess) { delete c; return fail(nullptr, LGC_EHIP, "hipGetDeviceProperties: %s", hipGetErrorString(pe)); }
         c->cus = prop.multiProcessorCount > 0 ? prop.multiProcessorCount : 1;
     }
-    const ScratchLayout L = scratch_layout(max_n, max_k, max_batch, true);
+    const ScratchLayout L = scratch_layout(max_n, max_k, max_batch, c->cus);
     if (!L.ok) { delete c; return fail(nullptr, LGC_EINVAL, "max_n * max_batch too large"); }
     void *block = nullptr;
     hipError_t e = hipMalloc(&block, L.bytes);
@@ -539,7 +546,6 @@ extern "C" void lgc_destroy(lgc_ctx *ctx) {
     (void)hipDeviceSynchronize();
     for (hipEvent_t e : ctx->ev) (void)hipEventDestroy(e);
     if (ctx->act[0]) (void)hipFree(ctx->act[0]);
-    if (ctx->shares.sums) (void)hipFree(ctx->shares.sums);
     if (ctx->seg_t) (void)hipFree(ctx->seg_t);
     if (ctx->seg_carry) (void)hipFree(ctx->seg_carry);
     if (ctx->seg_cand) (void)hipFree(ctx->seg_cand);
@@ -662,7 +668,7 @@ extern "C" lgc_status lgc_accumulate_topk_static(int device, const float *g, flo
     if (!aligned(g, 4) || !aligned(u, 4) || !aligned(v, 4) || !aligned(out_vals, 4) || !aligned(out_idx, 4))
         return fail(nullptr, LGC_EINVAL, "pointer not 4-byte aligned");
     // the same scratch a context for exactly (n, k, batch) would own, with one state set instead of two
-    const ScratchLayout L = scratch_layout(n, k, batch, false);
+    const ScratchLayout L = scratch_layout(n, k, batch, 0);
     if (!L.ok || L.bytes > kStaticScratchBytes)
         return fail(nullptr, LGC_EINVAL,
                     "lgc_accumulate_topk_static: n = %llu, k = %llu, batch = %d need %zu bytes of scratch, the static "
@@ -922,25 +928,6 @@ static lgc_status ensure_act(lgc_ctx *ctx, size_t floats) {
     HIP_TRY(ctx, hipMalloc((void **)&ctx->act[0], 2 * floats * 4));
     ctx->act[1] = ctx->act[0] + floats;
     ctx->act_floats = floats;
-    return LGC_OK;
-}
-
-// The same for the blocks that share a run: the counts start at zero.  Of one size whatever the calls, so that later reservations leave it alone.
-static lgc_status ensure_shares(lgc_ctx *ctx, const lgc_ae *ae) {
-    if (ctx->shares.sums || !encoder_fused_covers(ae->enc_dev.data(), (int)ae->enc_dev.size())) return LGC_OK;
-    EncoderScratch made = encoder_scratch(ctx->cus);
-    const size_t sums = made.sum_floats * 4, bytes = sums + made.taken_words * 4;
-    void *block = nullptr;
-    HIP_TRY(ctx, hipMalloc(&block, bytes));
-    hipError_t e = hipMemset((char *)block + sums, 0, bytes - sums);
-    if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (e != hipSuccess) {
-        (void)hipFree(block);
-        return fail(ctx, LGC_EHIP, "hipMemset: %s", hipGetErrorString(e));
-    }
-    made.sums = (float *)block;
-    made.taken = (uint32_t *)((char *)block + sums);
-    ctx->shares = made;
     return LGC_OK;
 }
 
@@ -1451,7 +1438,7 @@ extern "C" lgc_status lgc_reserve(lgc_ctx *ctx, const lgc_ae *ae, uint64_t k, in
     if (!guard.ok) return fail(ctx, LGC_EHIP, "cannot select device %d", ctx->device);
     return no_throw(ctx, [&]() -> lgc_status {
         lgc_status s = LGC_OK;
-        if (ae && k > 0 && ((s = ensure_act(ctx, act_need(ae, k, batch))) != LGC_OK || (s = ensure_shares(ctx, ae)) != LGC_OK)) return s;
+        if (ae && k > 0 && (s = ensure_act(ctx, act_need(ae, k, batch))) != LGC_OK) return s;
         if (seg && (s = ensure_seg_scratch(ctx, seg)) != LGC_OK) return s;
         return LGC_OK;
     });

@@ -276,14 +276,14 @@ struct FusedLimits {
 // l: the `split` layers with bf16 fragments and the layer that ends the stack, most: their largest magnitudes.  false: the stack's
 // weights are out of the split's range (fp32 kernels)
 bool fused_limits(const LayerDev *l, int split, const float *most, bool transposed, float slope, bool no_bias, FusedLimits &out);
-// Where blocks that share a run of positions meet: room for their sums; counts, which every call leaves at zero.  Without it no run is shared.
+// Where blocks that share a run of positions meet: room for their sums; counts, which every call leaves at zero
 struct EncoderScratch {
     float *sums = nullptr;
     size_t sum_floats = 0;
     uint32_t *taken = nullptr;
     uint32_t taken_words = 0;
 };
-EncoderScratch encoder_scratch(int cus);   // the sizes of what suffices for every call
+EncoderScratch encoder_scratch(uint64_t max_k, int max_batch, int cus);   // the sizes of what suffices for every call
 bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int count, const uint64_t *len, int batch, float slope,
                           const FusedLimits &limits, int cus, const EncoderScratch &scratch, hipStream_t st);
 bool launch_decoder_fused(const float *z, float *out, const LayerDev *l, int count, uint64_t l_z, const uint64_t *len, int batch,
