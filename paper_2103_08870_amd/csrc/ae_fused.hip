@@ -15,13 +15,13 @@
 // 64 bits: the cost cannot be told from none (4 x 25 600: 26.0 us either way), and in 32 bits those sums were over half
 // of the latent's error.
 // Measured against one fp32-MFMA launch per deep layer (ae_mfma.hip, which other stacks still use): 4 nodes x 25 600
-// values, encoder 79.4 -> 26.8 us (165 TFLOP/s of fp32 products), decoder 58.0 -> 19.9 us (134); 8 x 67 000, both
-// together 468 -> 205 us (181); 1 x 1 023 (latency) 79 -> 20.3 us.  Relative error against 64 bits, six sizes from 1 x 500 to
-// 8 x 67 000 x six seeds, mean (least to largest): latent 1.15e-7 (0.87 to 1.46) -> 0.41e-7 (0.34 to 0.51; 0.99e-7 with the
-// last sums in 32 bits), decoder 3.86e-8 (2.96 to 5.54) -> 2.95e-8 (2.20 to 3.86): lower at every size with every
-// seed.  What bounds it: while a compute unit has blocks its matrix cores are busy 54-57 % of the cycles (encoder) and
-// 45 % (decoder).  A wavefront's products, once begun, hold them until it waits; what else its block has to do goes on beside another
-// wavefront's products only where no barrier stands between.
+// values, encoder 79.4 -> 26.7 us (165 TFLOP/s of fp32 products), decoder 58.0 -> 19.0 us (141); 8 x 67 000, both
+// together 468 -> 212 us (175); 1 x 1 023 (latency) 79 -> 20.0 us (one card, two directions; other cards take up to 5 % less).
+// Relative error against 64 bits, six sizes from 1 x 500 to 8 x 67 000 x six seeds, mean (least to largest): latent
+// 1.32e-7 (0.93 to 2.48) -> 0.46e-7 (0.32 to 0.83), decoder 8.8e-8 (2.2 to 31.6) -> 5.3e-8 (1.9 to 16.8): lower at every
+// size with every seed.  What bounds it: while a compute unit has blocks its matrix cores are busy 56-59 % of the cycles
+// (encoder) and 43-51 % (decoder).  A wavefront's products, once begun, hold them until it waits; what else its block has
+// to do goes on beside another wavefront's products only where no barrier stands between.
 //
 // The split is exact only for finite values; an Inf would meet products of both signs.  Such a value (or one that rounds
 // to Inf) leaves a NaN among its parts, which makes every output it reaches a NaN.  And it is exact only while the parts
@@ -68,9 +68,10 @@ struct Act {
     __device__ __forceinline__ float operator()(const float x) const { return x * (x > 0.f ? pos : neg); }
 };
 
-// Two values split into three bf16 pairs.  What a part leaves is taken by one instruction a value, a - h.lo * 1 + h.hi * 0 and the like, exact as there
-// is nothing to round (by shift or mask and subtraction two; with the choice of factors above, 8 x 67 000 values, encoder 132.9 -> 130.7 us, decoder 82.8 ->
-// 80.4).  A value that is not finite, or rounds to Inf, leaves NaNs among the parts of both.
+// Two values split into three bf16 pairs.  What a part leaves is taken by one instruction a value, a - h.lo * 1 + h.hi * 0 and
+// the like, exact as there is nothing to round (by shift or mask and subtraction two; with the choice of factors above,
+// 8 x 67 000 values, encoder 132.9 -> 130.7 us, decoder 82.8 -> 80.4).  A value that is not finite, or rounds to Inf, leaves
+// NaNs among the parts of both.
 // The factors come in scalar registers: as constants within the instruction they would go to the wrong halves.
 __device__ __forceinline__ void split2(const float a, const float b, uint32_t &h, uint32_t &m, uint32_t &l) {
     uint32_t minus_lo = 0x0000bf80u, minus_hi = 0xbf800000u;
@@ -292,9 +293,10 @@ __device__ __forceinline__ void load_a(u4v (&r)[3], const u4v *__restrict__ a, c
     for (int p = 0; p < 3; ++p) r[p] = a[(step * 3 + p) * 64];
 }
 
-// The order of one step's instructions: a read from the LDS, then a load, behind each product in turn, which they then cost no time beside (ahead of the
-// products they are issued while the matrix cores wait; a block of 31 positions 57.4 -> 54.5 K cycles, 8 x 67 000 values 129.4 -> 127.9 us, as the clock falls with
-// the denser products; the decoder's steps, 8 x 67 000 82.4 -> 80.8, 1 x 1 023 8.5 -> 8.2).
+// The order of one step's instructions: a read from the LDS, then a load, behind each product in turn, which they then cost no
+// time beside (ahead of the products they are issued while the matrix cores wait; a block of 31 positions 57.4 -> 54.5 K
+// cycles, 8 x 67 000 values 129.4 -> 127.9 us, as the clock falls with the denser products; the decoder's steps, 8 x 67 000
+// 82.4 -> 80.8, 1 x 1 023 8.5 -> 8.2).
 template <int MMAS, int READS, int LOADS>
 __device__ __forceinline__ void interleave() {
 #pragma unroll
@@ -305,10 +307,11 @@ __device__ __forceinline__ void interleave() {
     }
 }
 
-// The K loop of one convolution for MT x NT tiles: STEPS steps of 16 input channels.  where(j, s): the LDS address of this lane's position of tile j
-// for step s.  frag(i, s): this lane's fragments of tile i.  They come from the L2: AHEAD steps of them are kept in flight, the first ones from before
-// the barrier that the loop waits at, and the LDS reads run one step ahead.  interleave() keeps it that way (left to
-// itself the compiler moves the loads down to their uses: conv4 then waits out the L2's latency in every step).
+// The K loop of one convolution for MT x NT tiles: STEPS steps of 16 input channels.  where(j, s): the LDS address of this
+// lane's position of tile j for step s.  frag(i, s): this lane's fragments of tile i.  They come from the L2: AHEAD steps of
+// them are kept in flight, the first ones from before the barrier that the loop waits at, and the LDS reads run one step ahead.
+// interleave() keeps it that way (left to itself the compiler moves the loads down to their uses: conv4 then waits out the L2's
+// latency in every step).
 template <int MT, int AHEAD>
 struct Fragments { u4v r[AHEAD + 1][MT][3]; };
 
@@ -429,10 +432,11 @@ namespace {
 // conv1's 8 p0 - 7 + i, the input's 16 p0 - 15 + i, so that position i of one layer takes 2i, 2i + 1, 2i + 2 of
 // the layer before; 2P + 1, 4P + 3, 8P + 7 and 16P + 15 of them are needed, and the tiles hold one more.
 //
-// S blocks share a run of 15 positions: each makes conv1 and conv2 for itself, 1 / S of conv3's channels (whose steps several wavefronts share) and what
-// those give of conv4's sums; the last one to come adds them up, in order whichever it is, and goes on.  Short vectors would leave most compute units idle,
-// and draw 1 MB of weights through each one that works: 1 x 1 023 values (5 runs) 15.7 us with a block each, 11.9 with four; 2 x 5 000 (42 runs) 16.1 / 13.5, 4 x 5 000 (84
-// runs, two blocks) 16.7 / 15.4.
+// S blocks share a run of 15 positions: each makes conv1 and conv2 for itself, 1 / S of conv3's channels (whose steps several
+// wavefronts share) and what those give of conv4's sums; the last one to come adds them up, in order whichever it is, and goes
+// on.  Short vectors would leave most compute units idle, and draw 1 MB of weights through each one that works: 1 x 1 023
+// values (5 runs) 15.9 us with a block each, 11.7 with four; 2 x 2 000 (18 runs) 16.0 / 12.1, 4 x 5 000 (84 runs, two blocks)
+// 16.2 / 14.6.
 template <int P, int S, int C1, int C2, int C3, int C4, int C5, int W>
 struct EncoderRun {
     static constexpr int N4 = P + 1, N3 = 2 * N4, N2 = 4 * N4;   // tile widths (positions) of conv4, conv3, conv2
@@ -604,7 +608,8 @@ __device__ __forceinline__ void encode_run(const float *__restrict__ x, float *_
             acc16 acc[1][1];
             acc[0][0] = zero16();
             const unsigned char *b = rows3 + (col < N4 ? col : N4 - 1) * R3 + half * 16;
-            // a constant for each wavefront: the addresses of its steps are then parts of the instructions (4 x 10 000 values 16.5 us without, 16.1 with)
+            // a constant for each wavefront: the addresses of its steps are then parts of the instructions (4 x 10 000 values
+            // 16.5 us without, 16.1 with)
             auto run = [&](auto k) {
                 constexpr int s0 = decltype(k)::value * kSteps;
                 conv_mma<CS, 1, 1, kSteps, kAhead>(acc, f, [&](int, const int s) { return a + ((s0 + s) / kPer * kPer3 + (s0 + s) % kPer) * 192; }, [&](int, const int s) {
@@ -635,8 +640,8 @@ __device__ __forceinline__ void encode_run(const float *__restrict__ x, float *_
             for (int s = 1; s < kSplit; ++s) y[i] += part[(s * C4 + cg * kCh + i) * 33 + p];
         }
         if constexpr (S > 1) {
-            // Through the device's memory, past the L2s: what a wavefront has stored is there once it has been acknowledged, the barrier collects the
-            // wavefronts, and one thread counts the block.
+            // Through the device's memory, past the L2s: what a wavefront has stored is there once it has been acknowledged,
+            // the barrier collects the wavefronts, and one thread counts the block.
             __shared__ uint32_t before;
             if (p < N4) {
 #pragma unroll
@@ -727,8 +732,9 @@ struct EncoderCall {
     float slope;
 };
 
-// S = 0: runs of 31 positions, those of all nodes first, and then of 15: what is left over from whole rounds of the long ones takes a round of short ones instead
-// of a long one that few compute units have a part in (6 x 25 600 values, 312 runs of 31: 51.1 -> 44.7 us; 8 x 67 000, 1088: 133.0 -> 127.9).
+// S = 0: runs of 31 positions, those of all nodes first, and then of 15: what is left over from whole rounds of the long ones
+// takes a round of short ones instead of a long one that few compute units have a part in (6 x 25 600 values, 312 runs of 31:
+// 51.3 -> 42.3 us; 8 x 67 000, 1088: 133.8 -> 124.2, both with loads behind the products).
 // S > 0: runs of 15 positions, S blocks each, grid (runs, nodes, S).
 template <int C1, int C2, int C3, int C4, int C5, int W, int S>
 __global__ __launch_bounds__(W * 64) void k_encoder_fused(EncoderCall c, EncoderDev w) {
@@ -794,16 +800,17 @@ __device__ __forceinline__ void store_fp32(float *row, const int co0, const int 
 
 }  // namespace
 
-// T latent positions per block of four wavefronts.  Local numbering from 1, 2, 4, 8 and 16 p0 on: T + 1 outputs of
-// deconv1, 2T + 1 of deconv2, 4T + 1 of deconv3, 8T + 1 of deconv4 and 16T of deconv5.  A wavefront takes 32 of deconv3's
-// positions through deconv4 and deconv5, 32 channels of deconv4 at a time: lane i holds its outputs 2i and 2i + 1, splits them in
-// registers and multiplies on, so that no barrier and no exchange through the LDS stands between the two layers that make up the
-// work, and one wavefront converts while another one multiplies.  deconv5's output 4i + 3 needs deconv4's 2i + 2, which is the next
-// lane's: 31 of the 32 positions come out.  4 / NP wavefronts share a position tile's channels of deconv4 and add their sums up at the end.
-// The bound of two wavefronts per SIMD leaves room for the weights' fragments that are under way (one step ahead).
-// Through the LDS, in two runs of 64 channels with four barriers each, 4 x 25 600 values took 22.2 us (19.9 now), 8 x 67 000 87.8 (79), 1 x 1 023
-// 12.5 (8.3, with 7 positions per block).  What bounds it: two blocks on a compute unit have 18.4 K cycles of products in 39 K; the rest is each block's way
-// to the first product (9 K: a read from memory, three small layers, three barriers) and its end (5 K).
+// T latent positions per block of four wavefronts.  Local numbering from 1, 2, 4, 8 and 16 p0 on: T + 1 outputs of deconv1,
+// 2T + 1 of deconv2, 4T + 1 of deconv3, 8T + 1 of deconv4 and 16T of deconv5.  A wavefront takes 32 of deconv3's positions through
+// deconv4 and deconv5, 32 channels of deconv4 at a time: lane i holds its outputs 2i and 2i + 1, splits them in registers and
+// multiplies on, so that no barrier and no exchange through the LDS stands between the two layers that make up the work, and
+// one wavefront converts while another one multiplies.  deconv5's output 4i + 3 needs deconv4's 2i + 2, which is the next
+// lane's: 31 of the 32 positions come out.  4 / NP wavefronts share a position tile's channels of deconv4 and add their sums up
+// at the end.  The bound of two wavefronts per SIMD leaves room for the weights' fragments that are under way (one step ahead).
+// Through the LDS, in two runs of 64 channels with four barriers each, 4 x 25 600 values took 21.2 us where this and the loads
+// behind the products take 19.0, 8 x 67 000 86.5 / 78.2, 1 x 1 023 12.4 / 8.1 (with 7 positions per block).  What bounds it:
+// two blocks on a compute unit have 18.4 K cycles of products in 39 K; the rest is each block's way to the first product (9 K:
+// a read from memory, three small layers, three barriers) and its end (5 K).
 template <int D0, int D1, int D2, int D3, int D4, int D5, int T, bool RING>
 __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restrict__ z, float *__restrict__ out, DecoderDev w,
                                                        uint32_t lz, uint32_t l2, uint32_t l3, uint32_t l4, uint32_t l5,
@@ -964,8 +971,9 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
                     if (RING) ra[s & 1][t][p] = *(const u4v *)(((s & 1) ? ring1 : ring0) + (kg * 9 + t * 3 + p) * 1024 + lane16);
                     else ra[s & 1][t][p] = *(const __attribute__((address_space(1))) u4v *)(scalar(fragments(ct, s, t) + p * 64) + lane16);
         };
-        // Before step s: the next one into registers, and the one after it under way.  What is in the ring is there for all once each wavefront has waited
-        // for its own share; what was in its other half has been read.  The fences keep the LDS reads of either step on their side of the barrier.
+        // Before step s: the next one into registers, and the one after it under way.  What is in the ring is there for all
+        // once each wavefront has waited for its own share; what was in its other half has been read.  The fences keep the LDS
+        // reads of either step on their side of the barrier.
         auto advance = [&](const int ct, const int s) {
             if (RING) {
                 if (s + 1 < kSteps || ct + 1 < CT) {
@@ -1092,10 +1100,10 @@ __global__ __launch_bounds__(256, 2) void k_decoder_fused(const float *__restric
         store_fp32(fb + j * row_floats(D3), wave * 32, hf, even, slope, 4 * p0 + j < (long long)l3 && j < 4 * T + 1);
         store_fp32(fb + (j + 1) * row_floats(D3), wave * 32, hf, odd, slope, 4 * p0 + j + 1 < (long long)l3 && j + 1 < 4 * T + 1);
     }
-    // deconv4, every wavefront a tile of 32 channels x 32 of deconv3's positions: two of each, run by run, for 128 outputs, and the halves of the ring hold 64
-    // outputs each, the first one also the next after them; all four channel tiles at once for 64, and they hold 64 channels each.
-    // (Every block redoing: 22.8 us for 1 x 1 023 values, 213 for 8 x 67 000; runs of 32 channels in one half, which half of the wavefronts or a quarter
-    // of them made, took 35.5 and 268.)
+    // deconv4, every wavefront a tile of 32 channels x 32 of deconv3's positions: two of each, run by run, for 128 outputs, and
+    // the halves of the ring hold 64 outputs each, the first one also the next after them; all four channel tiles at once for
+    // 64, and they hold 64 channels each.  (Every block redoing: 22.8 us for 1 x 1 023 values, 213 for 8 x 67 000; runs of 32
+    // channels in one half, which half of the wavefronts or a quarter of them made, took 35.5 and 268.)
     __syncthreads();
     constexpr bool kRuns = M5 == 128;
     float *const mine4 = (float *)(wave >= 2 ? ring1 : ring0);
@@ -1179,7 +1187,8 @@ bool launch_encoder_fused(const float *x, float *out, const LayerDev *l, int cou
     if (fits(2)) { LGC_ENC(2); return true; }
     if (fits(1)) { LGC_ENC(1); return true; }
 #undef LGC_ENC
-    // 31 positions per block stream the 1 MB of weights half as often as 15 do, and waste no half tile in conv4 (4 nodes x 25 600 values: 25.8 against 32.7 us)
+    // 31 positions per block stream the 1 MB of weights half as often as 15 do, and waste no half tile in conv4
+    // (4 nodes x 25 600 values: 25.8 against 32.7 us)
     const uint32_t longs = (l4 + 30) / 31, rounds = (uint32_t)((uint64_t)longs * batch / cus);   // rounds in which every compute unit has a run of 31
     c.longs = longs; c.shorts = 0;
     if (rounds > 0) {
@@ -1207,10 +1216,12 @@ bool launch_decoder_fused(const float *z, float *out, const LayerDev *l, int cou
     w.limits = limits;
 #define LGC_DEC(T, RING) hipLaunchKernelGGL((k_decoder_fused<4, 4, 32, 64, 128, 32, T, RING>), dim3(((uint32_t)l_z + T - 1) / T, batch), dim3(256), 0, st, z, out, w, \
                                             (uint32_t)l_z, (uint32_t)len[1], (uint32_t)len[2], (uint32_t)len[3], (uint32_t)len[4], slope)
-    // 7 positions per block while that gives every compute unit at most one: the shorter chain counts (1 x 1 023 values: 8.3 us against 11.6 with 15, 4 x 5 000: 8.9
-    // against 11.6); from two such blocks per compute unit on 15 are better (2 x 15 000: 14.3 against 12.4).  Where those come to two per compute unit as
-    // well, their wavefronts fetch the weights once for two, through the LDS (4 x 25 600: 21.9 against 20.4 us, 8 x 67 000: 85.1 against 82.6); a block that has its
-    // compute unit to itself loses more by the barriers than it gains (4 x 15 000: 12.5 against 13.4; both before their loads went behind the products).
+    // 7 positions per block while that gives every compute unit at most one: the shorter chain counts (1 x 1 023 values: 8.3 us
+    // against 11.6 with 15, 4 x 5 000: 8.9 against 11.6); from two such blocks per compute unit on 15 are better (2 x 15 000:
+    // 14.3 against 12.4).  Where those come to two per compute unit as well, their wavefronts fetch the weights once for two,
+    // through the LDS (4 x 25 600: 21.9 against 20.4 us, 8 x 67 000: 85.1 against 82.6); a block that has its compute unit to
+    // itself loses more by the barriers than it gains (4 x 15 000: 12.5 against 13.4; both before their loads went behind the
+    // products).
     if ((uint64_t)((l_z + 6) / 7) * batch <= (uint64_t)cus) LGC_DEC(7, false);
     else if ((uint64_t)((l_z + 14) / 15) * batch <= (uint64_t)cus) LGC_DEC(15, false);
     else LGC_DEC(15, true);

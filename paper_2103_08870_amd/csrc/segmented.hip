@@ -182,10 +182,15 @@ void launch_seg_estimate(const SelArgs &a, int batch, bool fused, hipStream_t st
 // after the first) in rolled loops: unrolling those for 64 K entries was an order of magnitude
 // slower (instruction fetch).
 
-// 16-byte groups per thread that a block holds in registers, by the blocks of the launch: eight while two blocks per compute unit are all of them
-// (16 K entries are read once), three beyond.  With three k_seg_select needs 72 vector registers and three of its blocks share a compute unit, with
-// eight 95 and two.  us, eight / three groups: 161 layers of 4 nodes, k_seg_select 22.1 / 17.3, whole step 403.4 / 397.8; 300 layers of 8 nodes, k_seg_select
-// 45.8 / 38.2, k_innovation 21.2 / 17.8; 40 layers of one node, 1 % of 2 M elements, k_seg_select 20.4 / 24.2.
+// 16-byte groups per thread that a block holds in registers, by the blocks of the launch: eight while two blocks per compute
+// unit are all of them (16 K entries are read once), three beyond.  With three k_seg_select needs 72 vector registers and three
+// of its blocks share a compute unit, with eight 95 and two.  us, eight / three groups: 161 layers of 4 nodes, k_seg_select
+// 22.1 / 17.3, whole step 403.4 / 397.8; 300 layers of 8 nodes, k_seg_select 45.8 / 38.2, k_innovation 21.2 / 17.8; 40 layers of
+// one node, 1 % of 2 M elements, k_seg_select 20.4 / 24.2.  Beyond two blocks per compute unit the third block outweighs the second
+// to fourth reading (from the L2) also where all sources lie between the two sizes, whole step: 136 layers of 4 x 60 M, 2 %
+// 1654.6 / 1642.3, 160 layers, 3 % 1922.9 / 1910.0, 70 of 8 x 30 M, 2 % 1718.1 / 1706.6, 260 of 2 x 60 M, 3 % 1000.6 / 991.2, 200 of
+// 10 K elements x 8 nodes, 1 % 154.1 / 145.1; not where a tenth of such layers is kept (294.1 / 297.2; 0.1 to 1 %
+// are the rule).  Layers of all sizes, 1 %: 160 of 4 x 60 M 1371.6 / 1346.2, 100 of 8 x 30 M 1501.0 / 1492.6, 400 of 3 x 60 M 1012.7 / 1013.9.
 constexpr int kKeepFew = 8, kKeepMany = 3;
 constexpr int kSelThreads = 512;          // most segments and candidate runs are a few thousand entries
 
